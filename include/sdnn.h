@@ -126,13 +126,13 @@ typedef struct {
  * shared columns (uniformly random links) nothing is gained. */
 #define SDNN_CLUSTER_ROWS 256 /* largest cluster */
 
-/* Inference nets (training = 0) whose widest layer has at most 4096 neurons can run sdnn_forward as ONE
- * launch in which a workgroup carries 4 samples through all layers with their activations held in
+/* Inference nets (training = 0) whose widest layer has at most 32768 neurons can run sdnn_forward as ONE
+ * launch in which a workgroup carries 1, 2 or 4 samples through all layers with their activations held in
  * LDS (the samples are independent, Section 5.1, so nothing is exchanged between workgroups); the
- * weights are streamed from a second, lane-major copy that sdnn_create builds (8 more bytes of
- * workspace per stored entry; sdnn_set_weights keeps it current).  Every row still adds its terms
- * in storage order: same bits as the per-layer kernels.  AUTO builds the copy and uses the launch
- * where it is faster (enough samples to fill the chip, or layers so small that per-layer launches
+ * weights are streamed from a second, lane-major copy that sdnn_create builds (6 more bytes of
+ * workspace per stored entry; sdnn_set_weights keeps it current; not built from 4 GiB on).  Every row still
+ * adds its terms in storage order: same bits as the per-layer kernels.  AUTO builds the copy and uses the
+ * launch where it is faster (enough samples to fill the chip, or layers so small that per-layer launches
  * are bound by their latency); ON uses it whenever the copy exists; OFF never builds it. */
 #define SDNN_LDS_AUTO 0
 #define SDNN_LDS_ON 1

@@ -45,8 +45,6 @@
 // device helpers
 // ---------------------------------------------------------------------------
 
-#define LDS_T 4        // samples a workgroup of the LDS-resident forward carries
-#define LDS_MAX_N 4096 // its widest layer: 2 buffers x 4096 x 4 samples x 4 B = 128 KiB of the CU's 160 KiB
 #define WAVES_PER_BLOCK 4 // product kernels: 4 rows per workgroup (measured best of 1, 2, 4, 8)
 #define UPD_WAVES 1       // update kernel: one wavefront per workgroup (measured best of 1, 2, 4, 8)
 #define BLOCK_THREADS (64 * WAVES_PER_BLOCK)
@@ -537,144 +535,237 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm_panel(const SpmmArgs a, 
 // ---------------------------------------------------------------------------
 // K1f: the whole feed-forward sweep (Eq. 3 for l = 1..L) in one launch, for nets whose widest layer
 // fits in LDS.  The batch vectors are independent (they are the columns of X, Section 5.1), so a
-// workgroup takes LDS_T of them through all layers by itself: their activations live in two LDS
-// buffers ([neuron][LDS_T] floats, one read and one written per layer, a workgroup barrier between
-// layers), and only W is streamed, from its lane-major copy: lane r of a wavefront walks row r of a
-// block of 64 rows, one coalesced 8-byte load per entry, one 16-byte LDS read for the LDS_T
-// activations the entry points at.  Every lane adds its row's terms in storage order in fp64: the
-// same sums as k_spmm.  Slots past the end of a row that is shorter than its block hold weight 0
-// and add an exact zero.
+// workgroup of 16 wavefronts takes T of them (1, 2 or 4) through all layers by itself, their
+// activations in one LDS buffer of [position][T] floats, and only W is streamed, from a lane-major copy.
+//
+// Copy of W: the rows of a layer, longest first, in blocks of 64 that are dealt to the wavefronts; lane r of
+// a wavefront walks row r of the block.  A block's entries come in chunks of sixteen per lane (zero weights
+// past the end of a row add an exact zero), each as two halves of 3 KiB: the 64 lanes' eight 16-bit positions
+// (16 bytes a lane), then two times four weights (16 bytes a lane): 6 bytes per entry in coalesced 16-byte
+// loads.  The chunks of one wavefront follow each other through all its blocks and all layers; the half after
+// next, of whatever block or layer, is requested as soon as the registers of the current one are free, so nothing
+// waits at the head of a row or of a layer.
+// Activations: row (block j of wavefront w, lane r) of a layer sits at position 64 (16 j + w) + r; the columns of
+// the next layer are stored as those positions.  Every lane adds its row's terms in storage order in fp64 (the
+// same sums as k_spmm).  A layer's results wait in registers until every wavefront has read its operands, and
+// then replace them: one buffer instead of two, i.e. twice the samples or twice the width per CU.
+//
+// What bounds it, in clocks of a CU per wavefront-wide entry (T = 1 / 2 / 4): vector instructions 4 / 6.5 / 10.5 (one
+// address, one weight conversion, T conversions and T multiply-adds), LDS reads at random positions 7 / 7 / 13 (measured
+// with reads alone; conflict-free 2.5 / 3 / 4.6, but making them so gained only 2 to 5 %), the stream of W 6 at the L1's
+// 64 bytes per clock.  Measured 8.1 / 9 / 14.  Against the earlier version (two LDS buffers, four samples, 8-byte entries
+// requested block by block, up to 4096 neurons): 4096 neurons, 1024 samples, 120 layers 2.28 -> 1.69 ms; and against a
+// launch per layer: 16384 neurons, 4096 samples, 48 layers 40.6 -> 14.0 ms; 1024 neurons, 64 samples, 120 layers 561 ->
+// 305 us; 8192 neurons with 820 entries per row, 2048 samples, 6 layers 11.6 -> 7.7 ms.
 // ---------------------------------------------------------------------------
-#define LDS_WAVES 16 // wavefronts per workgroup: one workgroup per CU
-#define LDS_U 8      // entries in flight per lane
-#define LDS_BLOCKS (LDS_MAX_N / 64 / LDS_WAVES) // blocks of 64 rows a wavefront has per layer, at most
-template <int ACT>
+#define LDS_WAVES 16            // wavefronts per workgroup: one workgroup per CU
+#define LDS_CHUNK 16            // entries per lane and chunk, in two halves of eight
+#define LDS_HALF_BYTES 3072     // a half: 64 lanes x (eight positions, weights 0..3, weights 4..7), 16 bytes each
+#define LDS_CHUNK_BYTES (2 * LDS_HALF_BYTES)
+#define LDS_MAX_FLOATS 32768    // positions x samples a workgroup holds: 128 KiB, and 32 result registers per lane
+struct LmLayer {                // one layer as k_fwd_lds walks it
+    int32_t nb;                 // blocks per wavefront
+    int32_t cs;                 // its chunk table: wavefront w's blocks start at lm_cs[cs + w (nb + 1) + j]
+    int32_t pos;                // its first position in the row and bias tables
+    int32_t n_pos;              // positions: 1024 nb
+};
+typedef float f32x32 __attribute__((ext_vector_type(32)));
+
+// Ends a phase in which the wavefronts of the workgroup exchange data through LDS only: waits for the LDS accesses, not
+// for the requested chunks of W.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Byte address of a position in the activation buffer: (low or high half of `pair`) << shift, in one instruction.
+template <int HI> __device__ __forceinline__ unsigned lds_address(unsigned pair, unsigned shift)
+{
+    unsigned a;
+    if constexpr (HI)
+        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(a) : "v"(shift), "v"(pair));
+    else
+        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0" : "=v"(a) : "v"(shift), "v"(pair));
+    return a;
+}
+
+template <int T> struct LdsPiece;
+template <> struct LdsPiece<1> { typedef float type; };
+template <> struct LdsPiece<2> { typedef float type __attribute__((ext_vector_type(2))); };
+template <> struct LdsPiece<4> { typedef float type __attribute__((ext_vector_type(4))); };
+
+template <int T, int ACT>
 __global__ void __launch_bounds__(64 * LDS_WAVES)
-k_fwd_lds(const LayerDev *__restrict__ layers, int n_layers, const float *__restrict__ X0, float *__restrict__ XL,
-          int B, int buf_floats, float cap, int vec_io)
+k_fwd_lds(const LmLayer *__restrict__ tab, const int32_t *__restrict__ lm_cs, const uint4 *__restrict__ lm, unsigned lm_bytes,
+          const float *__restrict__ lm_bias, const int32_t *__restrict__ lm_row, int n_layers, int n0,
+          const float *__restrict__ X0, float *__restrict__ XL, int B, float cap, int vec_io)
 {
     extern __shared__ __attribute__((aligned(16))) float lds_act[];
-    float *in = lds_act, *out = lds_act + buf_floats;
+    typedef typename LdsPiece<T>::type piece; // the T samples of one position: one LDS access
+    typedef __attribute__((address_space(3))) piece *lds_ptr;
+    typedef __attribute__((address_space(3))) char *lds_bytes;
+    const lds_ptr act = (lds_ptr)(__attribute__((address_space(3))) float *)lds_act; // the kernel's only LDS: at address 0
+    unsigned shift = T == 1 ? 2 : T == 2 ? 3 : 4;
+    asm("" : "+v"(shift)); // kept in a register for lds_address
+    typedef const LmLayer __attribute__((address_space(4))) *tab_ptr;
+    typedef const int32_t __attribute__((address_space(4))) *cs_ptr;
+    const tab_ptr stab = (tab_ptr)tab;
+    const cs_ptr scs = (cs_ptr)lm_cs;
+
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int s0 = blockIdx.x * LDS_T;
-    const bool full = s0 + LDS_T <= B && vec_io; // all LDS_T samples exist and rows of X are 16-byte aligned
+    // neighbouring samples share cache lines of X: an XCD takes a contiguous stretch of them
+    const int nwg = (int)gridDim.x, per = nwg >> 3, wg = (int)blockIdx.x;
+    const int grp = wg < 8 * per ? (wg & 7) * per + (wg >> 3) : wg;
+    const int s0 = grp * T;
+    const bool full = s0 + T <= B && vec_io; // all T samples exist and T-float pieces of a row of X are aligned
 
-    // X_0: the workgroup's LDS_T columns (zeros past the end of the batch)
-    const int n0 = layers[0].n_in;
-    for (int i = tid; i < n0; i += 64 * LDS_WAVES) {
+    for (int i = tid; i < n0; i += 64 * LDS_WAVES) { // X_0 at its own positions (zeros past the end of the batch)
         const float *src = X0 + (size_t)i * B + s0;
-        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        piece v;
         if (full) {
-            v = *reinterpret_cast<const float4 *>(src);
+            v = *reinterpret_cast<const piece *>(src);
+        } else if constexpr (T == 1) {
+            v = s0 < B ? src[0] : 0.0f;
         } else {
-            if (s0 + 0 < B) v.x = src[0];
-            if (s0 + 1 < B) v.y = src[1];
-            if (s0 + 2 < B) v.z = src[2];
-            if (s0 + 3 < B) v.w = src[3];
+#pragma unroll
+            for (int t = 0; t < T; ++t) v[t] = s0 + t < B ? src[t] : 0.0f;
         }
-        *reinterpret_cast<float4 *>(in + LDS_T * i) = v;
+        act[i] = v;
     }
-    __syncthreads();
 
-    // A wavefront takes the blocks wave, wave + LDS_WAVES, ... of every layer: at most LDS_BLOCKS of them.  Where
-    // they lie, their rows and biases do not depend on the activations, so all of it is requested at once, a layer
-    // ahead: a layer then starts with its first entries, not with a chain of dependent loads per block.
-    int off_n[LDS_BLOCKS], end_n[LDS_BLOCKS], row_n[LDS_BLOCKS];
-    float bias_n[LDS_BLOCKS];
-    auto request_meta = [&](int l) {
-        const LayerDev &L = layers[l];
-#pragma unroll
-        for (int j = 0; j < LDS_BLOCKS; ++j) {
-            const int b = wave + LDS_WAVES * j;
-            off_n[j] = end_n[j] = 0;
-            row_n[j] = -1;
-            bias_n[j] = 0.0f;
-            if (b < L.n_blocks) {
-                off_n[j] = L.lm_off[b];
-                end_n[j] = L.lm_off[b + 1];
-                row_n[j] = L.lm_row[b * 64 + lane];
-                bias_n[j] = L.lm_bias[b * 64 + lane];
-            }
-        }
+    // the wavefront's place in the copy of W, in bytes (the copy is smaller than 4 GiB), goes into the loads as a scalar
+    const __amdgpu_buffer_rsrc_t rlm = make_rsrc((const float *)lm, lm_bytes);
+    unsigned at = (unsigned)scs[stab[0].cs + wave * (stab[0].nb + 1)] * LDS_CHUNK_BYTES;
+    const int lane16 = 16 * lane;
+    struct Half { u32x4 c, wa, wb; } ha, hb;
+    auto request = [&](Half &h) {
+        h.c = __builtin_amdgcn_raw_buffer_load_b128(rlm, lane16, (int)at, 0);
+        h.wa = __builtin_amdgcn_raw_buffer_load_b128(rlm, lane16 + 1024, (int)at, 0);
+        h.wb = __builtin_amdgcn_raw_buffer_load_b128(rlm, lane16 + 2048, (int)at, 0);
+        at += LDS_HALF_BYTES;
     };
-    request_meta(0);
+    request(ha);
+    request(hb);
+    lds_barrier();
+
     for (int l = 0; l < n_layers; ++l) {
-        const LayerDev &L = layers[l];
-        const bool last = l == n_layers - 1;
-        int off_c[LDS_BLOCKS], end_c[LDS_BLOCKS], row_c[LDS_BLOCKS];
-        float bias_c[LDS_BLOCKS];
+        const int nb = stab[l].nb, cs0 = stab[l].cs + wave * (nb + 1), pos0 = stab[l].pos + 64 * wave + lane;
+        f32x32 res;
+        for (int j = 0; j < nb; ++j) {
+            const int n = scs[cs0 + j + 1] - scs[cs0 + j];
+            const float bias = lm_bias[pos0 + 1024 * j];
+            double acc[T];
 #pragma unroll
-        for (int j = 0; j < LDS_BLOCKS; ++j) { off_c[j] = off_n[j]; end_c[j] = end_n[j]; row_c[j] = row_n[j]; bias_c[j] = bias_n[j]; }
-        if (!last) request_meta(l + 1);
+            for (int t = 0; t < T; ++t) acc[t] = 0.0;
+            auto take = [&](Half &h) { // eight entries; then their registers are free for the half after next
+                unsigned a[8];
+                double w[8];
+                piece x[8];
 #pragma unroll
-        for (int j = 0; j < LDS_BLOCKS; ++j) {
-            if (wave + LDS_WAVES * j >= L.n_blocks) break;
-            const int off = off_c[j];
-            const int K = (end_c[j] - off) >> 6; // entries of the block's longest row
-            const int row = row_c[j];
-            const float bias = bias_c[j];
-            const int2 *__restrict__ e = L.lm + off + lane;
-            double acc[LDS_T];
-#pragma unroll
-            for (int t = 0; t < LDS_T; ++t) acc[t] = 0.0;
-            for (int k0 = 0; k0 < K; k0 += LDS_U) {
-                int2 ent[LDS_U];
-                float4 x[LDS_U];
-                if (k0 + LDS_U <= K) {
-#pragma unroll
-                    for (int u = 0; u < LDS_U; ++u) ent[u] = e[(k0 + u) * 64];
-                } else { // the block's last entries: the slots past them add an exact zero
-#pragma unroll
-                    for (int u = 0; u < LDS_U; ++u) ent[u] = k0 + u < K ? e[(k0 + u) * 64] : make_int2(0, 0);
+                for (int u = 0; u < 4; ++u) {
+                    a[2 * u] = lds_address<0>(h.c[u], shift);
+                    a[2 * u + 1] = lds_address<1>(h.c[u], shift);
                 }
 #pragma unroll
-                for (int u = 0; u < LDS_U; ++u) x[u] = *reinterpret_cast<const float4 *>(in + LDS_T * ent[u].x);
+                for (int u = 0; u < 8; ++u) x[u] = *(lds_ptr)((lds_bytes)0 + a[u]);
 #pragma unroll
-                for (int u = 0; u < LDS_U; ++u) {
-                    const double w = (double)__int_as_float(ent[u].y);
-                    acc[0] = fma(w, (double)x[u].x, acc[0]);
-                    acc[1] = fma(w, (double)x[u].y, acc[1]);
-                    acc[2] = fma(w, (double)x[u].z, acc[2]);
-                    acc[3] = fma(w, (double)x[u].w, acc[3]);
+                for (int u = 0; u < 4; ++u) {
+                    w[u] = (double)__uint_as_float(h.wa[u]);
+                    w[u + 4] = (double)__uint_as_float(h.wb[u]);
                 }
-            }
-            if (row >= 0) {
-                const double bd = (double)bias;
-                const float4 o = make_float4(act_apply(ACT, acc[0] + bd, cap), act_apply(ACT, acc[1] + bd, cap),
-                                             act_apply(ACT, acc[2] + bd, cap), act_apply(ACT, acc[3] + bd, cap));
-                if (!last) {
-                    *reinterpret_cast<float4 *>(out + LDS_T * row) = o;
-                } else {
-                    float *dst = XL + (size_t)row * B + s0;
-                    if (full) {
-                        *reinterpret_cast<float4 *>(dst) = o;
-                    } else {
-                        if (s0 + 0 < B) dst[0] = o.x;
-                        if (s0 + 1 < B) dst[1] = o.y;
-                        if (s0 + 2 < B) dst[2] = o.z;
-                        if (s0 + 3 < B) dst[3] = o.w;
+                request(h);
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int t = 0; t < T; ++t) {
+                        float xv;
+                        if constexpr (T == 1) xv = x[u];
+                        else xv = x[u][t];
+                        acc[t] = fma(w[u], (double)xv, acc[t]);
                     }
+            };
+            for (int i = 0; i < n; ++i) {
+                take(ha);
+                take(hb);
+            }
+            const double bd = (double)bias;
+#pragma unroll
+            for (int t = 0; t < T; ++t) res[j * T + t] = act_apply(ACT, acc[t] + bd, cap);
+        }
+        auto result = [&](int j) {
+            piece v;
+            if constexpr (T == 1) v = res[j];
+            else {
+#pragma unroll
+                for (int t = 0; t < T; ++t) v[t] = res[j * T + t];
+            }
+            return v;
+        };
+        if (l == n_layers - 1) {
+            for (int j = 0; j < nb; ++j) {
+                const int row = lm_row[pos0 + 1024 * j];
+                if (row < 0) continue;
+                float *dst = XL + (size_t)row * B + s0;
+                const piece v = result(j);
+                if (full) {
+                    *reinterpret_cast<piece *>(dst) = v;
+                } else if constexpr (T == 1) {
+                    if (s0 < B) dst[0] = v;
+                } else {
+#pragma unroll
+                    for (int t = 0; t < T; ++t)
+                        if (s0 + t < B) dst[t] = v[t];
                 }
             }
+            return;
         }
-        __syncthreads(); // the layer is complete before anyone reads it, and read before it is overwritten
-        float *t = in; in = out; out = t;
+        lds_barrier(); // every wavefront has read its operands
+        for (int j = 0; j < nb; ++j) act[64 * (LDS_WAVES * j + wave) + lane] = result(j);
+        lds_barrier(); // the layer is complete before anyone reads it
     }
 }
 
-// Rewrites the weights and biases of a layer's lane-major copy from the CSR values and the bias array
-// (after sdnn_set_weights).
-__global__ void __launch_bounds__(64) k_lm_refresh(const LayerDev *__restrict__ layer)
+// Writes a layer's part of the lane-major copy from its CSR arrays: biases and weights, and with prev_pos (the position of
+// every neuron of the layer below, NULL for the first layer: its own index) also the positions (prev_pos is looked at only
+// if with_cols).  One wavefront per block of 64 rows: grid = (blocks per wavefront, 16 wavefronts).
+__global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ layer, const LmLayer *__restrict__ tab,
+                                                const int32_t *__restrict__ lm_cs, uint4 *__restrict__ lm,
+                                                float *__restrict__ lm_bias, const int32_t *__restrict__ lm_row,
+                                                const int32_t *__restrict__ prev_pos, int with_cols)
 {
     const LayerDev &L = *layer;
-    const int b = blockIdx.x, lane = threadIdx.x;
-    const int row = L.lm_row[b * 64 + lane];
-    if (row < 0) return;
-    const int off = L.lm_off[b];
-    const int beg = L.row_ptr[row], len = L.row_ptr[row + 1] - beg;
-    for (int k = 0; k < len; ++k) L.lm[off + 64 * k + lane].y = __float_as_int(L.vals[beg + k]);
-    L.lm_bias[b * 64 + lane] = L.bias[row];
+    const int j = blockIdx.x, w = blockIdx.y, lane = threadIdx.x, nb = tab->nb;
+    const int at = tab->pos + 64 * (LDS_WAVES * j + w) + lane;
+    const int row = lm_row[at];
+    const int c0 = lm_cs[tab->cs + w * (nb + 1) + j], c1 = lm_cs[tab->cs + w * (nb + 1) + j + 1];
+    int beg = 0, end = 0;
+    float bias = 0.0f;
+    if (row >= 0) {
+        beg = L.row_ptr[row];
+        end = L.row_ptr[row + 1];
+        bias = L.bias[row];
+    }
+    lm_bias[at] = bias;
+    for (int hf = 0; hf < 2 * (c1 - c0); ++hf) {
+        uint4 *o = lm + ((size_t)c0 * LDS_CHUNK_BYTES + (size_t)hf * LDS_HALF_BYTES) / 16 + lane;
+        unsigned pk[4], wt[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int e = beg + hf * 8 + k;
+            unsigned pos = 0;
+            wt[k] = 0;
+            if (e < end) {
+                wt[k] = __float_as_uint(L.vals[e]);
+                if (with_cols) pos = (unsigned)(prev_pos ? prev_pos[L.col_idx[e]] : L.col_idx[e]);
+            }
+            if (k & 1) pk[k >> 1] |= pos << 16;
+            else pk[k >> 1] = pos;
+        }
+        if (with_cols) o[0] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+        o[64] = make_uint4(wt[0], wt[1], wt[2], wt[3]);
+        o[128] = make_uint4(wt[4], wt[5], wt[6], wt[7]);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1603,8 +1694,14 @@ struct sdnn_net {
     int occ_panel[2][4] = {};     // the same for k_spmm_panel<R,MODE>, R = 1, 2, 4, 8
     std::vector<int32_t> max_len[2]; // per layer: longest row of W (0) and of W^T (1)
     std::vector<char> clustered[2];  // per layer: reorder_rows found clusters in W (0), in W^T (1)
-    bool lds_ready = false;          // every layer has its lane-major copy (k_fwd_lds can run)
-    bool lds_attr_set = false;       // the kernels' dynamic LDS limit has been raised
+    uint4 *lm = nullptr;             // lane-major copy of W for k_fwd_lds, NULL: there is none
+    int32_t *lm_cs = nullptr, *lm_row = nullptr;
+    float *lm_bias = nullptr;
+    LmLayer *lm_layers = nullptr;
+    std::vector<int32_t> lm_nb;      // blocks per wavefront of every layer
+    size_t lm_chunks = 0;
+    int32_t lm_max_pos = 0;
+    bool lds_attr_set[3] = {};       // the dynamic LDS limit of k_fwd_lds<1 << k> has been raised
     int grad_parts = 0;           // > 0: the last backward pass left the entries' gradient in G[0..grad_parts)
     bool vals_t_stale = false;    // the CSR values were changed by something that does not maintain vals_t
     hipStream_t side = nullptr;   // second stream for the other half of the batch (small layers)
@@ -1672,9 +1769,11 @@ static inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 struct Plan {
     struct PerLayer {
         size_t row_ptr, col_idx, vals, bias, t_row_ptr, t_row_idx, t_perm, sched, t_sched, X, D, G[2], vals_t, mid_slot, mid_dst, mid_loc, mid, t_col;
-        size_t lm, lm_off, lm_row, lm_bias, lm_entries, lm_blocks;
     };
     std::vector<PerLayer> pl;
+    std::vector<LmLayer> lm_tab; // empty: no lane-major copy
+    size_t lm_n_chunks = 0, lm_n_cs = 0, lm_n_pos = 0, lm_n_rows = 0; // sizes of its arrays, all layers together
+    size_t lm = 0, lm_cs = 0, lm_layers = 0, lm_row = 0, lm_bias = 0, lm_pos = 0;
     size_t table = 0, x0 = 0, ping = 0, pong = 0, flags[2] = {0, 0}, map[2] = {0, 0}, n_live[2] = {0, 0}, total = 0;
 };
 
@@ -1724,26 +1823,63 @@ static bool grad_buffers_wanted(const sdnn_layer *layers, int32_t n_layers, cons
     return rows >= (int64_t)4096 * n_layers && (nnz < 128 * rows || cfg->max_batch <= 256);
 }
 
-// The LDS-resident forward (k_fwd_lds) carries LDS_T samples through all layers with two activation
-// buffers of (widest layer) x LDS_T floats in LDS; it is set up for inference nets whose widest
-// layer fits.
+// Chunks of a layer's lane-major copy: its rows, longest first, in blocks of 64, each as deep as its first row.
+static size_t lm_chunks(const sdnn_layer &y)
+{
+    std::vector<int32_t> rows_of_len; // a histogram is enough: the first rows of the blocks are rows 0, 64, 128, ... by length
+    for (int32_t r = 0; r < y.n_out; ++r) {
+        const size_t len = (size_t)(y.row_ptr[r + 1] - y.row_ptr[r]);
+        if (len >= rows_of_len.size()) rows_of_len.resize(len + 1, 0);
+        rows_of_len[len]++;
+    }
+    size_t total = 0;
+    int64_t before = 0; // rows longer than len
+    for (size_t len = rows_of_len.size(); len-- > 0;) {
+        const int64_t after = before + rows_of_len[len];
+        const int64_t firsts = (after + 63) / 64 - (before + 63) / 64; // multiples of 64 in [before, after)
+        total += (size_t)firsts * ((len + LDS_CHUNK - 1) / LDS_CHUNK);
+        before = after;
+    }
+    return total;
+}
+
+// The LDS-resident forward (k_fwd_lds) carries samples through all layers with their activations in LDS; it is set up
+// for inference nets whose widest layer fits with at least one sample.
 static bool lds_forward_wanted(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg)
 {
     if (cfg->training || cfg->lds_forward == SDNN_LDS_OFF) return false;
-    for (int32_t l = 0; l < n_layers; ++l)
-        if (layers[l].n_out > LDS_MAX_N || layers[l].n_in > LDS_MAX_N) return false;
-    return true;
+    size_t chunks = 1;
+    for (int32_t l = 0; l < n_layers; ++l) {
+        if (layers[l].n_out > LDS_MAX_FLOATS || layers[l].n_in > LDS_MAX_FLOATS) return false;
+        chunks += lm_chunks(layers[l]);
+    }
+    return chunks * LDS_CHUNK_BYTES < ((size_t)1 << 32); // the kernel addresses the copy with 32-bit offsets
 }
 
-// Row lengths, longest first: block b of the lane-major copy is as deep as its first row.
-static size_t lm_padded_entries(const sdnn_layer &y, std::vector<int32_t> &lens)
+// One layer's blocks dealt to the wavefronts: the deepest first, each to the wavefront with the fewest chunks so far that
+// has room (at most tab.nb blocks each).  Fills the layer's part of the row table (row[position], -1 where there is none),
+// of the position table (pos[row]) and of the chunk table, the latter with the blocks' depths for now.
+static void lm_deal_blocks(const sdnn_layer &y, const LmLayer &tab, int32_t *row, int32_t *pos, int32_t *cs)
 {
-    lens.resize((size_t)y.n_out);
-    for (int32_t r = 0; r < y.n_out; ++r) lens[r] = y.row_ptr[r + 1] - y.row_ptr[r];
-    std::sort(lens.begin(), lens.end(), std::greater<int32_t>());
-    size_t total = 0;
-    for (int32_t r = 0; r < y.n_out; r += 64) total += 64 * (size_t)lens[r];
-    return total;
+    std::vector<int32_t> order((size_t)y.n_out);
+    sdnn_row_schedule(y.n_out, y.row_ptr, order.data());
+    std::fill(row, row + tab.n_pos, -1);
+    std::fill(cs, cs + LDS_WAVES * (tab.nb + 1), 0);
+    int32_t load[LDS_WAVES] = {}, used[LDS_WAVES] = {};
+    for (int32_t r0 = 0; r0 < y.n_out; r0 += 64) {
+        const int32_t depth = (y.row_ptr[order[r0] + 1] - y.row_ptr[order[r0]] + LDS_CHUNK - 1) / LDS_CHUNK;
+        int w = -1;
+        for (int k = 0; k < LDS_WAVES; ++k)
+            if (used[k] < tab.nb && (w < 0 || load[k] < load[w])) w = k;
+        const int32_t j = used[w]++;
+        load[w] += depth;
+        cs[w * (tab.nb + 1) + j] = depth;
+        for (int32_t k = 0; k < 64 && r0 + k < y.n_out; ++k) {
+            const int32_t at = 64 * (LDS_WAVES * j + w) + k;
+            row[at] = order[(size_t)(r0 + k)];
+            pos[order[(size_t)(r0 + k)]] = at;
+        }
+    }
 }
 
 static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, Plan &pl)
@@ -1776,12 +1912,19 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
         const sdnn_layer &y = layers[l];
         nnz[l] = (size_t)y.row_ptr[y.n_out];
         Plan::PerLayer &q = pl.pl[l];
+        q.t_row_ptr = q.t_row_idx = q.t_perm = q.t_sched = 0;
         q.X = q.D = q.G[0] = q.G[1] = q.vals_t = q.mid_slot = q.mid_dst = q.mid_loc = q.mid = q.t_col = 0;
-        q.lm = q.lm_off = q.lm_row = q.lm_bias = q.lm_entries = q.lm_blocks = 0;
         if (lm) {
-            std::vector<int32_t> lens;
-            q.lm_entries = lm_padded_entries(y, lens);
-            q.lm_blocks = ((size_t)y.n_out + 63) / 64;
+            LmLayer t;
+            t.nb = ((y.n_out + 63) / 64 + LDS_WAVES - 1) / LDS_WAVES;
+            t.n_pos = 64 * LDS_WAVES * t.nb;
+            t.cs = (int32_t)pl.lm_n_cs;
+            t.pos = (int32_t)pl.lm_n_pos;
+            pl.lm_tab.push_back(t);
+            pl.lm_n_cs += (size_t)LDS_WAVES * (size_t)(t.nb + 1);
+            pl.lm_n_pos += (size_t)t.n_pos;
+            pl.lm_n_rows += (size_t)y.n_out;
+            pl.lm_n_chunks += lm_chunks(y);
         }
         max_n = std::max(max_n, (size_t)std::max(y.n_out, y.n_in));
     }
@@ -1796,18 +1939,20 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
     PLAN_KIND(col_idx, 4 * nnz[l])
     PLAN_KIND(vals, 4 * nnz[l])
     PLAN_KIND(bias, 4 * (size_t)y.n_out)
-    PLAN_KIND(t_row_ptr, 4 * ((size_t)y.n_in + 1))
-    PLAN_KIND(t_row_idx, 4 * nnz[l])
-    PLAN_KIND(t_perm, 4 * nnz[l])
     PLAN_KIND(sched, 16 * (size_t)y.n_out)
-    PLAN_KIND(t_sched, 16 * (size_t)y.n_in)
     if (lm) {
-        PLAN_KIND(lm, 8 * q.lm_entries)
-        PLAN_KIND(lm_off, 4 * (q.lm_blocks + 1))
-        PLAN_KIND(lm_row, 4 * 64 * q.lm_blocks)
-        PLAN_KIND(lm_bias, 4 * 64 * q.lm_blocks)
+        pl.lm = take(LDS_CHUNK_BYTES * (pl.lm_n_chunks + 1)); // a wavefront requests one chunk past its last
+        pl.lm_cs = take(4 * pl.lm_n_cs);
+        pl.lm_layers = take(sizeof(LmLayer) * (size_t)n_layers);
+        pl.lm_row = take(4 * pl.lm_n_pos);
+        pl.lm_bias = take(4 * pl.lm_n_pos);
+        pl.lm_pos = take(4 * pl.lm_n_rows);
     }
     if (cfg->training) {
+        PLAN_KIND(t_row_ptr, 4 * ((size_t)y.n_in + 1))
+        PLAN_KIND(t_row_idx, 4 * nnz[l])
+        PLAN_KIND(t_perm, 4 * nnz[l])
+        PLAN_KIND(t_sched, 16 * (size_t)y.n_in)
         pl.x0 = take(4 * (size_t)layers[0].n_in * mb);
         PLAN_KIND(X, 4 * (size_t)y.n_out * mb)
         PLAN_KIND(D, 4 * (size_t)y.n_out * mb)
@@ -1850,6 +1995,16 @@ extern "C" int sdnn_workspace_bytes(const sdnn_layer *layers, int32_t n_layers,
         return fail(nullptr, SDNN_ENOMEM, "host allocation failed");
     }
     *bytes = pl.total;
+    return SDNN_OK;
+}
+
+// (Re)writes layer l's part of the lane-major copy from its CSR arrays.
+static int launch_lm_fill(sdnn_net *net, int l, const int32_t *prev_pos, int with_cols, hipStream_t stream)
+{
+    if (net->lm_nb[l] == 0) return SDNN_OK;
+    hipLaunchKernelGGL(k_lm_fill, dim3((unsigned)net->lm_nb[l], LDS_WAVES), dim3(64), 0, stream, net->d_layers + l, net->lm_layers + l,
+                       net->lm_cs, net->lm, net->lm_bias, net->lm_row, prev_pos, with_cols);
+    HIP_TRY(net, hipGetLastError());
     return SDNN_OK;
 }
 
@@ -1906,29 +2061,39 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
         std::vector<int32_t> mid_dst;
         std::vector<uint16_t> mid_slot, mid_loc;
         std::vector<int32_t> t_col;
-        std::vector<int2> lm;
-        std::vector<int32_t> lm_off, lm_row;
-        std::vector<float> lm_bias;
         int32_t max_len = 0, t_max_len = 0;
         bool clustered = false, t_clustered = false; // reorder_rows found rows that share columns
         int rc = SDNN_OK;
     };
-    const bool want_lm = lds_forward_wanted(layers, n_layers, cfg);
+    const bool want_lm = !pl.lm_tab.empty();
+    std::vector<int32_t> lm_cs, lm_row, lm_pos;
+    std::vector<size_t> lm_first_row((size_t)n_layers, 0); // where a layer's part of lm_pos starts
+    try {
+        lm_cs.resize(pl.lm_n_cs);
+        lm_row.resize(pl.lm_n_pos);
+        lm_pos.resize(pl.lm_n_rows);
+    } catch (...) {
+        return fail_free(fail(nullptr, SDNN_ENOMEM, "host allocation failed"));
+    }
+    for (int32_t l = 1; l < n_layers; ++l) lm_first_row[l] = lm_first_row[l - 1] + (size_t)layers[l - 1].n_out;
+    const bool training = cfg->training != 0; // the transposed index serves the backward pass only
     const bool gw_ = grad_buffers_wanted(layers, n_layers, cfg);
     auto prepare = [&](int32_t l, HostIdx &h) {
         try {
             const sdnn_layer &y = layers[l];
             const size_t nnz = (size_t)y.row_ptr[y.n_out];
-            h.t_row_ptr.resize((size_t)y.n_in + 1);
-            h.t_row_idx.resize(nnz);
-            h.t_perm.resize(nnz);
             h.order.resize(y.n_out);
-            h.t_order.resize(y.n_in);
             h.sched.resize(y.n_out);
-            h.t_sched.resize(y.n_in);
-            h.rc = sdnn_transpose_pattern(y.n_out, y.n_in, y.row_ptr, y.col_idx, h.t_row_ptr.data(),
-                                          h.t_row_idx.data(), h.t_perm.data());
-            if (h.rc) return;
+            if (training) {
+                h.t_row_ptr.resize((size_t)y.n_in + 1);
+                h.t_row_idx.resize(nnz);
+                h.t_perm.resize(nnz);
+                h.t_order.resize(y.n_in);
+                h.t_sched.resize(y.n_in);
+                h.rc = sdnn_transpose_pattern(y.n_out, y.n_in, y.row_ptr, y.col_idx, h.t_row_ptr.data(),
+                                              h.t_row_idx.data(), h.t_perm.data());
+                if (h.rc) return;
+            }
             if (cfg->reorder_rows) {
                 // rows that share columns become neighbours and are dealt to one XCD
                 const size_t n_max = (size_t)std::max(y.n_out, y.n_in);
@@ -1943,18 +2108,20 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                                          cluster_of.data());
                 if (!h.rc) h.clustered = found(y.n_out);
                 if (!h.rc) h.rc = sdnn_deal_rows_to_xcds(y.n_out, y.row_ptr, clustered.data(), h.order.data());
-                if (!h.rc) h.rc = sdnn_cluster_rows(y.n_in, y.n_out, h.t_row_ptr.data(), h.t_row_idx.data(), SDNN_CLUSTER_ROWS,
-                                                    clustered.data(), cluster_of.data());
-                if (!h.rc) h.t_clustered = found(y.n_in);
-                if (!h.rc) h.rc = sdnn_deal_rows_to_xcds(y.n_in, h.t_row_ptr.data(), clustered.data(), h.t_order.data());
+                if (training) {
+                    if (!h.rc) h.rc = sdnn_cluster_rows(y.n_in, y.n_out, h.t_row_ptr.data(), h.t_row_idx.data(), SDNN_CLUSTER_ROWS,
+                                                        clustered.data(), cluster_of.data());
+                    if (!h.rc) h.t_clustered = found(y.n_in);
+                    if (!h.rc) h.rc = sdnn_deal_rows_to_xcds(y.n_in, h.t_row_ptr.data(), clustered.data(), h.t_order.data());
+                }
                 if (h.rc) return;
             } else {
                 sdnn_row_schedule(y.n_out, y.row_ptr, h.order.data());
-                sdnn_row_schedule(y.n_in, h.t_row_ptr.data(), h.t_order.data());
+                if (training) sdnn_row_schedule(y.n_in, h.t_row_ptr.data(), h.t_order.data());
             }
             for (int32_t r = 0; r < y.n_out; ++r)
                 h.sched[r] = make_int4(h.order[r], y.row_ptr[h.order[r]], y.row_ptr[h.order[r] + 1], 0);
-            for (int32_t r = 0; r < y.n_in; ++r)
+            for (size_t r = 0; r < h.t_sched.size(); ++r)
                 h.t_sched[r] = make_int4(h.t_order[r], h.t_row_ptr[h.t_order[r]], h.t_row_ptr[h.t_order[r] + 1], 0);
             if (gw_ && cfg->max_batch == 1) { // one sample per step: the fused sweep looks up each entry's row of W^T
                 h.t_col.resize(nnz);
@@ -1992,33 +2159,13 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 }
             }
             if (want_lm) {
-                // lane-major copy: always in longest-first order, whatever the row schedule is
-                std::vector<int32_t> by_len((size_t)y.n_out);
-                sdnn_row_schedule(y.n_out, y.row_ptr, by_len.data());
-                const int32_t nb = (y.n_out + 63) / 64;
-                h.lm_off.assign((size_t)nb + 1, 0);
-                h.lm_row.assign((size_t)nb * 64, -1);
-                h.lm_bias.assign((size_t)nb * 64, 0.0f);
-                for (int32_t b = 0; b < nb; ++b) {
-                    const int32_t first = by_len[(size_t)b * 64];
-                    h.lm_off[b + 1] = h.lm_off[b] + 64 * (y.row_ptr[first + 1] - y.row_ptr[first]);
-                }
-                h.lm.assign((size_t)h.lm_off[nb], make_int2(0, 0)); // padding: column 0, weight +0.0
-                for (int32_t b = 0; b < nb; ++b)
-                    for (int32_t lane = 0; lane < 64 && b * 64 + lane < y.n_out; ++lane) {
-                        const int32_t row = by_len[(size_t)b * 64 + lane];
-                        h.lm_row[(size_t)b * 64 + lane] = row;
-                        if (y.bias) h.lm_bias[(size_t)b * 64 + lane] = y.bias[row];
-                        for (int32_t p = y.row_ptr[row]; p < y.row_ptr[row + 1]; ++p) {
-                            int32_t bits;
-                            memcpy(&bits, &y.values[p], 4);
-                            h.lm[(size_t)h.lm_off[b] + 64 * (size_t)(p - y.row_ptr[row]) + lane] = make_int2(y.col_idx[p], bits);
-                        }
-                    }
+                const LmLayer &t = pl.lm_tab[l];
+                lm_deal_blocks(y, t, lm_row.data() + t.pos, lm_pos.data() + lm_first_row[l], lm_cs.data() + t.cs);
             }
             h.max_len = h.t_max_len = 0;
             for (int32_t r = 0; r < y.n_out; ++r) h.max_len = std::max(h.max_len, y.row_ptr[r + 1] - y.row_ptr[r]);
-            for (int32_t r = 0; r < y.n_in; ++r) h.t_max_len = std::max(h.t_max_len, h.t_row_ptr[r + 1] - h.t_row_ptr[r]);
+            if (training)
+                for (int32_t r = 0; r < y.n_in; ++r) h.t_max_len = std::max(h.t_max_len, h.t_row_ptr[r + 1] - h.t_row_ptr[r]);
         } catch (...) {
             h.rc = SDNN_ENOMEM;
         }
@@ -2072,11 +2219,11 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 d.col_idx = (const int32_t *)(base + q.col_idx);
                 d.vals = (float *)(base + q.vals);
                 d.bias = (float *)(base + q.bias);
-                d.t_row_ptr = (const int32_t *)(base + q.t_row_ptr);
-                d.t_row_idx = (const int32_t *)(base + q.t_row_idx);
-                d.t_perm = (const int32_t *)(base + q.t_perm);
+                d.t_row_ptr = training ? (const int32_t *)(base + q.t_row_ptr) : nullptr;
+                d.t_row_idx = training ? (const int32_t *)(base + q.t_row_idx) : nullptr;
+                d.t_perm = training ? (const int32_t *)(base + q.t_perm) : nullptr;
                 d.sched = (const int4 *)(base + q.sched);
-                d.t_sched = (const int4 *)(base + q.t_sched);
+                d.t_sched = training ? (const int4 *)(base + q.t_sched) : nullptr;
                 d.X = cfg->training ? (float *)(base + q.X) : nullptr;
                 d.D = cfg->training ? (float *)(base + q.D) : nullptr;
                 d.G[0] = gw ? (float *)(base + q.G[0]) : nullptr;
@@ -2087,12 +2234,6 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 d.mid_loc = gw ? (const uint16_t *)(base + q.mid_loc) : nullptr;
                 d.mid = gw ? (float *)(base + q.mid) : nullptr;
                 d.t_col = gw && cfg->max_batch == 1 ? (const int32_t *)(base + q.t_col) : nullptr;
-                d.lm = want_lm ? (int2 *)(base + q.lm) : nullptr;
-                d.lm_off = want_lm ? (const int32_t *)(base + q.lm_off) : nullptr;
-                d.lm_row = want_lm ? (const int32_t *)(base + q.lm_row) : nullptr;
-                d.lm_bias = want_lm ? (float *)(base + q.lm_bias) : nullptr;
-                d.n_blocks = want_lm ? (int32_t)q.lm_blocks : 0;
-                d.pad2_ = 0;
                 d.X_prev = !cfg->training ? nullptr
                            : l == 0       ? (float *)(base + pl.x0)
                                           : net->layers[l - 1].X;
@@ -2105,29 +2246,57 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 UP(d.col_idx, y.col_idx, 4 * nnz);
                 UP(d.vals, y.values, 4 * nnz);
                 UP(d.bias, y.bias ? y.bias : zeros.data(), 4 * (size_t)y.n_out);
-                UP(d.t_row_ptr, h.t_row_ptr.data(), 4 * ((size_t)y.n_in + 1));
-                UP(d.t_row_idx, h.t_row_idx.data(), 4 * nnz);
-                UP(d.t_perm, h.t_perm.data(), 4 * nnz);
                 UP(d.sched, h.sched.data(), 16 * (size_t)y.n_out);
-                UP(d.t_sched, h.t_sched.data(), 16 * (size_t)y.n_in);
+                if (training) {
+                    UP(d.t_row_ptr, h.t_row_ptr.data(), 4 * ((size_t)y.n_in + 1));
+                    UP(d.t_row_idx, h.t_row_idx.data(), 4 * nnz);
+                    UP(d.t_perm, h.t_perm.data(), 4 * nnz);
+                    UP(d.t_sched, h.t_sched.data(), 16 * (size_t)y.n_in);
+                }
                 if (gw) UP(d.vals_t, h.vals_t.data(), 4 * nnz);
                 if (gw) UP(d.mid_slot, h.mid_slot.data(), 2 * nnz);
                 if (gw) UP(d.mid_dst, h.mid_dst.data(), 4 * nnz);
                 if (gw) UP(d.mid_loc, h.mid_loc.data(), 2 * nnz);
                 if (d.t_col) UP(d.t_col, h.t_col.data(), 4 * nnz);
-                if (want_lm) {
-                    if (h.lm.size() != q.lm_entries)
-                        return fail_free(fail(nullptr, SDNN_EINVAL, "layer %d: lane-major copy does not match its plan", l + 1));
-                    UP(d.lm, h.lm.data(), 8 * h.lm.size());
-                    UP(d.lm_off, h.lm_off.data(), 4 * h.lm_off.size());
-                    UP(d.lm_row, h.lm_row.data(), 4 * h.lm_row.size());
-                    UP(d.lm_bias, h.lm_bias.data(), 4 * h.lm_bias.size());
-                }
             }
             SYNC(); // the group's host arrays are reused by the next group
         }
         net->d_layers = (LayerDev *)(base + pl.table);
         UP(net->d_layers, net->layers.data(), sizeof(LayerDev) * (size_t)n_layers);
+        if (want_lm) {
+            // from the blocks' depths to where their chunks lie: one wavefront's chunks follow each other through all layers
+            int64_t at = 0;
+            for (int w = 0; w < LDS_WAVES; ++w)
+                for (int32_t l = 0; l < n_layers; ++l) {
+                    const LmLayer &t = pl.lm_tab[l];
+                    int32_t *c = lm_cs.data() + t.cs + w * (t.nb + 1);
+                    for (int32_t j = 0; j <= t.nb; ++j) {
+                        const int32_t depth = c[j];
+                        c[j] = (int32_t)at;
+                        if (j < t.nb) at += depth;
+                    }
+                }
+            if ((size_t)at != pl.lm_n_chunks)
+                return fail_free(fail(nullptr, SDNN_EINVAL, "lane-major copy does not match its plan"));
+            net->lm = (uint4 *)(base + pl.lm);
+            net->lm_cs = (int32_t *)(base + pl.lm_cs);
+            net->lm_layers = (LmLayer *)(base + pl.lm_layers);
+            net->lm_row = (int32_t *)(base + pl.lm_row);
+            net->lm_bias = (float *)(base + pl.lm_bias);
+            net->lm_chunks = pl.lm_n_chunks;
+            for (const LmLayer &t : pl.lm_tab) net->lm_nb.push_back(t.nb);
+            net->lm_max_pos = layers[0].n_in;
+            for (const LmLayer &t : pl.lm_tab) net->lm_max_pos = std::max(net->lm_max_pos, t.n_pos);
+            int32_t *d_pos = (int32_t *)(base + pl.lm_pos);
+            UP(net->lm_cs, lm_cs.data(), 4 * lm_cs.size());
+            UP(net->lm_layers, pl.lm_tab.data(), sizeof(LmLayer) * (size_t)n_layers);
+            UP(net->lm_row, lm_row.data(), 4 * lm_row.size());
+            UP(d_pos, lm_pos.data(), 4 * lm_pos.size());
+            for (int32_t l = 0; l < n_layers; ++l) {
+                const int rc_fill = launch_lm_fill(net, l, l > 0 ? d_pos + lm_first_row[l - 1] : nullptr, 1, stream);
+                if (rc_fill) return fail_free(rc_fill);
+            }
+        }
         SYNC();
     } catch (...) {
         return fail_free(fail(nullptr, SDNN_ENOMEM, "host allocation failed during setup"));
@@ -2159,7 +2328,6 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
             net->d_n_live[k] = (int32_t *)(base + pl.n_live[k]);
         }
     }
-    net->lds_ready = want_lm;
     net->bias_nonpos = true;
     for (int32_t l = 1; l < n_layers; ++l)
         if (layers[l].bias)
@@ -2377,24 +2545,44 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, float 
     return SDNN_OK;
 }
 
-// Whether the single-launch LDS-resident forward is the faster way to run this block of B samples.
-static bool lds_forward_pays(const sdnn_net *net, int B)
+// What a forward pass over B samples takes with a launch per layer, in seconds: about 4 us per layer to launch, fetch the
+// entries and store, plus the gathered rows at the rate that the memory they come from delivers (measured on nets of
+// 32-entry rows, 300 to 30000 neurons, 1 to 2048 samples, to within a third; rows of hundreds of entries run 1.4 times
+// faster).
+static double per_layer_forward_seconds(const sdnn_net *net, int B)
 {
-    if (!net->lds_ready || net->cfg.lds_forward == SDNN_LDS_OFF) return false;
+    double t = 0.0;
+    const int tile = B > 128 ? 256 : B > 64 ? 128 : 64;
+    for (const LayerDev &d : net->layers) {
+        if (B == 1) { t += 3.7e-6 + 5.1e-12 * (double)d.nnz; continue; }
+        const double operand = 4.0 * tile * (double)d.n_in; // of one tile of samples
+        const double rate = operand <= 4.5e6 ? (tile == 256 ? 20e12 : 14e12) : operand <= 9e6 ? 13e12 : 9.5e12;
+        const double bytes = 4.0 * (double)d.nnz * (double)((B + tile - 1) / tile * tile);
+        t += 4e-6 + bytes / ((int64_t)d.nnz >= 128 * (int64_t)d.n_out ? 1.4 * rate : rate);
+    }
+    return t;
+}
+
+// Samples per workgroup with which the single-launch LDS-resident forward is the faster way to run this block of B
+// samples, 0: a launch per layer is.  Measured (same nets): a workgroup takes 0.8 us per layer plus 3.5 / 3.9 / 6.2 ns
+// per wavefront-wide entry with 1 / 2 / 4 samples; a CU runs one workgroup at a time.
+static int lds_forward_samples(const sdnn_net *net, int B)
+{
+    if (!net->lm || net->cfg.lds_forward == SDNN_LDS_OFF) return 0;
     for (const LayerDev &d : net->layers)
-        if (d.n_out == 0) return false; // an empty layer: leave it to the general path
-    if (net->cfg.lds_forward == SDNN_LDS_ON) return true;
-    // Measured on nets of 32-entry rows (N = 1024 and 4096, 120 layers): the single launch takes about
-    // 2 us + 0.13 ns per stored entry per layer for every round of workgroups (one workgroup of LDS_T samples
-    // per CU), the per-layer kernels about 4.5 us + 0.21 ps per entry and sample per layer.
-    int64_t nnz = 0;
-    for (const LayerDev &d : net->layers) nnz += d.nnz;
-    const double nnz_layer = (double)nnz / (double)net->n_layers;
-    const int wgs = (B + LDS_T - 1) / LDS_T;
-    const int rounds = (wgs + net->n_cu - 1) / std::max(net->n_cu, 1);
-    const double t_fused = rounds * (2.0e-6 + 0.13e-9 * nnz_layer);
-    const double t_layers = 4.5e-6 + 0.21e-12 * nnz_layer * (double)B;
-    return t_fused < t_layers;
+        if (d.n_out == 0) return 0; // an empty layer: leave it to the general path
+    static const double entry[3] = {3.5e-9, 3.9e-9, 6.2e-9};
+    int best = 0;
+    double t_best = 0.0;
+    for (int k = 0; k < 3; ++k) {
+        const int T = 1 << k;
+        if (T * net->lm_max_pos > LDS_MAX_FLOATS) break;
+        const int wgs = (B + T - 1) / T, rounds = (wgs + net->n_cu - 1) / std::max(net->n_cu, 1);
+        const double t = rounds * (net->n_layers * 0.8e-6 + LDS_CHUNK * (double)net->lm_chunks * entry[k]);
+        if (!best || t < t_best) { best = T; t_best = t; }
+    }
+    if (net->cfg.lds_forward == SDNN_LDS_ON) return best;
+    return t_best < per_layer_forward_seconds(net, B) ? best : 0;
 }
 
 // Eq. 3 for l = 1..L.  Inference nets stage the activations between the layers in ping / pong
@@ -2429,21 +2617,25 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
     hipStream_t stream = (hipStream_t)stream_;
     net->state = ST_IDLE;
     const int L = net->n_layers;
-    if (lds_forward_pays(net, B)) {
-        const void *fn = net->cfg.activation == ACT_SIGMOID ? (const void *)k_fwd_lds<ACT_SIGMOID> : (const void *)k_fwd_lds<ACT_RELU_CAP>;
-        int buf_floats = LDS_T * ((net->max_n + 3) & ~3);
-        const size_t lds_bytes = 2 * sizeof(float) * (size_t)buf_floats;
-        if (!net->lds_attr_set) { // more than the default 64 KiB of dynamic LDS per workgroup
-            HIP_TRY(net, hipFuncSetAttribute((const void *)k_fwd_lds<ACT_SIGMOID>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 4 * LDS_T * LDS_MAX_N));
-            HIP_TRY(net, hipFuncSetAttribute((const void *)k_fwd_lds<ACT_RELU_CAP>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 4 * LDS_T * LDS_MAX_N));
-            net->lds_attr_set = true;
+    if (const int T = lds_forward_samples(net, B)) {
+        const bool sig = net->cfg.activation == ACT_SIGMOID;
+        const int ti = T == 1 ? 0 : T == 2 ? 1 : 2;
+        static const void *const fns[2][3] = {
+            {(const void *)k_fwd_lds<1, ACT_RELU_CAP>, (const void *)k_fwd_lds<2, ACT_RELU_CAP>, (const void *)k_fwd_lds<4, ACT_RELU_CAP>},
+            {(const void *)k_fwd_lds<1, ACT_SIGMOID>, (const void *)k_fwd_lds<2, ACT_SIGMOID>, (const void *)k_fwd_lds<4, ACT_SIGMOID>}};
+        const void *fn = fns[sig ? 1 : 0][ti];
+        const size_t lds_bytes = sizeof(float) * (size_t)T * (size_t)net->lm_max_pos;
+        if (!net->lds_attr_set[ti]) { // more than the default 64 KiB of dynamic LDS per workgroup
+            HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * LDS_MAX_FLOATS));
+            net->lds_attr_set[ti] = true;
         }
-        const LayerDev *layers = net->d_layers;
-        int n_layers = L, b = B, vec_io = (B % 4 == 0 && aligned(d_X0, 16) && aligned(d_XL, 16)) ? 1 : 0;
+        int n_layers = L, n0 = net->layers[0].n_in, b = B;
+        int vec_io = (B % T == 0 && aligned(d_X0, 4 * T) && aligned(d_XL, 4 * T)) ? 1 : 0;
         float cap = net->cfg.act_cap;
-        void *args[] = {(void *)&layers, (void *)&n_layers, (void *)&d_X0, (void *)&d_XL, (void *)&b, (void *)&buf_floats,
-                        (void *)&cap, (void *)&vec_io};
-        HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)((B + LDS_T - 1) / LDS_T)), dim3(64 * LDS_WAVES), args, lds_bytes, stream));
+        unsigned lm_bytes = (unsigned)(LDS_CHUNK_BYTES * (net->lm_chunks + 1));
+        void *args[] = {(void *)&net->lm_layers, (void *)&net->lm_cs, (void *)&net->lm, (void *)&lm_bytes, (void *)&net->lm_bias, (void *)&net->lm_row,
+                        (void *)&n_layers, (void *)&n0, (void *)&d_X0, (void *)&d_XL, (void *)&b, (void *)&cap, (void *)&vec_io};
+        HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)((B + T - 1) / T)), dim3(64 * LDS_WAVES), args, lds_bytes, stream));
         HIP_TRY(net, hipGetLastError());
         net->B = B;
         net->state = ST_FORWARD;
@@ -2918,10 +3110,8 @@ extern "C" int sdnn_set_weights(sdnn_net *net, int32_t layer, const float *d_val
         rc = copy_dd(net, d.bias, d_bias, 4 * (size_t)d.n_out, stream_);
         if (layer > 1) net->bias_nonpos = false; // device data: its signs are not inspected
     }
-    if (!rc && (d_values || d_bias) && d.lm && d.n_blocks > 0) { // keep the lane-major copy current
-        hipLaunchKernelGGL(k_lm_refresh, dim3((unsigned)d.n_blocks), dim3(64), 0, (hipStream_t)stream_, net->d_layers + (layer - 1));
-        HIP_TRY(net, hipGetLastError());
-    }
+    if (!rc && (d_values || d_bias) && net->lm) // keep the lane-major copy current
+        rc = launch_lm_fill(net, layer - 1, nullptr, 0, (hipStream_t)stream_);
     return rc;
 }
 

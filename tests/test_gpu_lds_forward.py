@@ -1,0 +1,49 @@
+"""The single-launch forward with activations in LDS at the sizes where its layout changes: widths around the limits of
+4, 2 and 1 samples per workgroup (8192, 16384, 32768 positions), blocks of 64 rows and 1024 positions, rows around the
+16-entry chunks, samples that do not fill a workgroup.  Same bits as the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2104_11805_amd import sdnn, workloads as wl
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _ragged(seed, n_out, n_in, lengths):
+    """Row r holds lengths[r % len(lengths)] distinct random columns."""
+    rng = np.random.default_rng(seed)
+    deg = np.resize(np.asarray(lengths), n_out)
+    row_ptr = np.zeros(n_out + 1, np.int32)
+    np.cumsum(deg, out=row_ptr[1:])
+    cols = np.concatenate([np.sort(rng.choice(n_in, size=d, replace=False)) for d in deg]).astype(np.int32)
+    vals = (rng.standard_normal(cols.size) * 0.4).astype(np.float32)
+    return wl.Layer(n_out, n_in, row_ptr, cols, vals, (rng.standard_normal(n_out) * 0.2).astype(np.float32))
+
+
+@pytest.mark.parametrize("n,b", [(63, 9), (1024, 3), (1025, 6), (8192, 7), (8193, 5), (16384, 2), (16385, 3), (32768, 3)])
+def test_lds_forward_at_the_limits_of_its_layout(n, b):
+    lengths = (0, 1, 7, 8, 9, 15, 16, 17, 31, 33)
+    layers = [_ragged(9000 + n, n, 50, lengths), _ragged(9001 + n, n, n, lengths), _ragged(9002 + n, 70, n, (0, 5, 40))]
+    x = wl.normal_inputs(9003 + n, 50, b)
+    ref = P.O32.forward(layers, x, 2.0)[-1]
+    assert (ref > 0).any()
+    net = sdnn.Net(layers, 2.0, b, training=False, lds_forward=sdnn.SDNN_LDS_ON)
+    out = torch.full((70, b), -1.0, device=P.DEV)
+    net.sdnn_forward(P.dev(x), out)
+    assert np.array_equal(P.host(out), ref)
+    net.close()
+
+
+@pytest.mark.parametrize("b", [1, 255, 257, 511, 513, 1027, 2050])
+def test_lds_forward_samples_per_workgroup(b):
+    """Batches on both sides of one, two and four samples for each of the 256 CUs."""
+    layers = [_ragged(9100 + l, 300, 300, (3, 20, 34)) for l in range(3)]
+    x = wl.normal_inputs(9110, 300, b)
+    ref = P.O32.forward(layers, x, 1.5)[-1]
+    net = sdnn.Net(layers, 1.5, b, training=False, lds_forward=sdnn.SDNN_LDS_ON)
+    out = torch.full((300, b), -1.0, device=P.DEV)
+    net.sdnn_forward(P.dev(x), out)
+    assert np.array_equal(P.host(out), ref)
+    net.close()
