@@ -34,10 +34,7 @@
  * Pointers named d_* are DEVICE pointers, all others are HOST pointers.
  * `stream` is a hipStream_t passed as void* (NULL = the default stream).  All
  * device work is ordered on that stream and is asynchronous; argument and
- * state errors are reported synchronously.  (For small layers a pass runs its two
- * half-batches concurrently: the second half goes to a helper stream of the net,
- * forked from and joined back into `stream` with events, so the caller sees
- * ordinary stream order.)  The library never allocates device
+ * state errors are reported synchronously.  The library never allocates device
  * memory: the caller hands in one workspace at sdnn_create and keeps it alive
  * until sdnn_destroy.
  *
@@ -92,17 +89,15 @@ typedef struct {
 
 /* Where the batch allows it, sdnn_backward can form the gradient of the stored entries (Eq. 4) in
  * the same sweep that back-propagates through W_l (Eq. 7): both need the rows of Delta_l that an
- * entry points at.  Short rows (fewer than 128 entries on average): launches of at most 64 samples,
- * i.e. B <= 64, or B = 128 as two halves; long rows: B <= 256 and a multiple of 4 (four samples per
- * lane); one sample per step (B = 1) on a net created with max_batch == 1 whose layers all have 8192
- * inputs or more and short rows (4 more bytes per entry then); other batch sizes take the separate
- * kernels on the same net.  The net then keeps the values
+ * entry points at.  For batches of 2 to 256 samples (128 samples on short rows and up to 16384 neurons: as two
+ * windows of 64, each rounded to fp32); one sample per step (B = 1) on a net created with max_batch == 1 whose
+ * layers all have 8192 inputs or more and short rows (fewer than 128 entries on average; 4 more bytes per entry
+ * then); other batch sizes take the separate kernels on the same net.  The net then keeps the values
  * a second time, in the order of the transposed index, which that sweep reads in a stream; the
  * gradient is left in the same order, sdnn_sgd_step is a streaming pass over both and rebuilds the
  * CSR copy in a second pass that moves whole runs of entries.  Same results within the rounding of
- * the sum over samples; costs 24 more bytes of workspace per stored entry.  AUTO turns it on for
- * nets whose layers have 4096 rows or more on average (long rows: if max_batch <= 256), where it is
- * faster. */
+ * the sum over samples; costs 24 more bytes of workspace per stored entry.  AUTO turns it on where it is faster: nets
+ * with about 100 000 entries per layer and more, half of that if max_batch > 64. */
 #define SDNN_FUSE_AUTO 0
 #define SDNN_FUSE_ON 1
 #define SDNN_FUSE_OFF (-1)

@@ -37,6 +37,7 @@
 #include <mutex>
 #include <new>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "sdnn_internal.h"
@@ -164,18 +165,19 @@ struct SpmmArgs {
     const float *vals;
     const int32_t *perm;  // MODE 1 only
     const int4 *sched;    // per task: {row, first entry, end of entries, 0}, rows by decreasing length
-    const float *in;      // [n_cols][B]
+    const float *in;      // [n_cols][ld_in]
     size_t in_bytes;      // < 4 GiB
-    float *out;           // [n_rows][B]
-    const float *aux;     // MODE 0: bias [n_rows] (may be NULL); MODE 1: Xprev [n_rows][B]
-    int32_t n_rows, B;
+    float *out;           // [n_rows][ld_out]
+    const float *aux;     // MODE 0: bias [n_rows] (may be NULL); MODE 1: Xprev [n_rows][ld_out]
+    int32_t n_rows, B;    // B: samples (columns that matter)
+    int32_t ld_in, ld_out; // floats per activation row
     uint32_t n_tiles, n_rg, n_vblocks, tile_base;
     float cap;
     int32_t act;
     const int32_t *n_live; // NULL, or the number of leading columns of the block that still matter (device)
     int32_t *flags;        // NULL, or MODE 0: flags[s] is set to 1 for every sample s with a non-zero output
-    float *g_part;         // GRAD kernels: gradient of the stored entries over this launch's samples, in the order of
-                           // the transposed index [nnz]
+    float *g_part[2];      // GRAD kernels: gradient of the stored entries over the samples of the first / second tile, in the
+                           // order of the transposed index [nnz]
     int32_t store_out;     // GRAD kernels: 0 = only the gradient is wanted (first layer: there is no Delta_0)
 };
 
@@ -226,15 +228,15 @@ __device__ __forceinline__ RowMeta load_meta(const int4 *sched, const int32_t *i
 template <int V, int MODE, int U, int ACT>
 __device__ __forceinline__ void spmm_row(RowMeta m, const int32_t *idx, const float *vals,
                                          const int32_t *perm, const float *in, size_t in_bytes,
-                                         float *out, const float *aux, int B, float capf, int act,
-                                         unsigned tile, int lane, int32_t *flags)
+                                         float *out, const float *aux, int B, int ld_in, int ld_out, float capf,
+                                         int act, unsigned tile, int lane, int32_t *flags)
 {
     const int s_own = (int)tile * (64 * V) + lane * V;
     const bool live = s_own < B;
     const int s = live ? s_own : 0;
-    const size_t ld = (size_t)B;
-    const unsigned so = 4u * (unsigned)s;  // byte offset of the lane inside an activation row
-    const unsigned ldb = 4u * (unsigned)B; // bytes per activation row
+    const size_t ld = (size_t)ld_out;
+    const unsigned so = 4u * (unsigned)s;      // byte offset of the lane inside an activation row
+    const unsigned ldb = 4u * (unsigned)ld_in; // bytes per activation row
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(in, in_bytes);
 
     // operands of the epilogue, requested early so that they arrive with the gathers
@@ -384,7 +386,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
             if (r >= a.n_rows) continue;
             const RowMeta m = load_meta<MODE>(a.sched, a.idx, a.vals, a.perm, r, lane);
             for (unsigned tile = 0; tile < n_tiles; ++tile)
-                spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.cap, a.act,
+                spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.ld_in, a.ld_out, a.cap, a.act,
                                           tile + a.tile_base, lane, a.flags);
         }
         return;
@@ -395,8 +397,252 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
         const int r = __builtin_amdgcn_readfirstlane((int)(rg * WAVES_PER_BLOCK + wave));
         if (r >= a.n_rows) continue;
         const RowMeta m = load_meta<MODE>(a.sched, a.idx, a.vals, a.perm, r, lane);
-        spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.cap, a.act, tile + a.tile_base, lane, a.flags);
+        spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.ld_in, a.ld_out, a.cap, a.act, tile + a.tile_base, lane, a.flags);
     }
+}
+
+// ---------------------------------------------------------------------------
+// K1r / K2r: the product with several rows per wavefront, for batches that do not fill it with one.
+// A row takes G lanes, four consecutive samples per lane (so G = 16 for 64 samples, 32 for 128), and a
+// wavefront 64 / G rows: one gather instruction fetches 16 bytes a lane for 64 / G entries.  Every quad of
+// lanes holds 16 entries of its row, four per lane, and hands them round with quad_perm; slots past the end of
+// a row carry weight 0 and add an exact zero.  Same order of the sums as in k_spmm.
+//
+// A wavefront per row (k_spmm with one sample per lane) is bound by the rate of gather instructions (10 clocks each,
+// whatever the number of samples) up to 64 samples, and by the L2 misses of a 256-sample tile beyond.  Here
+// one instruction serves 2 to 16 entries.  Forward, us per layer, before and after: 65536 neurons, 16 samples 49.8 ->
+// 17.8; 16384 neurons 12.0 -> 5.9 (16), 13.5 -> 10.2 (64), 24.5 -> 21 (99), 53 -> 31.8 (256); 4096 neurons 7.9 -> 6.5 (128).
+// ---------------------------------------------------------------------------
+template <int LANE> __device__ __forceinline__ int quad_bcast(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, LANE * 0x55, 0xf, 0xf, true);
+}
+__device__ __forceinline__ float4 as_f4(u32x4 t)
+{
+    return make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w));
+}
+struct __attribute__((packed, aligned(4))) I4 { int v[4]; };
+struct __attribute__((packed, aligned(4))) F4 { float v[4]; };
+// The entries of a quad's row in groups of sixteen, four per lane: entries past the end of the row (what follows it in
+// the arrays is read) count as zeros.
+struct QuadEntries {
+    I4 c;
+    F4 w;
+    __device__ __forceinline__ void fetch(const int32_t *idx, const float *vals, int p, int end)
+    {
+        if (p < end) {
+            c = *(const I4 *)(idx + p);
+            w = *(const F4 *)(vals + p);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (p + i >= end) { c.v[i] = 0; w.v[i] = 0.0f; }
+    }
+};
+// The operand rows of the four entries that quad lane H holds, and their weights.
+template <int H>
+__device__ __forceinline__ void quad_gather(const QuadEntries &q, __amdgpu_buffer_rsrc_t rin, unsigned ldb, unsigned so,
+                                            float4 (&x)[4], int (&wv)[4])
+{
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const unsigned c = (unsigned)quad_bcast<H>(q.c.v[u]);
+        wv[u] = quad_bcast<H>(__float_as_int(q.w.v[u]));
+        x[u] = as_f4(__builtin_amdgcn_raw_buffer_load_b128(rin, (int)(__umul24(c, ldb) + so), 0, 0));
+    }
+}
+template <int G, int ACT>
+__global__ void __launch_bounds__(BLOCK_THREADS) k_rows(const SpmmArgs a)
+{
+    constexpr int R = 64 / G;
+    const int lane = threadIdx.x & 63;
+    // all row groups of the first tile of samples, then those of the second, ...
+    const unsigned tile = blockIdx.x / a.n_rg, rg = blockIdx.x - tile * a.n_rg;
+    const int r = (int)((rg * WAVES_PER_BLOCK + (threadIdx.x >> 6)) * R) + lane / G;
+    const unsigned ldb = 4u * (unsigned)a.ld_in;
+    const int s_own = (int)(tile + a.tile_base) * (4 * G) + 4 * (lane & (G - 1));
+    const bool live = s_own < a.B;
+    const int s = live ? s_own : 0;
+    const unsigned so = 4u * (unsigned)s;
+    const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
+    int4 t = make_int4(0, 0, 0, 0);
+    if (r < a.n_rows) t = a.sched[r];
+    const int row = t.x, end = t.z;
+    int p = t.y + 4 * (lane & 3), left = end - t.y; // left: entries of this lane's row still to do
+    QuadEntries q;
+    q.fetch(a.idx, a.vals, p, end);
+    const double b = a.aux ? (double)a.aux[row] : 0.0;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (bool more = __ballot(left > 0) != 0; more;) {
+        more = __ballot(left > 16) != 0;
+        float4 x[4][4];
+        int wv[4][4];
+        quad_gather<0>(q, rin, ldb, so, x[0], wv[0]);
+        quad_gather<1>(q, rin, ldb, so, x[1], wv[1]);
+        quad_gather<2>(q, rin, ldb, so, x[2], wv[2]);
+        quad_gather<3>(q, rin, ldb, so, x[3], wv[3]);
+        p += 16;
+        left -= 16;
+        if (more) q.fetch(a.idx, a.vals, p, end);
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double wk = (double)__int_as_float(wv[h][u]);
+                acc[0] = fma(wk, (double)x[h][u].x, acc[0]);
+                acc[1] = fma(wk, (double)x[h][u].y, acc[1]);
+                acc[2] = fma(wk, (double)x[h][u].z, acc[2]);
+                acc[3] = fma(wk, (double)x[h][u].w, acc[3]);
+            }
+    }
+    if (r >= a.n_rows || !live) return;
+    float o[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[v] = act_apply(ACT, acc[v] + b, a.cap);
+    float *dst = a.out + (size_t)row * a.ld_out + s;
+    if ((a.ld_out & 3) == 0 && ((size_t)a.out & 15) == 0) {
+        stv<4>(dst, o);
+    } else { // the caller's rows of B floats
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (s + v < a.B) dst[v] = o[v];
+    }
+}
+
+// Exchange with the lane that differs in one bit of its number (bits 1 and 0: exactly that lane; bit 3: lane ^ 8; bit 2:
+// lane ^ 7, which is as good where all lanes that agree in the higher bits hold the same set of values).
+template <int BIT> __device__ __forceinline__ double lane_exchange(double v)
+{
+    constexpr int CTRL = BIT == 3 ? 0x128 : BIT == 2 ? 0x141 : BIT == 1 ? 0x4e : 0xb1; // row_ror:8, row_half_mirror, quad_perm
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// One halving step of a sum over lanes of N values: the lane keeps the half of the values whose number has the bit that
+// its own number has in place BIT, and adds its partner's share of them.
+template <int N, int BIT> __device__ __forceinline__ void halve(double (&p)[4], int lane)
+{
+#pragma unroll
+    for (int j = 0; j < N / 2; ++j) {
+        if constexpr (BIT >= 4) {
+            const unsigned al = (unsigned)__double2loint(p[j]), ah = (unsigned)__double2hiint(p[j]);
+            const unsigned bl = (unsigned)__double2loint(p[j + N / 2]), bh = (unsigned)__double2hiint(p[j + N / 2]);
+            const auto lo = BIT == 5 ? __builtin_amdgcn_permlane32_swap(al, bl, false, false) : __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+            const auto hi = BIT == 5 ? __builtin_amdgcn_permlane32_swap(ah, bh, false, false) : __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+            p[j] = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+        } else {
+            const bool up = (lane >> BIT) & 1;
+            const double keep = up ? p[j + N / 2] : p[j], send = up ? p[j] : p[j + N / 2];
+            p[j] = keep + lane_exchange<BIT>(send);
+        }
+    }
+}
+// Sums of four values over the G lanes of a row: afterwards p[0] holds the sum of value reduced_index<G>(lane).
+template <int G> __device__ __forceinline__ void reduce4(double (&p)[4], int lane)
+{
+    if constexpr (G == 64) { halve<4, 5>(p, lane); halve<2, 4>(p, lane); }
+    if constexpr (G == 32) { halve<4, 4>(p, lane); halve<2, 3>(p, lane); }
+    if constexpr (G == 16) { halve<4, 3>(p, lane); halve<2, 2>(p, lane); }
+    if constexpr (G == 8) { halve<4, 2>(p, lane); halve<2, 1>(p, lane); }
+    if constexpr (G == 4) { halve<4, 1>(p, lane); halve<2, 0>(p, lane); }
+    if constexpr (G >= 64) p[0] += lane_exchange<3>(p[0]);
+    if constexpr (G >= 32) p[0] += lane_exchange<2>(p[0]);
+    if constexpr (G >= 16) p[0] += lane_exchange<1>(p[0]);
+    if constexpr (G >= 8) p[0] += lane_exchange<0>(p[0]);
+}
+template <int G> __device__ __forceinline__ int reduced_index(int lane) { return (lane / (G / 4)) & 3; }
+// The sum of a float over two neighbouring groups of 16 lanes, in all of them.
+__device__ __forceinline__ float add_neighbour16(float g)
+{
+    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(g), __float_as_uint(g), false, false);
+    return (float)((double)__uint_as_float(t[0]) + (double)__uint_as_float(t[1]));
+}
+
+// The backward sweep that also forms the gradient of the stored entries, in the manner of k_rows.  The lanes of row i of
+// W_l^T hold X_{l-1}(i, :), four samples each, gather Delta_l(j, :) for every entry (j, i) and sum its products with
+// X_{l-1}(i, :) over the samples: four in the lane, the rest over the row's lanes, four entries at a time while the
+// operand rows of the next four are on their way.
+// Against the sweep that parks the gathered rows in LDS (k_bwd_grad; four samples per lane for long rows): one instead of
+// twelve vector instructions per entry and 64 samples for the parking and its re-reading, and a gather instruction per 1024
+// bytes.  Backward and gradient, us per layer: 65536 neurons 80 -> 69.7 (64 samples), 70.6 -> 29.1 (16); 16384 neurons 21.1 ->
+// 14.4 (64), 31.8 -> 25.3 (128; two launches on two streams before); 10007 neurons, 99 samples 32.5 (two
+// separate kernels) -> 17.6 + 3; 8192 neurons of 820 entries 420 -> 331 (256 samples), 410 -> 127 (64).
+// TWO (G = 32, 128 samples): the gradient is the sum of two windows of 64 samples, each rounded to fp32 (what two launches
+// of 64 samples leave in two partial gradients).
+template <int G, bool TWO>
+__global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const SpmmArgs a)
+{
+    static_assert(!TWO || G == 32, "two windows of 16 lanes");
+    constexpr int R = 64 / G;
+    const int lane = threadIdx.x & 63;
+    const unsigned tile = blockIdx.x / a.n_rg, rg = blockIdx.x - tile * a.n_rg;
+    const int r = (int)((rg * WAVES_PER_BLOCK + (threadIdx.x >> 6)) * R) + lane / G;
+    const unsigned ldb = 4u * (unsigned)a.ld_in;
+    const int s_own = (int)tile * (4 * G) + 4 * (lane & (G - 1));
+    const bool live = s_own < a.B && r < a.n_rows;
+    const int s = s_own < a.B ? s_own : 0;
+    const unsigned so = 4u * (unsigned)s;
+    const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
+    float *__restrict__ g_part = tile == 0 ? a.g_part[0] : a.g_part[1];
+    int4 t = make_int4(0, 0, 0, 0);
+    if (r < a.n_rows) t = a.sched[r];
+    const int row = t.x, end = t.z;
+    int p = t.y + 4 * (lane & 3), left = end - t.y; // left: entries of this lane's row still to do
+    QuadEntries q, qn;
+    q.fetch(a.idx, a.vals, p, end);
+    float xp[4] = {0.0f, 0.0f, 0.0f, 0.0f}; // lanes outside the batch add nothing to the gradient
+    if (live) ldv<4>(a.aux + (size_t)row * a.ld_out + s, xp);
+    double xd[4], acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) xd[v] = (double)xp[v];
+    constexpr int SUM = TWO ? 16 : G; // lanes of a window
+    int e0 = t.y + reduced_index<SUM>(lane); // the entry whose gradient this lane stores
+    float4 x0[4], x1[4];
+    int w0[4], w1[4];
+    auto consume = [&](const float4 (&x)[4], const int (&wv)[4]) {
+        double pr[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double wk = (double)__int_as_float(wv[u]);
+            const double d0 = (double)x[u].x, d1 = (double)x[u].y, d2 = (double)x[u].z, d3 = (double)x[u].w;
+            acc[0] = fma(wk, d0, acc[0]);
+            acc[1] = fma(wk, d1, acc[1]);
+            acc[2] = fma(wk, d2, acc[2]);
+            acc[3] = fma(wk, d3, acc[3]);
+            pr[u] = fma(d3, xd[3], fma(d2, xd[2], fma(d1, xd[1], d0 * xd[0])));
+        }
+        // added here: the compiler would move these sums past the branches below and keep every converted operand until
+        // then (214 registers instead of 120)
+        asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
+        reduce4<SUM>(pr, lane);
+        float g = (float)pr[0];
+        if (TWO) g = add_neighbour16(g);
+        if ((lane & (SUM / 4 - 1)) == 0 && !(TWO && (lane & 16)) && e0 < end) g_part[e0] = g;
+        e0 += 4;
+    };
+    quad_gather<0>(q, rin, ldb, so, x0, w0);
+    for (bool more = __ballot(left > 0) != 0; more;) {
+        more = __ballot(left > 16) != 0;
+        p += 16;
+        left -= 16;
+        if (more) qn.fetch(a.idx, a.vals, p, end);
+        quad_gather<1>(q, rin, ldb, so, x1, w1);
+        consume(x0, w0);
+        quad_gather<2>(q, rin, ldb, so, x0, w0);
+        consume(x1, w1);
+        quad_gather<3>(q, rin, ldb, so, x1, w1);
+        consume(x0, w0);
+        if (more) {
+            q = qn;
+            quad_gather<0>(q, rin, ldb, so, x0, w0);
+        }
+        consume(x1, w1);
+    }
+    if (!a.store_out || !live) return;
+    float o[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[v] = act_backprop(a.act, acc[v], xp[v], a.cap);
+    stv<4>(a.out + (size_t)row * a.ld_out + s, o);
 }
 
 // ---------------------------------------------------------------------------
@@ -413,6 +659,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
 // an XCD's L2 holds one panel at a time and pulls each operand row in once per launch.
 // Rows must have at most 64 entries (checked by the host); one sample per lane.
 // ---------------------------------------------------------------------------
+#define PANEL_MIN_SAMPLES 40 // AUTO: narrower batches gather with several rows per wavefront (k_rows)
 #define PANEL_SLOTS 8 // gathers of one row segment that are in flight together; longer segments go round again
 
 // Requests the operand rows of entries k .. min(k + PANEL_SLOTS, ke) - 1 of a row (wave-uniform branches).
@@ -454,8 +701,8 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm_panel(const SpmmArgs a, 
     const int lane = threadIdx.x & 63;
     const unsigned wave = threadIdx.x >> 6;
     const int B = a.B;
-    const size_t ld = (size_t)B;
-    const unsigned ldb = 4u * (unsigned)B;
+    const size_t ld = (size_t)a.ld_out;
+    const unsigned ldb = 4u * (unsigned)a.ld_in;
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
     for (unsigned vb = blockIdx.x; vb < a.n_vblocks; vb += gridDim.x) {
         unsigned tile, rg;
@@ -786,16 +1033,15 @@ __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ lay
 #define GRAD_LD 68 // floats per parked entry: 64 samples + pad (rows stay 16-byte aligned, banks spread)
 #define GRAD_GE 16 // entries parked at a time: 4.6 KB of LDS per wavefront, which keeps 8 wavefronts per SIMD
 template <int U>
-__device__ __forceinline__ void spmm_row_grad(RowMeta m, const SpmmArgs &a, unsigned tile, int lane,
+__device__ __forceinline__ void spmm_row_grad(RowMeta m, const SpmmArgs &a, int lane,
                                               float *__restrict__ dt, float *__restrict__ xt)
 {
     const int B = a.B;
-    const int s_own = (int)tile * 64 + lane;
-    const bool live = s_own < B;
-    const int s = live ? s_own : 0;
-    const size_t ld = (size_t)B;
+    const bool live = lane < B;
+    const int s = live ? lane : 0;
+    const size_t ld = (size_t)a.ld_out;
     const unsigned so = 4u * (unsigned)s;
-    const unsigned ldb = 4u * (unsigned)B;
+    const unsigned ldb = 4u * (unsigned)a.ld_in;
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
 
     const float xp = a.aux[(size_t)m.row * ld + s]; // X_{l-1}(i, s): mask operand and gradient operand
@@ -859,7 +1105,7 @@ __device__ __forceinline__ void spmm_row_grad(RowMeta m, const SpmmArgs &a, unsi
             }
             sum += __shfl_xor(sum, 16);
             sum += __shfl_xor(sum, 32);
-            if (q == 0 && e < ng) a.g_part[base + g0 + e] = (float)sum; // the entry's place in the transposed index
+            if (q == 0 && e < ng) a.g_part[0][base + g0 + e] = (float)sum; // the entry's place in the transposed index
             wave_lds_sync(); // the next group's rows are parked over the ones just read
         }
     }
@@ -873,147 +1119,37 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_grad(const SpmmArgs a)
     const int lane = threadIdx.x & 63;
     const unsigned wave = threadIdx.x >> 6;
     for (unsigned vb = blockIdx.x; vb < a.n_vblocks; vb += gridDim.x) {
-        unsigned tile, rg;
-        map_block(vb, a.n_tiles, a.n_rg, tile, rg);
-        const int r = __builtin_amdgcn_readfirstlane((int)(rg * WAVES_PER_BLOCK + wave));
-        if (r >= a.n_rows) continue;
-        const RowMeta m = load_meta<0>(a.sched, a.idx, a.vals, nullptr, r, lane);
-        spmm_row_grad<U>(m, a, tile + a.tile_base, lane, dt[wave], xt[wave]);
-    }
-}
-
-// The same sweep for long rows and a batch of up to 256 samples in one launch: four samples per lane, as in the long-row
-// product kernels, a gathered row of Delta_l being 1 KiB.  Eight entries are parked at a time ([entry][256 samples],
-// padded: 8.3 KB per wavefront, four wavefronts per SIMD); lane (e, q) sums entry e over the q-th eighth of the
-// samples (32 of them), three shuffles add the eighths.
-#define GRAD4_LD 260 // floats per parked entry: 256 samples + pad
-#define GRAD4_GE 8
-template <int U>
-__global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_grad4(const SpmmArgs a)
-{
-    __shared__ __attribute__((aligned(16))) float dt_all[WAVES_PER_BLOCK][GRAD4_GE * GRAD4_LD];
-    __shared__ __attribute__((aligned(16))) float xt_all[WAVES_PER_BLOCK][256];
-    const int lane = threadIdx.x & 63;
-    const unsigned wave = threadIdx.x >> 6;
-    float *__restrict__ dt = dt_all[wave];
-    float *__restrict__ xt = xt_all[wave];
-    const int B = a.B; // a multiple of 4, at most 256: one tile
-    const size_t ld = (size_t)B;
-    const unsigned ldb = 4u * (unsigned)B;
-    const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
-    const int s_own = 4 * lane;
-    const bool live = s_own < B;
-    const int s = live ? s_own : 0;
-    const unsigned so = 4u * (unsigned)s;
-    const int e = lane & (GRAD4_GE - 1), q = lane / GRAD4_GE; // reducer of entry e over samples 32 q .. 32 q + 31
-    for (unsigned vb = blockIdx.x; vb < a.n_vblocks; vb += gridDim.x) {
         const int r = __builtin_amdgcn_readfirstlane((int)(vb * WAVES_PER_BLOCK + wave));
         if (r >= a.n_rows) continue;
-        // the row's task record and its entries are the same for all lanes and do not change inside the kernel: they
-        // are read through the scalar cache into scalar registers, eight columns and eight weights a group ahead
-        typedef int i32x4s __attribute__((ext_vector_type(4)));
-        typedef int i32x8 __attribute__((ext_vector_type(8)));
-        typedef float f32x8 __attribute__((ext_vector_type(8)));
-        const i32x4s task = ((const i32x4s __attribute__((address_space(4))) *)a.sched)[r];
-        RowMeta m;
-        m.row = task.x; m.beg = task.y; m.end = task.z;
-        const int __attribute__((address_space(4))) *sidx = (const int __attribute__((address_space(4))) *)a.idx;
-        const float __attribute__((address_space(4))) *svals = (const float __attribute__((address_space(4))) *)a.vals;
-        float xp[4];
-        ldv<4>(a.aux + (size_t)m.row * ld + s, xp); // X_{l-1}(i, s ..): mask operand and gradient operand
-        wave_lds_sync();                            // the previous row's X values have been read
-        {
-            float4 xz = make_float4(0.0f, 0.0f, 0.0f, 0.0f); // samples outside the batch add nothing to the gradient
-            if (live) xz = make_float4(xp[0], xp[1], xp[2], xp[3]);
-            *reinterpret_cast<float4 *>(xt + 4 * lane) = xz;
-        }
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        static_assert(U == GRAD4_GE, "a parked group is one batch of gathers");
-        // reduces the ng parked entries over the samples and stores their gradients at entries g .. g + ng - 1
-        auto reduce_parked = [&](int g, int ng) {
-            wave_lds_sync(); // the lanes now read what other lanes of the wavefront have parked
-            double sum = 0.0;
-            if (e < ng) {
-                const float4 *dp = reinterpret_cast<const float4 *>(dt + e * GRAD4_LD + 32 * q);
-                const float4 *xq = reinterpret_cast<const float4 *>(xt + 32 * q);
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const float4 d4 = dp[t], x4 = xq[t];
-                    sum = fma((double)d4.x, (double)x4.x, sum);
-                    sum = fma((double)d4.y, (double)x4.y, sum);
-                    sum = fma((double)d4.z, (double)x4.z, sum);
-                    sum = fma((double)d4.w, (double)x4.w, sum);
-                }
-            }
-            sum += __shfl_xor(sum, 8);
-            sum += __shfl_xor(sum, 16);
-            sum += __shfl_xor(sum, 32);
-            if (q == 0 && e < ng) a.g_part[g + e] = (float)sum; // the entry's place in the transposed index
-            wave_lds_sync(); // the next group's rows are parked over the ones just read
-        };
-        int g = m.beg;
-        i32x8 c, cn;
-        f32x8 w, wn;
-        if (g + 8 <= m.end) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) { c[k] = sidx[g + k]; w[k] = svals[g + k]; }
-        }
-        for (; g + 8 <= m.end; g += 8) {
-            if (g + 16 <= m.end) {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) { cn[k] = sidx[g + 8 + k]; wn[k] = svals[g + 8 + k]; }
-            }
-            float x[8][4];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) gatherv<4>(rin, so, (unsigned)c[k] * ldb, x[k]);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                float wf = w[k];
-                asm volatile("" : "+s"(wf)); // converted when it is used, not while the gathers are in flight
-                const double wk = (double)wf;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[v] = fma(wk, (double)x[k][v], acc[v]);
-                *reinterpret_cast<float4 *>(dt + k * GRAD4_LD + 4 * lane) = make_float4(x[k][0], x[k][1], x[k][2], x[k][3]);
-            }
-            reduce_parked(g, 8);
-            c = cn;
-            w = wn;
-        }
-        if (g < m.end) { // the row's last entries, fewer than eight: same order, every entry guarded (wave-uniform)
-            const int n = m.end - g;
-            float x[8][4];
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (k < n) gatherv<4>(rin, so, (unsigned)sidx[g + k] * ldb, x[k]);
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (k < n) {
-                    const double wk = (double)svals[g + k];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) acc[v] = fma(wk, (double)x[k][v], acc[v]);
-                    *reinterpret_cast<float4 *>(dt + k * GRAD4_LD + 4 * lane) = make_float4(x[k][0], x[k][1], x[k][2], x[k][3]);
-                }
-            reduce_parked(g, n);
-        }
-        if (a.store_out && live) {
-            float o[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] = act_backprop(a.act, acc[v], xp[v], a.cap);
-            stv<4>(a.out + (size_t)m.row * ld + s, o);
-        }
+        const RowMeta m = load_meta<0>(a.sched, a.idx, a.vals, nullptr, r, lane);
+        spmm_row_grad<U>(m, a, lane, dt[wave], xt[wave]);
     }
 }
 
 // ---------------------------------------------------------------------------
 // K3: output delta (Eq. 6):  D = dLoss * [0 < X_L < cap]
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_output_delta(const float *__restrict__ dloss,
-                                                      const float *__restrict__ xl,
-                                                      float *__restrict__ d, size_t n, float cap, int act)
+// Elementwise passes between the caller's rows of B floats and the library's rows of ld: a row takes 1 << w_log2 threads
+// of a workgroup (Bp, or all 256), columns B .. Bp - 1 of the destination are zeroed.
+#define FOR_ROW_ELEMENTS(n_rows, Bp, w_log2)                                                                  \
+    for (int row = (int)(blockIdx.x * (256u >> (w_log2)) + (threadIdx.x >> (w_log2))); row < (n_rows);          \
+         row += (int)(gridDim.x * (256u >> (w_log2))))                                                          \
+        for (int s = (int)(threadIdx.x & ((1u << (w_log2)) - 1u)); s < (Bp); s += 1 << (w_log2))
+__global__ void __launch_bounds__(256) k_output_delta(const float *__restrict__ dloss, const float *__restrict__ xl,
+                                                      float *__restrict__ d, int n_rows, int B, int ld, int Bp, int w_log2,
+                                                      float cap, int act)
 {
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-         e += (size_t)gridDim.x * blockDim.x)
-        d[e] = act_backprop(act, (double)dloss[e], xl[e], cap);
+    FOR_ROW_ELEMENTS(n_rows, Bp, w_log2)
+    {
+        const size_t at = (size_t)row * ld + s;
+        d[at] = s < B ? act_backprop(act, (double)dloss[(size_t)row * B + s], xl[at], cap) : 0.0f;
+    }
+}
+__global__ void __launch_bounds__(256) k_copy_rows(const float *__restrict__ src, int ld_src, float *__restrict__ dst, int ld_dst,
+                                                   int n_rows, int B, int Bp, int w_log2)
+{
+    FOR_ROW_ELEMENTS(n_rows, Bp, w_log2)
+        dst[(size_t)row * ld_dst + s] = s < B ? src[(size_t)row * ld_src + s] : 0.0f;
 }
 
 // ---------------------------------------------------------------------------
@@ -1194,7 +1330,7 @@ __global__ void __launch_bounds__(64) k_spmv_stage_grad(const SpmmArgs a, int R,
                 if (c[j] >= 0) {
                     const int q = (j0 + j) * 64 + lane;
                     prod[q + (q >> 5)] = (double)w[j] * (double)x[j];
-                    a.g_part[sb + q] = (float)((double)x[j] * (double)xi[j]);
+                    a.g_part[0][sb + q] = (float)((double)x[j] * (double)xi[j]);
                 }
         }
         if (!a.store_out) continue; // first layer: only the gradient (uniform for the workgroup)
@@ -1261,7 +1397,7 @@ k_update_b1(const LayerDev *__restrict__ layers, int layer0, int lpr_log2, float
 // registers for the whole row (long rows: otherwise it is read again for every 32-entry chunk).
 template <int V, int HOLD>
 __global__ void __launch_bounds__(64 * UPD_WAVES)
-k_update(const LayerDev *__restrict__ layers, int layer0, int n_layers, int interleave, int rows_per_wave, int B,
+k_update(const LayerDev *__restrict__ layers, int layer0, int n_layers, int interleave, int rows_per_wave, int B, int ld_,
          float lr, int update_bias, int emit, float *__restrict__ g_out, float *__restrict__ gb_out)
 {
     // interleaved: grid = (8 * row groups, groups of 8 layers), blockIdx.x % 8 is both the XCD and the
@@ -1277,7 +1413,7 @@ k_update(const LayerDev *__restrict__ layers, int layer0, int n_layers, int inte
   for (int r = r0; r < min(r0 + rows_per_wave, L.n_out); ++r) {
     const int4 task = L.sched[r];
     const int row = task.x, beg = task.y, end = task.z;
-    const size_t ld = (size_t)B;
+    const size_t ld = (size_t)ld_;
     const float *drow = L.D + (size_t)row * ld;
     const float *xp = L.X_prev;
     const double dlr = (double)lr;
@@ -1483,18 +1619,18 @@ __global__ void __launch_bounds__(256) k_refresh_vals_t(const LayerDev *__restri
 
 // 16 lanes per row, four rows per wavefront at a time, 16 consecutive rows per wavefront.
 // gb_out == NULL: bias -= lr * gb; otherwise the bias gradient of the one layer is stored there instead.
-__global__ void __launch_bounds__(BLOCK_THREADS) k_apply_bias(const LayerDev *__restrict__ layers, int B, float lr,
+__global__ void __launch_bounds__(BLOCK_THREADS) k_apply_bias(const LayerDev *__restrict__ layers, int B, int ld, float lr,
                                                               float *__restrict__ gb_out)
 {
     const LayerDev &L = layers[blockIdx.y];
     const int lane = threadIdx.x & 63, l = lane & 15;
     const int row0 = (blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6)) * 16 + (lane >> 4);
-    const bool vec = (B & 3) == 0; // rows of Delta are 16-byte aligned
+    const bool vec = (ld & 3) == 0; // rows of Delta are 16-byte aligned; columns past B are zero
     for (int k = 0; k < 4; ++k) {
         const int row = row0 + 4 * k;
         double sum = 0.0;
         if (row < L.n_out) {
-            const float *drow = L.D + (size_t)row * B;
+            const float *drow = L.D + (size_t)row * ld;
             if (vec) {
                 for (int s = 4 * l; s < B; s += 64) {
                     const float4 d = *reinterpret_cast<const float4 *>(drow + s);
@@ -1689,8 +1825,7 @@ struct sdnn_net {
     int n_cu = 0;                 // compute units of the device
     int occ_spmm[2][3][2][2] = {}; // resident workgroups per CU of k_spmm<V,MODE,U,tiles inner>, U = 8, 16
     int occ_grad = 0;             // the same for k_bwd_grad
-    int grad_v = 1;               // samples per lane of the fused sweep of the last backward pass (1: k_bwd_grad, 4: k_bwd_grad4,
-                                  // 0: one sample per step, k_spmv_stage_grad)
+    int grad_v = 4;               // the last fused sweep: 4 samples per lane, or 0: one sample per step (k_spmv_stage_grad)
     int occ_panel[2][4] = {};     // the same for k_spmm_panel<R,MODE>, R = 1, 2, 4, 8
     std::vector<int32_t> max_len[2]; // per layer: longest row of W (0) and of W^T (1)
     std::vector<char> clustered[2];  // per layer: reorder_rows found clusters in W (0), in W^T (1)
@@ -1704,12 +1839,11 @@ struct sdnn_net {
     bool lds_attr_set[3] = {};       // the dynamic LDS limit of k_fwd_lds<1 << k> has been raised
     int grad_parts = 0;           // > 0: the last backward pass left the entries' gradient in G[0..grad_parts)
     bool vals_t_stale = false;    // the CSR values were changed by something that does not maintain vals_t
-    hipStream_t side = nullptr;   // second stream for the other half of the batch (small layers)
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     int32_t *d_flags[2] = {nullptr, nullptr}, *d_map[2] = {nullptr, nullptr}, *d_n_live[2] = {nullptr, nullptr}; // inference: dead-sample skipping, two rounds' state
     bool bias_nonpos = false;     // every bias of layers 2..L is <= 0 (as uploaded; cleared when a bias is replaced)
     int state = ST_IDLE;
-    int32_t B = 0;
+    int32_t B = 0;                // samples of the last forward pass
+    int32_t Bp = 0, ld = 0;       // training: samples the kernels work on (padded_batch) and floats per row of X_l, Delta_l
     int32_t max_n = 0;
     char err[512] = "";
 };
@@ -1777,6 +1911,19 @@ struct Plan {
     size_t table = 0, x0 = 0, ping = 0, pong = 0, flags[2] = {0, 0}, map[2] = {0, 0}, n_live[2] = {0, 0}, total = 0;
 };
 
+// Samples that the kernels of a training net work on for a batch of B: whole groups of four (the samples past B have a
+// zero input and no loss: their deltas are zero and they add exact zeros to every gradient).
+static int padded_batch(int B) { return B == 1 ? 1 : (B + 3) & ~3; }
+// Floats per row of the library's own activation and delta arrays: 16-byte pieces stay aligned, a row touches as few
+// 128-byte lines as it can.
+static int row_stride(int B)
+{
+    if (B == 1) return 1;
+    for (int w = 4; w <= 32; w *= 2)
+        if (B <= w) return w;
+    return (B + 31) & ~31;
+}
+
 static int check_config(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg)
 {
     if (!layers || !cfg) return fail(nullptr, SDNN_EINVAL, "layers or cfg is NULL");
@@ -1805,22 +1952,22 @@ static int check_config(const sdnn_layer *layers, int32_t n_layers, const sdnn_c
     return SDNN_OK;
 }
 
-// The fused backward + gradient kernels pay from layers of 4096 rows on, whose launches are bound by gather
-// throughput; below that, where the latency of a launch binds, the separate update is faster (measured step
-// time against the separate kernels: 1024 rows +10 %, 4096 rows -5 %, 16384 rows -20 %, 65536 rows -30 %).
-// Nets with long rows take the fused sweep for batches of up to 256 samples (grad_fusable): AUTO sets it up for
-// them when max_batch allows it.
+// The fused backward + gradient kernels pay where launches are bound by gather throughput; where their latency binds,
+// the separate update is faster (measured, backward + update per layer, separate / fused: 2048 neurons of 32 entries,
+// 64 samples 7.3 / 7.7 us, 99 samples 9.7 / 8.8; 1024 neurons, 99 samples 7.6 / 8.6, 200 samples 10.3 / 8.5; 4096 neurons, 64
+// samples 9.9 / 8.4; 2048 neurons of 205 entries, 64 samples 24 / 28 us, 256 samples 43 / 33).  AUTO decides by the entries per layer and by whether the net is made for more than 64 samples.
 static bool grad_buffers_wanted(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg)
 {
     if (!cfg->training || cfg->fuse_gradient == SDNN_FUSE_OFF) return false;
     if (cfg->fuse_gradient == SDNN_FUSE_ON) return true;
-    int64_t rows = 0, nnz = 0;
+    int64_t nnz = 0, rows = 0;
     for (int32_t l = 0; l < n_layers; ++l) {
         rows += layers[l].n_out;
         nnz += layers[l].row_ptr ? layers[l].row_ptr[layers[l].n_out] : 0;
     }
-    // long rows: fused where the whole batch fits one launch of the four-samples-per-lane sweep
-    return rows >= (int64_t)4096 * n_layers && (nnz < 128 * rows || cfg->max_batch <= 256);
+    if (cfg->max_batch > 256 && nnz >= 128 * rows) return false; // batches that wide take the separate kernels
+    if (cfg->max_batch > 64) return nnz >= (int64_t)48000 * n_layers;
+    return nnz >= (int64_t)85000 * n_layers && (nnz < 128 * rows || rows >= (int64_t)4096 * n_layers); // few long rows: too few wavefronts
 }
 
 // Chunks of a layer's lane-major copy: its rows, longest first, in blocks of 64, each as deep as its first row.
@@ -1903,7 +2050,7 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
     };
     pl.pl.resize(n_layers);
     pl.table = take(sizeof(LayerDev) * (size_t)n_layers);
-    const size_t mb = (size_t)cfg->max_batch;
+    const size_t mb = (size_t)cfg->max_batch, mld = (size_t)row_stride(cfg->max_batch);
     const bool gw = grad_buffers_wanted(layers, n_layers, cfg);
     const bool lm = lds_forward_wanted(layers, n_layers, cfg);
     size_t max_n = 0;
@@ -1953,9 +2100,9 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
         PLAN_KIND(t_row_idx, 4 * nnz[l])
         PLAN_KIND(t_perm, 4 * nnz[l])
         PLAN_KIND(t_sched, 16 * (size_t)y.n_in)
-        pl.x0 = take(4 * (size_t)layers[0].n_in * mb);
-        PLAN_KIND(X, 4 * (size_t)y.n_out * mb)
-        PLAN_KIND(D, 4 * (size_t)y.n_out * mb)
+        pl.x0 = take(4 * (size_t)layers[0].n_in * mld);
+        PLAN_KIND(X, 4 * (size_t)y.n_out * mld)
+        PLAN_KIND(D, 4 * (size_t)y.n_out * mld)
         if (gw) {
             PLAN_KIND(G[0], 4 * nnz[l])
             PLAN_KIND(G[1], 4 * nnz[l])
@@ -1967,8 +2114,8 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
             if (cfg->max_batch == 1) PLAN_KIND(t_col, 4 * nnz[l])
         }
     } else {
-        pl.ping = take(4 * max_n * mb);
-        pl.pong = take(4 * max_n * mb);
+        pl.ping = take(4 * max_n * mld);
+        pl.pong = take(4 * max_n * mld);
         for (int k = 0; k < 2; ++k) {
             pl.flags[k] = take(4 * mb);
             pl.map[k] = take(4 * mb);
@@ -2311,11 +2458,6 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
         net->n_cu = prop.multiProcessorCount;
         void *scratch_dev = nullptr; // this GPU's copy of the fixed staging array of sdnn_forward_noalloc
         if (scratch_address(nullptr, &scratch_dev) != SDNN_OK) return fail_free(SDNN_EHIP);
-        // default priority, like every stream here
-        if (hipStreamCreateWithFlags(&net->side, hipStreamNonBlocking) != hipSuccess ||
-            hipEventCreateWithFlags(&net->ev_fork, hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&net->ev_join, hipEventDisableTiming) != hipSuccess)
-            return fail_free(fail(nullptr, SDNN_EHIP, "cannot create the side stream"));
     }
     if (cfg->training) {
         net->d_x0 = (float *)(base + pl.x0);
@@ -2340,41 +2482,32 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
 extern "C" void sdnn_destroy(sdnn_net *net)
 {
     if (!net) return;
-    if (net->side) { (void)hipStreamSynchronize(net->side); (void)hipStreamDestroy(net->side); }
-    if (net->ev_fork) (void)hipEventDestroy(net->ev_fork);
-    if (net->ev_join) (void)hipEventDestroy(net->ev_join);
     delete net;
 }
 
-// Forward and backward treat the samples independently (the batch vectors are columns of X), so a
-// pass over small layers is run as two half-batches on two streams: each stream's kernels depend
-// only on its own previous kernel, and while one stream sits in the latencies at the head or tail
-// of a kernel, the other one computes.  Returns the samples per lane to use (0 = do not split).
-static int split_v(const sdnn_net *net, int B)
+static unsigned ew_blocks(size_t n) // workgroups of 256 threads for an elementwise pass
 {
-    if (B % 128 != 0 || (int64_t)net->max_n * B > ((int64_t)1 << 21)) return 0;
-    // long rows (hundreds of entries) keep a wavefront busy for long: nothing to hide, and wider lanes pay more
-    int64_t nnz = 0, rows = 0;
-    for (const LayerDev &d : net->layers) { nnz += d.nnz; rows += d.n_out; }
-    if (nnz >= 128 * rows) return 0;
-    return B % 512 == 0 ? 4 : B % 256 == 0 ? 2 : 1; // two or more tiles of 64*V samples
+    size_t b = (n + 255) / 256;
+    return (unsigned)std::min<size_t>(std::max<size_t>(b, 1), 8192);
 }
 
-// After a failure between fork and join: bring the helper stream back into the caller's stream, so that the
-// caller's stream (or a capture in progress) is not left with a dangling fork.
-static void join_side(sdnn_net *net, hipStream_t stream)
+// The same for FOR_ROW_ELEMENTS: threads per row, and workgroups for n rows.
+static int row_threads_log2(int Bp)
 {
-    if (hipEventRecord(net->ev_join, net->side) == hipSuccess) (void)hipStreamWaitEvent(stream, net->ev_join, 0);
+    int w = 0;
+    while (w < 8 && (1 << w) < Bp) ++w;
+    return w;
 }
+static unsigned row_blocks(int n, int w_log2) { return ew_blocks((size_t)n << w_log2); }
 
 static inline bool aligned(const void *p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
-// Samples per lane for the row-per-wavefront product: as wide as the batch
-// and the alignment of the operands allow without idling most of the wave.
-static int pick_v_spmm(int B, const void *a, const void *b, const void *c)
+// Samples per lane for the row-per-wavefront product: as wide as the batch and the alignment of the operands' rows
+// allow without idling most of the wave.
+static int pick_v_spmm(int B, int ld_in, int ld_out, const void *in, const void *out)
 {
-    if (B % 4 == 0 && B > 128 && aligned(a, 16) && aligned(b, 16) && aligned(c, 16)) return 4;
-    if (B % 2 == 0 && B > 64 && aligned(a, 8) && aligned(b, 8) && aligned(c, 8)) return 2;
+    if (ld_in % 4 == 0 && ld_out % 4 == 0 && B > 128 && aligned(in, 16) && aligned(out, 16)) return 4;
+    if (ld_in % 2 == 0 && ld_out % 2 == 0 && B > 64 && aligned(in, 8) && aligned(out, 8)) return 2;
     return 1;
 }
 
@@ -2441,7 +2574,7 @@ static int launch_spmm_panel(sdnn_net *net, const LayerDev &d, SpmmArgs a, int B
     if (blocks > 0x7fffffffull) return fail(net, SDNN_EINVAL, "grid too large");
     a.n_vblocks = (uint32_t)blocks;
     uint64_t g = std::min<uint64_t>(blocks, (uint64_t)net->occ_panel[MODE][ri] * (uint64_t)net->n_cu);
-    if (g >= 8) g &= ~(uint64_t)7;
+    if (g >= 8 && g < blocks) g &= ~(uint64_t)7;
     int n_cols_arg = n_cols;
     void *args[] = {(void *)&a, (void *)&n_cols_arg, (void *)&panel};
     HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)g), dim3(BLOCK_THREADS), args, 0, stream));
@@ -2449,21 +2582,40 @@ static int launch_spmm_panel(sdnn_net *net, const LayerDev &d, SpmmArgs a, int B
     return SDNN_OK;
 }
 
-// part/n_parts: the batch tiles of the launch are the part-th of n_parts equal shares (n_parts = 2
-// when a pass is run as two independent half-batches on two streams); force_v: samples per lane, 0 = choose.
-template <int MODE>
-static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, float *out,
-                       const float *aux, int B, hipStream_t stream, int part = 0, int n_parts = 1, int force_v = 0,
-                       const int32_t *n_live = nullptr, int32_t *flags = nullptr, int sub_begin = 0, int sub_end = 0)
+// The several-rows-per-wavefront kernels form byte offsets as (24-bit column) x (24-bit row pitch).
+static bool rows_addressable(int n_cols, int ld) { return n_cols < (1 << 24) && ld < (1 << 22); }
+// Lanes per row of the several-rows-per-wavefront kernels that a tile of `width` samples needs.
+static int lanes_per_row(int width) { return width <= 16 ? 4 : width <= 32 ? 8 : width <= 64 ? 16 : width <= 128 ? 32 : 64; }
+// The same, doubled while the wavefronts are fewer than the chip's SIMDs (idle lanes cost nothing there: 4096 neurons,
+// 16 samples 5.4 -> 4.6 us).
+static int spread_lanes(const sdnn_net *net, int G, int n_rows)
 {
-    // sub_begin .. sub_end: the launch covers these samples only (sub_begin a multiple of SUB_ALIGN, or of 64 where
-    // every layer takes the panel sweep; sub_end == 0: all of them, split by part / n_parts)
+    while (G < 32 && (int64_t)n_rows * (2 * G) <= (int64_t)64 * 4 * net->n_cu) G *= 2;
+    return G;
+}
+template <int G>
+static const void *rows_fn_act(int act)
+{
+    return act == ACT_SIGMOID ? (const void *)k_rows<G, ACT_SIGMOID> : (const void *)k_rows<G, ACT_RELU_CAP>;
+}
+static const void *rows_fn(int G, int act)
+{
+    return G == 4 ? rows_fn_act<4>(act) : G == 8 ? rows_fn_act<8>(act) : G == 16 ? rows_fn_act<16>(act) : rows_fn_act<32>(act);
+}
+
+// in / out: rows of ld_in / ld_out floats.  sub_begin .. sub_end: the launch covers these samples only (sub_begin a
+// multiple of SUB_ALIGN, or of 64 where every layer takes the panel sweep; sub_end == 0: all of them).
+template <int MODE>
+static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld_in, float *out, int ld_out,
+                       const float *aux, int B, hipStream_t stream, const int32_t *n_live = nullptr, int32_t *flags = nullptr,
+                       int sub_begin = 0, int sub_end = 0)
+{
     const bool sub = sub_end > 0;
     if (!sub) sub_end = B;
     SpmmArgs a;
     a.n_live = n_live;
     a.flags = flags;
-    a.g_part = nullptr; a.store_out = 1;
+    a.g_part[0] = a.g_part[1] = nullptr; a.store_out = 1;
     if (MODE == 0) {
         a.row_ptr = d.row_ptr; a.idx = d.col_idx; a.perm = nullptr; a.sched = d.sched;
         a.n_rows = d.n_out;
@@ -2471,9 +2623,11 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, float 
         a.row_ptr = d.t_row_ptr; a.idx = d.t_row_idx; a.perm = d.t_perm; a.sched = d.t_sched;
         a.n_rows = d.n_in;
     }
-    a.vals = d.vals; a.in = in; a.out = out; a.aux = aux; a.B = B; a.cap = net->cfg.act_cap; a.act = net->cfg.activation;
+    a.vals = d.vals; a.in = in; a.out = out; a.aux = aux; a.B = B; a.ld_in = ld_in; a.ld_out = ld_out;
+    a.cap = net->cfg.act_cap; a.act = net->cfg.activation;
     if (a.n_rows == 0) return SDNN_OK;
-    a.in_bytes = 4 * (size_t)(MODE == 0 ? d.n_in : d.n_out) * (size_t)B;
+    const int n_cols = MODE == 0 ? d.n_in : d.n_out;
+    a.in_bytes = 4 * (size_t)n_cols * (size_t)ld_in;
     if (a.in_bytes >= ((size_t)1 << 32))
         return fail(net, SDNN_EINVAL, "activation block of %zu bytes exceeds 4 GiB: use a smaller B", a.in_bytes);
     if (B == 1) {
@@ -2490,29 +2644,50 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, float 
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;
     }
+    const int l = (int)(&d - net->layers.data());
+    const int width = sub_end - sub_begin;
     // Wide layers with short rows: when a 64-sample tile of the operand (n_cols x 256 B) is at least twice
     // the chip's eight L2s, the panel sweep is faster (measured, 65536 columns: forward of a 64-sample
     // minibatch 64.8 -> 53.6 us per layer, inference in blocks of 1024 samples 217 -> 179 ms per 24 layers;
     // 16384 columns and fewer: slower than the kernels below).  sdnn_config.panel_cols overrides.
-    if (!n_live && !flags && n_parts == 1 && force_v == 0 && net->cfg.panel_cols >= 0) {
-        const int l = (int)(&d - net->layers.data());
-        const int n_cols = MODE == 0 ? d.n_in : d.n_out;
+    if (!n_live && !flags && net->cfg.panel_cols >= 0) {
         int panel = net->cfg.panel_cols;
         // (not where reorder_rows has found clusters: their locality comes from the row order, which the
         // panel kernel's larger workgroups would deal to the XCDs differently: 9.8 vs 6.8 ms on a structured net)
-        if (panel == 0 && (int64_t)n_cols * 256 >= ((int64_t)8 << 20) && d.nnz > 0 && !net->clustered[MODE][l])
-            panel = sub_end - sub_begin > 448 ? 6144 : 8192; // eight or more tiles: every XCD sweeps tiles of its own
+        if (panel == 0 && width > PANEL_MIN_SAMPLES && (int64_t)n_cols * 256 >= ((int64_t)8 << 20) && d.nnz > 0 && !net->clustered[MODE][l])
+            panel = width > 448 ? 6144 : 8192; // eight or more tiles: every XCD sweeps tiles of its own
         if (panel > 0 && net->max_len[MODE][l] <= 64)
             return launch_spmm_panel<MODE>(net, d, a, B, panel, stream, sub_begin, sub_end);
     }
-    const int V = force_v ? force_v : pick_v_spmm(B, in, out, MODE == 1 ? aux : nullptr);
-    const uint32_t all_tiles = (uint32_t)((B + 64 * V - 1) / (64 * V));
-    a.tile_base = all_tiles * (uint32_t)part / (uint32_t)n_parts;
-    a.n_tiles = all_tiles * (uint32_t)(part + 1) / (uint32_t)n_parts - a.tile_base;
+    const bool long_rows = (int64_t)d.nnz >= 128 * (int64_t)a.n_rows;
+    // Forward over short rows: several rows per wavefront, in tiles of 128 samples, or of 64 or 32 where the operand of a
+    // wider tile would not fit an XCD's L2 (forward of 128 / 256 samples, us per layer, tiles of 32 / 64 / 128: 10007
+    // neurons 13.0 / 12.7 / 13.0 and 22.2 / 21.6 / 23.8; 16384: 17.7 / 19.1 / 25.7 and 31.8 / 35.3 / 48.3; 30000: 35.6 / 44.7 / 55.4
+    // and 67.8 / 85.9 / 108).  Few rows and few samples: a wavefront per row keeps more of the chip busy (1024
+    // neurons, 64 samples: 4.6 vs 4.7).  Long rows are too uneven to share a wavefront.
+    if (MODE == 0 && !n_live && !flags && !long_rows && (width > 64 || a.n_rows >= 2048) && !net->clustered[MODE][l] &&
+        rows_addressable(n_cols, ld_in)) {
+        int tile = 128;
+        while (tile > 32 && 4 * (int64_t)n_cols * tile > 4000000) tile /= 2;
+        const int G = sub_begin == 0 && width <= tile ? spread_lanes(net, lanes_per_row(width), a.n_rows) : lanes_per_row(std::min(tile, width));
+        const int rows_per_block = 64 / G * WAVES_PER_BLOCK;
+        a.tile_base = (uint32_t)(sub_begin / (4 * G));
+        a.n_tiles = (uint32_t)((width + 4 * G - 1) / (4 * G));
+        a.n_rg = (uint32_t)((a.n_rows + rows_per_block - 1) / rows_per_block);
+        const uint64_t grid = (uint64_t)a.n_tiles * a.n_rg;
+        if (grid > 0x7fffffffull) return fail(net, SDNN_EINVAL, "grid too large");
+        void *args[] = {(void *)&a};
+        HIP_TRY(net, hipLaunchKernel(rows_fn(G, net->cfg.activation), dim3((unsigned)grid), dim3(BLOCK_THREADS), args, 0, stream));
+        HIP_TRY(net, hipGetLastError());
+        return SDNN_OK;
+    }
+    const int V = pick_v_spmm(B, ld_in, ld_out, in, out);
+    a.tile_base = 0;
+    a.n_tiles = (uint32_t)((B + 64 * V - 1) / (64 * V));
     if (sub) {
         if (sub_begin % (64 * V) != 0) return fail(net, SDNN_EHIP, "internal: sub-block at sample %d, tiles of %d", sub_begin, 64 * V);
         a.tile_base = (uint32_t)(sub_begin / (64 * V));
-        a.n_tiles = (uint32_t)((sub_end - sub_begin + 64 * V - 1) / (64 * V));
+        a.n_tiles = (uint32_t)((width + 64 * V - 1) / (64 * V));
     }
     if (a.n_tiles == 0) return SDNN_OK;
     a.n_rg = (uint32_t)((a.n_rows + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
@@ -2523,7 +2698,6 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, float 
     // third of the occupancy) and a grid of what the chip holds at once, whose workgroups walk the
     // virtual blocks.  Long, uneven rows (hundreds of entries): 16 in flight and one workgroup per
     // virtual block, so that the hardware hands out the rows, longest first, as wavefronts retire.
-    const bool long_rows = (int64_t)d.nnz >= 128 * (int64_t)a.n_rows;
     uint64_t g = blocks;
     // short rows and a few batch tiles (shared by all XCDs): workgroups are dealt row groups and walk the tiles
     const bool tiles_inner = !long_rows && a.n_tiles >= 2 && a.n_tiles < 8;
@@ -2538,9 +2712,25 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, float 
         }
         g = std::min(g, (uint64_t)per_cu * (uint64_t)net->n_cu);
     }
-    if (g >= 8) g &= ~(uint64_t)7; // keeps virtual block id % 8 == workgroup id % 8 (XCD-wise tiles)
+    // a walking grid keeps virtual block id % 8 == workgroup id % 8 (XCD-wise tiles); one that covers every block at once
+    // is not cut (the few blocks left over would run by themselves: 1500 rows 5.7 instead of 4.3 us)
+    if (g >= 8 && g < (tiles_inner ? (uint64_t)a.n_rg : blocks)) g &= ~(uint64_t)7;
     void *args[] = {(void *)&a};
     HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)g), dim3(BLOCK_THREADS), args, 0, stream));
+    HIP_TRY(net, hipGetLastError());
+    return SDNN_OK;
+}
+
+// A block of n rows of B floats copied between arrays of different row strides; columns B .. Bp - 1 of dst are zeroed.
+static int launch_copy_rows(sdnn_net *net, const float *src, int ld_src, float *dst, int ld_dst, int n, int B, int Bp, hipStream_t stream)
+{
+    if (n == 0) return SDNN_OK;
+    if (ld_src == B && ld_dst == B && Bp == B) {
+        HIP_TRY(net, hipMemcpyAsync(dst, src, 4 * (size_t)n * B, hipMemcpyDeviceToDevice, stream));
+        return SDNN_OK;
+    }
+    const int w = row_threads_log2(Bp);
+    hipLaunchKernelGGL(k_copy_rows, dim3(row_blocks(n, w)), dim3(256), 0, stream, src, ld_src, dst, ld_dst, n, B, Bp, w);
     HIP_TRY(net, hipGetLastError());
     return SDNN_OK;
 }
@@ -2610,8 +2800,9 @@ static int sub_block_width(const sdnn_net *net, int B)
     return w >= B ? 0 : (int)w;
 }
 
+// `ld`: floats per row of the activations between the layers.
 static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL, void *stream_, float *ping,
-                        float *pong)
+                        float *pong, int ld)
 {
     const bool training = net->cfg.training != 0;
     hipStream_t stream = (hipStream_t)stream_;
@@ -2642,23 +2833,20 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
         return SDNN_OK;
     }
     const float *in = d_X0;
+    int ld_in = B;
+    const int Bp = padded_batch(B);
     if (training) {
-        const size_t bytes = 4 * (size_t)net->layers[0].n_in * B;
-        if (bytes) HIP_TRY(net, hipMemcpyAsync(net->d_x0, d_X0, bytes, hipMemcpyDeviceToDevice, stream));
+        const int rc = launch_copy_rows(net, d_X0, B, net->d_x0, ld, net->layers[0].n_in, B, Bp, stream);
+        if (rc) return rc;
         in = net->d_x0;
-    }
-    int sv = split_v(net, B);
-    if (sv > 1 && (!aligned(d_X0, 4 * sv) || (d_XL && !aligned(d_XL, 4 * sv)))) sv = 0;
-    if (sv) {
-        HIP_TRY(net, hipEventRecord(net->ev_fork, stream));
-        HIP_TRY(net, hipStreamWaitEvent(net->side, net->ev_fork, 0));
+        ld_in = ld;
     }
     // Inference on large activation blocks: the samples are independent (the columns of X, Section 5.1), so the
     // block is taken through all layers in sub-blocks whose two activation buffers stay in the memory-side
     // cache (what a layer wrote is what the next one gathers): measured on 65536-neuron layers, blocks of 1024
     // samples: 179 ms per 24 layers in one piece, 161 ms in sub-blocks of 64; 16384 neurons, 4096 samples: 41.5 ms
     // per 48 layers in one piece, 39.1 in sub-blocks of 256.
-    const int sub_w = training || sv ? 0 : sub_block_width(net, B);
+    const int sub_w = training ? 0 : sub_block_width(net, B);
     if (sub_w > 0) {
         for (int s0 = 0; s0 < B; s0 += sub_w) {
             const int s1 = std::min(B, s0 + sub_w);
@@ -2666,7 +2854,7 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
             for (int l = 0; l < L; ++l) {
                 const LayerDev &d = net->layers[l];
                 float *out = l == L - 1 ? d_XL : ((l & 1) ? pong : ping);
-                const int rc = launch_spmm<0>(net, d, sin, out, d.bias, B, stream, 0, 1, 0, nullptr, nullptr, s0, s1);
+                const int rc = launch_spmm<0>(net, d, sin, l == 0 ? B : ld, out, l == L - 1 ? B : ld, d.bias, B, stream, nullptr, nullptr, s0, s1);
                 if (rc) return rc;
                 sin = out;
             }
@@ -2678,24 +2866,19 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
     for (int l = 0; l < L; ++l) {
         const LayerDev &d = net->layers[l];
         float *out = training ? d.X : (l == L - 1 ? d_XL : ((l & 1) ? pong : ping));
-        int rc = sv ? launch_spmm<0>(net, d, in, out, d.bias, B, stream, 0, 2, sv)
-                    : launch_spmm<0>(net, d, in, out, d.bias, B, stream);
-        if (!rc && sv) rc = launch_spmm<0>(net, d, in, out, d.bias, B, net->side, 1, 2, sv);
-        if (rc) {
-            if (sv) join_side(net, stream);
-            return rc;
-        }
+        const int ld_out = !training && l == L - 1 ? B : ld;
+        const int rc = launch_spmm<0>(net, d, in, ld_in, out, ld_out, d.bias, training ? Bp : B, stream);
+        if (rc) return rc;
         in = out;
-    }
-    if (sv) {
-        HIP_TRY(net, hipEventRecord(net->ev_join, net->side));
-        HIP_TRY(net, hipStreamWaitEvent(stream, net->ev_join, 0));
+        ld_in = ld_out;
     }
     if (training && d_XL) {
-        const size_t bytes = 4 * (size_t)net->layers[L - 1].n_out * B;
-        if (bytes) HIP_TRY(net, hipMemcpyAsync(d_XL, net->layers[L - 1].X, bytes, hipMemcpyDeviceToDevice, stream));
+        const int rc = launch_copy_rows(net, net->layers[L - 1].X, ld, d_XL, B, net->layers[L - 1].n_out, B, B, stream);
+        if (rc) return rc;
     }
     net->B = B;
+    net->Bp = Bp;
+    net->ld = ld;
     net->state = ST_FORWARD;
     return SDNN_OK;
 }
@@ -2714,7 +2897,7 @@ extern "C" int sdnn_forward(sdnn_net *net, const float *d_X0, int32_t B, float *
 {
     const int rc = check_forward_args(net, d_X0, B, d_XL);
     if (rc) return rc;
-    return forward_impl(net, d_X0, B, d_XL, stream_, net->d_ping, net->d_pong);
+    return forward_impl(net, d_X0, B, d_XL, stream_, net->d_ping, net->d_pong, row_stride(B));
 }
 
 // ---------------------------------------------------------------------------
@@ -2738,15 +2921,11 @@ extern "C" int sdnn_forward_noalloc(sdnn_net *net, const float *d_X0, int32_t B,
     void *base = nullptr;
     rc = scratch_address(net, &base);
     if (rc) return rc;
-    return forward_impl(net, d_X0, B, d_XL, stream_, (float *)base, (float *)((char *)base + half));
+    const int ld = 4 * (size_t)net->max_n * (size_t)row_stride(B) <= half ? row_stride(B) : B;
+    return forward_impl(net, d_X0, B, d_XL, stream_, (float *)base, (float *)((char *)base + half), ld);
 }
 
 
-static unsigned ew_blocks(size_t n)
-{
-    size_t b = (n + 255) / 256;
-    return (unsigned)std::min<size_t>(std::max<size_t>(b, 1), 8192);
-}
 
 extern "C" int sdnn_forward_skip_dead(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL,
                                       int32_t check_every, int32_t *d_n_live, void *stream_)
@@ -2776,7 +2955,7 @@ extern "C" int sdnn_forward_skip_dead(sdnn_net *net, const float *d_X0, int32_t 
         float *out = (l & 1) ? net->d_pong : net->d_ping;
         // one sample: nothing to pack, this is the plain pass
         const bool check = (l + 1) % check_every == 0 && l + 1 < L && B > 1 && d.n_out > 0;
-        const int rc = launch_spmm<0>(net, d, in, out, d.bias, B, stream, 0, 1, 0, net->d_n_live[k & 1],
+        const int rc = launch_spmm<0>(net, d, in, B, out, B, d.bias, B, stream, net->d_n_live[k & 1],
                                       check ? net->d_flags[k & 1] : nullptr);
         if (rc) return rc;
         if (check) {
@@ -2801,63 +2980,78 @@ extern "C" int sdnn_forward_skip_dead(sdnn_net *net, const float *d_X0, int32_t 
     return SDNN_OK;
 }
 
-// Fused back-propagation + entry gradient of one layer for the part-th of n_parts 64-sample windows.
-// store_out = 0 for the first layer (gradient only: there is no Delta_0, out may be NULL).
-static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, int B, hipStream_t stream, int part,
-                           int store_out)
+// Batches of 128 on nets of short rows and up to 16384 neurons sum the gradient over two windows of 64 samples.
+static bool two_windows(const sdnn_net *net, int B)
 {
+    if (B != 128 || (int64_t)net->max_n * B > ((int64_t)1 << 21)) return false;
+    int64_t nnz = 0, rows = 0;
+    for (const LayerDev &d : net->layers) { nnz += d.nnz; rows += d.n_out; }
+    return nnz < 128 * rows;
+}
+
+// Fused back-propagation + entry gradient of one layer.  store_out = 0 for the first layer (gradient only: there is no
+// Delta_0, out may be NULL).
+static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStream_t stream, int store_out)
+{
+    const int B = net->Bp;
     SpmmArgs a;
     a.row_ptr = d.t_row_ptr; a.idx = d.t_row_idx; a.perm = nullptr; a.sched = d.t_sched; a.n_rows = d.n_in;
-    a.vals = d.vals_t; a.in = d.D; a.out = out; a.aux = d.X_prev; a.B = B; a.cap = net->cfg.act_cap;
+    a.vals = d.vals_t; a.in = d.D; a.out = out; a.aux = d.X_prev; a.B = B; a.ld_in = a.ld_out = net->ld; a.cap = net->cfg.act_cap;
     a.act = net->cfg.activation; a.n_live = nullptr; a.flags = nullptr;
-    a.g_part = d.G[part]; a.store_out = store_out;
+    a.g_part[0] = d.G[0]; a.g_part[1] = d.G[1]; a.store_out = store_out;
     if (a.n_rows == 0 || d.nnz == 0) {
         if (d.nnz == 0 && store_out && a.n_rows > 0) // no entries: Delta_{l-1} = 0, nothing to differentiate
-            return launch_spmm<1>(net, d, d.D, out, d.X_prev, B, stream, part, part == 0 && B <= 64 ? 1 : 2, 1);
+            return launch_spmm<1>(net, d, d.D, net->ld, out, net->ld, d.X_prev, B, stream);
         return SDNN_OK;
     }
-    a.in_bytes = 4 * (size_t)d.n_out * (size_t)B;
-    if (a.in_bytes >= ((size_t)1 << 32))
-        return fail(net, SDNN_EINVAL, "activation block of %zu bytes exceeds 4 GiB: use a smaller B", a.in_bytes);
-    a.tile_base = (uint32_t)part; // windows of 64 samples
+    a.in_bytes = 4 * (size_t)d.n_out * (size_t)net->ld;
+    a.tile_base = 0;
     a.n_tiles = 1;
     a.n_rg = (uint32_t)((a.n_rows + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
     a.n_vblocks = a.n_rg;
     if (net->grad_v == 0) { // B = 1
         const int R = a.n_rows >= 32768 ? 16 : 8;
-        a.row_ptr = d.t_row_ptr;
         const int32_t *t_col = d.t_col;
         hipLaunchKernelGGL((k_spmv_stage_grad<8>), dim3((unsigned)((a.n_rows + R - 1) / R)), dim3(64), 0, stream, a, R, t_col);
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;
     }
-    if (net->grad_v == 4) {
-        // long, uneven rows: one workgroup per four rows, so that the hardware hands out the rows, longest first, as
-        // wavefronts retire
-        a.tile_base = 0;
-        void *args4[] = {(void *)&a};
-        HIP_TRY(net, hipLaunchKernel((const void *)k_bwd_grad4<8>, dim3(a.n_vblocks), dim3(BLOCK_THREADS), args4, 0, stream));
+    void *args[] = {(void *)&a};
+    if (B <= 64 && ((a.n_rows <= 6144 && (int64_t)d.nnz < 128 * (int64_t)a.n_rows) || !rows_addressable(d.n_out, net->ld))) {
+        // few short rows: a wavefront for each keeps more of the chip busy than several rows per wavefront (4096 rows, 64
+        // samples: 7.3 vs 8.2 us; 6500 rows: 9.9 vs 9.0)
+        const void *fn = (const void *)k_bwd_grad<8>;
+        if (net->occ_grad == 0) {
+            HIP_TRY(net, hipOccupancyMaxActiveBlocksPerMultiprocessor(&net->occ_grad, fn, BLOCK_THREADS, 0));
+            if (net->occ_grad < 1) net->occ_grad = 1;
+        }
+        uint64_t g = std::min<uint64_t>(a.n_vblocks, (uint64_t)net->occ_grad * (uint64_t)net->n_cu);
+        if (g >= 8 && g < a.n_vblocks) g &= ~(uint64_t)7;
+        HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)g), dim3(BLOCK_THREADS), args, 0, stream));
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;
     }
-    const void *fn = (const void *)k_bwd_grad<8>;
-    if (net->occ_grad == 0) {
-        HIP_TRY(net, hipOccupancyMaxActiveBlocksPerMultiprocessor(&net->occ_grad, fn, BLOCK_THREADS, 0));
-        if (net->occ_grad < 1) net->occ_grad = 1;
-    }
-    uint64_t g = std::min<uint64_t>(a.n_vblocks, (uint64_t)net->occ_grad * (uint64_t)net->n_cu);
-    if (g >= 8) g &= ~(uint64_t)7;
-    void *args[] = {(void *)&a};
-    HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)g), dim3(BLOCK_THREADS), args, 0, stream));
+    // two windows: as two tiles (and two partial gradients) where the operand is larger than L2 (16384 neurons: 27.5 -> 25.3
+    // us per layer), else in one (4096 neurons: 10.2 -> 8.9)
+    const bool two = two_windows(net, B);
+    int G = lanes_per_row(net->grad_parts == 2 ? 64 : B);
+    if (!two) G = spread_lanes(net, G, a.n_rows);
+    const int rows_per_block = 64 / G * WAVES_PER_BLOCK;
+    a.n_tiles = (uint32_t)net->grad_parts;
+    a.n_rg = (uint32_t)((a.n_rows + rows_per_block - 1) / rows_per_block);
+    const void *fn = G == 4 ? (const void *)k_bwd_rows<4, false> : G == 8 ? (const void *)k_bwd_rows<8, false>
+                     : G == 16 ? (const void *)k_bwd_rows<16, false> : G == 64 ? (const void *)k_bwd_rows<64, false>
+                     : two ? (const void *)k_bwd_rows<32, true> : (const void *)k_bwd_rows<32, false>;
+    HIP_TRY(net, hipLaunchKernel(fn, dim3(a.n_tiles * a.n_rg), dim3(BLOCK_THREADS), args, 0, stream));
     HIP_TRY(net, hipGetLastError());
     return SDNN_OK;
 }
 
-// The fused kernels take launches of at most 64 samples with one sample per lane: the whole batch
-// (B <= 64) or its two halves on two streams (B = 128 on small layers); rows must be short.
-static int grad_fusable(const sdnn_net *net, int B, int sv, int *v)
+// Whether the backward pass over this batch also forms the gradient: the number of partial gradients, 0 = it does not.
+// *v: samples per lane (0: one sample per step).
+static int grad_fusable(const sdnn_net *net, int B, int *v)
 {
-    *v = 1;
+    *v = 4;
     if (net->layers[0].G[0] == nullptr) return 0;
     if (B == 1) { // one sample per step: wide layers with short rows only (among those that k_spmv_stage takes)
         // measured step of the 120-layer sigmoid nets, fused vs separate: 65536 rows 6.39 vs 7.80 ms, 16384 rows 2.27
@@ -2868,16 +3062,10 @@ static int grad_fusable(const sdnn_net *net, int B, int sv, int *v)
         *v = 0;
         return 1;
     }
-    int64_t nnz = 0, rows = 0;
-    for (const LayerDev &d : net->layers) { nnz += d.nnz; rows += d.n_out; }
-    if (nnz >= 128 * rows) { // long rows: the whole batch in one launch, four samples per lane (k_bwd_grad4)
-        if (B > 256 || B % 4 != 0) return 0;
-        *v = 4;
-        return 1;
-    }
-    if (sv == 1 && B == 128) return 2;
-    if (sv == 0 && B <= 64) return 1;
-    return 0;
+    if (B > 256) return 0;
+    for (const LayerDev &d : net->layers)
+        if (B > 64 && !rows_addressable(d.n_out, net->ld)) return 0;
+    return two_windows(net, B) && 4 * (int64_t)net->max_n * B > 6500000 ? 2 : 1;
 }
 
 extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)
@@ -2888,16 +3076,15 @@ extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)
         return fail(net, SDNN_ESTATE, "sdnn_backward needs a directly preceding sdnn_forward");
     if (!d_dLoss) return fail(net, SDNN_EINVAL, "d_dLoss is NULL");
     hipStream_t stream = (hipStream_t)stream_;
-    const int L = net->n_layers, B = net->B;
+    const int L = net->n_layers, B = net->Bp;
     const LayerDev &last = net->layers[L - 1];
-    const size_t n = (size_t)last.n_out * B;
-    if (n) {
-        hipLaunchKernelGGL(k_output_delta, dim3(ew_blocks(n)), dim3(256), 0, stream, d_dLoss, last.X,
-                           last.D, n, net->cfg.act_cap, net->cfg.activation);
+    if (last.n_out > 0) {
+        const int w = row_threads_log2(B);
+        hipLaunchKernelGGL(k_output_delta, dim3(row_blocks(last.n_out, w)), dim3(256), 0, stream, d_dLoss, last.X, last.D, last.n_out,
+                           net->B, net->ld, B, w, net->cfg.act_cap, net->cfg.activation);
         HIP_TRY(net, hipGetLastError());
     }
-    const int sv = split_v(net, B);
-    const int gp = grad_fusable(net, B, sv, &net->grad_v);
+    const int gp = grad_fusable(net, B, &net->grad_v);
     net->grad_parts = gp;
     if (gp && net->vals_t_stale) { // the CSR values were replaced or stepped by the separate update since the last sweep
         int max_nnz = 0;
@@ -2910,39 +3097,16 @@ extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)
         }
         net->vals_t_stale = false;
     }
-    if (sv) {
-        HIP_TRY(net, hipEventRecord(net->ev_fork, stream));
-        HIP_TRY(net, hipStreamWaitEvent(net->side, net->ev_fork, 0));
-    }
     for (int l = L - 1; l >= (gp ? 0 : 1); --l) {
         const LayerDev &d = net->layers[l];
         // Delta_{l} (0-based l-1) = (W^T Delta_{l+1}) masked by X_{l}
         float *dprev = l >= 1 ? net->layers[l - 1].D : nullptr;
-        int rc;
-        if (gp) {
-            rc = launch_bwd_grad(net, d, dprev, B, stream, 0, l >= 1);
-            if (!rc && gp == 2) rc = launch_bwd_grad(net, d, dprev, B, net->side, 1, l >= 1);
-        } else {
-            rc = sv ? launch_spmm<1>(net, d, d.D, dprev, d.X_prev, B, stream, 0, 2, sv)
-                    : launch_spmm<1>(net, d, d.D, dprev, d.X_prev, B, stream);
-            if (!rc && sv) rc = launch_spmm<1>(net, d, d.D, dprev, d.X_prev, B, net->side, 1, 2, sv);
-        }
-        if (rc) {
-            if (sv) join_side(net, stream);
-            return rc;
-        }
-    }
-    if (sv) {
-        HIP_TRY(net, hipEventRecord(net->ev_join, net->side));
-        HIP_TRY(net, hipStreamWaitEvent(stream, net->ev_join, 0));
+        const int rc = gp ? launch_bwd_grad(net, d, dprev, stream, l >= 1)
+                          : launch_spmm<1>(net, d, d.D, net->ld, dprev, net->ld, d.X_prev, B, stream);
+        if (rc) return rc;
     }
     net->state = ST_BACKWARD;
     return SDNN_OK;
-}
-
-static int pick_v_update(int B, const void *a, const void *b)
-{
-    return (B % 4 == 0 && aligned(a, 16) && aligned(b, 16)) ? 4 : 1;
 }
 
 static int launch_update(sdnn_net *net, int layer0, int n_layers, float lr, int emit, float *g,
@@ -2951,7 +3115,7 @@ static int launch_update(sdnn_net *net, int layer0, int n_layers, float lr, int 
     int max_rows = 0;
     for (int l = layer0; l < layer0 + n_layers; ++l) max_rows = std::max(max_rows, net->layers[l].n_out);
     if (max_rows == 0) return SDNN_OK;
-    const int B = net->B;
+    const int B = net->Bp;
     if (B == 1) {
         // lanes per row: the power of two that covers the mean row length, 8..64
         int64_t nnz = 0, rows = 0;
@@ -2968,8 +3132,6 @@ static int launch_update(sdnn_net *net, int layer0, int n_layers, float lr, int 
         }
         return SDNN_OK;
     }
-    // all activation / delta buffers are 256-byte aligned; rows are aligned iff B % 4 == 0
-    const int V = pick_v_update(B, net->layers[layer0].D, net->layers[layer0].X_prev);
     // short rows: a wavefront takes several rows one after the other (fewer, longer-lived wavefronts); long rows: one
     int64_t nnz = 0, rows = 0;
     for (int l = layer0; l < layer0 + n_layers; ++l) { nnz += net->layers[l].nnz; rows += net->layers[l].n_out; }
@@ -2980,15 +3142,13 @@ static int launch_update(sdnn_net *net, int layer0, int n_layers, float lr, int 
     for (int l0 = 0; l0 < n_layers; l0 += 65535) {
         const int nl = std::min(65535, n_layers - l0);
         dim3 grid(interleave ? 8u * n_rg : n_rg, (unsigned)(interleave ? (nl + 7) / 8 : nl));
-        if (V == 4 && rpw == 1 && B <= 256) // long rows: the row of Delta stays in registers
+        // rows of Delta and X are whole 16-byte pieces; long rows: the row of Delta stays in registers
+        if (rpw == 1 && B <= 256)
             hipLaunchKernelGGL((k_update<4, 4>), grid, dim3(64 * UPD_WAVES), 0, stream, net->d_layers,
-                               layer0 + l0, nl, interleave, rpw, B, lr, net->cfg.update_bias, emit, g, gb);
-        else if (V == 4)
-            hipLaunchKernelGGL((k_update<4, 0>), grid, dim3(64 * UPD_WAVES), 0, stream, net->d_layers,
-                               layer0 + l0, nl, interleave, rpw, B, lr, net->cfg.update_bias, emit, g, gb);
+                               layer0 + l0, nl, interleave, rpw, B, net->ld, lr, net->cfg.update_bias, emit, g, gb);
         else
-            hipLaunchKernelGGL((k_update<1, 0>), grid, dim3(64 * UPD_WAVES), 0, stream, net->d_layers,
-                               layer0 + l0, nl, interleave, rpw, B, lr, net->cfg.update_bias, emit, g, gb);
+            hipLaunchKernelGGL((k_update<4, 0>), grid, dim3(64 * UPD_WAVES), 0, stream, net->d_layers,
+                               layer0 + l0, nl, interleave, rpw, B, net->ld, lr, net->cfg.update_bias, emit, g, gb);
         HIP_TRY(net, hipGetLastError());
     }
     return SDNN_OK;
@@ -3015,7 +3175,7 @@ extern "C" int sdnn_sgd_step(sdnn_net *net, float lr, void *stream_)
             }
             if (max_rows > 0 && net->cfg.update_bias)
                 hipLaunchKernelGGL(k_apply_bias, dim3((unsigned)((max_rows + 16 * WAVES_PER_BLOCK - 1) / (16 * WAVES_PER_BLOCK)), (unsigned)nl),
-                                   dim3(BLOCK_THREADS), 0, (hipStream_t)stream_, net->d_layers + l0, net->B, lr, (float *)nullptr);
+                                   dim3(BLOCK_THREADS), 0, (hipStream_t)stream_, net->d_layers + l0, net->Bp, net->ld, lr, (float *)nullptr);
             HIP_TRY(net, hipGetLastError());
         }
     } else {
@@ -3045,7 +3205,7 @@ extern "C" int sdnn_weight_grad(sdnn_net *net, int32_t layer, float *d_g, float 
                                d.t_perm, d_g, d.nnz);
         if (d_gb && d.n_out > 0)
             hipLaunchKernelGGL(k_apply_bias, dim3((unsigned)((d.n_out + 16 * WAVES_PER_BLOCK - 1) / (16 * WAVES_PER_BLOCK)), 1u),
-                               dim3(BLOCK_THREADS), 0, stream, net->d_layers + (layer - 1), net->B, 0.0f, d_gb);
+                               dim3(BLOCK_THREADS), 0, stream, net->d_layers + (layer - 1), net->Bp, net->ld, 0.0f, d_gb);
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;
     }
@@ -3067,7 +3227,7 @@ extern "C" int sdnn_get_activation(sdnn_net *net, int32_t layer, float *d_dst, v
     if (!d_dst) return fail(net, SDNN_EINVAL, "d_dst is NULL");
     const float *src = layer == 0 ? net->d_x0 : net->layers[layer - 1].X;
     const size_t n = layer == 0 ? net->layers[0].n_in : net->layers[layer - 1].n_out;
-    return copy_dd(net, d_dst, src, 4 * n * net->B, stream_);
+    return launch_copy_rows(net, src, net->ld, d_dst, net->B, (int)n, net->B, net->B, (hipStream_t)stream_);
 }
 
 extern "C" int sdnn_get_delta(sdnn_net *net, int32_t layer, float *d_dst, void *stream_)
@@ -3077,7 +3237,8 @@ extern "C" int sdnn_get_delta(sdnn_net *net, int32_t layer, float *d_dst, void *
     if (net->state != ST_BACKWARD) return fail(net, SDNN_ESTATE, "no backward pass to read");
     if (layer < 1 || layer > net->n_layers) return fail(net, SDNN_EINVAL, "layer out of range");
     if (!d_dst) return fail(net, SDNN_EINVAL, "d_dst is NULL");
-    return copy_dd(net, d_dst, net->layers[layer - 1].D, 4 * (size_t)net->layers[layer - 1].n_out * net->B, stream_);
+    return launch_copy_rows(net, net->layers[layer - 1].D, net->ld, d_dst, net->B, net->layers[layer - 1].n_out, net->B, net->B,
+                            (hipStream_t)stream_);
 }
 
 extern "C" int sdnn_get_weights(sdnn_net *net, int32_t layer, float *d_values, float *d_bias, void *stream_)

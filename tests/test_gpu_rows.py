@@ -1,0 +1,73 @@
+"""The kernels with several matrix rows per wavefront (forward, and backward with the gradient) at the sizes where their
+layout changes: batches around 16, 32, 64, 128 and 256 samples (lanes per row), batches that are no multiple of four (zero
+samples fill the last group), tiles of samples, row lengths around the 16-entry groups, rows left over at the end."""
+import numpy as np
+import pytest
+
+from paper_2104_11805_amd import workloads as wl
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(seed, n_out, n_in, lengths):
+    """Row r holds lengths[r % len(lengths)] distinct random columns."""
+    rng = np.random.default_rng(seed)
+    deg = np.resize(np.asarray(lengths), n_out)
+    row_ptr = np.zeros(n_out + 1, np.int32)
+    np.cumsum(deg, out=row_ptr[1:])
+    cols = np.concatenate([np.sort(rng.choice(n_in, size=d, replace=False)) for d in deg]).astype(np.int32)
+    vals = (rng.standard_normal(cols.size) * 0.4).astype(np.float32)
+    return wl.Layer(n_out, n_in, row_ptr, cols, vals, (rng.standard_normal(n_out) * 0.2).astype(np.float32))
+
+
+def _step(layers, b, seed, fuse, activation="relu"):
+    work = wl.Workload("rows", layers, 3.0, wl.normal_inputs(seed, layers[0].n_in, b), b, "mse", 0.05,
+                       targets=wl.uniform_targets(seed + 1, layers[-1].n_out, b), activation=activation)
+    g = P.gpu_train_step(work, work.x_infer, fuse_gradient=fuse)
+    o = P.oracle_train_step(work, work.x_infer)
+    st = P.compare_step(g, o, f"rows b={b} fuse={fuse} {activation}", exact_fwd=(activation == "relu"))
+    assert st["live_g"] == len(layers)
+    if activation == "relu":
+        assert st["bitexact_d"] == len(layers)
+
+
+@pytest.mark.parametrize("b", [2, 3, 4, 15, 17, 31, 33, 63, 66, 97, 127, 129, 200, 255, 257])
+def test_batch_sizes_around_the_lanes_per_row(b):
+    layers = [_layer(9300, 2113, 250, (0, 1, 3, 15, 16, 17, 31, 33, 40)), _layer(9301, 75, 2113, (70, 16, 5, 90))]
+    _step(layers, b, 9310, fuse=1)
+
+
+@pytest.mark.parametrize("b,fuse,activation", [(5, -1, "relu"), (99, -1, "relu"), (30, 1, "sigmoid"), (99, 1, "sigmoid")])
+def test_separate_update_and_sigmoid(b, fuse, activation):
+    layers = [_layer(9320, 2113, 250, (2, 9, 16, 40)), _layer(9321, 75, 2113, (70, 16, 5, 90))]
+    _step(layers, b, 9330, fuse, activation)
+
+
+@pytest.mark.parametrize("n_in,n_mid,b", [(9001, 2500, 128), (17003, 6500, 256), (17003, 6500, 130)])
+def test_tiles_of_samples_on_operands_larger_than_l2(n_in, n_mid, b):
+    """Forward tiles of 64 and 32 samples (operands of 4.6 and 17 MB), backward in halves of 128 samples."""
+    layers = [_layer(9340, n_mid, n_in, (4, 20)), _layer(9341, 8001, n_mid, (3, 6)), _layer(9342, 33, 8001, (200, 17))]
+    _step(layers, b, 9350, fuse=1)
+
+
+def test_a_smaller_batch_after_a_larger_one():
+    """The arrays' row pitch follows the batch: nothing of the earlier, wider batch may show."""
+    import torch
+    from paper_2104_11805_amd import sdnn
+    layers = [_layer(9360, 2113, 250, (2, 9, 16, 40)), _layer(9361, 75, 2113, (70, 16, 5, 90))]
+    net = sdnn.Net(layers, 3.0, 131, training=True, fuse_gradient=1)
+    for b in (131, 6, 50, 1, 99):
+        x, y = wl.normal_inputs(9370 + b, 250, b), wl.uniform_targets(9380 + b, 75, b)
+        xl = torch.empty(75, b, device=P.DEV)
+        net.sdnn_forward(P.dev(x), xl)
+        net.sdnn_backward(sdnn.sdnn_mse_dloss(xl, P.dev(y)))
+        xs, deltas, grads, _ = P.O32.train_step(layers, x, 3.0, lambda v: P.mse_dloss(v, y), 0.0)
+        assert np.array_equal(P.host(xl), xs[-1]), b
+        assert np.array_equal(P.host(net.sdnn_get_activation(1, b)), xs[1]), b
+        for k in (1, 2):
+            assert np.array_equal(P.host(net.sdnn_get_delta(k, b)), deltas[k]), b
+            for got, ref in zip(net.sdnn_weight_grad(k), grads[k - 1]):
+                P.assert_grad_close(P.host(got), ref, f"b={b} layer {k}")
+        net.sdnn_sgd_step(0.0)
+    net.close()
