@@ -841,11 +841,33 @@ template <> struct LdsPiece<1> { typedef float type; };
 template <> struct LdsPiece<2> { typedef float type __attribute__((ext_vector_type(2))); };
 template <> struct LdsPiece<4> { typedef float type __attribute__((ext_vector_type(4))); };
 
-template <int T, int ACT>
-__global__ void __launch_bounds__(64 * LDS_WAVES)
-k_fwd_lds(const LmLayer *__restrict__ tab, const int32_t *__restrict__ lm_cs, const uint4 *__restrict__ lm, unsigned lm_bytes,
-          const float *__restrict__ lm_bias, const int32_t *__restrict__ lm_row, int n_layers, int n0,
-          const float *__restrict__ X0, float *__restrict__ XL, int B, float cap, int vec_io)
+// What a launch takes through which layers.
+struct LdsForward {
+    const LmLayer *tab;
+    const int32_t *lm_cs;
+    const uint4 *lm;
+    const float *lm_bias;
+    const int32_t *lm_row;
+    unsigned lm_bytes;
+    int32_t l0, l1;        // layers l0 .. l1 - 1 (0-based)
+    int32_t n_in;          // neurons of the input (l0 == 0: at positions of their own number)
+    const float *in;       // [n_in][ld_in]
+    float *out;            // [n_out(l1 - 1)][ld_out]
+    int32_t ld_in, ld_out;
+    int32_t B;             // samples
+    int32_t vec_io;        // rows of in and out are whole T-float pieces
+    float cap;
+    // parts of a pass that drops dead samples (k_fwd_lds_part)
+    const int32_t *n_live; // samples that are left; workgroups past them end at once
+    const int32_t *src_col; // the column of `in` that holds sample k of them
+    const int32_t *dst_col; // the column of `out` that sample k goes to (NULL: k)
+    int32_t *alive;        // alive[k] = whether sample k has a non-zero activation at the end (NULL: not wanted)
+    int32_t max_pos;       // positions of the LDS buffer
+};
+
+// PART: a stretch of layers for the samples that are still alive.
+template <int T, int ACT, bool PART>
+__device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_samples)
 {
     extern __shared__ __attribute__((aligned(16))) float lds_act[];
     typedef typename LdsPiece<T>::type piece; // the T samples of one position: one LDS access
@@ -856,34 +878,48 @@ k_fwd_lds(const LmLayer *__restrict__ tab, const int32_t *__restrict__ lm_cs, co
     asm("" : "+v"(shift)); // kept in a register for lds_address
     typedef const LmLayer __attribute__((address_space(4))) *tab_ptr;
     typedef const int32_t __attribute__((address_space(4))) *cs_ptr;
-    const tab_ptr stab = (tab_ptr)tab;
-    const cs_ptr scs = (cs_ptr)lm_cs;
+    const tab_ptr stab = (tab_ptr)a.tab;
+    const cs_ptr scs = (cs_ptr)a.lm_cs;
+    const float *__restrict__ lm_bias = a.lm_bias;
+    const int32_t *__restrict__ lm_row = a.lm_row;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // neighbouring samples share cache lines of X: an XCD takes a contiguous stretch of them
-    const int nwg = (int)gridDim.x, per = nwg >> 3, wg = (int)blockIdx.x;
-    const int grp = wg < 8 * per ? (wg & 7) * per + (wg >> 3) : wg;
     const int s0 = grp * T;
-    const bool full = s0 + T <= B && vec_io; // all T samples exist and T-float pieces of a row of X are aligned
+    const bool full = s0 + T <= n_samples && a.vec_io; // all T samples exist and T-float pieces of a row of X are aligned
+    int src[T]; // PART: the samples' columns
+    if constexpr (PART) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) src[t] = a.src_col[min(s0 + t, n_samples - 1)];
+    }
 
-    for (int i = tid; i < n0; i += 64 * LDS_WAVES) { // X_0 at its own positions (zeros past the end of the batch)
-        const float *src = X0 + (size_t)i * B + s0;
+    // the input at its positions (l0 == 0: a neuron's own number; else where the layer below would have put it), zeros
+    // past the end of the batch
+    const int n_fill = PART && a.l0 > 0 ? stab[a.l0 - 1].n_pos : a.n_in;
+    for (int i = tid; i < n_fill; i += 64 * LDS_WAVES) {
+        const int row = PART && a.l0 > 0 ? lm_row[stab[a.l0 - 1].pos + i] : i;
+        const float *p = a.in + (size_t)max(row, 0) * a.ld_in;
         piece v;
-        if (full) {
-            v = *reinterpret_cast<const piece *>(src);
+        if constexpr (PART) {
+            if constexpr (T == 1) v = p[src[0]];
+            else {
+#pragma unroll
+                for (int t = 0; t < T; ++t) v[t] = p[src[t]];
+            }
+        } else if (full) {
+            v = *reinterpret_cast<const piece *>(p + s0);
         } else if constexpr (T == 1) {
-            v = s0 < B ? src[0] : 0.0f;
+            v = s0 < n_samples ? p[s0] : 0.0f;
         } else {
 #pragma unroll
-            for (int t = 0; t < T; ++t) v[t] = s0 + t < B ? src[t] : 0.0f;
+            for (int t = 0; t < T; ++t) v[t] = s0 + t < n_samples ? p[s0 + t] : 0.0f;
         }
         act[i] = v;
     }
 
     // the wavefront's place in the copy of W, in bytes (the copy is smaller than 4 GiB), goes into the loads as a scalar
-    const __amdgpu_buffer_rsrc_t rlm = make_rsrc((const float *)lm, lm_bytes);
-    unsigned at = (unsigned)scs[stab[0].cs + wave * (stab[0].nb + 1)] * LDS_CHUNK_BYTES;
+    const __amdgpu_buffer_rsrc_t rlm = make_rsrc((const float *)a.lm, a.lm_bytes);
+    unsigned at = (unsigned)scs[stab[a.l0].cs + wave * (stab[a.l0].nb + 1)] * LDS_CHUNK_BYTES;
     const int lane16 = 16 * lane;
     struct Half { u32x4 c, wa, wb; } ha, hb;
     auto request = [&](Half &h) {
@@ -894,28 +930,39 @@ k_fwd_lds(const LmLayer *__restrict__ tab, const int32_t *__restrict__ lm_cs, co
     };
     request(ha);
     request(hb);
+    // All the workgroups of an XCD stream through the same copy of W at about the same time, and whoever comes first to a
+    // line waits for memory.  So they share that out: before a layer's last block each wavefront touches one line in so many
+    // of the next layer's stream (3001 neurons, 120 layers, copies of W that come from HBM: 1.08 -> 0.92 ms).
+    const unsigned xcd_wg = (blockIdx.x >> 3) % max(1u, min(32u, gridDim.x >> 3));
+    unsigned touched = 0;
     lds_barrier();
 
-    for (int l = 0; l < n_layers; ++l) {
+    for (int l = a.l0; l < a.l1; ++l) {
         const int nb = stab[l].nb, cs0 = stab[l].cs + wave * (nb + 1), pos0 = stab[l].pos + 64 * wave + lane;
         f32x32 res;
         for (int j = 0; j < nb; ++j) {
+            if (j > 0 && j == nb - 1 && l + 1 < a.l1) { // see above (one block per layer: it would only hold the wavefront up)
+                asm volatile("" ::"v"(touched));
+                const int c0 = scs[stab[l + 1].cs + wave * (stab[l + 1].nb + 1)], c1 = scs[stab[l + 1].cs + wave * (stab[l + 1].nb + 1) + stab[l + 1].nb];
+                const unsigned line = (unsigned)c0 * LDS_CHUNK_BYTES + 128u * (64u * xcd_wg + (unsigned)lane);
+                if (line < (unsigned)c1 * LDS_CHUNK_BYTES) touched = __builtin_amdgcn_raw_buffer_load_b32(rlm, (int)line, 0, 0);
+            }
             const int n = scs[cs0 + j + 1] - scs[cs0 + j];
             const float bias = lm_bias[pos0 + 1024 * j];
             double acc[T];
 #pragma unroll
             for (int t = 0; t < T; ++t) acc[t] = 0.0;
             auto take = [&](Half &h) { // eight entries; then their registers are free for the half after next
-                unsigned a[8];
+                unsigned ad[8];
                 double w[8];
                 piece x[8];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    a[2 * u] = lds_address<0>(h.c[u], shift);
-                    a[2 * u + 1] = lds_address<1>(h.c[u], shift);
+                    ad[2 * u] = lds_address<0>(h.c[u], shift);
+                    ad[2 * u + 1] = lds_address<1>(h.c[u], shift);
                 }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = *(lds_ptr)((lds_bytes)0 + a[u]);
+                for (int u = 0; u < 8; ++u) x[u] = *(lds_ptr)((lds_bytes)0 + ad[u]);
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     w[u] = (double)__uint_as_float(h.wa[u]);
@@ -938,7 +985,7 @@ k_fwd_lds(const LmLayer *__restrict__ tab, const int32_t *__restrict__ lm_cs, co
             }
             const double bd = (double)bias;
 #pragma unroll
-            for (int t = 0; t < T; ++t) res[j * T + t] = act_apply(ACT, acc[t] + bd, cap);
+            for (int t = 0; t < T; ++t) res[j * T + t] = act_apply(ACT, acc[t] + bd, a.cap);
         }
         auto result = [&](int j) {
             piece v;
@@ -949,20 +996,47 @@ k_fwd_lds(const LmLayer *__restrict__ tab, const int32_t *__restrict__ lm_cs, co
             }
             return v;
         };
-        if (l == n_layers - 1) {
+        if (l == a.l1 - 1) {
+            unsigned nz = 0; // bit t: this lane has a non-zero result for sample t
             for (int j = 0; j < nb; ++j) {
                 const int row = lm_row[pos0 + 1024 * j];
                 if (row < 0) continue;
-                float *dst = XL + (size_t)row * B + s0;
+                float *dst = a.out + (size_t)row * a.ld_out;
                 const piece v = result(j);
-                if (full) {
-                    *reinterpret_cast<piece *>(dst) = v;
+                if constexpr (PART) {
+#pragma unroll
+                    for (int t = 0; t < T; ++t) {
+                        float x;
+                        if constexpr (T == 1) x = v;
+                        else x = v[t];
+                        if (s0 + t < n_samples) dst[a.dst_col ? a.dst_col[s0 + t] : s0 + t] = x;
+                        nz |= x != 0.0f ? 1u << t : 0u;
+                    }
+                } else if (full) {
+                    *reinterpret_cast<piece *>(dst + s0) = v;
                 } else if constexpr (T == 1) {
-                    if (s0 < B) dst[0] = v;
+                    if (s0 < n_samples) dst[s0] = v;
                 } else {
 #pragma unroll
                     for (int t = 0; t < T; ++t)
-                        if (s0 + t < B) dst[t] = v[t];
+                        if (s0 + t < n_samples) dst[s0 + t] = v[t];
+                }
+            }
+            if constexpr (PART) {
+                if (a.alive) { // the buffer is free: every wavefront leaves a word in it
+                    lds_barrier();
+                    __attribute__((address_space(3))) unsigned *word = (__attribute__((address_space(3))) unsigned *)(__attribute__((address_space(3))) float *)lds_act;
+#pragma unroll
+                    for (int t = 0; t < T; ++t) {
+                        const bool any = __ballot((nz >> t) & 1u) != 0;
+                        if (lane == 0) word[wave * T + t] = any ? 1u : 0u;
+                    }
+                    lds_barrier();
+                    if (tid < T && s0 + tid < n_samples) {
+                        unsigned any = 0;
+                        for (int w = 0; w < LDS_WAVES; ++w) any |= word[w * T + tid];
+                        a.alive[s0 + tid] = (int)any;
+                    }
                 }
             }
             return;
@@ -971,6 +1045,60 @@ k_fwd_lds(const LmLayer *__restrict__ tab, const int32_t *__restrict__ lm_cs, co
         for (int j = 0; j < nb; ++j) act[64 * (LDS_WAVES * j + wave) + lane] = result(j);
         lds_barrier(); // the layer is complete before anyone reads it
     }
+}
+
+template <int T, int ACT>
+__global__ void __launch_bounds__(64 * LDS_WAVES) k_fwd_lds(const LdsForward a)
+{
+    // neighbouring samples share cache lines of X: an XCD takes a contiguous stretch of them
+    const int nwg = (int)gridDim.x, per = nwg >> 3, wg = (int)blockIdx.x;
+    lds_forward<T, ACT, false>(a, wg < 8 * per ? (wg & 7) * per + (wg >> 3) : wg, a.B);
+}
+
+// A stretch of layers for the samples that are still alive, as many per workgroup as it takes to give every CU one (the
+// fewer, the sooner a layer is done).
+__global__ void __launch_bounds__(64 * LDS_WAVES) k_fwd_lds_part(const LdsForward a, int n_cu)
+{
+    const int n = *a.n_live, wg = (int)blockIdx.x;
+    if (4 * a.max_pos <= LDS_MAX_FLOATS && n > 2 * n_cu) {
+        if (4 * wg < n) lds_forward<4, ACT_RELU_CAP, true>(a, wg, n);
+    } else if (2 * a.max_pos <= LDS_MAX_FLOATS && n > n_cu) {
+        if (2 * wg < n) lds_forward<2, ACT_RELU_CAP, true>(a, wg, n);
+    } else {
+        if (wg < n) lds_forward<1, ACT_RELU_CAP, true>(a, wg, n);
+    }
+}
+
+// After a stretch: the samples that are left, in order (src_col: their columns in the stretch's output, sample: their numbers
+// in the caller's block).  One workgroup; alive == NULL: all of the B samples, the start of a pass.
+__global__ void __launch_bounds__(1024) k_live_columns(const int32_t *__restrict__ alive, const int32_t *__restrict__ n_in,
+                                                       const int32_t *__restrict__ sample_in, int B, int32_t *__restrict__ n_out,
+                                                       int32_t *__restrict__ src_col, int32_t *__restrict__ sample)
+{
+    __shared__ int wave_sum[16];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int n = alive ? *n_in : B;
+    int base = 0;
+    for (int c0 = 0; c0 < n; c0 += 1024) {
+        const int c = c0 + t;
+        const bool on = c < n && (!alive || alive[c] != 0);
+        const unsigned long long m = __ballot(on);
+        if (lane == 0) wave_sum[wave] = (int)__popcll(m);
+        __syncthreads();
+        int before = base, all = 0;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) before += wave_sum[w];
+            all += wave_sum[w];
+        }
+        if (on) {
+            const int k = before + (int)__popcll(m & ((1ull << lane) - 1ull));
+            src_col[k] = c;
+            sample[k] = alive ? sample_in[c] : c;
+        }
+        base += all;
+        __syncthreads();
+    }
+    if (t == 0) *n_out = base;
 }
 
 // Writes a layer's part of the lane-major copy from its CSR arrays: biases and weights, and with prev_pos (the position of
@@ -1836,9 +1964,11 @@ struct sdnn_net {
     std::vector<int32_t> lm_nb;      // blocks per wavefront of every layer
     size_t lm_chunks = 0;
     int32_t lm_max_pos = 0;
+    bool lds_part_attr_set = false;
     bool lds_attr_set[3] = {};       // the dynamic LDS limit of k_fwd_lds<1 << k> has been raised
     int grad_parts = 0;           // > 0: the last backward pass left the entries' gradient in G[0..grad_parts)
     bool vals_t_stale = false;    // the CSR values were changed by something that does not maintain vals_t
+    int32_t *d_alive = nullptr;
     int32_t *d_flags[2] = {nullptr, nullptr}, *d_map[2] = {nullptr, nullptr}, *d_n_live[2] = {nullptr, nullptr}; // inference: dead-sample skipping, two rounds' state
     bool bias_nonpos = false;     // every bias of layers 2..L is <= 0 (as uploaded; cleared when a bias is replaced)
     int state = ST_IDLE;
@@ -1908,7 +2038,7 @@ struct Plan {
     std::vector<LmLayer> lm_tab; // empty: no lane-major copy
     size_t lm_n_chunks = 0, lm_n_cs = 0, lm_n_pos = 0, lm_n_rows = 0; // sizes of its arrays, all layers together
     size_t lm = 0, lm_cs = 0, lm_layers = 0, lm_row = 0, lm_bias = 0, lm_pos = 0;
-    size_t table = 0, x0 = 0, ping = 0, pong = 0, flags[2] = {0, 0}, map[2] = {0, 0}, n_live[2] = {0, 0}, total = 0;
+    size_t table = 0, x0 = 0, ping = 0, pong = 0, alive = 0, flags[2] = {0, 0}, map[2] = {0, 0}, n_live[2] = {0, 0}, total = 0;
 };
 
 // Samples that the kernels of a training net work on for a batch of B: whole groups of four (the samples past B have a
@@ -2116,6 +2246,7 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
     } else {
         pl.ping = take(4 * max_n * mld);
         pl.pong = take(4 * max_n * mld);
+        pl.alive = take(4 * mb);
         for (int k = 0; k < 2; ++k) {
             pl.flags[k] = take(4 * mb);
             pl.map[k] = take(4 * mb);
@@ -2464,6 +2595,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
     } else {
         net->d_ping = (float *)(base + pl.ping);
         net->d_pong = (float *)(base + pl.pong);
+        net->d_alive = (int32_t *)(base + pl.alive);
         for (int k = 0; k < 2; ++k) {
             net->d_flags[k] = (int32_t *)(base + pl.flags[k]);
             net->d_map[k] = (int32_t *)(base + pl.map[k]);
@@ -2737,18 +2869,16 @@ static int launch_copy_rows(sdnn_net *net, const float *src, int ld_src, float *
 
 // What a forward pass over B samples takes with a launch per layer, in seconds: about 4 us per layer to launch, fetch the
 // entries and store, plus the gathered rows at the rate that the memory they come from delivers (measured on nets of
-// 32-entry rows, 300 to 30000 neurons, 1 to 2048 samples, to within a third; rows of hundreds of entries run 1.4 times
-// faster).
+// 32-entry rows, 1024 to 30000 neurons, and of 100 to 800 entries, 1 to 256 samples, to within a fourth).
 static double per_layer_forward_seconds(const sdnn_net *net, int B)
 {
     double t = 0.0;
-    const int tile = B > 128 ? 256 : B > 64 ? 128 : 64;
     for (const LayerDev &d : net->layers) {
         if (B == 1) { t += 3.7e-6 + 5.1e-12 * (double)d.nnz; continue; }
-        const double operand = 4.0 * tile * (double)d.n_in; // of one tile of samples
-        const double rate = operand <= 4.5e6 ? (tile == 256 ? 20e12 : 14e12) : operand <= 9e6 ? 13e12 : 9.5e12;
-        const double bytes = 4.0 * (double)d.nnz * (double)((B + tile - 1) / tile * tile);
-        t += 4e-6 + bytes / ((int64_t)d.nnz >= 128 * (int64_t)d.n_out ? 1.4 * rate : rate);
+        const bool long_rows = (int64_t)d.nnz >= 128 * (int64_t)d.n_out;
+        const int width = !long_rows ? (B + 3) & ~3 : B > 128 ? (B + 255) & ~255 : B > 64 ? 128 : 64;
+        const double rate = long_rows ? (B > 128 ? 26e12 : B > 64 ? 17e12 : 14e12) : d.n_in <= 4500 ? 24e12 : d.n_in <= 16384 ? 19e12 : 15e12;
+        t += 4e-6 + 4.0 * (double)d.nnz * width / rate;
     }
     return t;
 }
@@ -2773,6 +2903,18 @@ static int lds_forward_samples(const sdnn_net *net, int B)
     }
     if (net->cfg.lds_forward == SDNN_LDS_ON) return best;
     return t_best < per_layer_forward_seconds(net, B) ? best : 0;
+}
+
+static LdsForward lds_args(const sdnn_net *net, int l0, int l1, const float *in, int ld_in, float *out, int ld_out, int B)
+{
+    LdsForward a;
+    memset(&a, 0, sizeof a);
+    a.tab = net->lm_layers; a.lm_cs = net->lm_cs; a.lm = net->lm; a.lm_bias = net->lm_bias; a.lm_row = net->lm_row;
+    a.lm_bytes = (unsigned)(LDS_CHUNK_BYTES * (net->lm_chunks + 1));
+    a.l0 = l0; a.l1 = l1; a.n_in = net->layers[l0].n_in;
+    a.in = in; a.out = out; a.ld_in = ld_in; a.ld_out = ld_out; a.B = B;
+    a.cap = net->cfg.act_cap; a.max_pos = net->lm_max_pos;
+    return a;
 }
 
 // Eq. 3 for l = 1..L.  Inference nets stage the activations between the layers in ping / pong
@@ -2820,12 +2962,9 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
             HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * LDS_MAX_FLOATS));
             net->lds_attr_set[ti] = true;
         }
-        int n_layers = L, n0 = net->layers[0].n_in, b = B;
-        int vec_io = (B % T == 0 && aligned(d_X0, 4 * T) && aligned(d_XL, 4 * T)) ? 1 : 0;
-        float cap = net->cfg.act_cap;
-        unsigned lm_bytes = (unsigned)(LDS_CHUNK_BYTES * (net->lm_chunks + 1));
-        void *args[] = {(void *)&net->lm_layers, (void *)&net->lm_cs, (void *)&net->lm, (void *)&lm_bytes, (void *)&net->lm_bias, (void *)&net->lm_row,
-                        (void *)&n_layers, (void *)&n0, (void *)&d_X0, (void *)&d_XL, (void *)&b, (void *)&cap, (void *)&vec_io};
+        LdsForward a = lds_args(net, 0, L, d_X0, B, d_XL, B, B);
+        a.vec_io = (B % T == 0 && aligned(d_X0, 4 * T) && aligned(d_XL, 4 * T)) ? 1 : 0;
+        void *args[] = {(void *)&a};
         HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)((B + T - 1) / T)), dim3(64 * LDS_WAVES), args, lds_bytes, stream));
         HIP_TRY(net, hipGetLastError());
         net->B = B;
@@ -2927,6 +3066,56 @@ extern "C" int sdnn_forward_noalloc(sdnn_net *net, const float *d_X0, int32_t B,
 
 
 
+// The pass in stretches of layers with the activations in LDS: after 1, 3, 7, 15, ... times check_every layers and at the last
+// check the samples that are left are counted and their columns listed; the next stretch reads those columns and gives each
+// workgroup as few of them as fill the chip.  Nothing waits for the host: workgroups past the live samples end at once.
+static int skip_dead_lds(sdnn_net *net, const float *d_X0, int B, float *d_XL, int check_every, int32_t *d_n_live, hipStream_t stream)
+{
+    const int L = net->n_layers, n_last = net->layers[L - 1].n_out, ld = row_stride(B);
+    const int last_check = (L - 1) / check_every * check_every;
+    int t_max = 4;
+    while (t_max > 1 && t_max * net->lm_max_pos > LDS_MAX_FLOATS) t_max /= 2;
+    const size_t lds_bytes = sizeof(float) * (size_t)t_max * (size_t)net->lm_max_pos;
+    if (!net->lds_part_attr_set) {
+        HIP_TRY(net, hipFuncSetAttribute((const void *)k_fwd_lds_part, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * LDS_MAX_FLOATS));
+        net->lds_part_attr_set = true;
+    }
+    const unsigned grid = (unsigned)std::max(std::min(B, net->n_cu), (B + t_max - 1) / t_max);
+    // slot k & 1 holds the state of stretch k: d_n_live how many samples it takes, d_flags their columns in its input,
+    // d_map their numbers in the caller's block
+    int32_t *alive = net->d_alive;
+    hipLaunchKernelGGL(k_live_columns, dim3(1), dim3(1024), 0, stream, (const int32_t *)nullptr, (const int32_t *)nullptr,
+                       (const int32_t *)nullptr, B, net->d_n_live[0], net->d_flags[0], net->d_map[0]);
+    hipLaunchKernelGGL(k_fill_f32, dim3(ew_blocks((size_t)n_last * B)), dim3(256), 0, stream, d_XL, (size_t)n_last * B, 0.0f);
+    HIP_TRY(net, hipGetLastError());
+    const float *in = d_X0;
+    int ld_in = B, k = 0, step = check_every;
+    for (int l0 = 0; l0 < L; ++k) {
+        const bool last = l0 >= last_check;
+        int l1 = L;
+        if (!last) {
+            l1 = std::min(last_check, l0 + step);
+            step = (int)std::min<int64_t>(2 * (int64_t)step, 1 << 30) / check_every * check_every;
+        }
+        float *out = last ? d_XL : (k & 1) ? net->d_pong : net->d_ping;
+        LdsForward a = lds_args(net, l0, l1, in, ld_in, out, last ? B : ld, B);
+        a.n_live = net->d_n_live[k & 1];
+        a.src_col = net->d_flags[k & 1];
+        a.dst_col = last ? net->d_map[k & 1] : nullptr;
+        a.alive = last ? nullptr : alive;
+        hipLaunchKernelGGL(k_fwd_lds_part, dim3(grid), dim3(64 * LDS_WAVES), lds_bytes, stream, a, net->n_cu);
+        if (!last)
+            hipLaunchKernelGGL(k_live_columns, dim3(1), dim3(1024), 0, stream, (const int32_t *)alive, net->d_n_live[k & 1], net->d_map[k & 1],
+                               B, net->d_n_live[(k + 1) & 1], net->d_flags[(k + 1) & 1], net->d_map[(k + 1) & 1]);
+        HIP_TRY(net, hipGetLastError());
+        if (last && d_n_live) HIP_TRY(net, hipMemcpyAsync(d_n_live, net->d_n_live[k & 1], 4, hipMemcpyDeviceToDevice, stream));
+        in = out;
+        ld_in = ld;
+        l0 = l1;
+    }
+    return SDNN_OK;
+}
+
 extern "C" int sdnn_forward_skip_dead(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL,
                                       int32_t check_every, int32_t *d_n_live, void *stream_)
 {
@@ -2945,6 +3134,12 @@ extern "C" int sdnn_forward_skip_dead(sdnn_net *net, const float *d_X0, int32_t 
     hipStream_t stream = (hipStream_t)stream_;
     net->state = ST_IDLE;
     const int L = net->n_layers;
+    if (B > 1 && lds_forward_samples(net, B)) {
+        const int rc = skip_dead_lds(net, d_X0, B, d_XL, check_every, d_n_live, stream);
+        if (rc) return rc;
+        net->B = B;
+        return SDNN_OK;
+    }
     hipLaunchKernelGGL(k_skip_init, dim3(ew_blocks((size_t)B)), dim3(256), 0, stream, net->d_map[0], net->d_flags[0],
                        net->d_flags[1], net->d_n_live[0], B);
     HIP_TRY(net, hipGetLastError());

@@ -143,3 +143,23 @@ def test_skip_dead_seeded_random_nets(seed):
     net.sdnn_forward_skip_dead(P.dev(work.x_infer), out, check_every=k)
     assert np.array_equal(P.host(out), ref), f"seed {seed}: sizes {sizes} b {b} every {k}"
     net.close()
+
+
+@pytest.mark.parametrize("b,every", [(700, 1), (700, 4), (300, 2), (2050, 3)])
+def test_skip_dead_in_stretches_with_the_activations_in_lds(b, every):
+    """Wide enough blocks of narrow nets run in stretches of layers inside LDS: 4, 2 and 1 samples per workgroup as the
+    samples die out, a last stretch of every length; samples that die at different depths next to samples that never do."""
+    work = _mixed_config1(b, n_layers=11)
+    xs = P.O32.forward(work.layers, work.x_infer, work.act_cap)
+    alive = [int((x != 0).any(axis=0).sum()) for x in xs]
+    assert alive[1] > alive[-1] > 0
+    net = sdnn.Net(work.layers, work.act_cap, b, training=False, lds_forward=sdnn.SDNN_LDS_ON)
+    out = torch.full((work.layers[-1].n_out, b), 7.0, device=P.DEV)
+    n_live = torch.full((1,), -1, dtype=torch.int32, device=P.DEV)
+    for _ in range(2):
+        net.sdnn_forward_skip_dead(P.dev(work.x_infer), out, check_every=every, n_live=n_live)
+        assert np.array_equal(P.host(out), xs[-1])
+        assert int(n_live.item()) == alive[(11 - 1) // every * every]
+    net.sdnn_forward_skip_dead(torch.zeros_like(P.dev(work.x_infer)), out, check_every=every, n_live=n_live)
+    assert not out.any() and int(n_live.item()) == 0
+    net.close()
