@@ -33,6 +33,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <algorithm>
+#include <atomic>
 #include <functional>
 #include <mutex>
 #include <new>
@@ -1416,71 +1417,223 @@ __global__ void __launch_bounds__(64) k_spmv_stage(const SpmmArgs a, int R)
     }
 }
 
-// The same kernel as the backward sweep of a one-sample step that also forms the gradient (B = 1 has no sum over
-// samples: g(j, i) = Delta_l(j) X_{l-1}(i), one product per entry).  The rows are those of W_l^T, the values are read
-// from their copy in that order, and the lane that holds entry (j, i) for the product also has Delta_l(j); it fetches
-// X_{l-1}(i) through t_col and stores the gradient at the entry's place in the transposed index, in a stream.
-template <int J>
-__global__ void __launch_bounds__(64) k_spmv_stage_grad(const SpmmArgs a, int R, const int32_t *__restrict__ t_col)
+// ---------------------------------------------------------------------------
+// Nets made for one sample per step (max_batch == 1, rows of moderate length), and inference calls with one sample on
+// nets that hold the lane-major copy of k_fwd_lds: a lane per row over a lane-major copy, so that columns and weights come
+// in coalesced 16-byte loads and nothing is parked or exchanged; up to 32 gathers of single activations are in flight per
+// lane.  Training nets keep one copy of W and one of W^T and step both (no gradient of the entries is stored and no value
+// moves from one order to the other); the CSR values are written out when they are asked for.
+// What bounds them: a launch and its chain of dependent loads (3.2 us) plus, on wide layers, a 128-byte line from L2 for
+// every gathered activation.  Forward / backward / step, us per layer, before (products staged in LDS, a gradient array, the
+// values moved from the transposed to the CSR order) and after: 1024 neurons 4.6 / 4.8 / 0.2 -> 3.2 / 3.7 / 0.1; 16384 neurons
+// 6.1 / 8.7 / 3.9 -> 3.7 / 5.5 / 1.9; 65536 neurons 14.9 / 22.3 / 15.7 -> 10.5 / 10.7 / 19.5.
+// ---------------------------------------------------------------------------
+#define B1_MAX_LDS (160 * 1024) // bytes of the step's LDS copy of a vector
+#define B1_LOAD 4 // chunks requested together
+template <bool WIDE> struct B1 { // columns of 2 bytes, or (more than 65536 of them) 4
+    static constexpr unsigned CHUNK_BYTES = WIDE ? 4096 : 3072, WEIGHTS = WIDE ? 2048 : 1024;
+};
+struct SpmvLmArgs {
+    const int32_t *cs;   // training: chunk table of the layer; inference: lm_cs
+    const int2 *row;     // training: {row, entries} per lane; inference: NULL
+    const int32_t *lm_row; // inference, last layer: the row of a position (NULL on the layers before: results stay at their positions)
+    const uint4 *lm;
+    unsigned lm_bytes;
+    const float *in;
+    unsigned in_bytes;
+    const float *aux;    // MODE 0: biases, MODE 1: X_{l-1}; in the order of the results' places
+    float *out;
+    float cap;
+    int32_t act;
+    int32_t nb, tab_cs, tab_pos; // inference: the layer's LmLayer
+};
+template <int MODE, bool WIDE, bool TRAIN>
+__global__ void __launch_bounds__(64) k_spmv_lm(const SpmvLmArgs a)
 {
-    __shared__ double prod[SPMV_STAGE + SPMV_STAGE / 32];
-    const int lane = threadIdx.x;
-    const int r0 = blockIdx.x * R;
-    const int nr = min(R, a.n_rows - r0); // >= 1 by the grid size
-    const int row = r0 + lane;
-    int p = 0, end = 0;
-    if (lane < nr) { p = a.row_ptr[row]; end = a.row_ptr[row + 1]; }
-    const int e0 = a.row_ptr[r0], e1 = a.row_ptr[r0 + nr];
+    const int lane = threadIdx.x, b = blockIdx.x;
+    typedef const int32_t __attribute__((address_space(4))) *cs_ptr;
+    const cs_ptr scs = (cs_ptr)a.cs;
+    int c0, n, place; // first chunk, chunks, where the result goes
+    if constexpr (TRAIN) {
+        c0 = scs[b];
+        n = scs[b + 1] - c0;
+        place = a.row[64 * b + lane].x;
+    } else { // position 64 (16 j + w) + lane: block j of wavefront w, two chunks of eight for each of its sixteen entries
+        const int j = b / LDS_WAVES, w = b - j * LDS_WAVES, at = a.tab_cs + w * (a.nb + 1) + j;
+        c0 = 2 * scs[at];
+        n = 2 * scs[at + 1] - c0;
+        place = 64 * b + lane;
+    }
+    const __amdgpu_buffer_rsrc_t rlm = make_rsrc((const float *)a.lm, a.lm_bytes), rin = make_rsrc(a.in, a.in_bytes);
+    float aux = 0.0f;
+    int dst = place;
+    if constexpr (TRAIN) {
+        if (a.aux) aux = a.aux[max(place, 0)];
+    } else {
+        aux = a.aux[a.tab_pos + place];
+        if (a.lm_row) dst = a.lm_row[a.tab_pos + place];
+    }
     double acc = 0.0;
-    for (int sb = e0; sb < e1; sb += SPMV_STAGE) {
-        const int se = min(sb + SPMV_STAGE, e1);
-        for (int j0 = 0; j0 * 64 < se - sb; j0 += J) {
-            int c[J], ti[J];
-            float w[J], x[J], xi[J];
+    unsigned at = (unsigned)c0 * B1<WIDE>::CHUNK_BYTES;
+    for (int i = 0; i < n; i += B1_LOAD, at += B1_LOAD * B1<WIDE>::CHUNK_BYTES) {
+        u32x4 c[B1_LOAD], ch[B1_LOAD], wa[B1_LOAD], wb[B1_LOAD];
+        float x[B1_LOAD][8];
 #pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const int e = sb + (j0 + j) * 64 + lane;
-                c[j] = -1;
-                if (e < se) {
-                    c[j] = a.idx[e];
-                    w[j] = a.vals[e];
-                    ti[j] = t_col[e];
+        for (int u = 0; u < B1_LOAD; ++u)
+            if (i + u < n) {
+                const int o = (int)(at + u * B1<WIDE>::CHUNK_BYTES);
+                c[u] = __builtin_amdgcn_raw_buffer_load_b128(rlm, 16 * lane, o, 0);
+                if (WIDE) ch[u] = __builtin_amdgcn_raw_buffer_load_b128(rlm, 16 * lane + 1024, o, 0);
+                wa[u] = __builtin_amdgcn_raw_buffer_load_b128(rlm, 16 * lane + B1<WIDE>::WEIGHTS, o, 0);
+                wb[u] = __builtin_amdgcn_raw_buffer_load_b128(rlm, 16 * lane + B1<WIDE>::WEIGHTS + 1024, o, 0);
+            }
+#pragma unroll
+        for (int u = 0; u < B1_LOAD; ++u)
+            if (i + u < n) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const unsigned col = WIDE ? (k < 4 ? c[u][k & 3] : ch[u][k & 3]) : (k & 1) ? c[u][k >> 1] >> 16 : c[u][k >> 1] & 0xffffu;
+                    x[u][k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rin, (int)(4u * col), 0, 0));
                 }
             }
 #pragma unroll
-            for (int j = 0; j < J; ++j)
-                if (c[j] >= 0) {
-                    x[j] = a.in[c[j]];
-                    xi[j] = a.aux[ti[j]];
-                }
+        for (int u = 0; u < B1_LOAD; ++u)
+            if (i + u < n) {
 #pragma unroll
-            for (int j = 0; j < J; ++j)
-                if (c[j] >= 0) {
-                    const int q = (j0 + j) * 64 + lane;
-                    prod[q + (q >> 5)] = (double)w[j] * (double)x[j];
-                    a.g_part[0][sb + q] = (float)((double)x[j] * (double)xi[j]);
-                }
-        }
-        if (!a.store_out) continue; // first layer: only the gradient (uniform for the workgroup)
-        __syncthreads();
-        const int pe = min(end, se); // my row's entries inside this segment are [p, pe)
-        if (p < pe) {
-            for (; p < pe; p += 4) { // four parked products requested together, added one after the other
-                double v[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int q = min(p + k, pe - 1) - sb;
-                    v[k] = prod[q + (q >> 5)];
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (p + k < pe) acc += v[k];
+                for (int k = 0; k < 8; ++k)
+                    acc = fma((double)__uint_as_float(k < 4 ? wa[u][k & 3] : wb[u][k & 3]), (double)x[u][k], acc);
             }
-            p = pe;
-        }
+    }
+    if (dst < 0) return;
+    if (MODE == 0) a.out[dst] = act_apply(a.act, acc + (double)aux, a.cap);
+    else a.out[dst] = act_backprop(a.act, acc, aux, a.cap);
+}
+
+// The step of such a net: w -= lr (delta_j x_i) on both copies, in a stream over each; the lane's own row gives one of the
+// two factors, the other is gathered: from the vector's copy in LDS where it fits, since from L2 every 4-byte gather pulls in
+// a 128-byte line (16384 neurons: 3.6 -> 1.9 us per layer).  grid = (parts, 2, layers): a workgroup takes every parts-th group
+// of 16 blocks of W (blockIdx.y = 0) or of W^T.
+template <bool WIDE, bool IN_LDS>
+__global__ void __launch_bounds__(64 * LDS_WAVES) k_update_lm(const LayerDev *__restrict__ layers, float lr, int update_bias)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds_vec[];
+    typedef __attribute__((address_space(1))) float *gf;
+    typedef const __attribute__((address_space(1))) float *gcf;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(1))) f32x4 *gcf4;
+    const LayerDev &L = layers[blockIdx.z];
+    const int lane = threadIdx.x & 63, o = blockIdx.y, nb = L.b1_blocks[o];
+    int b = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * LDS_WAVES + (threadIdx.x >> 6)));
+    const gcf mine = (gcf)(o ? L.X_prev : L.D), other = (gcf)(o ? L.D : L.X_prev);
+    const int n_other = o ? L.n_out : L.n_in;
+    if constexpr (IN_LDS) {
+        for (int i = threadIdx.x; i < n_other / 4; i += 64 * LDS_WAVES) reinterpret_cast<f32x4 *>(lds_vec)[i] = ((gcf4)other)[i];
+        if ((int)threadIdx.x < (n_other & 3)) lds_vec[(n_other & ~3) + threadIdx.x] = other[(n_other & ~3) + threadIdx.x];
         __syncthreads();
     }
-    if (a.store_out && lane < nr) a.out[row] = act_backprop(a.act, acc, a.aux[row], a.cap);
+    const __amdgpu_buffer_rsrc_t rv = make_rsrc(o ? L.D : L.X_prev, 4 * (size_t)n_other);
+    const __amdgpu_buffer_rsrc_t rlm = make_rsrc((const float *)L.b1_lm[o], (size_t)L.b1_cs[o][nb] * B1<WIDE>::CHUNK_BYTES);
+    const double dlr = (double)lr;
+    for (; b < nb; b += gridDim.x * LDS_WAVES) {
+        const int c0 = L.b1_cs[o][b], n = L.b1_cs[o][b + 1] - c0;
+        const int2 r = L.b1_row[o][64 * b + lane];
+        const double d = r.x >= 0 ? (double)mine[r.x] : 0.0;
+        unsigned at = (unsigned)c0 * B1<WIDE>::CHUNK_BYTES;
+        for (int i = 0; i < n; i += 2, at += 2 * B1<WIDE>::CHUNK_BYTES) {
+            u32x4 c[2], ch[2], w[2][2];
+            float v[2][8];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (i + u < n) {
+                    const int q = (int)(at + u * B1<WIDE>::CHUNK_BYTES);
+                    c[u] = __builtin_amdgcn_raw_buffer_load_b128(rlm, 16 * lane, q, 0);
+                    if (WIDE) ch[u] = __builtin_amdgcn_raw_buffer_load_b128(rlm, 16 * lane + 1024, q, 0);
+                    w[u][0] = __builtin_amdgcn_raw_buffer_load_b128(rlm, 16 * lane + B1<WIDE>::WEIGHTS, q, 0);
+                    w[u][1] = __builtin_amdgcn_raw_buffer_load_b128(rlm, 16 * lane + B1<WIDE>::WEIGHTS + 1024, q, 0);
+                }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (i + u < n) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const unsigned col = WIDE ? (k < 4 ? c[u][k & 3] : ch[u][k & 3]) : (k & 1) ? c[u][k >> 1] >> 16 : c[u][k >> 1] & 0xffffu;
+                        if (IN_LDS) v[u][k] = lds_vec[col];
+                        else v[u][k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rv, (int)(4u * col), 0, 0));
+                    }
+                }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (i + u < n) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const float g = (float)(d * (double)v[u][k]);
+                        const float old = __uint_as_float(w[u][k >> 2][k & 3]);
+                        if (8 * (i + u) + k < r.y) w[u][k >> 2][k & 3] = __float_as_uint((float)((double)old - dlr * (double)g)); // padding stays zero
+                    }
+                    const int q = (int)(at + u * B1<WIDE>::CHUNK_BYTES);
+                    __builtin_amdgcn_raw_buffer_store_b128(w[u][0], rlm, 16 * lane + B1<WIDE>::WEIGHTS, q, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(w[u][1], rlm, 16 * lane + B1<WIDE>::WEIGHTS + 1024, q, 0);
+                }
+        }
+        if (o == 0 && update_bias && r.x >= 0) {
+            const gf bias = (gf)L.bias;
+            bias[r.x] = (float)((double)bias[r.x] - dlr * d);
+        }
+    }
+}
+
+// Writes one of the two copies of a layer from its CSR arrays (dir 0: W, 1: W^T through the transposed index).
+template <bool WIDE>
+__global__ void __launch_bounds__(64) k_b1_fill(const LayerDev *__restrict__ layer, int o, int with_cols)
+{
+    const LayerDev &L = *layer;
+    const int lane = threadIdx.x, b = blockIdx.x;
+    const int c0 = L.b1_cs[o][b], n = L.b1_cs[o][b + 1] - c0;
+    const int2 r = L.b1_row[o][64 * b + lane];
+    const int beg = r.x >= 0 ? (o ? L.t_row_ptr[r.x] : L.row_ptr[r.x]) : 0;
+    for (int i = 0; i < n; ++i) {
+        unsigned col[8], w[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            col[k] = w[k] = 0;
+            if (8 * i + k < r.y) {
+                const int e = beg + 8 * i + k;
+                w[k] = __float_as_uint(L.vals[o ? L.t_perm[e] : e]);
+                if (with_cols) col[k] = (unsigned)(o ? L.t_row_idx[e] : L.col_idx[e]);
+            }
+        }
+        uint4 *dst = (uint4 *)L.b1_lm[o] + (size_t)(c0 + i) * (B1<WIDE>::CHUNK_BYTES / 16) + lane;
+        if (with_cols) {
+            if (WIDE) {
+                dst[0] = make_uint4(col[0], col[1], col[2], col[3]);
+                dst[64] = make_uint4(col[4], col[5], col[6], col[7]);
+            } else {
+                dst[0] = make_uint4(col[0] | col[1] << 16, col[2] | col[3] << 16, col[4] | col[5] << 16, col[6] | col[7] << 16);
+            }
+        }
+        dst[B1<WIDE>::WEIGHTS / 16] = make_uint4(w[0], w[1], w[2], w[3]);
+        dst[B1<WIDE>::WEIGHTS / 16 + 64] = make_uint4(w[4], w[5], w[6], w[7]);
+    }
+}
+
+// The values of a layer in CSR order, from the copy of W.
+template <bool WIDE>
+__global__ void __launch_bounds__(64) k_b1_values(const LayerDev *__restrict__ layer, float *__restrict__ values)
+{
+    const LayerDev &L = *layer;
+    const int lane = threadIdx.x, b = blockIdx.x;
+    const int c0 = L.b1_cs[0][b], n = L.b1_cs[0][b + 1] - c0;
+    const int2 r = L.b1_row[0][64 * b + lane];
+    if (r.x < 0) return;
+    float *dst = values + L.row_ptr[r.x];
+    for (int i = 0; i < n; ++i) {
+        const uint4 *src = (const uint4 *)L.b1_lm[0] + (size_t)(c0 + i) * (B1<WIDE>::CHUNK_BYTES / 16) + B1<WIDE>::WEIGHTS / 16 + lane;
+        const uint4 a = src[0], c = src[64];
+        const unsigned w[8] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (8 * i + k < r.y) dst[8 * i + k] = __uint_as_float(w[k]);
+    }
 }
 
 // Update for B = 1: no sum over samples, so the lanes take the entries of the rows:
@@ -1953,7 +2106,8 @@ struct sdnn_net {
     int n_cu = 0;                 // compute units of the device
     int occ_spmm[2][3][2][2] = {}; // resident workgroups per CU of k_spmm<V,MODE,U,tiles inner>, U = 8, 16
     int occ_grad = 0;             // the same for k_bwd_grad
-    int grad_v = 4;               // the last fused sweep: 4 samples per lane, or 0: one sample per step (k_spmv_stage_grad)
+    bool b1_attr_set = false;
+    bool b1 = false, b1_wide = false; // made for one sample per step: lane-major copies of W and W^T; with 4-byte columns
     int occ_panel[2][4] = {};     // the same for k_spmm_panel<R,MODE>, R = 1, 2, 4, 8
     std::vector<int32_t> max_len[2]; // per layer: longest row of W (0) and of W^T (1)
     std::vector<char> clustered[2];  // per layer: reorder_rows found clusters in W (0), in W^T (1)
@@ -1961,7 +2115,7 @@ struct sdnn_net {
     int32_t *lm_cs = nullptr, *lm_row = nullptr;
     float *lm_bias = nullptr;
     LmLayer *lm_layers = nullptr;
-    std::vector<int32_t> lm_nb;      // blocks per wavefront of every layer
+    std::vector<LmLayer> lm_tab;     // host copy of lm_layers
     size_t lm_chunks = 0;
     int32_t lm_max_pos = 0;
     bool lds_part_attr_set = false;
@@ -2032,9 +2186,12 @@ static inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 // Workspace plan: offsets of every array, in one pass (also used to size it).
 struct Plan {
     struct PerLayer {
-        size_t row_ptr, col_idx, vals, bias, t_row_ptr, t_row_idx, t_perm, sched, t_sched, X, D, G[2], vals_t, mid_slot, mid_dst, mid_loc, mid, t_col;
+        size_t row_ptr, col_idx, vals, bias, t_row_ptr, t_row_idx, t_perm, sched, t_sched, X, D, G[2], vals_t, mid_slot, mid_dst, mid_loc, mid, b1_cs[2], b1_row[2], b1_lm[2];
+        int32_t b1_blocks[2];
+        size_t b1_chunks[2];
     };
     std::vector<PerLayer> pl;
+    size_t b1_chunk_bytes = 0;   // 0: no lane-major copies for one sample per step
     std::vector<LmLayer> lm_tab; // empty: no lane-major copy
     size_t lm_n_chunks = 0, lm_n_cs = 0, lm_n_pos = 0, lm_n_rows = 0; // sizes of its arrays, all layers together
     size_t lm = 0, lm_cs = 0, lm_layers = 0, lm_row = 0, lm_bias = 0, lm_pos = 0;
@@ -2088,7 +2245,7 @@ static int check_config(const sdnn_layer *layers, int32_t n_layers, const sdnn_c
 // samples 9.9 / 8.4; 2048 neurons of 205 entries, 64 samples 24 / 28 us, 256 samples 43 / 33).  AUTO decides by the entries per layer and by whether the net is made for more than 64 samples.
 static bool grad_buffers_wanted(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg)
 {
-    if (!cfg->training || cfg->fuse_gradient == SDNN_FUSE_OFF) return false;
+    if (!cfg->training || cfg->fuse_gradient == SDNN_FUSE_OFF || cfg->max_batch == 1) return false;
     if (cfg->fuse_gradient == SDNN_FUSE_ON) return true;
     int64_t nnz = 0, rows = 0;
     for (int32_t l = 0; l < n_layers; ++l) {
@@ -2159,6 +2316,83 @@ static void lm_deal_blocks(const sdnn_layer &y, const LmLayer &tab, int32_t *row
     }
 }
 
+// Runs fn(0 .. n - 1) on up to 16 host threads (here if there are no more threads); fn must not throw.
+template <class F> static void for_each_layer(int32_t n, F fn)
+{
+    const int32_t hw = (int32_t)std::max(1u, std::min(std::thread::hardware_concurrency(), 16u)), nt = std::min(n, hw);
+    std::vector<std::thread> workers;
+    auto work = [&](int32_t first) {
+        for (int32_t l = first; l < n; l += nt) fn(l);
+    };
+    int32_t started = 1;
+    for (; started < nt; ++started) {
+        try {
+            workers.emplace_back(work, started);
+        } catch (...) {
+            break;
+        }
+    }
+    work(0);
+    for (int32_t k = started; k < nt; ++k) work(k);
+    for (std::thread &w : workers) w.join();
+}
+
+// Nets made for one sample per step take a lane per row over lane-major copies of W and W^T where no row is so long that its
+// lane would run on by itself.  Chunks of eight entries of the rows, longest first, in blocks of 64; false: too long a row.
+#define B1_MAX_ROW 512
+static bool b1_chunks(const int32_t *len, int32_t n, size_t *chunks)
+{
+    int64_t rows_of_len[B1_MAX_ROW + 1] = {}, before = 0;
+    for (int32_t r = 0; r < n; ++r) {
+        if (len[r] > B1_MAX_ROW) return false;
+        rows_of_len[len[r]]++;
+    }
+    *chunks = 0;
+    for (int k = B1_MAX_ROW; k >= 0; --k) { // a block is as deep as its first row
+        const int64_t after = before + rows_of_len[k];
+        *chunks += (size_t)((after + 63) / 64 - (before + 63) / 64) * (size_t)((k + 7) / 8);
+        before = after;
+    }
+    return true;
+}
+// Fills the plan's chunk counts; leaves b1_chunk_bytes 0 where the net does not take that layout.
+static void plan_b1(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, Plan &pl)
+{
+    pl.b1_chunk_bytes = 0;
+    if (!cfg->training || cfg->max_batch != 1) return;
+    bool wide = false;
+    for (int32_t l = 0; l < n_layers; ++l) {
+        const sdnn_layer &y = layers[l];
+        const int64_t nnz = y.row_ptr[y.n_out];
+        if (nnz > 0 && !y.col_idx) return;
+        if (nnz > ((int64_t)1 << 28) || y.n_out > (1 << 24) || y.n_in > (1 << 24)) return; // a copy stays below 4 GiB
+        if (nnz >= 128 * (int64_t)std::max(y.n_out, 1) || nnz >= 128 * (int64_t)std::max(y.n_in, 1)) return;
+        wide |= y.n_out > 65536 || y.n_in > 65536;
+    }
+    std::atomic<bool> fits(true);
+    for_each_layer(n_layers, [&](int32_t l) {
+        const sdnn_layer &y = layers[l];
+        Plan::PerLayer &q = pl.pl[l];
+        if (!fits) return;
+        try {
+            std::vector<int32_t> len((size_t)std::max(y.n_out, y.n_in));
+            for (int32_t r = 0; r < y.n_out; ++r) len[(size_t)r] = y.row_ptr[r + 1] - y.row_ptr[r];
+            if (!b1_chunks(len.data(), y.n_out, &q.b1_chunks[0])) { fits = false; return; }
+            std::fill(len.begin(), len.end(), 0);
+            const int32_t nnz = y.row_ptr[y.n_out];
+            for (int32_t p = 0; p < nnz; ++p)
+                if ((uint32_t)y.col_idx[p] < (uint32_t)y.n_in) len[(size_t)y.col_idx[p]]++;
+            if (!b1_chunks(len.data(), y.n_in, &q.b1_chunks[1])) { fits = false; return; }
+        } catch (...) {
+            fits = false;
+            return;
+        }
+        q.b1_blocks[0] = (y.n_out + 63) / 64;
+        q.b1_blocks[1] = (y.n_in + 63) / 64;
+    });
+    if (fits) pl.b1_chunk_bytes = wide ? 4096 : 3072;
+}
+
 static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, Plan &pl)
 {
     // Arrays of 1 MiB and more start on a multiple of their size rounded down to a power of two, at most
@@ -2183,18 +2417,22 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
     const size_t mb = (size_t)cfg->max_batch, mld = (size_t)row_stride(cfg->max_batch);
     const bool gw = grad_buffers_wanted(layers, n_layers, cfg);
     const bool lm = lds_forward_wanted(layers, n_layers, cfg);
-    size_t max_n = 0;
+    size_t max_n = 0, max_pos = 0;
     std::vector<size_t> nnz((size_t)n_layers);
     for (int32_t l = 0; l < n_layers; ++l) {
         const sdnn_layer &y = layers[l];
         nnz[l] = (size_t)y.row_ptr[y.n_out];
         Plan::PerLayer &q = pl.pl[l];
         q.t_row_ptr = q.t_row_idx = q.t_perm = q.t_sched = 0;
-        q.X = q.D = q.G[0] = q.G[1] = q.vals_t = q.mid_slot = q.mid_dst = q.mid_loc = q.mid = q.t_col = 0;
+        q.X = q.D = q.G[0] = q.G[1] = q.vals_t = q.mid_slot = q.mid_dst = q.mid_loc = q.mid = 0;
+        q.b1_cs[0] = q.b1_cs[1] = q.b1_row[0] = q.b1_row[1] = q.b1_lm[0] = q.b1_lm[1] = 0;
+        q.b1_blocks[0] = q.b1_blocks[1] = 0;
+        q.b1_chunks[0] = q.b1_chunks[1] = 0;
         if (lm) {
             LmLayer t;
             t.nb = ((y.n_out + 63) / 64 + LDS_WAVES - 1) / LDS_WAVES;
             t.n_pos = 64 * LDS_WAVES * t.nb;
+            max_pos = std::max(max_pos, (size_t)t.n_pos);
             t.cs = (int32_t)pl.lm_n_cs;
             t.pos = (int32_t)pl.lm_n_pos;
             pl.lm_tab.push_back(t);
@@ -2205,6 +2443,8 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
         }
         max_n = std::max(max_n, (size_t)std::max(y.n_out, y.n_in));
     }
+    plan_b1(layers, n_layers, cfg, pl);
+    const bool b1 = pl.b1_chunk_bytes != 0;
 #define PLAN_KIND(field, bytes_expr)                                   \
     for (int32_t l = 0; l < n_layers; ++l) {                           \
         const sdnn_layer &y = layers[l];                               \
@@ -2241,11 +2481,18 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
             PLAN_KIND(mid_dst, 4 * nnz[l])
             PLAN_KIND(mid_loc, 2 * nnz[l])
             PLAN_KIND(mid, 4 * nnz[l])
-            if (cfg->max_batch == 1) PLAN_KIND(t_col, 4 * nnz[l])
+        }
+        if (b1) {
+            PLAN_KIND(b1_cs[0], 4 * ((size_t)q.b1_blocks[0] + 1))
+            PLAN_KIND(b1_cs[1], 4 * ((size_t)q.b1_blocks[1] + 1))
+            PLAN_KIND(b1_row[0], 8 * 64 * (size_t)q.b1_blocks[0])
+            PLAN_KIND(b1_row[1], 8 * 64 * (size_t)q.b1_blocks[1])
+            PLAN_KIND(b1_lm[0], pl.b1_chunk_bytes * q.b1_chunks[0])
+            PLAN_KIND(b1_lm[1], pl.b1_chunk_bytes * q.b1_chunks[1])
         }
     } else {
-        pl.ping = take(4 * max_n * mld);
-        pl.pong = take(4 * max_n * mld);
+        pl.ping = take(4 * std::max(max_n * mld, max_pos)); // one sample on the lane-major copy: a float per position
+        pl.pong = take(4 * std::max(max_n * mld, max_pos));
         pl.alive = take(4 * mb);
         for (int k = 0; k < 2; ++k) {
             pl.flags[k] = take(4 * mb);
@@ -2279,10 +2526,23 @@ extern "C" int sdnn_workspace_bytes(const sdnn_layer *layers, int32_t n_layers,
 // (Re)writes layer l's part of the lane-major copy from its CSR arrays.
 static int launch_lm_fill(sdnn_net *net, int l, const int32_t *prev_pos, int with_cols, hipStream_t stream)
 {
-    if (net->lm_nb[l] == 0) return SDNN_OK;
-    hipLaunchKernelGGL(k_lm_fill, dim3((unsigned)net->lm_nb[l], LDS_WAVES), dim3(64), 0, stream, net->d_layers + l, net->lm_layers + l,
+    if (net->lm_tab[l].nb == 0) return SDNN_OK;
+    hipLaunchKernelGGL(k_lm_fill, dim3((unsigned)net->lm_tab[l].nb, LDS_WAVES), dim3(64), 0, stream, net->d_layers + l, net->lm_layers + l,
                        net->lm_cs, net->lm, net->lm_bias, net->lm_row, prev_pos, with_cols);
     HIP_TRY(net, hipGetLastError());
+    return SDNN_OK;
+}
+
+// (Re)writes both copies of layer l from its CSR arrays.
+static int launch_b1_fill(sdnn_net *net, int l, int with_cols, hipStream_t stream)
+{
+    const LayerDev &d = net->layers[l];
+    for (int o = 0; o < 2; ++o) {
+        if (d.b1_blocks[o] == 0) continue;
+        if (net->b1_wide) hipLaunchKernelGGL(k_b1_fill<true>, dim3((unsigned)d.b1_blocks[o]), dim3(64), 0, stream, net->d_layers + l, o, with_cols);
+        else hipLaunchKernelGGL(k_b1_fill<false>, dim3((unsigned)d.b1_blocks[o]), dim3(64), 0, stream, net->d_layers + l, o, with_cols);
+        HIP_TRY(net, hipGetLastError());
+    }
     return SDNN_OK;
 }
 
@@ -2338,7 +2598,8 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
         std::vector<float> vals_t;
         std::vector<int32_t> mid_dst;
         std::vector<uint16_t> mid_slot, mid_loc;
-        std::vector<int32_t> t_col;
+        std::vector<int32_t> b1_cs[2];
+        std::vector<int2> b1_row[2];
         int32_t max_len = 0, t_max_len = 0;
         bool clustered = false, t_clustered = false; // reorder_rows found rows that share columns
         int rc = SDNN_OK;
@@ -2356,6 +2617,9 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
     for (int32_t l = 1; l < n_layers; ++l) lm_first_row[l] = lm_first_row[l - 1] + (size_t)layers[l - 1].n_out;
     const bool training = cfg->training != 0; // the transposed index serves the backward pass only
     const bool gw_ = grad_buffers_wanted(layers, n_layers, cfg);
+    const bool b1 = pl.b1_chunk_bytes != 0;
+    net->b1_wide = pl.b1_chunk_bytes == 4096;
+    net->b1 = b1;
     auto prepare = [&](int32_t l, HostIdx &h) {
         try {
             const sdnn_layer &y = layers[l];
@@ -2401,10 +2665,21 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 h.sched[r] = make_int4(h.order[r], y.row_ptr[h.order[r]], y.row_ptr[h.order[r] + 1], 0);
             for (size_t r = 0; r < h.t_sched.size(); ++r)
                 h.t_sched[r] = make_int4(h.t_order[r], h.t_row_ptr[h.t_order[r]], h.t_row_ptr[h.t_order[r] + 1], 0);
-            if (gw_ && cfg->max_batch == 1) { // one sample per step: the fused sweep looks up each entry's row of W^T
-                h.t_col.resize(nnz);
-                for (int32_t i = 0; i < y.n_in; ++i)
-                    for (int32_t q = h.t_row_ptr[i]; q < h.t_row_ptr[i + 1]; ++q) h.t_col[(size_t)q] = i;
+            for (int o = 0; o < (b1 ? 2 : 0); ++o) { // blocks of 64 rows, longest first, whatever the row schedule is
+                const int32_t n = o ? y.n_in : y.n_out, *ptr = o ? h.t_row_ptr.data() : y.row_ptr;
+                std::vector<int32_t> by_len((size_t)n);
+                sdnn_row_schedule(n, ptr, by_len.data());
+                const int32_t nb = pl.pl[l].b1_blocks[o];
+                h.b1_cs[o].assign((size_t)nb + 1, 0);
+                h.b1_row[o].assign((size_t)nb * 64, make_int2(-1, 0));
+                for (int32_t b = 0; b < nb; ++b) {
+                    const int32_t first = by_len[(size_t)b * 64];
+                    h.b1_cs[o][(size_t)b + 1] = h.b1_cs[o][(size_t)b] + (ptr[first + 1] - ptr[first] + 7) / 8;
+                    for (int32_t k = 0; k < 64 && 64 * b + k < n; ++k) {
+                        const int32_t row = by_len[(size_t)b * 64 + k];
+                        h.b1_row[o][(size_t)b * 64 + k] = make_int2(row, ptr[row + 1] - ptr[row]);
+                    }
+                }
             }
             if (gw_) { // the values in the order of the transposed index, for the fused backward sweep
                 h.vals_t.resize(nnz);
@@ -2511,7 +2786,16 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 d.mid_dst = gw ? (const int32_t *)(base + q.mid_dst) : nullptr;
                 d.mid_loc = gw ? (const uint16_t *)(base + q.mid_loc) : nullptr;
                 d.mid = gw ? (float *)(base + q.mid) : nullptr;
-                d.t_col = gw && cfg->max_batch == 1 ? (const int32_t *)(base + q.t_col) : nullptr;
+                for (int o = 0; o < 2; ++o) {
+                    d.b1_blocks[o] = q.b1_blocks[o];
+                    d.b1_cs[o] = b1 ? (const int32_t *)(base + q.b1_cs[o]) : nullptr;
+                    d.b1_row[o] = b1 ? (const int2 *)(base + q.b1_row[o]) : nullptr;
+                    d.b1_lm[o] = b1 ? (int4 *)(base + q.b1_lm[o]) : nullptr;
+                    if (b1) {
+                        UP(d.b1_cs[o], h.b1_cs[o].data(), 4 * h.b1_cs[o].size());
+                        UP(d.b1_row[o], h.b1_row[o].data(), 8 * h.b1_row[o].size());
+                    }
+                }
                 d.X_prev = !cfg->training ? nullptr
                            : l == 0       ? (float *)(base + pl.x0)
                                           : net->layers[l - 1].X;
@@ -2535,12 +2819,16 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 if (gw) UP(d.mid_slot, h.mid_slot.data(), 2 * nnz);
                 if (gw) UP(d.mid_dst, h.mid_dst.data(), 4 * nnz);
                 if (gw) UP(d.mid_loc, h.mid_loc.data(), 2 * nnz);
-                if (d.t_col) UP(d.t_col, h.t_col.data(), 4 * nnz);
             }
             SYNC(); // the group's host arrays are reused by the next group
         }
         net->d_layers = (LayerDev *)(base + pl.table);
         UP(net->d_layers, net->layers.data(), sizeof(LayerDev) * (size_t)n_layers);
+        if (b1)
+            for (int32_t l = 0; l < n_layers; ++l) {
+                const int rc_fill = launch_b1_fill(net, l, 1, stream);
+                if (rc_fill) return fail_free(rc_fill);
+            }
         if (want_lm) {
             // from the blocks' depths to where their chunks lie: one wavefront's chunks follow each other through all layers
             int64_t at = 0;
@@ -2562,7 +2850,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
             net->lm_row = (int32_t *)(base + pl.lm_row);
             net->lm_bias = (float *)(base + pl.lm_bias);
             net->lm_chunks = pl.lm_n_chunks;
-            for (const LmLayer &t : pl.lm_tab) net->lm_nb.push_back(t.nb);
+            net->lm_tab = pl.lm_tab;
             net->lm_max_pos = layers[0].n_in;
             for (const LmLayer &t : pl.lm_tab) net->lm_max_pos = std::max(net->lm_max_pos, t.n_pos);
             int32_t *d_pos = (int32_t *)(base + pl.lm_pos);
@@ -2762,6 +3050,18 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
     a.in_bytes = 4 * (size_t)n_cols * (size_t)ld_in;
     if (a.in_bytes >= ((size_t)1 << 32))
         return fail(net, SDNN_EINVAL, "activation block of %zu bytes exceeds 4 GiB: use a smaller B", a.in_bytes);
+    if (B == 1 && net->b1) {
+        const int o = MODE;
+        SpmvLmArgs b;
+        memset(&b, 0, sizeof b);
+        b.cs = d.b1_cs[o]; b.row = d.b1_row[o]; b.lm = (const uint4 *)d.b1_lm[o]; b.in = in; b.in_bytes = (unsigned)a.in_bytes; b.aux = aux; b.out = out;
+        b.lm_bytes = 0xffffffffu; // every chunk that the table names is there
+        b.cap = a.cap; b.act = a.act;
+        if (net->b1_wide) hipLaunchKernelGGL((k_spmv_lm<MODE, true, true>), dim3((unsigned)d.b1_blocks[o]), dim3(64), 0, stream, b);
+        else hipLaunchKernelGGL((k_spmv_lm<MODE, false, true>), dim3((unsigned)d.b1_blocks[o]), dim3(64), 0, stream, b);
+        HIP_TRY(net, hipGetLastError());
+        return SDNN_OK;
+    }
     if (B == 1) {
         const int64_t nnz = d.nnz;
         if (a.n_rows >= SPMV_STAGE_MIN_ROWS && nnz < 128 * (int64_t)a.n_rows) {
@@ -2967,6 +3267,27 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
         void *args[] = {(void *)&a};
         HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)((B + T - 1) / T)), dim3(64 * LDS_WAVES), args, lds_bytes, stream));
         HIP_TRY(net, hipGetLastError());
+        net->B = B;
+        net->state = ST_FORWARD;
+        return SDNN_OK;
+    }
+    if (B == 1 && !training && net->lm && net->cfg.panel_cols <= 0) { // a lane per row over the same copy of W
+        const float *in = d_X0;
+        size_t n_in = (size_t)net->layers[0].n_in;
+        for (int l = 0; l < L; ++l) {
+            const bool last = l == L - 1;
+            SpmvLmArgs b;
+            memset(&b, 0, sizeof b);
+            b.cs = net->lm_cs; b.lm = net->lm; b.lm_bytes = (unsigned)(LDS_CHUNK_BYTES * (net->lm_chunks + 1));
+            b.lm_row = last ? net->lm_row : nullptr; b.aux = net->lm_bias;
+            b.in = in; b.in_bytes = (unsigned)(4 * n_in); b.out = last ? d_XL : ((l & 1) ? pong : ping);
+            b.cap = net->cfg.act_cap; b.act = net->cfg.activation;
+            b.nb = net->lm_tab[l].nb; b.tab_cs = net->lm_tab[l].cs; b.tab_pos = net->lm_tab[l].pos;
+            n_in = (size_t)net->lm_tab[l].n_pos;
+            in = b.out;
+            if (b.nb > 0) hipLaunchKernelGGL((k_spmv_lm<0, false, false>), dim3((unsigned)(LDS_WAVES * b.nb)), dim3(64), 0, stream, b);
+            HIP_TRY(net, hipGetLastError());
+        }
         net->B = B;
         net->state = ST_FORWARD;
         return SDNN_OK;
@@ -3204,13 +3525,6 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
     a.n_tiles = 1;
     a.n_rg = (uint32_t)((a.n_rows + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
     a.n_vblocks = a.n_rg;
-    if (net->grad_v == 0) { // B = 1
-        const int R = a.n_rows >= 32768 ? 16 : 8;
-        const int32_t *t_col = d.t_col;
-        hipLaunchKernelGGL((k_spmv_stage_grad<8>), dim3((unsigned)((a.n_rows + R - 1) / R)), dim3(64), 0, stream, a, R, t_col);
-        HIP_TRY(net, hipGetLastError());
-        return SDNN_OK;
-    }
     void *args[] = {(void *)&a};
     if (B <= 64 && ((a.n_rows <= 6144 && (int64_t)d.nnz < 128 * (int64_t)a.n_rows) || !rows_addressable(d.n_out, net->ld))) {
         // few short rows: a wavefront for each keeps more of the chip busy than several rows per wavefront (4096 rows, 64
@@ -3243,20 +3557,9 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
 }
 
 // Whether the backward pass over this batch also forms the gradient: the number of partial gradients, 0 = it does not.
-// *v: samples per lane (0: one sample per step).
-static int grad_fusable(const sdnn_net *net, int B, int *v)
+static int grad_fusable(const sdnn_net *net, int B)
 {
-    *v = 4;
-    if (net->layers[0].G[0] == nullptr) return 0;
-    if (B == 1) { // one sample per step: wide layers with short rows only (among those that k_spmv_stage takes)
-        // measured step of the 120-layer sigmoid nets, fused vs separate: 65536 rows 6.39 vs 7.80 ms, 16384 rows 2.27
-        // vs 2.59, 4096 rows 1.57 vs 1.51 (launch-bound: one more launch per step than it saves)
-        if (net->layers[0].t_col == nullptr) return 0;
-        for (const LayerDev &d : net->layers)
-            if (d.n_in < 8192 || (int64_t)d.nnz >= 128 * (int64_t)d.n_in) return 0;
-        *v = 0;
-        return 1;
-    }
+    if (net->layers[0].G[0] == nullptr || B == 1) return 0;
     if (B > 256) return 0;
     for (const LayerDev &d : net->layers)
         if (B > 64 && !rows_addressable(d.n_out, net->ld)) return 0;
@@ -3279,7 +3582,7 @@ extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)
                            net->B, net->ld, B, w, net->cfg.act_cap, net->cfg.activation);
         HIP_TRY(net, hipGetLastError());
     }
-    const int gp = grad_fusable(net, B, &net->grad_v);
+    const int gp = grad_fusable(net, B);
     net->grad_parts = gp;
     if (gp && net->vals_t_stale) { // the CSR values were replaced or stepped by the separate update since the last sweep
         int max_nnz = 0;
@@ -3373,6 +3676,27 @@ extern "C" int sdnn_sgd_step(sdnn_net *net, float lr, void *stream_)
                                    dim3(BLOCK_THREADS), 0, (hipStream_t)stream_, net->d_layers + l0, net->Bp, net->ld, lr, (float *)nullptr);
             HIP_TRY(net, hipGetLastError());
         }
+    } else if (net->b1) {
+        int max_blocks = 1;
+        for (const LayerDev &d : net->layers) max_blocks = std::max({max_blocks, d.b1_blocks[0], d.b1_blocks[1]});
+        const bool in_lds = 4 * (int64_t)net->max_n <= B1_MAX_LDS;
+        const int groups = (max_blocks + LDS_WAVES - 1) / LDS_WAVES;
+        // In LDS: enough workgroups to fill the chip twice, and no more of them than pay for filling their LDS.  Else as many as
+        // there are groups of blocks, so that the chip works on few layers at a time and their vectors stay in L2.
+        const int parts = in_lds ? std::min(groups, std::max(8, 2 * net->n_cu / net->n_layers)) : groups;
+        const void *fn = net->b1_wide ? (in_lds ? (const void *)k_update_lm<true, true> : (const void *)k_update_lm<true, false>)
+                                      : (in_lds ? (const void *)k_update_lm<false, true> : (const void *)k_update_lm<false, false>);
+        const size_t lds = in_lds ? (4 * (size_t)net->max_n + 15) & ~(size_t)15 : 0;
+        if (in_lds && !net->b1_attr_set) {
+            HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, B1_MAX_LDS));
+            net->b1_attr_set = true;
+        }
+        for (int l0 = 0; l0 < net->n_layers; l0 += 65535) {
+            const LayerDev *first = net->d_layers + l0;
+            void *args[] = {(void *)&first, (void *)&lr, (void *)&net->cfg.update_bias};
+            HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)parts, 2, (unsigned)std::min(65535, net->n_layers - l0)), dim3(64 * LDS_WAVES), args, lds,
+                                         (hipStream_t)stream_));
+        }
     } else {
         rc = launch_update(net, 0, net->n_layers, lr, 0, nullptr, nullptr, (hipStream_t)stream_);
         if (net->layers[0].vals_t) net->vals_t_stale = true; // this kernel steps the CSR copy only
@@ -3442,7 +3766,15 @@ extern "C" int sdnn_get_weights(sdnn_net *net, int32_t layer, float *d_values, f
     if (layer < 1 || layer > net->n_layers) return fail(net, SDNN_EINVAL, "layer out of range");
     const LayerDev &d = net->layers[layer - 1];
     int rc = SDNN_OK;
-    if (d_values) rc = copy_dd(net, d_values, d.vals, 4 * (size_t)d.nnz, stream_);
+    if (d_values && net->b1) { // the values that are stepped are those of the lane-major copy
+        if (d.nnz > 0) {
+            if (net->b1_wide) hipLaunchKernelGGL(k_b1_values<true>, dim3((unsigned)d.b1_blocks[0]), dim3(64), 0, (hipStream_t)stream_, net->d_layers + (layer - 1), d_values);
+            else hipLaunchKernelGGL(k_b1_values<false>, dim3((unsigned)d.b1_blocks[0]), dim3(64), 0, (hipStream_t)stream_, net->d_layers + (layer - 1), d_values);
+            HIP_TRY(net, hipGetLastError());
+        }
+    } else if (d_values) {
+        rc = copy_dd(net, d_values, d.vals, 4 * (size_t)d.nnz, stream_);
+    }
     if (!rc && d_bias) rc = copy_dd(net, d_bias, d.bias, 4 * (size_t)d.n_out, stream_);
     return rc;
 }
@@ -3466,6 +3798,7 @@ extern "C" int sdnn_set_weights(sdnn_net *net, int32_t layer, const float *d_val
         rc = copy_dd(net, d.bias, d_bias, 4 * (size_t)d.n_out, stream_);
         if (layer > 1) net->bias_nonpos = false; // device data: its signs are not inspected
     }
+    if (!rc && d_values && net->b1) rc = launch_b1_fill(net, layer - 1, 0, (hipStream_t)stream_);
     if (!rc && (d_values || d_bias) && net->lm) // keep the lane-major copy current
         rc = launch_lm_fill(net, layer - 1, nullptr, 0, (hipStream_t)stream_);
     return rc;

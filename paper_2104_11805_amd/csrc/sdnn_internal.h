@@ -5,7 +5,7 @@
 
 #include "../../include/sdnn.h"
 
-#include <hip/hip_vector_types.h> // int4
+#include <hip/hip_vector_types.h> // int4, int2
 
 void sdnn_set_global_error(const char *fmt, ...);
 const char *sdnn_global_error();
@@ -27,8 +27,6 @@ struct LayerDev {
     float *D;                 // Delta_l  [n_out][B]  (training mode)
     float *G[2];              // [nnz] each: gradient of the stored entries over one half of the batch, in the order of
                               // the transposed index (fused backward sweep; training mode)
-    const int32_t *t_col;     // [nnz]: the row of W^T (column of W) of each entry of the transposed index; only on nets
-                              // created for one sample per step (max_batch == 1) with the fused sweep, NULL otherwise
     float *vals_t;            // [nnz]: the values in the order of the transposed index (vals_t[q] == vals[t_perm[q]]),
                               // read by the fused backward sweep; NULL where that sweep is not set up
     // The way back from the transposed order to the CSR order, in two passes that both move whole runs (NULL with
@@ -40,4 +38,11 @@ struct LayerDev {
     const int32_t *mid_dst;   // [nnz]: mid_dst[span start + k] = the place in mid of the span's entry of rank k
     const uint16_t *mid_loc;  // [nnz]: t_perm of the entry at that place of mid, minus its chunk's start
     float *mid;               // [nnz]
+    // Nets made for one sample per step: lane-major copies of W (0) and W^T (1), the only values such a net steps.  The
+    // rows, longest first, in blocks of 64; a block's entries come in chunks of eight per lane (B1_CHUNK_BYTES: the
+    // lanes' eight columns, 2 or 4 bytes each, then twice four weights), zero weights past the end of a row.
+    int32_t b1_blocks[2];
+    const int32_t *b1_cs[2];  // [b1_blocks + 1]: first chunk of a block
+    const int2 *b1_row[2];    // [64 b1_blocks]: {row, entries} of a lane, row -1 past the last row
+    int4 *b1_lm[2];
 };
