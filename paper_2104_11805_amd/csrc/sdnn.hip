@@ -177,6 +177,7 @@ struct SpmmArgs {
     int32_t act;
     const int32_t *n_live; // NULL, or the number of leading columns of the block that still matter (device)
     int32_t *flags;        // NULL, or MODE 0: flags[s] is set to 1 for every sample s with a non-zero output
+    int32_t n_cols;        // rows of `in` (k_rows, k_bwd_rows)
     float *g_part[2];      // GRAD kernels: gradient of the stored entries over the samples of the first / second tile, in the
                            // order of the transposed index [nnz]
     int32_t store_out;     // GRAD kernels: 0 = only the gradient is wanted (first layer: there is no Delta_0)
@@ -407,7 +408,8 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
 // A row takes G lanes, four consecutive samples per lane (so G = 16 for 64 samples, 32 for 128), and a
 // wavefront 64 / G rows: one gather instruction fetches 16 bytes a lane for 64 / G entries.  Every quad of
 // lanes holds 16 entries of its row, four per lane, and hands them round with quad_perm; slots past the end of
-// a row carry weight 0 and add an exact zero.  Same order of the sums as in k_spmm.
+// a row carry weight 0 and a column outside the operand, which reads as 0 (a neuron's activation might be infinite or NaN):
+// they add an exact zero.  Same order of the sums as in k_spmm.
 //
 // A wavefront per row (k_spmm with one sample per lane) is bound by the rate of gather instructions (10 clocks each,
 // whatever the number of samples) up to 64 samples, and by the L2 misses of a 256-sample tile beyond.  Here
@@ -425,11 +427,11 @@ __device__ __forceinline__ float4 as_f4(u32x4 t)
 struct __attribute__((packed, aligned(4))) I4 { int v[4]; };
 struct __attribute__((packed, aligned(4))) F4 { float v[4]; };
 // The entries of a quad's row in groups of sixteen, four per lane: entries past the end of the row (what follows it in
-// the arrays is read) count as zeros.
+// the arrays is read) count as zeros, at column n_cols: past the end of the operand.
 struct QuadEntries {
     I4 c;
     F4 w;
-    __device__ __forceinline__ void fetch(const int32_t *idx, const float *vals, int p, int end)
+    __device__ __forceinline__ void fetch(const int32_t *idx, const float *vals, int p, int end, int n_cols)
     {
         if (p < end) {
             c = *(const I4 *)(idx + p);
@@ -437,7 +439,7 @@ struct QuadEntries {
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (p + i >= end) { c.v[i] = 0; w.v[i] = 0.0f; }
+            if (p + i >= end) { c.v[i] = n_cols; w.v[i] = 0.0f; }
     }
 };
 // The operand rows of the four entries that quad lane H holds, and their weights.
@@ -471,7 +473,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_rows(const SpmmArgs a)
     const int row = t.x, end = t.z;
     int p = t.y + 4 * (lane & 3), left = end - t.y; // left: entries of this lane's row still to do
     QuadEntries q;
-    q.fetch(a.idx, a.vals, p, end);
+    q.fetch(a.idx, a.vals, p, end, a.n_cols);
     const double b = a.aux ? (double)a.aux[row] : 0.0;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (bool more = __ballot(left > 0) != 0; more;) {
@@ -484,7 +486,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_rows(const SpmmArgs a)
         quad_gather<3>(q, rin, ldb, so, x[3], wv[3]);
         p += 16;
         left -= 16;
-        if (more) q.fetch(a.idx, a.vals, p, end);
+        if (more) q.fetch(a.idx, a.vals, p, end, a.n_cols);
 #pragma unroll
         for (int h = 0; h < 4; ++h)
 #pragma unroll
@@ -590,7 +592,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const SpmmArgs a)
     const int row = t.x, end = t.z;
     int p = t.y + 4 * (lane & 3), left = end - t.y; // left: entries of this lane's row still to do
     QuadEntries q, qn;
-    q.fetch(a.idx, a.vals, p, end);
+    q.fetch(a.idx, a.vals, p, end, a.n_cols);
     float xp[4] = {0.0f, 0.0f, 0.0f, 0.0f}; // lanes outside the batch add nothing to the gradient
     if (live) ldv<4>(a.aux + (size_t)row * a.ld_out + s, xp);
     double xd[4], acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -626,7 +628,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const SpmmArgs a)
         more = __ballot(left > 16) != 0;
         p += 16;
         left -= 16;
-        if (more) qn.fetch(a.idx, a.vals, p, end);
+        if (more) qn.fetch(a.idx, a.vals, p, end, a.n_cols);
         quad_gather<1>(q, rin, ldb, so, x1, w1);
         consume(x0, w0);
         quad_gather<2>(q, rin, ldb, so, x0, w0);
@@ -787,8 +789,8 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm_panel(const SpmmArgs a, 
 // activations in one LDS buffer of [position][T] floats, and only W is streamed, from a lane-major copy.
 //
 // Copy of W: the rows of a layer, longest first, in blocks of 64 that are dealt to the wavefronts; lane r of
-// a wavefront walks row r of the block.  A block's entries come in chunks of sixteen per lane (zero weights
-// past the end of a row add an exact zero), each as two halves of 3 KiB: the 64 lanes' eight 16-bit positions
+// a wavefront walks row r of the block.  A block's entries come in chunks of sixteen per lane (past the end of a row:
+// zero weights at a position of their own that always holds zeros), each as two halves of 3 KiB: the 64 lanes' eight 16-bit positions
 // (16 bytes a lane), then two times four weights (16 bytes a lane): 6 bytes per entry in coalesced 16-byte
 // loads.  The chunks of one wavefront follow each other through all its blocks and all layers; the half after
 // next, of whatever block or layer, is requested as soon as the registers of the current one are free, so nothing
@@ -863,7 +865,7 @@ struct LdsForward {
     const int32_t *src_col; // the column of `in` that holds sample k of them
     const int32_t *dst_col; // the column of `out` that sample k goes to (NULL: k)
     int32_t *alive;        // alive[k] = whether sample k has a non-zero activation at the end (NULL: not wanted)
-    int32_t max_pos;       // positions of the LDS buffer
+    int32_t max_pos;       // positions of the LDS buffer; one more follows, which holds zeros
 };
 
 // PART: a stretch of layers for the samples that are still alive.
@@ -917,6 +919,7 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
         }
         act[i] = v;
     }
+    if (tid < T) lds_act[T * a.max_pos + tid] = 0.0f; // where the slots past the end of a row point
 
     // the wavefront's place in the copy of W, in bytes (the copy is smaller than 4 GiB), goes into the loads as a scalar
     const __amdgpu_buffer_rsrc_t rlm = make_rsrc((const float *)a.lm, a.lm_bytes);
@@ -1108,7 +1111,7 @@ __global__ void __launch_bounds__(1024) k_live_columns(const int32_t *__restrict
 __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ layer, const LmLayer *__restrict__ tab,
                                                 const int32_t *__restrict__ lm_cs, uint4 *__restrict__ lm,
                                                 float *__restrict__ lm_bias, const int32_t *__restrict__ lm_row,
-                                                const int32_t *__restrict__ prev_pos, int with_cols)
+                                                const int32_t *__restrict__ prev_pos, int with_cols, int pad_pos)
 {
     const LayerDev &L = *layer;
     const int j = blockIdx.x, w = blockIdx.y, lane = threadIdx.x, nb = tab->nb;
@@ -1129,7 +1132,7 @@ __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ lay
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int e = beg + hf * 8 + k;
-            unsigned pos = 0;
+            unsigned pos = (unsigned)pad_pos; // zeros in k_fwd_lds, past the end of the operand in k_spmv_lm
             wt[k] = 0;
             if (e < end) {
                 wt[k] = __float_as_uint(L.vals[e]);
@@ -1454,10 +1457,13 @@ __global__ void __launch_bounds__(64) k_spmv_lm(const SpmvLmArgs a)
     typedef const int32_t __attribute__((address_space(4))) *cs_ptr;
     const cs_ptr scs = (cs_ptr)a.cs;
     int c0, n, place; // first chunk, chunks, where the result goes
+    [[maybe_unused]] int len = 0; // TRAIN: entries of the lane's row
     if constexpr (TRAIN) {
         c0 = scs[b];
         n = scs[b + 1] - c0;
-        place = a.row[64 * b + lane].x;
+        const int2 r = a.row[64 * b + lane];
+        place = r.x;
+        len = r.y;
     } else { // position 64 (16 j + w) + lane: block j of wavefront w, two chunks of eight for each of its sixteen entries
         const int j = b / LDS_WAVES, w = b - j * LDS_WAVES, at = a.tab_cs + w * (a.nb + 1) + j;
         c0 = 2 * scs[at];
@@ -1496,6 +1502,13 @@ __global__ void __launch_bounds__(64) k_spmv_lm(const SpmvLmArgs a)
                     x[u][k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rin, (int)(4u * col), 0, 0));
                 }
             }
+        if (TRAIN && !WIDE && a.in_bytes > 4u * 0xffffu) { // 65536 columns: no 2-byte column is outside the operand
+#pragma unroll
+            for (int u = 0; u < B1_LOAD; ++u)
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (i + u < n && 8 * (i + u) + k >= len) x[u][k] = 0.0f;
+        }
 #pragma unroll
         for (int u = 0; u < B1_LOAD; ++u)
             if (i + u < n) {
@@ -1591,11 +1604,15 @@ __global__ void __launch_bounds__(64) k_b1_fill(const LayerDev *__restrict__ lay
     const int c0 = L.b1_cs[o][b], n = L.b1_cs[o][b + 1] - c0;
     const int2 r = L.b1_row[o][64 * b + lane];
     const int beg = r.x >= 0 ? (o ? L.t_row_ptr[r.x] : L.row_ptr[r.x]) : 0;
+    // slots past the end of a row: weight 0, and a column past the end of the operand, which k_spmv_lm reads as 0 (a masked one
+    // where 2 bytes hold none)
+    const unsigned n_cols = (unsigned)(o ? L.n_out : L.n_in), pad = WIDE ? n_cols : min(n_cols, 0xffffu);
     for (int i = 0; i < n; ++i) {
         unsigned col[8], w[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            col[k] = w[k] = 0;
+            col[k] = pad;
+            w[k] = 0;
             if (8 * i + k < r.y) {
                 const int e = beg + 8 * i + k;
                 w[k] = __float_as_uint(L.vals[o ? L.t_perm[e] : e]);
@@ -2528,7 +2545,7 @@ static int launch_lm_fill(sdnn_net *net, int l, const int32_t *prev_pos, int wit
 {
     if (net->lm_tab[l].nb == 0) return SDNN_OK;
     hipLaunchKernelGGL(k_lm_fill, dim3((unsigned)net->lm_tab[l].nb, LDS_WAVES), dim3(64), 0, stream, net->d_layers + l, net->lm_layers + l,
-                       net->lm_cs, net->lm, net->lm_bias, net->lm_row, prev_pos, with_cols);
+                       net->lm_cs, net->lm, net->lm_bias, net->lm_row, prev_pos, with_cols, net->lm_max_pos);
     HIP_TRY(net, hipGetLastError());
     return SDNN_OK;
 }
@@ -3002,8 +3019,12 @@ static int launch_spmm_panel(sdnn_net *net, const LayerDev &d, SpmmArgs a, int B
     return SDNN_OK;
 }
 
-// The several-rows-per-wavefront kernels form byte offsets as (24-bit column) x (24-bit row pitch).
-static bool rows_addressable(int n_cols, int ld) { return n_cols < (1 << 24) && ld < (1 << 22); }
+// The several-rows-per-wavefront kernels form byte offsets as (24-bit column) x (24-bit row pitch) in 32 bits, up to and
+// including those of the row past the end.
+static bool rows_addressable(int n_cols, int ld)
+{
+    return n_cols < (1 << 24) && ld < (1 << 22) && 4 * ((int64_t)n_cols + 2) * ld < ((int64_t)1 << 32);
+}
 // Lanes per row of the several-rows-per-wavefront kernels that a tile of `width` samples needs.
 static int lanes_per_row(int width) { return width <= 16 ? 4 : width <= 32 ? 8 : width <= 64 ? 16 : width <= 128 ? 32 : 64; }
 // The same, doubled while the wavefronts are fewer than the chip's SIMDs (idle lanes cost nothing there: 4096 neurons,
@@ -3047,6 +3068,7 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
     a.cap = net->cfg.act_cap; a.act = net->cfg.activation;
     if (a.n_rows == 0) return SDNN_OK;
     const int n_cols = MODE == 0 ? d.n_in : d.n_out;
+    a.n_cols = n_cols;
     a.in_bytes = 4 * (size_t)n_cols * (size_t)ld_in;
     if (a.in_bytes >= ((size_t)1 << 32))
         return fail(net, SDNN_EINVAL, "activation block of %zu bytes exceeds 4 GiB: use a smaller B", a.in_bytes);
@@ -3257,9 +3279,9 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
             {(const void *)k_fwd_lds<1, ACT_RELU_CAP>, (const void *)k_fwd_lds<2, ACT_RELU_CAP>, (const void *)k_fwd_lds<4, ACT_RELU_CAP>},
             {(const void *)k_fwd_lds<1, ACT_SIGMOID>, (const void *)k_fwd_lds<2, ACT_SIGMOID>, (const void *)k_fwd_lds<4, ACT_SIGMOID>}};
         const void *fn = fns[sig ? 1 : 0][ti];
-        const size_t lds_bytes = sizeof(float) * (size_t)T * (size_t)net->lm_max_pos;
+        const size_t lds_bytes = sizeof(float) * (size_t)T * ((size_t)net->lm_max_pos + 1);
         if (!net->lds_attr_set[ti]) { // more than the default 64 KiB of dynamic LDS per workgroup
-            HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * LDS_MAX_FLOATS));
+            HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (LDS_MAX_FLOATS + 4)));
             net->lds_attr_set[ti] = true;
         }
         LdsForward a = lds_args(net, 0, L, d_X0, B, d_XL, B, B);
@@ -3396,9 +3418,9 @@ static int skip_dead_lds(sdnn_net *net, const float *d_X0, int B, float *d_XL, i
     const int last_check = (L - 1) / check_every * check_every;
     int t_max = 4;
     while (t_max > 1 && t_max * net->lm_max_pos > LDS_MAX_FLOATS) t_max /= 2;
-    const size_t lds_bytes = sizeof(float) * (size_t)t_max * (size_t)net->lm_max_pos;
+    const size_t lds_bytes = sizeof(float) * (size_t)t_max * ((size_t)net->lm_max_pos + 1);
     if (!net->lds_part_attr_set) {
-        HIP_TRY(net, hipFuncSetAttribute((const void *)k_fwd_lds_part, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * LDS_MAX_FLOATS));
+        HIP_TRY(net, hipFuncSetAttribute((const void *)k_fwd_lds_part, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (LDS_MAX_FLOATS + 4)));
         net->lds_part_attr_set = true;
     }
     const unsigned grid = (unsigned)std::max(std::min(B, net->n_cu), (B + t_max - 1) / t_max);
@@ -3520,6 +3542,7 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
             return launch_spmm<1>(net, d, d.D, net->ld, out, net->ld, d.X_prev, B, stream);
         return SDNN_OK;
     }
+    a.n_cols = d.n_out;
     a.in_bytes = 4 * (size_t)d.n_out * (size_t)net->ld;
     a.tile_base = 0;
     a.n_tiles = 1;
@@ -3679,14 +3702,14 @@ extern "C" int sdnn_sgd_step(sdnn_net *net, float lr, void *stream_)
     } else if (net->b1) {
         int max_blocks = 1;
         for (const LayerDev &d : net->layers) max_blocks = std::max({max_blocks, d.b1_blocks[0], d.b1_blocks[1]});
-        const bool in_lds = 4 * (int64_t)net->max_n <= B1_MAX_LDS;
+        const bool in_lds = 4 * ((int64_t)net->max_n + 4) <= B1_MAX_LDS; // the slots past the end of a row read one place more
         const int groups = (max_blocks + LDS_WAVES - 1) / LDS_WAVES;
         // In LDS: enough workgroups to fill the chip twice, and no more of them than pay for filling their LDS.  Else as many as
         // there are groups of blocks, so that the chip works on few layers at a time and their vectors stay in L2.
         const int parts = in_lds ? std::min(groups, std::max(8, 2 * net->n_cu / net->n_layers)) : groups;
         const void *fn = net->b1_wide ? (in_lds ? (const void *)k_update_lm<true, true> : (const void *)k_update_lm<true, false>)
                                       : (in_lds ? (const void *)k_update_lm<false, true> : (const void *)k_update_lm<false, false>);
-        const size_t lds = in_lds ? (4 * (size_t)net->max_n + 15) & ~(size_t)15 : 0;
+        const size_t lds = in_lds ? (4 * ((size_t)net->max_n + 1) + 15) & ~(size_t)15 : 0;
         if (in_lds && !net->b1_attr_set) {
             HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, B1_MAX_LDS));
             net->b1_attr_set = true;

@@ -1,0 +1,86 @@
+"""Infinite and NaN activations stay with the rows that gather them: the slots that fill up a row's last group of entries
+carry weight 0, and 0 times infinity is NaN, so they must not read a neuron's value.  One case per kernel that fills up
+rows; row lengths around the groups of 8 and 16 entries, bad values at the first and the last neuron.  Exact: a row that
+does not gather a bad value has the bits that it has without bad values anywhere."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2104_11805_amd import sdnn, workloads as wl
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = (0, 1, 7, 8, 9, 15, 16, 17, 31, 33)
+
+
+def _layer(seed, n_out, n_in):
+    rng = np.random.default_rng(seed)
+    deg = np.resize(np.asarray(LENGTHS), n_out)
+    row_ptr = np.zeros(n_out + 1, np.int32)
+    np.cumsum(deg, out=row_ptr[1:])
+    cols = np.concatenate([np.sort(rng.choice(n_in, size=d, replace=False)) for d in deg]).astype(np.int32)
+    cols[row_ptr[3]], cols[row_ptr[6] - 1] = 0, n_in - 1  # rows of 8 and 15 entries
+    vals = (rng.standard_normal(cols.size) * 0.4).astype(np.float32)
+    return wl.Layer(n_out, n_in, row_ptr, cols, vals, (-0.1 * rng.random(n_out)).astype(np.float32))
+
+
+def _gathers(layer, neurons):
+    """Whether a row of the layer has one of the columns."""
+    hit = np.isin(layer.col_idx, neurons)
+    return np.add.reduceat(np.append(hit, False), layer.row_ptr[:-1]).astype(bool) & (np.diff(layer.row_ptr) > 0)
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+@pytest.mark.parametrize("mode,n_in,b", [("infer", 2050, 1), ("infer", 2050, 7), ("infer", 2050, 600), ("skip_dead", 2050, 7),
+                                         ("layers", 2050, 70), ("train", 2050, 1), ("train", 65536, 1), ("train", 65537, 1),
+                                         ("train", 2050, 6), ("train", 2050, 70), ("train", 2050, 130)])
+def test_forward(mode, n_in, b, bad):
+    n_out = 2113
+    layer = _layer(9500, n_out, n_in)
+    lds = {"infer": sdnn.SDNN_LDS_ON, "skip_dead": sdnn.SDNN_LDS_ON}.get(mode, sdnn.SDNN_LDS_OFF)
+    x = wl.normal_inputs(9501, n_in, b)
+    x_bad = x.copy()
+    x_bad[[0, -1], :] = bad
+    outs = []
+    for v in (x, x_bad):
+        net = sdnn.Net([layer], 2.0, b, training=(mode == "train"), lds_forward=lds)
+        out = torch.empty(n_out, b, device=P.DEV)
+        if mode == "skip_dead":
+            net.sdnn_forward_skip_dead(P.dev(v), out, 1)
+        else:
+            net.sdnn_forward(P.dev(v), out)
+        outs.append(P.host(out))
+        net.close()
+    touched = _gathers(layer, [0, n_in - 1])
+    assert touched.any() and not touched.all()
+    assert np.array_equal(outs[0][~touched], outs[1][~touched])
+    if np.isnan(bad):
+        assert np.isnan(outs[1][touched]).all()
+    else: # one infinite term: the cap or zero by its weight's sign (both of them: perhaps NaN)
+        both = _gathers(layer, [0]) & _gathers(layer, [n_in - 1])
+        assert np.isin(outs[1][touched & ~both], [0.0, 2.0]).all()
+
+
+@pytest.mark.parametrize("b", [1, 6, 70, 130, 200])
+def test_backward(b):
+    layers = [_layer(9510, 7001, 300), _layer(9511, 2113, 7001)]
+    x = wl.normal_inputs(9512, 300, b)
+    d = wl.normal_inputs(9513, 2113, b)
+    d_bad = d.copy()
+    d_bad[[0, 9], :] = np.inf
+    deltas = []
+    for v in (d, d_bad):
+        net = sdnn.Net(layers, 1e30, b, training=True, fuse_gradient=1, activation="sigmoid")
+        xl = torch.empty(2113, b, device=P.DEV)
+        net.sdnn_forward(P.dev(x), xl)
+        net.sdnn_backward(P.dev(v))
+        deltas.append(P.host(net.sdnn_get_delta(1, b)))
+        net.close()
+    touched = np.zeros(7001, bool)
+    for r in (0, 9):
+        touched[layers[1].col_idx[layers[1].row_ptr[r]:layers[1].row_ptr[r + 1]]] = True
+    assert touched.any()
+    assert np.isfinite(deltas[0]).all()
+    assert np.array_equal(deltas[0][~touched], deltas[1][~touched])
+    assert not np.isfinite(deltas[1][touched]).any()
