@@ -13,18 +13,24 @@
 //     needed per 8 edges before the weight is rewritten in place.
 //   * W^T: the transposed index lists, per column, the source rows and the
 //     positions of the values in the CSR array.
-//   * layers of 4096 rows and more: the backward sweep also forms the gradient
-//     of the stored entries (k_bwd_grad, gathered rows parked in LDS) and reads
-//     the values from a copy in the order of the transposed index; the descent
-//     step is then a streaming pass over that copy (k_apply) and a second one
-//     that rebuilds the CSR copy (k_spread_vals).
+//   * short rows: several rows per wavefront, four samples per lane (k_rows).
+//   * nets with enough entries per layer: the backward sweep also forms the
+//     gradient of the stored entries (k_bwd_rows; few short rows: k_bwd_grad,
+//     gathered rows parked in LDS) and reads the values from a copy in the order
+//     of the transposed index; the descent step is then a streaming pass over
+//     that copy (k_apply) and a second one that rebuilds the CSR copy
+//     (k_spread_vals).
+//   * inference on layers of up to 32768 neurons: one launch, activations in LDS
+//     (k_fwd_lds).
 //   * inference on large activation blocks goes through all layers in
 //     sub-blocks of samples, so that a layer's output is still in the
 //     memory-side cache when the next layer gathers it.
-//   * one sample per step (B = 1): lanes over entries / rows instead of samples
-//     (k_spmv_stage, k_spmv_wave, k_spmv, k_update_b1).
-//   * inference that drops dead samples: flags set by the forward epilogue,
-//     in-place packing on the device (k_pack), no host synchronisation.
+//   * one sample per step (B = 1): a lane per row over lane-major copies of W and
+//     W^T (k_spmv_lm, k_update_lm), or lanes over entries / rows (k_spmv_stage,
+//     k_spmv_wave, k_spmv, k_update_b1).
+//   * inference that drops dead samples: stretches of layers in LDS with the live
+//     samples listed between them (k_fwd_lds_part, k_live_columns), or flags set by
+//     the forward epilogue and in-place packing (k_pack); no host synchronisation.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -160,14 +166,16 @@ __device__ __forceinline__ void map_block(unsigned bid, unsigned n_tiles, unsign
 //   MODE 1 (backward, Eq. 7):  out = sum * [0 < Xprev[row] < cap]; the values
 //                              are read through the transposed index (perm)
 // ---------------------------------------------------------------------------
+// 128 bytes: two cache lines of kernel arguments, which every wavefront of a launch waits for (with what only the gradient
+// sweeps need in it, and 64-bit sizes, a launch of 256 workgroups takes 0.04 us longer).
 struct SpmmArgs {
-    const int32_t *row_ptr;
     const int32_t *idx;
     const float *vals;
     const int32_t *perm;  // MODE 1 only
     const int4 *sched;    // per task: {row, first entry, end of entries, 0}, rows by decreasing length
     const float *in;      // [n_cols][ld_in]
-    size_t in_bytes;      // < 4 GiB
+    uint32_t in_bytes;
+    int32_t n_cols;
     float *out;           // [n_rows][ld_out]
     const float *aux;     // MODE 0: bias [n_rows] (may be NULL); MODE 1: Xprev [n_rows][ld_out]
     int32_t n_rows, B;    // B: samples (columns that matter)
@@ -177,11 +185,14 @@ struct SpmmArgs {
     int32_t act;
     const int32_t *n_live; // NULL, or the number of leading columns of the block that still matter (device)
     int32_t *flags;        // NULL, or MODE 0: flags[s] is set to 1 for every sample s with a non-zero output
-    int32_t n_cols;        // rows of `in` (k_rows, k_bwd_rows)
-    float *g_part[2];      // GRAD kernels: gradient of the stored entries over the samples of the first / second tile, in the
-                           // order of the transposed index [nnz]
-    int32_t store_out;     // GRAD kernels: 0 = only the gradient is wanted (first layer: there is no Delta_0)
+    const int32_t *row_ptr;
 };
+struct GradArgs : SpmmArgs {
+    float *g_part[2];  // gradient of the stored entries over the samples of the first / second tile, in the order of the
+                       // transposed index [nnz]
+    int32_t store_out; // 0 = only the gradient is wanted (first layer: there is no Delta_0)
+};
+static_assert(sizeof(SpmmArgs) == 128, "see above");
 
 // The part of a row task that does not depend on the previous layer's output:
 // which row, where its entries are, and its first (up to) 64 entries, entry k
@@ -573,7 +584,7 @@ __device__ __forceinline__ float add_neighbour16(float g)
 // TWO (G = 32, 128 samples): the gradient is the sum of two windows of 64 samples, each rounded to fp32 (what two launches
 // of 64 samples leave in two partial gradients).
 template <int G, bool TWO>
-__global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const SpmmArgs a)
+__global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const GradArgs a)
 {
     static_assert(!TWO || G == 32, "two windows of 16 lanes");
     constexpr int R = 64 / G;
@@ -1165,7 +1176,7 @@ __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ lay
 #define GRAD_LD 68 // floats per parked entry: 64 samples + pad (rows stay 16-byte aligned, banks spread)
 #define GRAD_GE 16 // entries parked at a time: 4.6 KB of LDS per wavefront, which keeps 8 wavefronts per SIMD
 template <int U>
-__device__ __forceinline__ void spmm_row_grad(RowMeta m, const SpmmArgs &a, int lane,
+__device__ __forceinline__ void spmm_row_grad(RowMeta m, const GradArgs &a, int lane,
                                               float *__restrict__ dt, float *__restrict__ xt)
 {
     const int B = a.B;
@@ -1244,7 +1255,7 @@ __device__ __forceinline__ void spmm_row_grad(RowMeta m, const SpmmArgs &a, int 
     if (a.store_out && live) a.out[(size_t)m.row * ld + s] = act_backprop(a.act, acc, xp, a.cap);
 }
 template <int U>
-__global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_grad(const SpmmArgs a)
+__global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_grad(const GradArgs a)
 {
     __shared__ __attribute__((aligned(16))) float dt[WAVES_PER_BLOCK][GRAD_GE * GRAD_LD];
     __shared__ __attribute__((aligned(16))) float xt[WAVES_PER_BLOCK][64];
@@ -3056,7 +3067,6 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
     SpmmArgs a;
     a.n_live = n_live;
     a.flags = flags;
-    a.g_part[0] = a.g_part[1] = nullptr; a.store_out = 1;
     if (MODE == 0) {
         a.row_ptr = d.row_ptr; a.idx = d.col_idx; a.perm = nullptr; a.sched = d.sched;
         a.n_rows = d.n_out;
@@ -3069,14 +3079,15 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
     if (a.n_rows == 0) return SDNN_OK;
     const int n_cols = MODE == 0 ? d.n_in : d.n_out;
     a.n_cols = n_cols;
-    a.in_bytes = 4 * (size_t)n_cols * (size_t)ld_in;
-    if (a.in_bytes >= ((size_t)1 << 32))
-        return fail(net, SDNN_EINVAL, "activation block of %zu bytes exceeds 4 GiB: use a smaller B", a.in_bytes);
+    const size_t in_bytes = 4 * (size_t)n_cols * (size_t)ld_in;
+    if (in_bytes >= ((size_t)1 << 32))
+        return fail(net, SDNN_EINVAL, "activation block of %zu bytes exceeds 4 GiB: use a smaller B", in_bytes);
+    a.in_bytes = (uint32_t)in_bytes;
     if (B == 1 && net->b1) {
         const int o = MODE;
         SpmvLmArgs b;
         memset(&b, 0, sizeof b);
-        b.cs = d.b1_cs[o]; b.row = d.b1_row[o]; b.lm = (const uint4 *)d.b1_lm[o]; b.in = in; b.in_bytes = (unsigned)a.in_bytes; b.aux = aux; b.out = out;
+        b.cs = d.b1_cs[o]; b.row = d.b1_row[o]; b.lm = (const uint4 *)d.b1_lm[o]; b.in = in; b.in_bytes = a.in_bytes; b.aux = aux; b.out = out;
         b.lm_bytes = 0xffffffffu; // every chunk that the table names is there
         b.cap = a.cap; b.act = a.act;
         if (net->b1_wide) hipLaunchKernelGGL((k_spmv_lm<MODE, true, true>), dim3((unsigned)d.b1_blocks[o]), dim3(64), 0, stream, b);
@@ -3532,7 +3543,7 @@ static bool two_windows(const sdnn_net *net, int B)
 static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStream_t stream, int store_out)
 {
     const int B = net->Bp;
-    SpmmArgs a;
+    GradArgs a;
     a.row_ptr = d.t_row_ptr; a.idx = d.t_row_idx; a.perm = nullptr; a.sched = d.t_sched; a.n_rows = d.n_in;
     a.vals = d.vals_t; a.in = d.D; a.out = out; a.aux = d.X_prev; a.B = B; a.ld_in = a.ld_out = net->ld; a.cap = net->cfg.act_cap;
     a.act = net->cfg.activation; a.n_live = nullptr; a.flags = nullptr;
@@ -3543,7 +3554,7 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
         return SDNN_OK;
     }
     a.n_cols = d.n_out;
-    a.in_bytes = 4 * (size_t)d.n_out * (size_t)net->ld;
+    a.in_bytes = (uint32_t)(4 * (size_t)d.n_out * (size_t)net->ld);
     a.tile_base = 0;
     a.n_tiles = 1;
     a.n_rg = (uint32_t)((a.n_rows + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
