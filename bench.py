@@ -87,18 +87,12 @@ def run_config(cfg, args, steps, warmup, headline):
     create_s = time.time() - t0
     log(f"config {cfg}: training net created in {create_s:.1f} s, workspace {net.workspace_bytes / 2**30:.2f} GiB")
     # which kernels the library picks for this shape (its measured launch policy, restated here to name them):
-    # short rows and small layers run as two half-batches on two streams; layers of >= 4096 rows form the gradient in
-    # the backward sweep where a launch holds at most 64 samples (short rows) or the batch at most 256 (long rows)
+    # nets with enough entries per layer form the gradient in the backward sweep for every batch of 2 to 256 samples
     short_rows = nnz_total < 128 * N * L
-    split = short_rows and Bt % 128 == 0 and N * Bt <= 2 ** 21
     fuse_opt = args.fuse_gradient if headline else 0
-    fused = ((N >= 4096 or fuse_opt > 0) and fuse_opt >= 0
-             and ((short_rows and ((split and Bt == 128) or (not split and 1 < Bt <= 64)))
-                  or (not short_rows and Bt <= 256 and Bt % 4 == 0)))
-    if split:
-        v = 4 if Bt % 512 == 0 else 2 if Bt % 256 == 0 else 1
-    else:
-        v = 4 if (Bt % 4 == 0 and Bt > 128) else 2 if (Bt % 2 == 0 and Bt > 64) else 1
+    by_size = (nnz_total >= 48000 * L and (short_rows or Bt <= 256)) if Bt > 64 else (nnz_total >= 85000 * L and (short_rows or N >= 4096))
+    fused = 1 < Bt <= 256 and fuse_opt >= 0 and (fuse_opt > 0 or by_size)
+    v = 4 if Bt > 128 else 2 if Bt > 64 else 1
     x0 = to_dev(work.x_train)
     xl = torch.empty(work.layers[-1].n_out, Bt, device=dev)
     dl = torch.empty_like(xl)
@@ -186,9 +180,9 @@ def run_config(cfg, args, steps, warmup, headline):
     # separate backward: layers L..2 only; fused sweep: all layers, the first one without a Delta output
     bb -= (4 * first.n_in * Bt) if fused else layer_bytes(first.n_out, first.nnz, Bt, fused)[1]
     panels = short_rows and N * 256 >= (8 << 20) and (args.panel_cols >= 0 or not headline)   # the library's policy
-    kernels = {"forward": "k_spmm_panel<8,0>" if panels else f"k_spmm<{v},0,{8 if short_rows else 16}>",
-               "backward": ("k_bwd_grad<8>" if short_rows else "k_bwd_grad4<8>") if fused else f"k_spmm<{v},1,{8 if short_rows else 16}>",
-               "update": "k_apply + k_gather_vals + k_apply_bias" if fused else "k_update<4>"}
+    kernels = {"forward": "k_spmm_panel<8,0>" if panels else f"k_spmm<{v},0,{8 if short_rows else 16}>" if not short_rows or (Bt <= 64 and N < 2048) else "k_rows",
+               "backward": ("k_bwd_grad<8>" if Bt <= 64 and short_rows and N <= 6144 else "k_bwd_rows") if fused else f"k_spmm<{v},1,{8 if short_rows else 16}>",
+               "update": "k_apply + k_spread_vals + k_apply_bias" if fused else "k_update<4>"}
     passes = {"forward": (fwd_ms, fb, L), "backward": (bwd_ms, bb, L if fused else L - 1), "update": (upd_ms, ub, 1)}
     dom = max(passes, key=lambda k: passes[k][0])
     d_ms, d_bytes, d_units = passes[dom]
@@ -200,13 +194,13 @@ def run_config(cfg, args, steps, warmup, headline):
     if os.path.exists(tpath) and density_arg is None:
         t = json.load(open(tpath))
         k = t["kernels"].get(dom)
-        if k:
+        if k and k["kernel"] == kernels[dom]:   # counted on the kernel that runs now
             traffic = int(1024 * (k["fetch_KiB"] * t["scale"]["FETCH_SIZE"] + k["write_KiB"] * t["scale"]["WRITE_SIZE"]))
     roofline = {"bound": "hbm", "kernel": kernels[dom], "pass": dom, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "units_per_step": d_units, "unit_of_work": "one layer" if dom != "update" else "all layers",
                 "avg_unit_us": round(d_ms * 1e3 / d_units, 3), "bytes_per_unit": int(d_bytes / d_units),
-                "kernel_launches_per_unit": 2 if (dom != "update" and split) else 1,
+                "kernel_launches_per_unit": 1,
                 "per_pass_frac": {p: round(passes[p][1] / (passes[p][0] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4) for p in passes},
                 "step_frac": round((fb + bb + ub) / (ms_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     net.close()
