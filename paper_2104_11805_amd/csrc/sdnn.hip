@@ -2538,9 +2538,13 @@ extern "C" int sdnn_workspace_bytes(const sdnn_layer *layers, int32_t n_layers,
     if (!bytes) return fail(nullptr, SDNN_EINVAL, "bytes is NULL");
     int rc = check_config(layers, n_layers, cfg);
     if (rc) return rc;
-    for (int32_t l = 0; l < n_layers; ++l)
-        if (layers[l].row_ptr[0] != 0 || layers[l].row_ptr[layers[l].n_out] < 0)
-            return fail(nullptr, SDNN_EINVAL, "layer %d: malformed row_ptr", l + 1);
+    for (int32_t l = 0; l < n_layers; ++l) { // the plan counts rows by their length
+        const sdnn_layer &y = layers[l];
+        bool ok = y.row_ptr[0] == 0;
+        for (int32_t r = 0; ok && r < y.n_out; ++r)
+            ok = y.row_ptr[r + 1] >= y.row_ptr[r] && y.row_ptr[r + 1] - y.row_ptr[r] <= y.n_in;
+        if (!ok) return fail(nullptr, SDNN_EINVAL, "layer %d: malformed row_ptr", l + 1);
+    }
     Plan pl;
     try {
         make_plan(layers, n_layers, cfg, pl);

@@ -83,9 +83,21 @@ extern "C" int sdnn_row_schedule(int32_t n_rows, const int32_t *row_ptr, int32_t
         sdnn_set_global_error("NULL pointer or negative size");
         return SDNN_EINVAL;
     }
-    try { // counting sort by decreasing length, stable
-        int32_t longest = 0;
-        for (int32_t r = 0; r < n_rows; ++r) longest = std::max(longest, row_ptr[r + 1] - row_ptr[r]);
+    int32_t longest = 0;
+    for (int32_t r = 0; r < n_rows; ++r) {
+        if (row_ptr[r + 1] < row_ptr[r]) {
+            sdnn_set_global_error("row_ptr decreases at row %d", r);
+            return SDNN_EINVAL;
+        }
+        longest = std::max(longest, row_ptr[r + 1] - row_ptr[r]);
+    }
+    try {
+        if (longest / 16 > n_rows) { // a few long rows: counting would take more memory than the rows do
+            std::iota(order, order + n_rows, 0);
+            std::stable_sort(order, order + n_rows, [&](int32_t a, int32_t b) { return row_ptr[a + 1] - row_ptr[a] > row_ptr[b + 1] - row_ptr[b]; });
+            return SDNN_OK;
+        }
+        // counting sort by decreasing length, stable
         std::vector<int32_t> at((size_t)longest + 2, 0); // at[longest - len]: the next place of a row of that length
         for (int32_t r = 0; r < n_rows; ++r) at[(size_t)(longest - (row_ptr[r + 1] - row_ptr[r])) + 1]++;
         for (int32_t k = 0; k <= longest; ++k) at[(size_t)k + 1] += at[(size_t)k];

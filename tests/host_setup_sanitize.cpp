@@ -46,8 +46,19 @@ int main()
             bad[rnd() % nnz] = n_in + (int)(rnd() % 5);
             if (sdnn_check_csr(n_out, n_in, row_ptr.data(), bad.data()) != SDNN_EINVAL) return 8;
         }
+        {
+            std::vector<int32_t> bad(row_ptr);
+            const int r = (int)(rnd() % n_out);
+            bad[r] = bad[r + 1] + 1 + (int)(rnd() % 300);
+            if (sdnn_row_schedule(n_out, bad.data(), order.data()) != SDNN_EINVAL) return 14;
+        }
     }
     if (sdnn_check_csr(3, 3, nullptr, nullptr) != SDNN_EINVAL) return 9;
+    {   // a row of any length that the type holds
+        const int32_t row_ptr[] = {0, 5, 2000000005, 2000000005};
+        int32_t order[3];
+        if (sdnn_row_schedule(3, row_ptr, order) || order[0] != 1 || order[1] != 0 || order[2] != 2) return 15;
+    }
     std::puts("host setup: ok");
     return 0;
 }

@@ -169,6 +169,21 @@ def test_workspace_bytes_and_argument_errors_without_gpu():
     assert l.sdnn_forward_noalloc(None, None, 1, None, None) == sdnn.SDNN_EINVAL
 
 
+@pytest.mark.parametrize("training,max_batch", [(0, 4), (1, 1), (1, 16)])
+@pytest.mark.parametrize("row_ptr", [(0, 3, 2, 4), (0, 300, 3, 4), (0, 2, 2, -1), (1, 2, 3, 4), (0, 9, 9, 9)])
+def test_workspace_bytes_refuses_a_malformed_row_ptr(row_ptr, training, max_batch):
+    """Decreasing, not starting at 0, or a row of more entries than there are columns: an error, whatever the plan counts."""
+    rp, ci, va = np.array(row_ptr, np.int32), np.zeros(400, np.int32), np.zeros(400, np.float32)
+    arr = (sdnn.sdnn_layer * 1)(sdnn.sdnn_layer(3, 8, rp.ctypes.data, ci.ctypes.data, va.ctypes.data, None))
+    cfg = sdnn.sdnn_config(32.0, max_batch, training, 1, 0)
+    n = C.c_size_t(0)
+    assert sdnn.lib().sdnn_workspace_bytes(arr, 1, C.byref(cfg), C.byref(n)) == sdnn.SDNN_EINVAL
+    assert "row_ptr" in sdnn.last_error()
+    if row_ptr[1] > row_ptr[2]:
+        order = np.zeros(3, np.int32)
+        assert sdnn.lib().sdnn_row_schedule(3, rp.ctypes.data, order.ctypes.data) == sdnn.SDNN_EINVAL
+
+
 def test_malformed_layer_is_rejected_by_create_without_gpu():
     net = wl.tiny_net(2, sizes=(7, 9, 6))
     net.layers[1].col_idx = net.layers[1].col_idx.copy()
