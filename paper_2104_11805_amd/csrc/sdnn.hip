@@ -3060,14 +3060,14 @@ static const void *rows_fn(int G, int act)
 }
 
 // in / out: rows of ld_in / ld_out floats.  sub_begin .. sub_end: the launch covers these samples only (sub_begin a
-// multiple of SUB_ALIGN, or of 64 where every layer takes the panel sweep; sub_end == 0: all of them).
+// multiple of SUB_ALIGN, or of 64 where every layer takes the panel sweep for all but the narrowest blocks; sub_end == 0: all
+// of them).
 template <int MODE>
 static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld_in, float *out, int ld_out,
                        const float *aux, int B, hipStream_t stream, const int32_t *n_live = nullptr, int32_t *flags = nullptr,
                        int sub_begin = 0, int sub_end = 0)
 {
-    const bool sub = sub_end > 0;
-    if (!sub) sub_end = B;
+    if (sub_end == 0) sub_end = B;
     SpmmArgs a;
     a.n_live = n_live;
     a.flags = flags;
@@ -3150,14 +3150,11 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;
     }
-    const int V = pick_v_spmm(B, ld_in, ld_out, in, out);
-    a.tile_base = 0;
-    a.n_tiles = (uint32_t)((B + 64 * V - 1) / (64 * V));
-    if (sub) {
-        if (sub_begin % (64 * V) != 0) return fail(net, SDNN_EHIP, "internal: sub-block at sample %d, tiles of %d", sub_begin, 64 * V);
-        a.tile_base = (uint32_t)(sub_begin / (64 * V));
-        a.n_tiles = (uint32_t)((width + 64 * V - 1) / (64 * V));
-    }
+    int V = pick_v_spmm(B, ld_in, ld_out, in, out);
+    // a sub-block starts at a multiple of 64 samples: in a pass cut for the panel sweep the last one comes here if it is narrow
+    while (sub_begin % (64 * V) != 0) V /= 2;
+    a.tile_base = (uint32_t)(sub_begin / (64 * V));
+    a.n_tiles = (uint32_t)((width + 64 * V - 1) / (64 * V));
     if (a.n_tiles == 0) return SDNN_OK;
     a.n_rg = (uint32_t)((a.n_rows + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
     const uint64_t blocks = (uint64_t)a.n_tiles * a.n_rg;
@@ -3258,7 +3255,8 @@ static LdsForward lds_args(const sdnn_net *net, int l0, int l1, const float *in,
 // (each at least 4 * max_n * B bytes); training nets keep every X_l in the workspace and ignore them.
 // Width in samples of the sub-blocks that an inference pass is cut into, 0 = one piece.  A sub-block's share of an
 // activation buffer is held to SUB_BYTES; the width is a multiple of SUB_ALIGN (the widest tile of the product
-// kernels), or of 64 where every layer takes the panel sweep (64-sample tiles throughout).
+// kernels), or of 64 where every layer takes the panel sweep (64-sample tiles; a last block of at most PANEL_MIN_SAMPLES goes to
+// other kernels, whose tiles then have to start at its first sample).
 #define SUB_BYTES ((int64_t)16 << 20)
 #define SUB_ALIGN 256
 static int sub_block_width(const sdnn_net *net, int B)

@@ -1,0 +1,64 @@
+// Stands in for the HIP runtime under libsdnn (loaded ahead of it by tests/routes.py): launches are written to a log and
+// nothing runs, so that what a call launches, copies or refuses can be checked on a machine without a GPU, at sizes that
+// need no memory.
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <string>
+#include <cxxabi.h>
+#include <hip/hip_runtime.h>
+
+static std::string text;
+static std::map<const void *, std::string> &names()
+{
+    static std::map<const void *, std::string> m; // the library registers its kernels before this file's own statics are set up
+    return m;
+}
+
+extern "C" {
+const char *stub_log() { return text.c_str(); }
+void stub_clear() { text.clear(); }
+
+void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipRegisterFunction(void **, const void *fn, char *, const char *name, unsigned, void *, void *, dim3 *, dim3 *, int *)
+{
+    int status = 0;
+    char *plain = abi::__cxa_demangle(name, nullptr, nullptr, &status);
+    std::string s = status == 0 ? plain : name;
+    free(plain);
+    if (s.compare(0, 5, "void ") == 0) s.erase(0, 5);
+    names()[fn] = s.substr(0, s.find('('));
+}
+static struct { dim3 g, b; size_t lds; hipStream_t s; } call;
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t s) { call = {g, b, lds, s}; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t *s)
+{
+    *g = call.g; *b = call.b; *lds = call.lds; *s = call.s;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **, size_t lds, hipStream_t)
+{
+    // what the runtime refuses: 2^32 work items in a dimension, more LDS than a workgroup can have
+    if ((unsigned long long)g.x * b.x >= 1ull << 32 || g.y > 65535 || g.z > 65535 || g.x == 0 || g.y == 0 || g.z == 0 || lds > 160 * 1024)
+        return hipErrorInvalidConfiguration;
+    char line[512];
+    snprintf(line, sizeof line, "%s %u %u %u\n", names()[fn].c_str(), g.x, g.y, g.z);
+    text += line;
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *, const void *, size_t bytes, hipMemcpyKind, hipStream_t)
+{
+    text += "memcpy " + std::to_string(bytes) + "\n";
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) { p->multiProcessorCount = 256; return hipSuccess; } // the header appends the version
+const char *hipGetErrorString(hipError_t e) { return e == hipErrorInvalidConfiguration ? "invalid configuration" : "no error"; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *) { *p = (void *)((size_t)1 << 44); return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = 8; return hipSuccess; }
+}
