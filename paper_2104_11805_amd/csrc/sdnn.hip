@@ -182,7 +182,8 @@ struct SpmmArgs {
     int32_t ld_in, ld_out; // floats per activation row
     uint32_t n_tiles, n_rg, n_vblocks, tile_base;
     float cap;
-    int32_t act;
+    int16_t act;
+    int16_t n_pad;         // the last n_pad of the B samples only fill up a group of four: whatever the kernel computes for them, zeros are stored
     const int32_t *n_live; // NULL, or the number of leading columns of the block that still matter (device)
     int32_t *flags;        // NULL, or MODE 0: flags[s] is set to 1 for every sample s with a non-zero output
     const int32_t *row_ptr;
@@ -241,7 +242,7 @@ __device__ __forceinline__ RowMeta load_meta(const int4 *sched, const int32_t *i
 template <int V, int MODE, int U, int ACT>
 __device__ __forceinline__ void spmm_row(RowMeta m, const int32_t *idx, const float *vals,
                                          const int32_t *perm, const float *in, size_t in_bytes,
-                                         float *out, const float *aux, int B, int ld_in, int ld_out, float capf,
+                                         float *out, const float *aux, int B, int n_pad, int ld_in, int ld_out, float capf,
                                          int act, unsigned tile, int lane, int32_t *flags)
 {
     const int s_own = (int)tile * (64 * V) + lane * V;
@@ -366,6 +367,9 @@ __device__ __forceinline__ void spmm_row(RowMeta m, const int32_t *idx, const fl
 #pragma unroll
         for (int v = 0; v < V; ++v) o[v] = act_backprop(act, acc[v], xp[v], capf);
     }
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+        if (s + v >= B - n_pad) o[v] = 0.0f;
     if (live) stv<V>(out + (size_t)m.row * ld + s, o);
     if (MODE == 0 && flags != nullptr && live) { // other rows store the same 1: no ordering needed
 #pragma unroll
@@ -399,7 +403,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
             if (r >= a.n_rows) continue;
             const RowMeta m = load_meta<MODE>(a.sched, a.idx, a.vals, a.perm, r, lane);
             for (unsigned tile = 0; tile < n_tiles; ++tile)
-                spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.ld_in, a.ld_out, a.cap, a.act,
+                spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.n_pad, a.ld_in, a.ld_out, a.cap, a.act,
                                           tile + a.tile_base, lane, a.flags);
         }
         return;
@@ -410,7 +414,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
         const int r = __builtin_amdgcn_readfirstlane((int)(rg * WAVES_PER_BLOCK + wave));
         if (r >= a.n_rows) continue;
         const RowMeta m = load_meta<MODE>(a.sched, a.idx, a.vals, a.perm, r, lane);
-        spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.ld_in, a.ld_out, a.cap, a.act, tile + a.tile_base, lane, a.flags);
+        spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.n_pad, a.ld_in, a.ld_out, a.cap, a.act, tile + a.tile_base, lane, a.flags);
     }
 }
 
@@ -512,7 +516,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_rows(const SpmmArgs a)
     if (r >= a.n_rows || !live) return;
     float o[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) o[v] = act_apply(ACT, acc[v] + b, a.cap);
+    for (int v = 0; v < 4; ++v) o[v] = s + v < a.B - a.n_pad ? act_apply(ACT, acc[v] + b, a.cap) : 0.0f;
     float *dst = a.out + (size_t)row * a.ld_out + s;
     if ((a.ld_out & 3) == 0 && ((size_t)a.out & 15) == 0) {
         stv<4>(dst, o);
@@ -655,7 +659,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const GradArgs a)
     if (!a.store_out || !live) return;
     float o[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) o[v] = act_backprop(a.act, acc[v], xp[v], a.cap);
+    for (int v = 0; v < 4; ++v) o[v] = s + v < a.B - a.n_pad ? act_backprop(a.act, acc[v], xp[v], a.cap) : 0.0f;
     stv<4>(a.out + (size_t)row * a.ld_out + s, o);
 }
 
@@ -788,7 +792,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm_panel(const SpmmArgs a, 
             float o;
             if (MODE == 0) o = act_apply(ACT, acc[r] + (a.aux ? (double)a.aux[row[r]] : 0.0), a.cap);
             else o = act_backprop(a.act, acc[r], xp[r], a.cap);
-            if (live) a.out[(size_t)row[r] * ld + s] = o;
+            if (live) a.out[(size_t)row[r] * ld + s] = s < B - a.n_pad ? o : 0.0f;
         }
     }
 }
@@ -1252,7 +1256,7 @@ __device__ __forceinline__ void spmm_row_grad(RowMeta m, const GradArgs &a, int 
             wave_lds_sync(); // the next group's rows are parked over the ones just read
         }
     }
-    if (a.store_out && live) a.out[(size_t)m.row * ld + s] = act_backprop(a.act, acc, xp, a.cap);
+    if (a.store_out && live) a.out[(size_t)m.row * ld + s] = s < B - a.n_pad ? act_backprop(a.act, acc, xp, a.cap) : 0.0f;
 }
 template <int U>
 __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_grad(const GradArgs a)
@@ -2226,8 +2230,9 @@ struct Plan {
     size_t table = 0, x0 = 0, ping = 0, pong = 0, alive = 0, flags[2] = {0, 0}, map[2] = {0, 0}, n_live[2] = {0, 0}, total = 0;
 };
 
-// Samples that the kernels of a training net work on for a batch of B: whole groups of four (the samples past B have a
-// zero input and no loss: their deltas are zero and they add exact zeros to every gradient).
+// Samples that the kernels of a training net work on for a batch of B: whole groups of four.  The samples past B are zero
+// in every X_l and Delta_l (the kernels store zeros for them: what a zero input turns into on its way may be infinite), so
+// that they add exact zeros to every gradient.
 static int padded_batch(int B) { return B == 1 ? 1 : (B + 3) & ~3; }
 // Floats per row of the library's own activation and delta arrays: 16-byte pieces stay aligned, a row touches as few
 // 128-byte lines as it can.
@@ -3061,11 +3066,11 @@ static const void *rows_fn(int G, int act)
 
 // in / out: rows of ld_in / ld_out floats.  sub_begin .. sub_end: the launch covers these samples only (sub_begin a
 // multiple of SUB_ALIGN, or of 64 where every layer takes the panel sweep for all but the narrowest blocks; sub_end == 0: all
-// of them).
+// of them).  n_pad: see SpmmArgs.
 template <int MODE>
 static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld_in, float *out, int ld_out,
                        const float *aux, int B, hipStream_t stream, const int32_t *n_live = nullptr, int32_t *flags = nullptr,
-                       int sub_begin = 0, int sub_end = 0)
+                       int sub_begin = 0, int sub_end = 0, int n_pad = 0)
 {
     if (sub_end == 0) sub_end = B;
     SpmmArgs a;
@@ -3079,7 +3084,7 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
         a.n_rows = d.n_in;
     }
     a.vals = d.vals; a.in = in; a.out = out; a.aux = aux; a.B = B; a.ld_in = ld_in; a.ld_out = ld_out;
-    a.cap = net->cfg.act_cap; a.act = net->cfg.activation;
+    a.cap = net->cfg.act_cap; a.act = (int16_t)net->cfg.activation; a.n_pad = (int16_t)n_pad;
     if (a.n_rows == 0) return SDNN_OK;
     const int n_cols = MODE == 0 ? d.n_in : d.n_out;
     a.n_cols = n_cols;
@@ -3362,7 +3367,8 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
         const LayerDev &d = net->layers[l];
         float *out = training ? d.X : (l == L - 1 ? d_XL : ((l & 1) ? pong : ping));
         const int ld_out = !training && l == L - 1 ? B : ld;
-        const int rc = launch_spmm<0>(net, d, in, ld_in, out, ld_out, d.bias, training ? Bp : B, stream);
+        const int rc = training ? launch_spmm<0>(net, d, in, ld_in, out, ld_out, d.bias, Bp, stream, nullptr, nullptr, 0, 0, Bp - B)
+                                : launch_spmm<0>(net, d, in, ld_in, out, ld_out, d.bias, B, stream);
         if (rc) return rc;
         in = out;
         ld_in = ld_out;
@@ -3548,11 +3554,11 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
     GradArgs a;
     a.row_ptr = d.t_row_ptr; a.idx = d.t_row_idx; a.perm = nullptr; a.sched = d.t_sched; a.n_rows = d.n_in;
     a.vals = d.vals_t; a.in = d.D; a.out = out; a.aux = d.X_prev; a.B = B; a.ld_in = a.ld_out = net->ld; a.cap = net->cfg.act_cap;
-    a.act = net->cfg.activation; a.n_live = nullptr; a.flags = nullptr;
+    a.act = (int16_t)net->cfg.activation; a.n_pad = (int16_t)(net->Bp - net->B); a.n_live = nullptr; a.flags = nullptr;
     a.g_part[0] = d.G[0]; a.g_part[1] = d.G[1]; a.store_out = store_out;
     if (a.n_rows == 0 || d.nnz == 0) {
         if (d.nnz == 0 && store_out && a.n_rows > 0) // no entries: Delta_{l-1} = 0, nothing to differentiate
-            return launch_spmm<1>(net, d, d.D, net->ld, out, net->ld, d.X_prev, B, stream);
+            return launch_spmm<1>(net, d, d.D, net->ld, out, net->ld, d.X_prev, B, stream, nullptr, nullptr, 0, 0, a.n_pad);
         return SDNN_OK;
     }
     a.n_cols = d.n_out;
@@ -3636,7 +3642,7 @@ extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)
         // Delta_{l} (0-based l-1) = (W^T Delta_{l+1}) masked by X_{l}
         float *dprev = l >= 1 ? net->layers[l - 1].D : nullptr;
         const int rc = gp ? launch_bwd_grad(net, d, dprev, stream, l >= 1)
-                          : launch_spmm<1>(net, d, d.D, net->ld, dprev, net->ld, d.X_prev, B, stream);
+                          : launch_spmm<1>(net, d, d.D, net->ld, dprev, net->ld, d.X_prev, B, stream, nullptr, nullptr, 0, 0, B - net->B);
         if (rc) return rc;
     }
     net->state = ST_BACKWARD;

@@ -84,3 +84,38 @@ def test_backward(b):
     assert np.isfinite(deltas[0]).all()
     assert np.array_equal(deltas[0][~touched], deltas[1][~touched])
     assert not np.isfinite(deltas[1][touched]).any()
+
+
+def _hot_and_cold(n, degree, n_layers):
+    """The first half of the neurons is exactly zero for inputs of 1 and grows without bound for inputs of 0; the other half
+    stays alive.  A row's links lie in its own half."""
+    half = n // 2
+    cols = np.sort((np.arange(half)[:, None] + np.arange(degree)) % half, axis=1)
+    cols = np.concatenate([cols, cols + half]).astype(np.int32).ravel()
+    row_ptr = np.arange(0, n * degree + 1, degree, dtype=np.int32)
+    layers = []
+    for l in range(n_layers):
+        vals = np.full((n, degree), 0.9 / degree, np.float32)
+        vals[:half] = -1.0 / degree if l == 0 else 10.0
+        bias = np.zeros(n, np.float32)
+        bias[:half] = l == 0
+        layers.append(wl.Layer(n, n, row_ptr, cols, vals.ravel(), bias))
+    return layers
+
+
+@pytest.mark.parametrize("n,degree,b,fuse", [(64, 1, 3, 1), (64, 1, 3, -1), (256, 128, 3, -1), (256, 128, 67, 1), (256, 128, 130, -1),
+                                             (2050, 1, 67, -1), (7000, 1, 3, 1), (7000, 1, 67, 1), (7000, 1, 130, -1),
+                                             (33000, 1, 43, -1), (33000, 1, 43, 1)])
+def test_samples_that_fill_up_a_batch_add_nothing(n, degree, b, fuse):
+    """Batches that are no multiple of four on an uncapped ReLU: a sample with zero input would reach infinity, and infinity
+    times its zero delta is NaN.  One case per kernel that forms gradients or stores activations."""
+    layers = _hot_and_cold(n, degree, 42 if degree == 1 else 15)
+    x = np.ones((n, b), np.float32)
+    x[n // 2:] = np.abs(wl.normal_inputs(9520, n - n // 2, b)) + 0.1
+    work = wl.Workload("fill", layers, np.inf, x, b, "mse", 0.05, targets=wl.uniform_targets(9521, n, b), activation="relu")
+    with np.errstate(over="ignore"):
+        zero_input = P.O32.forward(layers, np.zeros((n, 1), np.float32), np.inf)[-1]
+    assert np.isinf(zero_input[:n // 2]).all()
+    g = P.gpu_train_step(work, x, fuse_gradient=fuse)
+    st = P.compare_step(g, P.oracle_train_step(work, x), f"n={n} b={b} fuse={fuse}")
+    assert st["live_g"] == st["live_d"] == len(layers) and st["bitexact_d"] == len(layers)
