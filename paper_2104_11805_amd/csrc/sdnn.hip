@@ -3427,6 +3427,12 @@ extern "C" int sdnn_forward_noalloc(sdnn_net *net, const float *d_X0, int32_t B,
 }
 
 
+// Whether a block of n_a rows of B floats at a and one of n_b rows at b share memory.
+static bool overlap(const float *a, int n_a, const float *b, int n_b, int B)
+{
+    const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+    return pa < pb + 4 * (size_t)n_b * B && pb < pa + 4 * (size_t)n_a * B;
+}
 
 // The pass in stretches of layers with the activations in LDS: after 1, 3, 7, 15, ... times check_every layers and at the last
 // check the samples that are left are counted and their columns listed; the next stretch reads those columns and gives each
@@ -3448,8 +3454,9 @@ static int skip_dead_lds(sdnn_net *net, const float *d_X0, int B, float *d_XL, i
     int32_t *alive = net->d_alive;
     hipLaunchKernelGGL(k_live_columns, dim3(1), dim3(1024), 0, stream, (const int32_t *)nullptr, (const int32_t *)nullptr,
                        (const int32_t *)nullptr, B, net->d_n_live[0], net->d_flags[0], net->d_map[0]);
-    hipLaunchKernelGGL(k_fill_f32, dim3(ew_blocks((size_t)n_last * B)), dim3(256), 0, stream, d_XL, (size_t)n_last * B, 0.0f);
     HIP_TRY(net, hipGetLastError());
+    // d_XL may share memory with d_X0: it is written once d_X0 has been read, by a pass of one stretch through a buffer
+    const bool staged = last_check == 0 && overlap(d_X0, net->layers[0].n_in, d_XL, n_last, B);
     const float *in = d_X0;
     int ld_in = B, k = 0, step = check_every;
     for (int l0 = 0; l0 < L; ++k) {
@@ -3459,7 +3466,9 @@ static int skip_dead_lds(sdnn_net *net, const float *d_X0, int B, float *d_XL, i
             l1 = std::min(last_check, l0 + step);
             step = (int)std::min<int64_t>(2 * (int64_t)step, 1 << 30) / check_every * check_every;
         }
-        float *out = last ? d_XL : (k & 1) ? net->d_pong : net->d_ping;
+        float *out = last && !staged ? d_XL : (k & 1) ? net->d_pong : net->d_ping;
+        if (last && k > 0) // the samples that have died (a pass of one stretch stores every column)
+            hipLaunchKernelGGL(k_fill_f32, dim3(ew_blocks((size_t)n_last * B)), dim3(256), 0, stream, d_XL, (size_t)n_last * B, 0.0f);
         LdsForward a = lds_args(net, l0, l1, in, ld_in, out, last ? B : ld, B);
         a.n_live = net->d_n_live[k & 1];
         a.src_col = net->d_flags[k & 1];
@@ -3470,6 +3479,7 @@ static int skip_dead_lds(sdnn_net *net, const float *d_X0, int B, float *d_XL, i
             hipLaunchKernelGGL(k_live_columns, dim3(1), dim3(1024), 0, stream, (const int32_t *)alive, net->d_n_live[k & 1], net->d_map[k & 1],
                                B, net->d_n_live[(k + 1) & 1], net->d_flags[(k + 1) & 1], net->d_map[(k + 1) & 1]);
         HIP_TRY(net, hipGetLastError());
+        if (staged) HIP_TRY(net, hipMemcpyAsync(d_XL, out, 4 * (size_t)n_last * B, hipMemcpyDeviceToDevice, stream));
         if (last && d_n_live) HIP_TRY(net, hipMemcpyAsync(d_n_live, net->d_n_live[k & 1], 4, hipMemcpyDeviceToDevice, stream));
         in = out;
         ld_in = ld;

@@ -163,3 +163,21 @@ def test_skip_dead_in_stretches_with_the_activations_in_lds(b, every):
     net.sdnn_forward_skip_dead(torch.zeros_like(P.dev(work.x_infer)), out, check_every=every, n_live=n_live)
     assert not out.any() and int(n_live.item()) == 0
     net.close()
+
+
+@pytest.mark.parametrize("every", [2, 100])
+@pytest.mark.parametrize("shift", [0, 1, 700 * 3 + 5, -(700 * 2 + 8)])
+@pytest.mark.parametrize("lds", [sdnn.SDNN_LDS_ON, sdnn.SDNN_LDS_OFF])
+def test_skip_dead_in_place(every, shift, lds):
+    """The result over the input, or shifted against it by some floats: in several stretches and in one."""
+    work = _mixed_config1(700, n_layers=5)
+    ref = P.O32.forward(work.layers, work.x_infer, work.act_cap)[-1]
+    assert (ref != 0).any() and not (ref != 0).any(axis=0).all()
+    net = sdnn.Net(work.layers, work.act_cap, 700, training=False, lds_forward=lds)
+    n = work.x_infer.size
+    room = torch.full((n + 2 * 4096,), 7.0, device=P.DEV)
+    x, out = room[4096:4096 + n].view(-1, 700), room[4096 + shift:4096 + shift + n].view(-1, 700)
+    x.copy_(P.dev(work.x_infer))
+    net.sdnn_forward_skip_dead(x, out, check_every=every)
+    assert np.array_equal(P.host(out), ref)
+    net.close()
