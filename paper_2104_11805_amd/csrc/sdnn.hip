@@ -3256,6 +3256,13 @@ static LdsForward lds_args(const sdnn_net *net, int l0, int l1, const float *in,
     return a;
 }
 
+// Whether a block of n_a rows of B floats at a and one of n_b rows at b share memory.
+static bool overlap(const float *a, int n_a, const float *b, int n_b, int B)
+{
+    const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+    return pa < pb + 4 * (size_t)n_b * B && pb < pa + 4 * (size_t)n_a * B;
+}
+
 // Eq. 3 for l = 1..L.  Inference nets stage the activations between the layers in ping / pong
 // (each at least 4 * max_n * B bytes); training nets keep every X_l in the workspace and ignore them.
 // Width in samples of the sub-blocks that an inference pass is cut into, 0 = one piece.  A sub-block's share of an
@@ -3290,7 +3297,9 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
     hipStream_t stream = (hipStream_t)stream_;
     net->state = ST_IDLE;
     const int L = net->n_layers;
-    if (const int T = lds_forward_samples(net, B)) {
+    // a workgroup reads and writes columns of its own: d_XL may be d_X0 itself, but not lie across it
+    const bool shifted = d_XL && d_XL != d_X0 && overlap(d_X0, net->layers[0].n_in, d_XL, net->layers[L - 1].n_out, B);
+    if (const int T = shifted ? 0 : lds_forward_samples(net, B)) {
         const bool sig = net->cfg.activation == ACT_SIGMOID;
         const int ti = T == 1 ? 0 : T == 2 ? 1 : 2;
         static const void *const fns[2][3] = {
@@ -3426,13 +3435,6 @@ extern "C" int sdnn_forward_noalloc(sdnn_net *net, const float *d_X0, int32_t B,
     return forward_impl(net, d_X0, B, d_XL, stream_, (float *)base, (float *)((char *)base + half), ld);
 }
 
-
-// Whether a block of n_a rows of B floats at a and one of n_b rows at b share memory.
-static bool overlap(const float *a, int n_a, const float *b, int n_b, int B)
-{
-    const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
-    return pa < pb + 4 * (size_t)n_b * B && pb < pa + 4 * (size_t)n_a * B;
-}
 
 // The pass in stretches of layers with the activations in LDS: after 1, 3, 7, 15, ... times check_every layers and at the last
 // check the samples that are left are counted and their columns listed; the next stretch reads those columns and gives each

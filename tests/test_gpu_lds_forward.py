@@ -47,3 +47,18 @@ def test_lds_forward_samples_per_workgroup(b):
     net.sdnn_forward(P.dev(x), out)
     assert np.array_equal(P.host(out), ref)
     net.close()
+
+
+@pytest.mark.parametrize("shift", [0, 1, -5, 600 * 3 + 2, -(600 * 2 + 1)])
+def test_lds_forward_over_its_input(shift):
+    """The result over the input, or shifted against it by some floats, as the per-layer launches take it."""
+    layers = [_ragged(9200 + l, 5000, 5000, (3, 20, 34)) for l in range(2)]
+    x = wl.normal_inputs(9210, 5000, 600)
+    ref = P.O32.forward(layers, x, 1.5)[-1]
+    net = sdnn.Net(layers, 1.5, 600, training=False, lds_forward=sdnn.SDNN_LDS_ON)
+    room = torch.empty(x.size + 2 * 4096, device=P.DEV)
+    x0, out = room[4096:4096 + x.size].view(-1, 600), room[4096 + shift:4096 + shift + x.size].view(-1, 600)
+    x0.copy_(P.dev(x))
+    net.sdnn_forward(x0, out)
+    assert np.array_equal(P.host(out), ref)
+    net.close()

@@ -17,3 +17,13 @@ def test_last_narrow_block_of_a_wide_net(links):
             if 0 < B % 64 <= 40:
                 assert log[-1].startswith("k_spmm<") and B // 64 * 64 % (64 * int(log[-1][7])) == 0, (B, log)
     """)
+
+
+def test_result_across_the_input():
+    """A result that overlaps the input without being the same block: a launch per layer, which has read the input by then."""
+    routes.run("""
+        net = Net([layer(5000, 5000, (8,))] * 3, 2000, lds_forward=1)
+        for shift, lds in [(0, True), (4, False), (-4, False), (4 * 5000 * 2000 - 4, False), (4 * 5000 * 2000, True), (-4 * 5000 * 2000, True)]:
+            rc, log = net("sdnn_forward", X0, 2000, X0 + shift, None)
+            assert rc == 0 and (len(log) == 1 and log[0].startswith("k_fwd_lds")) == lds, (shift, log)
+    """)
