@@ -569,12 +569,6 @@ template <int G> __device__ __forceinline__ void reduce4(double (&p)[4], int lan
     if constexpr (G >= 8) p[0] += lane_exchange<0>(p[0]);
 }
 template <int G> __device__ __forceinline__ int reduced_index(int lane) { return (lane / (G / 4)) & 3; }
-// The sum of a float over two neighbouring groups of 16 lanes, in all of them.
-__device__ __forceinline__ float add_neighbour16(float g)
-{
-    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(g), __float_as_uint(g), false, false);
-    return (float)((double)__uint_as_float(t[0]) + (double)__uint_as_float(t[1]));
-}
 
 // The backward sweep that also forms the gradient of the stored entries, in the manner of k_rows.  The lanes of row i of
 // W_l^T hold X_{l-1}(i, :), four samples each, gather Delta_l(j, :) for every entry (j, i) and sum its products with
@@ -585,12 +579,9 @@ __device__ __forceinline__ float add_neighbour16(float g)
 // bytes.  Backward and gradient, us per layer: 65536 neurons 80 -> 69.7 (64 samples), 70.6 -> 29.1 (16); 16384 neurons 21.1 ->
 // 14.4 (64), 31.8 -> 25.3 (128; two launches on two streams before); 10007 neurons, 99 samples 32.5 (two
 // separate kernels) -> 17.6 + 3; 8192 neurons of 820 entries 420 -> 331 (256 samples), 410 -> 127 (64).
-// TWO (G = 32, 128 samples): the gradient is the sum of two windows of 64 samples, each rounded to fp32 (what two launches
-// of 64 samples leave in two partial gradients).
-template <int G, bool TWO>
+template <int G>
 __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const GradArgs a)
 {
-    static_assert(!TWO || G == 32, "two windows of 16 lanes");
     constexpr int R = 64 / G;
     const int lane = threadIdx.x & 63;
     const unsigned tile = blockIdx.x / a.n_rg, rg = blockIdx.x - tile * a.n_rg;
@@ -613,8 +604,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const GradArgs a)
     double xd[4], acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int v = 0; v < 4; ++v) xd[v] = (double)xp[v];
-    constexpr int SUM = TWO ? 16 : G; // lanes of a window
-    int e0 = t.y + reduced_index<SUM>(lane); // the entry whose gradient this lane stores
+    int e0 = t.y + reduced_index<G>(lane); // the entry whose gradient this lane stores
     float4 x0[4], x1[4];
     int w0[4], w1[4];
     auto consume = [&](const float4 (&x)[4], const int (&wv)[4]) {
@@ -632,10 +622,8 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const GradArgs a)
         // added here: the compiler would move these sums past the branches below and keep every converted operand until
         // then (214 registers instead of 120)
         asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
-        reduce4<SUM>(pr, lane);
-        float g = (float)pr[0];
-        if (TWO) g = add_neighbour16(g);
-        if ((lane & (SUM / 4 - 1)) == 0 && !(TWO && (lane & 16)) && e0 < end) g_part[e0] = g;
+        reduce4<G>(pr, lane);
+        if ((lane & (G / 4 - 1)) == 0 && e0 < end) g_part[e0] = (float)pr[0];
         e0 += 4;
     };
     quad_gather<0>(q, rin, ldb, so, x0, w0);
@@ -3549,10 +3537,14 @@ extern "C" int sdnn_forward_skip_dead(sdnn_net *net, const float *d_X0, int32_t 
     return SDNN_OK;
 }
 
-// Batches of 128 on nets of short rows and up to 16384 neurons sum the gradient over two windows of 64 samples.
-static bool two_windows(const sdnn_net *net, int B)
+// Two whole tiles of 64 samples whose operand together is larger than L2: the sweep takes them as two tiles, each with a
+// partial gradient of its own, rounded to fp32 (16384 neurons of 32 entries: 27.5 -> 25.3 us per layer; 4096 neurons, where
+// the operand fits: 10.2 in two tiles, 8.9 in one).  The batches around it (filled up to 128 samples or not) keep one sum over all of
+// their samples in fp64, rounded once.
+static bool two_tiles(const sdnn_net *net)
 {
-    if (B != 128 || (int64_t)net->max_n * B > ((int64_t)1 << 21)) return false;
+    const int64_t bytes = 4 * (int64_t)net->max_n * 128;
+    if (net->B != 128 || bytes <= 6500000 || bytes > ((int64_t)1 << 23)) return false;
     int64_t nnz = 0, rows = 0;
     for (const LayerDev &d : net->layers) { nnz += d.nnz; rows += d.n_out; }
     return nnz < 128 * rows;
@@ -3594,17 +3586,13 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;
     }
-    // two windows: as two tiles (and two partial gradients) where the operand is larger than L2 (16384 neurons: 27.5 -> 25.3
-    // us per layer), else in one (4096 neurons: 10.2 -> 8.9)
-    const bool two = two_windows(net, B);
     int G = lanes_per_row(net->grad_parts == 2 ? 64 : B);
-    if (!two) G = spread_lanes(net, G, a.n_rows);
+    if (net->grad_parts == 1) G = spread_lanes(net, G, a.n_rows);
     const int rows_per_block = 64 / G * WAVES_PER_BLOCK;
     a.n_tiles = (uint32_t)net->grad_parts;
     a.n_rg = (uint32_t)((a.n_rows + rows_per_block - 1) / rows_per_block);
-    const void *fn = G == 4 ? (const void *)k_bwd_rows<4, false> : G == 8 ? (const void *)k_bwd_rows<8, false>
-                     : G == 16 ? (const void *)k_bwd_rows<16, false> : G == 64 ? (const void *)k_bwd_rows<64, false>
-                     : two ? (const void *)k_bwd_rows<32, true> : (const void *)k_bwd_rows<32, false>;
+    const void *fn = G == 4 ? (const void *)k_bwd_rows<4> : G == 8 ? (const void *)k_bwd_rows<8> : G == 16 ? (const void *)k_bwd_rows<16>
+                     : G == 32 ? (const void *)k_bwd_rows<32> : (const void *)k_bwd_rows<64>;
     HIP_TRY(net, hipLaunchKernel(fn, dim3(a.n_tiles * a.n_rg), dim3(BLOCK_THREADS), args, 0, stream));
     HIP_TRY(net, hipGetLastError());
     return SDNN_OK;
@@ -3617,7 +3605,7 @@ static int grad_fusable(const sdnn_net *net, int B)
     if (B > 256) return 0;
     for (const LayerDev &d : net->layers)
         if (B > 64 && !rows_addressable(d.n_out, net->ld)) return 0;
-    return two_windows(net, B) && 4 * (int64_t)net->max_n * B > 6500000 ? 2 : 1;
+    return two_tiles(net) ? 2 : 1;
 }
 
 extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)

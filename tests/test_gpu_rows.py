@@ -46,9 +46,31 @@ def test_separate_update_and_sigmoid(b, fuse, activation):
 
 @pytest.mark.parametrize("n_in,n_mid,b", [(9001, 2500, 128), (17003, 6500, 256), (17003, 6500, 130)])
 def test_tiles_of_samples_on_operands_larger_than_l2(n_in, n_mid, b):
-    """Forward tiles of 64 and 32 samples (operands of 4.6 and 17 MB), backward in halves of 128 samples."""
+    """Forward tiles of 64 and 32 samples (operands of 4.6 and 17 MB), backward over operands of 2 to 8 MB."""
     layers = [_layer(9340, n_mid, n_in, (4, 20)), _layer(9341, 8001, n_mid, (3, 6)), _layer(9342, 33, 8001, (200, 17))]
     _step(layers, b, 9350, fuse=1)
+
+
+@pytest.mark.parametrize("b", [124, 125, 126, 127, 128, 129])
+def test_gradient_is_rounded_once(b):
+    """Samples 64 and up cancel the first 64 but for one part in 2^20: a sum over all samples in fp64, rounded once, is within
+    half a unit in the last place (2^-24) of the exact one, plus 2^-53 per term; rounded halves are off by about 2^-24 * 2^20."""
+    import torch
+    from paper_2104_11805_amd import sdnn
+    lay = _layer(9390, 2113, 250, (2, 9, 16, 40))
+    lay.values[:], lay.bias[:] = 0.0, 1.0          # every neuron is active: Delta is the loss gradient
+    x, d = wl.normal_inputs(9391, 250, 64), wl.normal_inputs(9392, 2113, 64)
+    x = np.concatenate([x, x, x], axis=1)[:, :b].copy()
+    d = np.concatenate([d, (-d * (1 + 2.0 ** -20)).astype(np.float32), d], axis=1)[:, :b].copy()
+    net = sdnn.Net([lay], float("inf"), b, training=True, fuse_gradient=1)
+    net.sdnn_forward(P.dev(x), torch.empty(2113, b, device=P.DEV))
+    net.sdnn_backward(P.dev(d))
+    got = P.host(net.sdnn_weight_grad(1)[0]).astype(np.float64)
+    rows = np.repeat(np.arange(2113), np.diff(lay.row_ptr))
+    terms = d[rows].astype(np.float64) * x[lay.col_idx].astype(np.float64)
+    ref = terms.sum(axis=1)
+    assert (np.abs(got - ref) <= 2.0 ** -24 * np.abs(ref) + 2 * b * 2.0 ** -53 * np.abs(terms).sum(axis=1)).all()
+    net.close()
 
 
 def test_a_smaller_batch_after_a_larger_one():

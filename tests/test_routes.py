@@ -27,3 +27,16 @@ def test_result_across_the_input():
             rc, log = net("sdnn_forward", X0, 2000, X0 + shift, None)
             assert rc == 0 and (len(log) == 1 and log[0].startswith("k_fwd_lds")) == lds, (shift, log)
     """)
+
+
+def test_gradient_over_two_tiles_of_samples():
+    """Two partial gradients only where the batch itself is 128 samples and the operand lies between 6.5 and 8.4 MB: not for
+    the batches that are filled up to 128."""
+    routes.run("""
+        for n, B, G, tiles in [(12695, 128, 32, 1), (12696, 128, 16, 2), (16384, 128, 16, 2), (16385, 128, 32, 1), (16384, 124, 32, 1),
+                               (16384, 125, 32, 1), (16384, 127, 32, 1), (16384, 129, 64, 1), (4096, 128, 32, 1)]:
+            net = Net([layer(n, n, (32,))], 300, training=True)
+            assert net("sdnn_forward", X0, B, XL, None)[0] == 0
+            rc, log = net("sdnn_backward", DL, None)
+            assert rc == 0 and log[-1] == f"k_bwd_rows<{G}> {tiles * -(-n // (256 // G))} 1 1", (n, B, log)
+    """)
