@@ -3618,13 +3618,19 @@ extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)
     hipStream_t stream = (hipStream_t)stream_;
     const int L = net->n_layers, B = net->Bp;
     const LayerDev &last = net->layers[L - 1];
+    const int gp = grad_fusable(net, B);
+    for (int l = gp ? 0 : 1; l < L; ++l) { // the operands of the products below: refused before anything is launched
+        const LayerDev &d = net->layers[l];
+        const size_t bytes = 4 * (size_t)d.n_out * (size_t)net->ld;
+        if (d.n_in > 0 && (l > 0 || d.nnz > 0) && bytes >= ((size_t)1 << 32))
+            return fail(net, SDNN_EINVAL, "activation block of %zu bytes exceeds 4 GiB: use a smaller B", bytes);
+    }
     if (last.n_out > 0) {
         const int w = row_threads_log2(B);
         hipLaunchKernelGGL(k_output_delta, dim3(row_blocks(last.n_out, w)), dim3(256), 0, stream, d_dLoss, last.X, last.D, last.n_out,
                            net->B, net->ld, B, w, net->cfg.act_cap, net->cfg.activation);
         HIP_TRY(net, hipGetLastError());
     }
-    const int gp = grad_fusable(net, B);
     net->grad_parts = gp;
     if (gp && net->vals_t_stale) { // the CSR values were replaced or stepped by the separate update since the last sweep
         int max_nnz = 0;

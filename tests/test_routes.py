@@ -40,3 +40,19 @@ def test_gradient_over_two_tiles_of_samples():
             rc, log = net("sdnn_backward", DL, None)
             assert rc == 0 and log[-1] == f"k_bwd_rows<{G}> {tiles * -(-n // (256 // G))} 1 1", (n, B, log)
     """)
+
+
+def test_backward_refuses_an_operand_of_4_gib():
+    """The last layer's own block is an operand of the sweep that forms the gradient (and of back-propagation, where there is a
+    layer below): byte offsets into it are 32 bits.  Nothing is launched."""
+    routes.run("""
+        n = 17000000                                   # x 64 samples x 4 bytes: just over 4 GiB
+        wide = layer(n, 8, (1, 0, 0, 0))
+        for layers, fuse, refused in [([wide], 1, True), ([wide], -1, False), ([layer(8, 4, (2,)), wide], -1, True)]:
+            net = Net(layers, 64, training=True, fuse_gradient=fuse)
+            assert net("sdnn_forward", X0, 64, XL, None)[0] == 0, sdnn.last_error(net.h)
+            rc, log = net("sdnn_backward", DL, None)
+            assert (rc, log) == (sdnn.SDNN_EINVAL, []) if refused else (rc == 0 and log), (rc, log)
+            assert not refused or "4 GiB" in sdnn.last_error(net.h)
+            lib.sdnn_destroy(net.h)
+    """)
