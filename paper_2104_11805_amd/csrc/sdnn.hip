@@ -2231,6 +2231,14 @@ static int row_stride(int B)
         if (B <= w) return w;
     return (B + 31) & ~31;
 }
+// The same on a net whose widest layer has max_n neurons: where the filled-up rows would make a block of 4 GiB or more, which
+// the products refuse, rows of whole groups of four samples, or else of B floats (kernels without wide loads).
+static int row_pitch(int64_t max_n, int B)
+{
+    for (const int w : {row_stride(B), padded_batch(B)})
+        if (4 * max_n * w < ((int64_t)1 << 32)) return w;
+    return B;
+}
 
 static int check_config(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg)
 {
@@ -2435,7 +2443,6 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
     };
     pl.pl.resize(n_layers);
     pl.table = take(sizeof(LayerDev) * (size_t)n_layers);
-    const size_t mb = (size_t)cfg->max_batch, mld = (size_t)row_stride(cfg->max_batch);
     const bool gw = grad_buffers_wanted(layers, n_layers, cfg);
     const bool lm = lds_forward_wanted(layers, n_layers, cfg);
     size_t max_n = 0, max_pos = 0;
@@ -2464,6 +2471,7 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
         }
         max_n = std::max(max_n, (size_t)std::max(y.n_out, y.n_in));
     }
+    const size_t mb = (size_t)cfg->max_batch, mld = (size_t)row_pitch((int64_t)max_n, cfg->max_batch);
     plan_b1(layers, n_layers, cfg, pl);
     const bool b1 = pl.b1_chunk_bytes != 0;
 #define PLAN_KIND(field, bytes_expr)                                   \
@@ -3331,7 +3339,7 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
     }
     const float *in = d_X0;
     int ld_in = B;
-    const int Bp = padded_batch(B);
+    const int Bp = ld < padded_batch(B) ? B : padded_batch(B);
     if (training) {
         const int rc = launch_copy_rows(net, d_X0, B, net->d_x0, ld, net->layers[0].n_in, B, Bp, stream);
         if (rc) return rc;
@@ -3395,7 +3403,7 @@ extern "C" int sdnn_forward(sdnn_net *net, const float *d_X0, int32_t B, float *
 {
     const int rc = check_forward_args(net, d_X0, B, d_XL);
     if (rc) return rc;
-    return forward_impl(net, d_X0, B, d_XL, stream_, net->d_ping, net->d_pong, row_stride(B));
+    return forward_impl(net, d_X0, B, d_XL, stream_, net->d_ping, net->d_pong, row_pitch(net->max_n, B));
 }
 
 // ---------------------------------------------------------------------------
@@ -3429,7 +3437,7 @@ extern "C" int sdnn_forward_noalloc(sdnn_net *net, const float *d_X0, int32_t B,
 // workgroup as few of them as fill the chip.  Nothing waits for the host: workgroups past the live samples end at once.
 static int skip_dead_lds(sdnn_net *net, const float *d_X0, int B, float *d_XL, int check_every, int32_t *d_n_live, hipStream_t stream)
 {
-    const int L = net->n_layers, n_last = net->layers[L - 1].n_out, ld = row_stride(B);
+    const int L = net->n_layers, n_last = net->layers[L - 1].n_out, ld = row_pitch(net->max_n, B);
     const int last_check = (L - 1) / check_every * check_every;
     int t_max = 4;
     while (t_max > 1 && t_max * net->lm_max_pos > LDS_MAX_FLOATS) t_max /= 2;
@@ -3550,6 +3558,9 @@ static bool two_tiles(const sdnn_net *net)
     return nnz < 128 * rows;
 }
 
+// Whether k_bwd_rows can take this layer's Delta: rows of whole 16-byte pieces, within its offsets.
+static bool wide_rows(const sdnn_net *net, const LayerDev &d) { return (net->ld & 3) == 0 && rows_addressable(d.n_out, net->ld); }
+
 // Fused back-propagation + entry gradient of one layer.  store_out = 0 for the first layer (gradient only: there is no
 // Delta_0, out may be NULL).
 static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStream_t stream, int store_out)
@@ -3572,7 +3583,7 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
     a.n_rg = (uint32_t)((a.n_rows + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK);
     a.n_vblocks = a.n_rg;
     void *args[] = {(void *)&a};
-    if (B <= 64 && ((a.n_rows <= 6144 && (int64_t)d.nnz < 128 * (int64_t)a.n_rows) || !rows_addressable(d.n_out, net->ld))) {
+    if (B <= 64 && ((a.n_rows <= 6144 && (int64_t)d.nnz < 128 * (int64_t)a.n_rows) || !wide_rows(net, d))) {
         // few short rows: a wavefront for each keeps more of the chip busy than several rows per wavefront (4096 rows, 64
         // samples: 7.3 vs 8.2 us; 6500 rows: 9.9 vs 9.0)
         const void *fn = (const void *)k_bwd_grad<8>;
@@ -3604,7 +3615,7 @@ static int grad_fusable(const sdnn_net *net, int B)
     if (net->layers[0].G[0] == nullptr || B == 1) return 0;
     if (B > 256) return 0;
     for (const LayerDev &d : net->layers)
-        if (B > 64 && !rows_addressable(d.n_out, net->ld)) return 0;
+        if (B > 64 && !wide_rows(net, d)) return 0;
     return two_tiles(net) ? 2 : 1;
 }
 
@@ -3688,8 +3699,12 @@ static int launch_update(sdnn_net *net, int layer0, int n_layers, float lr, int 
     for (int l0 = 0; l0 < n_layers; l0 += 65535) {
         const int nl = std::min(65535, n_layers - l0);
         dim3 grid(interleave ? 8u * n_rg : n_rg, (unsigned)(interleave ? (nl + 7) / 8 : nl));
-        // rows of Delta and X are whole 16-byte pieces; long rows: the row of Delta stays in registers
-        if (rpw == 1 && B <= 256)
+        // rows of Delta and X are whole 16-byte pieces, but for the blocks that row_pitch says; long rows: the row of Delta stays
+        // in registers
+        if (net->ld & 3)
+            hipLaunchKernelGGL((k_update<1, 0>), grid, dim3(64 * UPD_WAVES), 0, stream, net->d_layers,
+                               layer0 + l0, nl, interleave, rpw, B, net->ld, lr, net->cfg.update_bias, emit, g, gb);
+        else if (rpw == 1 && B <= 256)
             hipLaunchKernelGGL((k_update<4, 4>), grid, dim3(64 * UPD_WAVES), 0, stream, net->d_layers,
                                layer0 + l0, nl, interleave, rpw, B, net->ld, lr, net->cfg.update_bias, emit, g, gb);
         else

@@ -108,3 +108,52 @@ def test_last_narrow_block_on_a_narrow_last_layer(b):
     net.sdnn_forward(P.dev(x), out)
     assert np.array_equal(P.host(out), ref) and (ref > 0).any()
     net.close()
+
+
+@pytest.mark.parametrize("fuse", [-1, 1])
+def test_rows_that_are_not_filled_up(fuse):
+    """17e6 neurons x 63 samples: below 4 GiB only with rows of 63 floats (no wide loads).  The two narrow ends of the net make
+    the reference small: the middle neurons that the last layer reads, in fp64."""
+    import torch
+    from paper_2104_11805_amd import sdnn
+    n, b, lr = 17_000_000, 63, 0.5
+    rng = np.random.default_rng(9410)
+    rp = (np.arange(n + 1, dtype=np.int64) + 3) // 4                           # one entry in every fourth row
+    first = wl.Layer(n, 8, rp.astype(np.int32), rng.integers(0, 8, rp[-1]).astype(np.int32),
+                     rng.standard_normal(rp[-1]).astype(np.float32), np.full(n, 0.25, np.float32))
+    cols = np.sort(rng.choice(n, (8, 50), replace=False).astype(np.int32) // 4 * 4, axis=1)   # rows of the first layer with an entry
+    cols[:, -1] = n - 4
+    assert (np.diff(cols, axis=1) > 0).all()
+    last = wl.Layer(8, n, np.arange(0, 401, 50, dtype=np.int32), cols.ravel(), rng.standard_normal(400).astype(np.float32),
+                    np.full(8, 1.0, np.float32))
+    x, d = wl.normal_inputs(9411, 8, b), wl.normal_inputs(9412, 8, b)
+    # reference: the neurons `used` of the middle layer, whose entries are at used // 4
+    used, at = np.unique(cols, return_inverse=True)
+    w1, c1, w2, at = first.values[used // 4].astype(np.float64), first.col_idx[used // 4], last.values.astype(np.float64), at.ravel()
+    row2 = np.repeat(np.arange(8), 50)
+    x1 = np.minimum(np.maximum(w1[:, None] * x[c1] + 0.25, 0.0), 8.0).astype(np.float32)
+    x2 = np.ones((8, b))
+    np.add.at(x2, row2, w2[:, None] * x1[at])
+    x2 = np.minimum(np.maximum(x2, 0.0), 8.0).astype(np.float32)
+    d2 = np.where((x2 > 0) & (x2 < 8), d, np.float32(0.0))
+    back = np.zeros((used.size, b))
+    np.add.at(back, at, w2[:, None] * d2[row2])
+    d1 = np.where((x1 > 0) & (x1 < 8), back, 0.0).astype(np.float32)
+    g1 = (d1.astype(np.float64) * x[c1]).sum(axis=1)
+    g2 = (d2[row2].astype(np.float64) * x1[at]).sum(axis=1)
+    net = sdnn.Net([first, last], 8.0, b, training=True, fuse_gradient=fuse)
+    xl = torch.empty(8, b, device=P.DEV)
+    net.sdnn_forward(P.dev(x), xl)
+    P.assert_forward_close(P.host(xl), x2)
+    net.sdnn_backward(P.dev(d))
+    mid = torch.from_numpy(used.astype(np.int64)).to(P.DEV)
+    P.assert_forward_close(P.host(net.sdnn_get_activation(1, b)[mid]), x1)
+    P.assert_grad_close(P.host(net.sdnn_get_delta(1, b)[mid]), d1)
+    net.sdnn_sgd_step(lr)
+    v1, v2 = net.sdnn_get_weights(1)[0], P.host(net.sdnn_get_weights(2)[0])
+    P.assert_grad_close(P.host(v1[mid // 4]), (w1 - lr * g1).astype(np.float32))
+    rest = torch.ones(v1.numel(), dtype=torch.bool, device=P.DEV)
+    rest[mid // 4] = False                                                     # nobody reads those neurons: no gradient
+    assert torch.equal(v1[rest], P.dev(first.values)[rest])
+    P.assert_grad_close(v2, (w2 - lr * g2).astype(np.float32))
+    net.close()

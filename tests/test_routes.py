@@ -56,3 +56,27 @@ def test_backward_refuses_an_operand_of_4_gib():
             assert not refused or "4 GiB" in sdnn.last_error(net.h)
             lib.sdnn_destroy(net.h)
     """)
+
+
+@pytest.mark.parametrize("training", [False, True])
+@pytest.mark.parametrize("fuse", [-1, 1])
+def test_blocks_below_4_gib_are_taken_whatever_their_row_pitch(training, fuse):
+    """17e6 neurons: 63 samples fit 32-bit offsets, 64 do not; 33 would not with rows of 64 floats."""
+    routes.run(f"""
+        n = 17000000
+        layers = [layer(n, 8, (1, 0, 0, 0)), layer(8, n, (5, 40))]
+        for max_batch, batches in [(63, (33, 63, 2, 61, 50)), (33, (33, 32, 5)), (64, (64, 60))]:
+            net = Net(layers, max_batch, training={training}, fuse_gradient={fuse})
+            rows = n + 8 + ({training} and n + 8 + 8 or n)             # X_0, X_l, Delta_l or two activation buffers
+            assert net.bytes < 4 * rows * (max_batch + 3) + 300 * n, net.bytes
+            for B in batches:
+                rc, log = net("sdnn_forward", X0, B, XL, None)
+                assert rc == (sdnn.SDNN_EINVAL if B == 64 else 0), (B, sdnn.last_error(net.h))
+                if B == 64 or not {training}:
+                    continue
+                rc, log = net("sdnn_backward", DL, None)
+                assert rc == 0 and (B != 63 or not any("k_bwd_rows" in l for l in log)), (B, log)
+                rc, log = net("sdnn_sgd_step", C.c_float(0.1), None)
+                assert rc == 0 and ({fuse} == 1 or ("<1, 0>" in log[0]) == (B > 60)), (B, log)
+            lib.sdnn_destroy(net.h)
+    """)
