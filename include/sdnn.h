@@ -137,7 +137,8 @@ typedef struct {
 /* ---- setup (Algorithm 1's inputs {W^k}; the paper likewise precomputes its
  *      per-layer index maps once, outside the timed iterations) ------------- */
 
-/* Number of workspace bytes sdnn_create needs for these layers and config.  The library's own activation blocks have rows of
+/* Number of workspace bytes sdnn_create needs for these layers and config.  values, bias and col_idx may be NULL here (training
+ * nets of max_batch == 1: a bound without col_idx, the exact number with it).  The library's own activation blocks have rows of
  * whole 128-byte lines (4, 8, 16 or 32 floats up to 32 samples, multiples of 32 beyond), so that a batch just past such a
  * number takes up to twice its samples' bytes (33: 64 floats per row).  A block that a product reads must stay below 4 GiB
  * (SDNN_EINVAL otherwise): rows are filled up only as far as that allows, so the limit is 4 n B < 2^32. */

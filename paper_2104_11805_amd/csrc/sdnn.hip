@@ -2384,7 +2384,16 @@ static bool b1_chunks(const int32_t *len, int32_t n, size_t *chunks)
     }
     return true;
 }
-// Fills the plan's chunk counts; leaves b1_chunk_bytes 0 where the net does not take that layout.
+// At most as many chunks as b1_chunks counts for n rows of nnz entries together (none longer than B1_MAX_ROW, or it counts
+// none): the first block is no deeper than the longest row that there can be, and every later one no deeper than the mean
+// of the 64 rows before it.
+static size_t b1_chunks_bound(int32_t n, int64_t nnz, int32_t longest)
+{
+    const int64_t nb = ((int64_t)n + 63) / 64;
+    return (size_t)((std::min(longest, B1_MAX_ROW) + 7) / 8 + (nnz / 64 + 7 * nb) / 8 + 1);
+}
+// Fills the plan's chunk counts; leaves b1_chunk_bytes 0 where the net does not take that layout.  Without col_idx (only the
+// sizes are asked for): a bound.
 static void plan_b1(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, Plan &pl)
 {
     pl.b1_chunk_bytes = 0;
@@ -2393,7 +2402,6 @@ static void plan_b1(const sdnn_layer *layers, int32_t n_layers, const sdnn_confi
     for (int32_t l = 0; l < n_layers; ++l) {
         const sdnn_layer &y = layers[l];
         const int64_t nnz = y.row_ptr[y.n_out];
-        if (nnz > 0 && !y.col_idx) return;
         if (nnz > ((int64_t)1 << 28) || y.n_out > (1 << 24) || y.n_in > (1 << 24)) return; // a copy stays below 4 GiB
         if (nnz >= 128 * (int64_t)std::max(y.n_out, 1) || nnz >= 128 * (int64_t)std::max(y.n_in, 1)) return;
         wide |= y.n_out > 65536 || y.n_in > 65536;
@@ -2409,9 +2417,13 @@ static void plan_b1(const sdnn_layer *layers, int32_t n_layers, const sdnn_confi
             if (!b1_chunks(len.data(), y.n_out, &q.b1_chunks[0])) { fits = false; return; }
             std::fill(len.begin(), len.end(), 0);
             const int32_t nnz = y.row_ptr[y.n_out];
-            for (int32_t p = 0; p < nnz; ++p)
-                if ((uint32_t)y.col_idx[p] < (uint32_t)y.n_in) len[(size_t)y.col_idx[p]]++;
-            if (!b1_chunks(len.data(), y.n_in, &q.b1_chunks[1])) { fits = false; return; }
+            if (nnz > 0 && !y.col_idx) {
+                q.b1_chunks[1] = b1_chunks_bound(y.n_in, nnz, y.n_out);
+            } else {
+                for (int32_t p = 0; p < nnz; ++p)
+                    if ((uint32_t)y.col_idx[p] < (uint32_t)y.n_in) len[(size_t)y.col_idx[p]]++;
+                if (!b1_chunks(len.data(), y.n_in, &q.b1_chunks[1])) { fits = false; return; }
+            }
         } catch (...) {
             fits = false;
             return;

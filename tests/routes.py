@@ -32,14 +32,17 @@ class Net:
         self.keep = layers
         arr = (sdnn.sdnn_layer * len(layers))()
         for k, (n_out, n_in, rp, ci, va, bi) in enumerate(layers):
-            arr[k] = sdnn.sdnn_layer(n_out, n_in, rp.ctypes.data, ci.ctypes.data, va.ctypes.data, None if bi is None else bi.ctypes.data)
+            arr[k] = sdnn.sdnn_layer(n_out, n_in, rp.ctypes.data, ci.ctypes.data if col_idx else None, va.ctypes.data,
+                                     None if bi is None else bi.ctypes.data)
         self.arr = arr
         opt = dict(update_bias=1, activation=0, fuse_gradient=0, panel_cols=0, reorder_rows=0, lds_forward=0)
         opt.update(options)
         self.cfg = sdnn.sdnn_config(act_cap, max_batch, int(training), *opt.values())
         n = C.c_size_t()
         assert lib.sdnn_workspace_bytes(arr, len(layers), C.byref(self.cfg), C.byref(n)) == 0, sdnn.last_error()
-        self.bytes = n.value
+        self.bytes = n.value                          # col_idx=False: sized without the columns
+        for k, l in enumerate(layers):
+            arr[k].col_idx = l[3].ctypes.data
         self.h = C.c_void_p()
         rc = lib.sdnn_create(arr, len(layers), C.byref(self.cfg), C.c_void_p(ADDR), n, None, C.byref(self.h))
         assert rc == 0, sdnn.last_error()

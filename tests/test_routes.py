@@ -80,3 +80,18 @@ def test_blocks_below_4_gib_are_taken_whatever_their_row_pitch(training, fuse):
                 assert rc == 0 and ({fuse} == 1 or ("<1, 0>" in log[0]) == (B > 60)), (B, log)
             lib.sdnn_destroy(net.h)
     """)
+
+
+@pytest.mark.parametrize("n_out,n_in,lengths", [(64, 64, (64,)), (300, 300, (1, 0, 7)), (1000, 64, (33,)), (64, 1000, (9, 100)),
+                                                (700, 90, (88, 3, 16)), (5, 3, (0,)), (513, 2, (1,)), (3000, 70000, (40, 64)),
+                                                (70000, 3000, (2, 5))])
+def test_workspace_sized_without_the_columns(n_out, n_in, lengths):
+    """A net of one sample per step: what the sizes alone give is enough for sdnn_create, whatever the columns are (here as
+    uneven as the row lengths allow: every row starts at column 0)."""
+    routes.run(f"""
+        layers = [layer({n_out}, {n_in}, {lengths}), layer({n_in}, {n_out}, {lengths[:1]})]
+        for max_batch, training in [(1, True), (7, True), (1, False)]:
+            a, b = Net(layers, max_batch, training=training, col_idx=False), Net(layers, max_batch, training=training)
+            assert a.bytes >= b.bytes and (a.bytes == b.bytes or (max_batch, training) == (1, True)), (a.bytes, b.bytes)
+            assert a("sdnn_forward", X0, 1, XL, None) == b("sdnn_forward", X0, 1, XL, None)
+    """)
