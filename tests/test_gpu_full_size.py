@@ -61,7 +61,7 @@ def cfg3():
 
 
 def test_config3_full_size_training_step(cfg3):
-    """N=16384, all 480 layers, minibatch 128 (two half-batch launch chains, gradient formed in the backward sweep)."""
+    """N=16384, all 480 layers, minibatch 128 (two tiles of 64 samples in the backward sweep that forms the gradient)."""
     assert len(cfg3.layers) == 480 and cfg3.x_train.shape == (16384, 128) and cfg3.total_nnz == 251658240
     st = P.full_step_compare(cfg3, cfg3.x_train, "cfg3 full", log=_log)
     assert st["bitexact_x"] == 480 and st["bitexact_d"] == 480

@@ -62,6 +62,28 @@ def test_forward(mode, n_in, b, bad):
         assert np.isin(outs[1][touched & ~both], [0.0, 2.0]).all()
 
 
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_one_sample_with_a_launch_per_layer(bad):
+    """Inference with one sample where the single launch does not pay (tests/test_routes.py checks the kernel): both layers'
+    slots past the end of a row lie past the widest layer's positions, and the second layer's rows among them."""
+    layers = [_layer(9503, 30000, 2050), _layer(9504, 2113, 30000)]
+    x = wl.normal_inputs(9505, 2050, 1)
+    x_bad = x.copy()
+    x_bad[[0, -1], :] = bad
+    outs = []
+    for v in (x, x_bad):
+        net = sdnn.Net(layers, np.inf, 1, training=False)
+        out = torch.empty(2113, 1, device=P.DEV)
+        net.sdnn_forward(P.dev(v), out)
+        outs.append(P.host(out))
+        net.close()
+    assert np.array_equal(outs[0], P.O32.forward(layers, x, np.inf)[-1])
+    touched = _gathers(layers[1], np.flatnonzero(_gathers(layers[0], [0, 2049])))
+    assert touched.any() and not touched.all()
+    assert np.isfinite(outs[0]).all() and np.array_equal(outs[0][~touched], outs[1][~touched])
+    assert not np.isfinite(outs[1][touched]).all()
+
+
 @pytest.mark.parametrize("b", [1, 6, 70, 130, 200])
 def test_backward(b):
     layers = [_layer(9510, 7001, 300), _layer(9511, 2113, 7001)]

@@ -220,13 +220,13 @@ def test_paper_training_setup_one_vector_per_step():
 
 @pytest.mark.parametrize("training", [False, True])
 def test_two_stream_half_batches_match_oracle(training):
-    """B a multiple of 128 on small layers: forward (and backward) run as two half-batch chains on
-    two streams; inference mode shares the ping-pong buffers between them."""
+    """B a multiple of 128 on small layers, several passes in a row over the same buffers (inference: the two that the
+    activations go through)."""
     work = wl.make_config(1, n=512, n_layers=9, b_infer=256, b_train=256, density=0.4)
     ref = P.O32.forward(work.layers, work.x_infer, work.act_cap)
     net = sdnn.Net(work.layers, work.act_cap, 256, training=training)
     out = torch.empty(512, 256, device=P.DEV)
-    for _ in range(3):                       # repeated passes: the fork/join events are reused
+    for _ in range(3):
         out.zero_()
         net.sdnn_forward(P.dev(work.x_infer), out)
         assert np.array_equal(P.host(out), ref[-1])
@@ -306,8 +306,7 @@ def test_paper_training_setup_wide_net_two_steps():
 
 @pytest.mark.parametrize("b", [256, 64, 1])
 def test_training_step_captured_in_a_graph_replays_like_eager(b):
-    """The library allocates nothing and orders all work on the caller's stream (the helper stream
-    of the two-half-batch path is forked and joined with events), so a whole step can be captured
+    """The library allocates nothing and orders all work on the caller's stream, so a whole step can be captured
     in a HIP graph.  Every replay is checked against an eager twin net, with eager work and
     synchronisations between the replays; the oracle checks the first step."""
     work = wl.make_config(1, n=512, n_layers=7, b_infer=b, b_train=b, density=0.4)
@@ -347,9 +346,8 @@ def test_training_step_captured_in_a_graph_replays_like_eager(b):
 @pytest.mark.parametrize("b", [5, 64, 128, 130])
 @pytest.mark.parametrize("activation", ["relu", "sigmoid"])
 def test_fused_backward_and_gradient(b, activation):
-    """SDNN_FUSE_ON: back-propagation and the gradient of the stored entries in one sweep (whole batch
-    for B <= 64, two half-batch launches for B = 128; B = 130 cannot be fused and takes the separate
-    update), then the streaming descent step.  Uneven rows, several 16-entry groups per row, empty rows."""
+    """SDNN_FUSE_ON: back-propagation and the gradient of the stored entries in one sweep, then the streaming
+    descent step.  Uneven rows, several 16-entry groups per row, empty rows."""
     work = wl.tiny_net(81, sizes=(150, 90, 200, 60, 110), density=0.25, b=b)
     work.activation = activation
     lens = np.concatenate([np.diff(l.row_ptr) for l in work.layers])
@@ -362,7 +360,7 @@ def test_fused_backward_and_gradient(b, activation):
     for k in range(1, 5):
         assert np.array_equal(g["deltas"][k], plain["deltas"][k]), "the fused sweep must back-propagate the same bits"
     for (v, bias), (pv, pb) in zip(g["new"], plain["new"]):
-        P.assert_grad_close(v, pv, "fused vs separate update")     # two fp32 partial sums instead of one
+        P.assert_grad_close(v, pv, "fused vs separate update")     # another order of the sum over samples
         P.assert_grad_close(bias, pb, "fused vs separate bias update")
 
 

@@ -75,3 +75,23 @@ def test_one_sample_inference_on_the_lane_major_copy(n):
     net.sdnn_forward_noalloc(P.dev(x), out)
     assert np.array_equal(P.host(out), ref)
     net.close()
+
+
+# widths of nets of which tests/test_routes.py checks that one sample takes a launch per layer on the copy of the LDS forward
+LANE_MAJOR_NETS = [(90, 64, 30000, 70), (90, 1025, 30000, 1024, 70), (2050, 30000, 63)]
+LANE_MAJOR_LENGTHS = (0, 1, 9, 16, 17, 33)
+
+
+@pytest.mark.parametrize("sizes", LANE_MAJOR_NETS)
+def test_one_sample_inference_with_a_launch_per_layer(sizes):
+    """Narrow layers next to one that is too wide for the single launch to pay: positions and slots past the end of a row
+    are those of the widest layer."""
+    layers = [_layer(9590 + l, n_out, n_in, LANE_MAJOR_LENGTHS) for l, (n_in, n_out) in enumerate(zip(sizes, sizes[1:]))]
+    x = wl.normal_inputs(9599, sizes[0], 1)
+    ref = P.O32.forward(layers, x, 2.0)[-1]
+    net = sdnn.Net(layers, 2.0, 4, training=False)
+    for call in (net.sdnn_forward, net.sdnn_forward_noalloc):
+        out = torch.full((sizes[-1], 1), -1.0, device=P.DEV)
+        call(P.dev(x), out)
+        assert np.array_equal(P.host(out), ref) and (ref > 0).any()
+    net.close()

@@ -165,6 +165,29 @@ def test_skip_dead_in_stretches_with_the_activations_in_lds(b, every):
     net.close()
 
 
+@pytest.mark.parametrize("sizes,b", [((50, 9000, 300, 9000, 70), 600), ((50, 300, 17000, 1025, 70), 300), ((300, 50, 8192, 1, 1030, 9), 1100)])
+@pytest.mark.parametrize("every", [1, 2])
+def test_skip_dead_in_stretches_of_layers_of_different_widths(sizes, b, every):
+    """Widths beyond 4 and 2 samples per workgroup (8192 and 16384 positions), narrow layers between wide ones: a stretch's
+    input and output have positions of their own."""
+    from tests.test_gpu_lds_forward import _ragged
+    layers = [_ragged(9600 + l, n_out, n_in, [min(n_in, k) for k in (3, 20, 34)]) for l, (n_in, n_out) in enumerate(zip(sizes, sizes[1:]))]
+    for lay in layers:
+        lay.bias = -0.2 * np.abs(lay.bias)
+    x = wl.normal_inputs(9610, sizes[0], b) * np.where(np.arange(b) % 3 == 0, 1e-3, np.where(np.arange(b) % 7 == 0, 0.0, 1.0)).astype(np.float32)
+    xs = P.O32.forward(layers, x, 2.0)
+    alive = [int((v != 0).any(axis=0).sum()) for v in xs]
+    assert b > alive[1] > b // 2 and (xs[-1] > 0).any()
+    net = sdnn.Net(layers, 2.0, b, training=False, lds_forward=sdnn.SDNN_LDS_ON)
+    out = torch.full((sizes[-1], b), 7.0, device=P.DEV)
+    n_live = torch.full((1,), -1, dtype=torch.int32, device=P.DEV)
+    net.sdnn_forward_skip_dead(P.dev(x), out, check_every=every, n_live=n_live)
+    assert np.array_equal(P.host(out), xs[-1])
+    L = len(layers)
+    assert int(n_live.item()) == alive[(L - 1) // every * every]
+    net.close()
+
+
 @pytest.mark.parametrize("every", [2, 100])
 @pytest.mark.parametrize("shift", [0, 1, 700 * 3 + 5, -(700 * 2 + 8)])
 @pytest.mark.parametrize("lds", [sdnn.SDNN_LDS_ON, sdnn.SDNN_LDS_OFF])

@@ -95,3 +95,14 @@ def test_workspace_sized_without_the_columns(n_out, n_in, lengths):
             assert a.bytes >= b.bytes and (a.bytes == b.bytes or (max_batch, training) == (1, True)), (a.bytes, b.bytes)
             assert a("sdnn_forward", X0, 1, XL, None) == b("sdnn_forward", X0, 1, XL, None)
     """)
+
+
+def test_one_sample_takes_a_launch_per_layer_on_the_lane_major_copy():
+    """The nets of tests/test_gpu_single_sample.py and tests/test_gpu_nonfinite.py."""
+    routes.run("""
+        for sizes in [(90, 64, 30000, 70), (90, 1025, 30000, 1024, 70), (2050, 30000, 63), (2050, 30000, 2113)]:
+            net = Net([layer(o, i, (0, 1, 9, 16, 17, 33)) for i, o in zip(sizes, sizes[1:])], 4)
+            for call in ("sdnn_forward", "sdnn_forward_noalloc"):
+                rc, log = net(call, X0, 1, XL, None)
+                assert rc == 0 and len(log) == len(sizes) - 1 and all(l.startswith("k_spmv_lm<0, false, false>") for l in log), log
+    """)
