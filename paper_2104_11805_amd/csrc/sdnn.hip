@@ -429,7 +429,10 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
 // A wavefront per row (k_spmm with one sample per lane) is bound by the rate of gather instructions (10 clocks each,
 // whatever the number of samples) up to 64 samples, and by the L2 misses of a 256-sample tile beyond.  Here
 // one instruction serves 2 to 16 entries.  Forward, us per layer, before and after: 65536 neurons, 16 samples 49.8 ->
-// 17.8; 16384 neurons 12.0 -> 5.9 (16), 13.5 -> 10.2 (64), 24.5 -> 21 (99), 53 -> 31.8 (256); 4096 neurons 7.9 -> 6.5 (128).
+// 17.8; 16384 neurons 12.7 -> 6.8 (16), 13.4 -> 10.2 (64), 23.1 -> 17.4 (100), 53 -> 31 (256); no gain at 4096 neurons and 128
+// samples (6.7 in two half batches on two streams, 6.8 in this one launch).
+// A last tile that the batch fills only in part must not touch lines of its own for the idle lanes (when they read the
+// batch's first samples: 32000 neurons, 33 samples 31.2 us per layer, with the tile's first 19.6; 100 samples 50 and 38.4).
 // ---------------------------------------------------------------------------
 template <int LANE> __device__ __forceinline__ int quad_bcast(int v)
 {
@@ -478,9 +481,10 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_rows(const SpmmArgs a)
     const unsigned tile = blockIdx.x / a.n_rg, rg = blockIdx.x - tile * a.n_rg;
     const int r = (int)((rg * WAVES_PER_BLOCK + (threadIdx.x >> 6)) * R) + lane / G;
     const unsigned ldb = 4u * (unsigned)a.ld_in;
-    const int s_own = (int)(tile + a.tile_base) * (4 * G) + 4 * (lane & (G - 1));
+    // lanes past the end of the batch redo the tile's first samples: the lines that the other lanes fetch anyway
+    const int s_tile = (int)(tile + a.tile_base) * (4 * G), s_own = s_tile + 4 * (lane & (G - 1));
     const bool live = s_own < a.B;
-    const int s = live ? s_own : 0;
+    const int s = live ? s_own : s_tile;
     const unsigned so = 4u * (unsigned)s;
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
     int4 t = make_int4(0, 0, 0, 0);
