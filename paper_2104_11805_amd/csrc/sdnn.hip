@@ -1114,7 +1114,9 @@ __global__ void __launch_bounds__(1024) k_live_columns(const int32_t *__restrict
 
 // Writes a layer's part of the lane-major copy from its CSR arrays: biases and weights, and with prev_pos (the position of
 // every neuron of the layer below, NULL for the first layer: its own index) also the positions (prev_pos is looked at only
-// if with_cols).  One wavefront per block of 64 rows: grid = (blocks per wavefront, 16 wavefronts).
+// if with_cols).  grid = (blocks per wavefront, 16 wavefronts, parts): a workgroup of one wavefront takes every parts-th half
+// chunk of a block of 64 rows (all of them one after the other: sdnn_set_weights on 8192 rows of up to 2048 entries 199 us, in
+// parts 57).
 __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ layer, const LmLayer *__restrict__ tab,
                                                 const int32_t *__restrict__ lm_cs, uint4 *__restrict__ lm,
                                                 float *__restrict__ lm_bias, const int32_t *__restrict__ lm_row,
@@ -1132,8 +1134,8 @@ __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ lay
         end = L.row_ptr[row + 1];
         bias = L.bias[row];
     }
-    lm_bias[at] = bias;
-    for (int hf = 0; hf < 2 * (c1 - c0); ++hf) {
+    if (blockIdx.z == 0) lm_bias[at] = bias;
+    for (int hf = blockIdx.z; hf < 2 * (c1 - c0); hf += gridDim.z) {
         uint4 *o = lm + ((size_t)c0 * LDS_CHUNK_BYTES + (size_t)hf * LDS_HALF_BYTES) / 16 + lane;
         unsigned pk[4], wt[8];
 #pragma unroll
@@ -1602,7 +1604,8 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) k_update_lm(const LayerDev *__
     }
 }
 
-// Writes one of the two copies of a layer from its CSR arrays (dir 0: W, 1: W^T through the transposed index).
+// Writes one of the two copies of a layer from its CSR arrays (o = 0: W, 1: W^T through the transposed index).  grid = (blocks,
+// parts): a workgroup takes every parts-th chunk of a block.
 template <bool WIDE>
 __global__ void __launch_bounds__(64) k_b1_fill(const LayerDev *__restrict__ layer, int o, int with_cols)
 {
@@ -1614,7 +1617,7 @@ __global__ void __launch_bounds__(64) k_b1_fill(const LayerDev *__restrict__ lay
     // slots past the end of a row: weight 0, and a column past the end of the operand, which k_spmv_lm reads as 0 (a masked one
     // where 2 bytes hold none)
     const unsigned n_cols = (unsigned)(o ? L.n_out : L.n_in), pad = WIDE ? n_cols : min(n_cols, 0xffffu);
-    for (int i = 0; i < n; ++i) {
+    for (int i = blockIdx.y; i < n; i += gridDim.y) {
         unsigned col[8], w[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -1640,7 +1643,8 @@ __global__ void __launch_bounds__(64) k_b1_fill(const LayerDev *__restrict__ lay
     }
 }
 
-// The values of a layer in CSR order, from the copy of W.
+// The values of a layer in CSR order, from the copy of W.  grid = (blocks, parts), as above (1024 rows of up to 256 entries:
+// 47 us with a block's chunks one after the other, 15 in parts).
 template <bool WIDE>
 __global__ void __launch_bounds__(64) k_b1_values(const LayerDev *__restrict__ layer, float *__restrict__ values)
 {
@@ -1650,7 +1654,7 @@ __global__ void __launch_bounds__(64) k_b1_values(const LayerDev *__restrict__ l
     const int2 r = L.b1_row[0][64 * b + lane];
     if (r.x < 0) return;
     float *dst = values + L.row_ptr[r.x];
-    for (int i = 0; i < n; ++i) {
+    for (int i = blockIdx.y; i < n; i += gridDim.y) {
         const uint4 *src = (const uint4 *)L.b1_lm[0] + (size_t)(c0 + i) * (B1<WIDE>::CHUNK_BYTES / 16) + B1<WIDE>::WEIGHTS / 16 + lane;
         const uint4 a = src[0], c = src[64];
         const unsigned w[8] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
@@ -2572,11 +2576,15 @@ extern "C" int sdnn_workspace_bytes(const sdnn_layer *layers, int32_t n_layers,
     return SDNN_OK;
 }
 
+// Parts that the passes over a lane-major copy cut its blocks into: at most four chunks of eight entries one after the other
+// in the longest row, at most 64 parts.
+static unsigned fill_parts(int32_t longest) { return (unsigned)std::min(std::max((longest + 31) / 32, 1), 64); }
+
 // (Re)writes layer l's part of the lane-major copy from its CSR arrays.
 static int launch_lm_fill(sdnn_net *net, int l, const int32_t *prev_pos, int with_cols, hipStream_t stream)
 {
     if (net->lm_tab[l].nb == 0) return SDNN_OK;
-    hipLaunchKernelGGL(k_lm_fill, dim3((unsigned)net->lm_tab[l].nb, LDS_WAVES), dim3(64), 0, stream, net->d_layers + l, net->lm_layers + l,
+    hipLaunchKernelGGL(k_lm_fill, dim3((unsigned)net->lm_tab[l].nb, LDS_WAVES, fill_parts(net->max_len[0][l])), dim3(64), 0, stream, net->d_layers + l, net->lm_layers + l,
                        net->lm_cs, net->lm, net->lm_bias, net->lm_row, prev_pos, with_cols, net->lm_max_pos);
     HIP_TRY(net, hipGetLastError());
     return SDNN_OK;
@@ -2588,8 +2596,9 @@ static int launch_b1_fill(sdnn_net *net, int l, int with_cols, hipStream_t strea
     const LayerDev &d = net->layers[l];
     for (int o = 0; o < 2; ++o) {
         if (d.b1_blocks[o] == 0) continue;
-        if (net->b1_wide) hipLaunchKernelGGL(k_b1_fill<true>, dim3((unsigned)d.b1_blocks[o]), dim3(64), 0, stream, net->d_layers + l, o, with_cols);
-        else hipLaunchKernelGGL(k_b1_fill<false>, dim3((unsigned)d.b1_blocks[o]), dim3(64), 0, stream, net->d_layers + l, o, with_cols);
+        const dim3 grid((unsigned)d.b1_blocks[o], fill_parts(net->max_len[o][l]));
+        if (net->b1_wide) hipLaunchKernelGGL(k_b1_fill<true>, grid, dim3(64), 0, stream, net->d_layers + l, o, with_cols);
+        else hipLaunchKernelGGL(k_b1_fill<false>, grid, dim3(64), 0, stream, net->d_layers + l, o, with_cols);
         HIP_TRY(net, hipGetLastError());
     }
     return SDNN_OK;
@@ -3847,8 +3856,9 @@ extern "C" int sdnn_get_weights(sdnn_net *net, int32_t layer, float *d_values, f
     int rc = SDNN_OK;
     if (d_values && net->b1) { // the values that are stepped are those of the lane-major copy
         if (d.nnz > 0) {
-            if (net->b1_wide) hipLaunchKernelGGL(k_b1_values<true>, dim3((unsigned)d.b1_blocks[0]), dim3(64), 0, (hipStream_t)stream_, net->d_layers + (layer - 1), d_values);
-            else hipLaunchKernelGGL(k_b1_values<false>, dim3((unsigned)d.b1_blocks[0]), dim3(64), 0, (hipStream_t)stream_, net->d_layers + (layer - 1), d_values);
+            const dim3 grid((unsigned)d.b1_blocks[0], fill_parts(net->max_len[0][layer - 1]));
+            if (net->b1_wide) hipLaunchKernelGGL(k_b1_values<true>, grid, dim3(64), 0, (hipStream_t)stream_, net->d_layers + (layer - 1), d_values);
+            else hipLaunchKernelGGL(k_b1_values<false>, grid, dim3(64), 0, (hipStream_t)stream_, net->d_layers + (layer - 1), d_values);
             HIP_TRY(net, hipGetLastError());
         }
     } else if (d_values) {
