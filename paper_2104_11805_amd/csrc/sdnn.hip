@@ -3075,6 +3075,13 @@ static int spread_lanes(const sdnn_net *net, int G, int n_rows)
     while (G < 32 && (int64_t)n_rows * (2 * G) <= (int64_t)64 * 4 * net->n_cu) G *= 2;
     return G;
 }
+// Samples per tile of the forward product: as many as let a tile's operand stay in an XCD's L2 (launch_spmm has the figures).
+static int forward_tile(int n_cols)
+{
+    int tile = 128;
+    while (tile > 32 && 4 * (int64_t)n_cols * tile > 4000000) tile /= 2;
+    return tile;
+}
 template <int G>
 static const void *rows_fn_act(int act)
 {
@@ -3162,8 +3169,7 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
     // neurons, 64 samples: 4.6 vs 4.7).  Long rows are too uneven to share a wavefront.
     if (MODE == 0 && !n_live && !flags && !long_rows && (width > 64 || a.n_rows >= 2048) && !net->clustered[MODE][l] &&
         rows_addressable(n_cols, ld_in)) {
-        int tile = 128;
-        while (tile > 32 && 4 * (int64_t)n_cols * tile > 4000000) tile /= 2;
+        const int tile = forward_tile(n_cols);
         const int G = sub_begin == 0 && width <= tile ? spread_lanes(net, lanes_per_row(width), a.n_rows) : lanes_per_row(std::min(tile, width));
         const int rows_per_block = 64 / G * WAVES_PER_BLOCK;
         a.tile_base = (uint32_t)(sub_begin / (4 * G));
@@ -3227,38 +3233,63 @@ static int launch_copy_rows(sdnn_net *net, const float *src, int ld_src, float *
     return SDNN_OK;
 }
 
-// What a forward pass over B samples takes with a launch per layer, in seconds: about 4 us per layer to launch, fetch the
-// entries and store, plus the gathered rows at the rate that the memory they come from delivers (measured on nets of
-// 32-entry rows, 1024 to 30000 neurons, and of 100 to 800 entries, 1 to 256 samples, to within a fourth).
+// What a forward pass over B samples takes with a launch per layer, in seconds: 4.4 us per layer to launch, fetch the
+// entries and store, plus the longer of two things: the gathered rows, in whole tiles of samples, at the rate that the
+// memory they come from delivers, and the chain of gathers of the longest row.
 static double per_layer_forward_seconds(const sdnn_net *net, int B)
 {
     double t = 0.0;
-    for (const LayerDev &d : net->layers) {
-        if (B == 1) { t += 3.7e-6 + 5.1e-12 * (double)d.nnz; continue; }
-        const bool long_rows = (int64_t)d.nnz >= 128 * (int64_t)d.n_out;
-        const int width = !long_rows ? (B + 3) & ~3 : B > 128 ? (B + 255) & ~255 : B > 64 ? 128 : 64;
-        const double rate = long_rows ? (B > 128 ? 26e12 : B > 64 ? 17e12 : 14e12) : d.n_in <= 4500 ? 24e12 : d.n_in <= 16384 ? 19e12 : 15e12;
-        t += 4e-6 + 4.0 * (double)d.nnz * width / rate;
+    for (int l = 0; l < net->n_layers; ++l) {
+        const LayerDev &d = net->layers[l];
+        const double nnz = (double)d.nnz, longest = net->max_len[0][l];
+        if (B == 1) { // a lane per row
+            t += 3.7e-6 + 5.1e-12 * nnz + 28e-9 * std::max(0.0, longest - 32.0);
+            continue;
+        }
+        double rate, chain;
+        int width;
+        if ((int64_t)d.nnz >= 128 * (int64_t)d.n_out) { // a wavefront per row
+            width = B > 128 ? (B + 255) & ~255 : B > 64 ? 128 : 64;
+            rate = B > 128 ? 22e12 : B > 64 ? 17e12 : 14e12;
+            chain = B > 64 ? 50e-9 : 28e-9;
+        } else if (B <= 64 && d.n_out < 2048) {
+            width = 64;
+            rate = 20e12;
+            chain = 28e-9;
+        } else { // several rows per wavefront
+            const int tile = std::min(forward_tile(d.n_in), 4 * lanes_per_row(B));
+            width = (B + tile - 1) / tile * tile;
+            rate = (B > 256 ? 0.9 : 1.0) * (23e12 - 9e12 * std::min(std::max((d.n_in - 5000) / 27768.0, 0.0), 1.0));
+            chain = 54e-9;
+        }
+        t += 4.4e-6 + std::max(4.0 * nnz * width / rate, chain * longest);
     }
     return t;
 }
 
 // Samples per workgroup with which the single-launch LDS-resident forward is the faster way to run this block of B
-// samples, 0: a launch per layer is.  Measured (same nets): a workgroup takes 0.8 us per layer plus 3.5 / 3.9 / 6.2 ns
-// per wavefront-wide entry with 1 / 2 / 4 samples; a CU runs one workgroup at a time.
+// samples, 0: a launch per layer is.  A workgroup takes 0.8 us per layer plus 3.5 / 3.9 / 6.2 ns per wavefront-wide entry with
+// 1 / 2 / 4 samples; a CU runs one workgroup at a time, and where few of them share the stream of W (a round of fewer than 96),
+// they wait for it: up to 1 us per layer and 0.35 ns per entry more.
+// Against both paths measured at 1500 to 32000 neurons of 32 entries and 16 to 1100 samples (24 layers), and at 1024 to 8192 neurons
+// of uneven rows (a tenth of the columns in the mean), the choice costs at most 2 %.  us per pass, per layer / single launch:
+// 3001 neurons 141 / 153 (64 samples), 169 / 150 (100); 8000 neurons 311 / 358 (150), 388 / 359 (200); 16384 neurons 668 / 717
+// (200), 948 / 793 (300); 32000 neurons 1197 / 1382 (150), 1604 / 1385 (200), 2374 / 2987 (300: a second round), 3526 / 2907 (450);
+// uneven rows, 1024 neurons 107 / 49 (100), 2000 neurons 129 / 143 (64), 172 / 140 (100).
 static int lds_forward_samples(const sdnn_net *net, int B)
 {
     if (!net->lm || net->cfg.lds_forward == SDNN_LDS_OFF) return 0;
     for (const LayerDev &d : net->layers)
         if (d.n_out == 0) return 0; // an empty layer: leave it to the general path
     static const double entry[3] = {3.5e-9, 3.9e-9, 6.2e-9};
+    const double L = net->n_layers, entries = LDS_CHUNK * (double)net->lm_chunks;
     int best = 0;
     double t_best = 0.0;
     for (int k = 0; k < 3; ++k) {
-        const int T = 1 << k;
+        const int T = 1 << k, n_cu = std::max(net->n_cu, 1);
         if (T * net->lm_max_pos > LDS_MAX_FLOATS) break;
-        const int wgs = (B + T - 1) / T, rounds = (wgs + net->n_cu - 1) / std::max(net->n_cu, 1);
-        const double t = rounds * (net->n_layers * 0.8e-6 + LDS_CHUNK * (double)net->lm_chunks * entry[k]);
+        const int wgs = (B + T - 1) / T, rounds = (wgs + n_cu - 1) / n_cu, last = wgs - (rounds - 1) * n_cu;
+        const double t = rounds * (L * 0.8e-6 + entries * entry[k]) + std::max(0.0, 1.0 - last / 96.0) * (L * 1e-6 + entries * 0.35e-9);
         if (!best || t < t_best) { best = T; t_best = t; }
     }
     if (net->cfg.lds_forward == SDNN_LDS_ON) return best;

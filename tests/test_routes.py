@@ -106,3 +106,24 @@ def test_one_sample_takes_a_launch_per_layer_on_the_lane_major_copy():
                 rc, log = net(call, X0, 1, XL, None)
                 assert rc == 0 and len(log) == len(sizes) - 1 and all(l.startswith("k_spmv_lm<0, false, false>") for l in log), log
     """)
+
+
+def test_single_launch_or_a_launch_per_layer():
+    """Where one of the two paths was measured at least 7 % faster than the other (32 entries per row; uneven rows: a tenth of
+    the columns in the mean), that one is taken."""
+    routes.run("""
+        for n, layers, single, per_layer in [(1500, 24, (16, 100, 1100), ()), (3001, 24, (100, 450), (2, 33, 64)), (5000, 24, (150, 700), (2, 64, 100)),
+                                             (8000, 24, (200, 450), (1, 100, 150)), (16384, 24, (300, 1100), (1, 64, 100, 150, 200)),
+                                             (20000, 24, (450, 700), (1, 100, 150, 300)), (32000, 24, (200, 256, 450, 700), (1, 33, 100, 150, 300))]:
+            net = Net([layer(n, n, (32,))] * layers, 1100)
+            for B in single + per_layer:
+                rc, log = net("sdnn_forward", X0, B, XL, None)
+                assert rc == 0 and (len(log) == 1) == (B in single), (n, B, log)
+        tail = (np.arange(4097) + 0.5) ** (-1 / 1.2)
+        for n, single, per_layer in [(1024, (1, 2, 64, 100, 450), ()), (2000, (100, 200, 450, 1100), (1, 2, 64)), (4097, (450,), (1, 2, 64, 200))]:
+            deg = np.clip(np.round(tail[:n] / tail[:n].mean() * 0.12 * n), 1, n // 4).astype(int)
+            net = Net([layer(n, n, deg)] * 6, 1100)
+            for B in single + per_layer:
+                rc, log = net("sdnn_forward", X0, B, XL, None)
+                assert rc == 0 and (len(log) == 1) == (B in single), (n, B, deg.mean(), log)
+    """)
