@@ -3167,8 +3167,9 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
     // neurons 13.0 / 12.7 / 13.0 and 22.2 / 21.6 / 23.8; 16384: 17.7 / 19.1 / 25.7 and 31.8 / 35.3 / 48.3; 30000: 35.6 / 44.7 / 55.4
     // and 67.8 / 85.9 / 108).  Few rows and few samples: a wavefront per row keeps more of the chip busy (1024
     // neurons, 64 samples: 4.6 vs 4.7).  Long rows are too uneven to share a wavefront.
+    // (A launch holds less than 2^32 threads, 2^24 of these workgroups of 1024 results each: k_spmm walks its blocks.)
     if (MODE == 0 && !n_live && !flags && !long_rows && (width > 64 || a.n_rows >= 2048) && !net->clustered[MODE][l] &&
-        rows_addressable(n_cols, ld_in)) {
+        rows_addressable(n_cols, ld_in) && ((int64_t)a.n_rows + 64) * (width + 128) < ((int64_t)1 << 34)) {
         const int tile = forward_tile(n_cols);
         const int G = sub_begin == 0 && width <= tile ? spread_lanes(net, lanes_per_row(width), a.n_rows) : lanes_per_row(std::min(tile, width));
         const int rows_per_block = 64 / G * WAVES_PER_BLOCK;
@@ -3176,7 +3177,6 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
         a.n_tiles = (uint32_t)((width + 4 * G - 1) / (4 * G));
         a.n_rg = (uint32_t)((a.n_rows + rows_per_block - 1) / rows_per_block);
         const uint64_t grid = (uint64_t)a.n_tiles * a.n_rg;
-        if (grid > 0x7fffffffull) return fail(net, SDNN_EINVAL, "grid too large");
         void *args[] = {(void *)&a};
         HIP_TRY(net, hipLaunchKernel(rows_fn(G, net->cfg.activation), dim3((unsigned)grid), dim3(BLOCK_THREADS), args, 0, stream));
         HIP_TRY(net, hipGetLastError());

@@ -127,3 +127,14 @@ def test_single_launch_or_a_launch_per_layer():
                 rc, log = net("sdnn_forward", X0, B, XL, None)
                 assert rc == 0 and (len(log) == 1) == (B in single), (n, B, deg.mean(), log)
     """)
+
+
+def test_more_results_than_a_launch_has_threads():
+    """Layers of 2^34 results in a launch and more: the kernel that walks its blocks.  (The stand-in refuses launches of 2^32
+    threads.)"""
+    routes.run("""
+        net = Net([layer(68000000, 8, (1, 0, 0, 0))], 256)
+        for B, kernel in [(100, "k_rows<"), (256, "k_spmm<")]:
+            rc, log = net("sdnn_forward", X0, B, XL, None)
+            assert rc == 0 and len(log) == 1 and log[0].startswith(kernel), (B, log, sdnn.last_error(net.h))
+    """)
