@@ -89,16 +89,19 @@ typedef struct {
 
 /* Where the batch allows it, sdnn_backward can form the gradient of the stored entries (Eq. 4) in
  * the same sweep that back-propagates through W_l (Eq. 7): both need the rows of Delta_l that an
- * entry points at.  For batches of 2 to 256 samples; other batch sizes take the separate kernels on the same net.  A
- * gradient is summed over the samples in fp64 and rounded once, except for batches of exactly 128 samples on nets of
- * short rows whose widest layer has 12696 to 16384 neurons: two sums over 64 samples each, rounded to fp32, then
- * added.  The net then keeps the values a second time, in the order of the transposed index, which that sweep reads in a stream; the
- * gradient is left in the same order, sdnn_sgd_step is a streaming pass over both and rebuilds the
- * CSR copy in a second pass that moves whole runs of entries.  Same results within the rounding of
- * the sum over samples; costs 24 more bytes of workspace per stored entry.  AUTO turns it on where it is faster: nets
- * with about 100 000 entries per layer and more, half of that if max_batch > 64.  (Nets made for one sample per
- * step, max_batch == 1, keep lane-major copies of W and W^T instead where no row has more than 512 entries and the mean
- * is below 128, and step both; fuse_gradient says nothing there.) */
+ * entry points at.  For batches of 2 to 256 samples; other batch sizes take the separate kernels
+ * on the same net.  A gradient is summed over the samples in fp64 and rounded once, except for
+ * batches of exactly 128 samples on nets of short rows whose widest layer has 12696 to 16384
+ * neurons: two sums over 64 samples each, rounded to fp32, then added.  The net then keeps the
+ * values a second time, in the order of the transposed index, which that sweep reads in a stream;
+ * the gradient is left in the same order, sdnn_sgd_step is a streaming pass over both and rebuilds
+ * the CSR copy in a second pass that moves whole runs of entries.  Same results within the
+ * rounding of the sum over samples; costs 24 more bytes of workspace per stored entry.  AUTO turns
+ * it on where it is faster: nets of 48 000 entries per layer and more if max_batch > 64 (but not
+ * long rows, 128 entries and more in the mean, if max_batch > 256), of 85 000 otherwise (long
+ * rows: from 4096 rows per layer on).  (Nets made for one sample per step, max_batch == 1, keep
+ * lane-major copies of W and W^T instead where no row has more than 512 entries and the mean is
+ * below 128, and step both; fuse_gradient says nothing there.) */
 #define SDNN_FUSE_AUTO 0
 #define SDNN_FUSE_ON 1
 #define SDNN_FUSE_OFF (-1)

@@ -1535,7 +1535,7 @@ __global__ void __launch_bounds__(64) k_spmv_lm(const SpmvLmArgs a)
 // two factors, the other is gathered: from the vector's copy in LDS where it fits, since from L2 every 4-byte gather pulls in
 // a 128-byte line (16384 neurons: 3.6 -> 1.9 us per layer).  grid = (parts, 2, layers): a workgroup takes every parts-th group
 // of 16 blocks of W (blockIdx.y = 0) or of W^T.
-template <bool WIDE, bool IN_LDS>
+template <bool WIDE, bool IN_LDS> // not both: more than 65536 neurons do not fit LDS
 __global__ void __launch_bounds__(64 * LDS_WAVES) k_update_lm(const LayerDev *__restrict__ layers, float lr, int update_bias)
 {
     extern __shared__ __attribute__((aligned(16))) float lds_vec[];
@@ -3803,8 +3803,8 @@ extern "C" int sdnn_sgd_step(sdnn_net *net, float lr, void *stream_)
         // In LDS: enough workgroups to fill the chip twice, and no more of them than pay for filling their LDS.  Else as many as
         // there are groups of blocks, so that the chip works on few layers at a time and their vectors stay in L2.
         const int parts = in_lds ? std::min(groups, std::max(8, 2 * net->n_cu / net->n_layers)) : groups;
-        const void *fn = net->b1_wide ? (in_lds ? (const void *)k_update_lm<true, true> : (const void *)k_update_lm<true, false>)
-                                      : (in_lds ? (const void *)k_update_lm<false, true> : (const void *)k_update_lm<false, false>);
+        const void *fn = in_lds ? (const void *)k_update_lm<false, true>
+                         : net->b1_wide ? (const void *)k_update_lm<true, false> : (const void *)k_update_lm<false, false>;
         const size_t lds = in_lds ? (4 * ((size_t)net->max_n + 1) + 15) & ~(size_t)15 : 0;
         if (in_lds && !net->b1_attr_set) {
             HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, B1_MAX_LDS));
