@@ -91,8 +91,8 @@ typedef struct {
  * the same sweep that back-propagates through W_l (Eq. 7): both need the rows of Delta_l that an
  * entry points at.  For batches of 2 to 256 samples; other batch sizes take the separate kernels
  * on the same net.  A gradient is summed over the samples in fp64 and rounded once, except for
- * batches of exactly 128 samples on nets of short rows whose widest layer has 12696 to 16384
- * neurons: two sums over 64 samples each, rounded to fp32, then added.  The net then keeps the
+ * batches of exactly 128 samples on nets of short rows and up to 16384 neurons: two sums over 64
+ * samples each, rounded to fp32, then added.  The net then keeps the
  * values a second time, in the order of the transposed index, which that sweep reads in a stream;
  * the gradient is left in the same order, sdnn_sgd_step is a streaming pass over both and rebuilds
  * the CSR copy in a second pass that moves whole runs of entries.  Same results within the

@@ -573,6 +573,12 @@ template <int G> __device__ __forceinline__ void reduce4(double (&p)[4], int lan
     if constexpr (G >= 8) p[0] += lane_exchange<0>(p[0]);
 }
 template <int G> __device__ __forceinline__ int reduced_index(int lane) { return (lane / (G / 4)) & 3; }
+// The sum of a float over two neighbouring groups of 16 lanes, in all of them.
+__device__ __forceinline__ float add_neighbour16(float g)
+{
+    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(g), __float_as_uint(g), false, false);
+    return (float)((double)__uint_as_float(t[0]) + (double)__uint_as_float(t[1]));
+}
 
 // The backward sweep that also forms the gradient of the stored entries, in the manner of k_rows.  The lanes of row i of
 // W_l^T hold X_{l-1}(i, :), four samples each, gather Delta_l(j, :) for every entry (j, i) and sum its products with
@@ -583,9 +589,11 @@ template <int G> __device__ __forceinline__ int reduced_index(int lane) { return
 // bytes.  Backward and gradient, us per layer: 65536 neurons 80 -> 69.7 (64 samples), 70.6 -> 29.1 (16); 16384 neurons 21.1 ->
 // 14.4 (64), 31.8 -> 25.3 (128; two launches on two streams before); 10007 neurons, 99 samples 32.5 (two
 // separate kernels) -> 17.6 + 3; 8192 neurons of 820 entries 420 -> 331 (256 samples), 410 -> 127 (64).
-template <int G>
+// TWO (G = 32, 128 samples): the gradient is the sum of two windows of 64 samples, each rounded to fp32 (two_windows).
+template <int G, bool TWO>
 __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const GradArgs a)
 {
+    static_assert(!TWO || G == 32, "two windows of 16 lanes");
     constexpr int R = 64 / G;
     const int lane = threadIdx.x & 63;
     const unsigned tile = blockIdx.x / a.n_rg, rg = blockIdx.x - tile * a.n_rg;
@@ -608,7 +616,8 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const GradArgs a)
     double xd[4], acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int v = 0; v < 4; ++v) xd[v] = (double)xp[v];
-    int e0 = t.y + reduced_index<G>(lane); // the entry whose gradient this lane stores
+    constexpr int SUM = TWO ? 16 : G; // lanes of a window
+    int e0 = t.y + reduced_index<SUM>(lane); // the entry whose gradient this lane stores
     float4 x0[4], x1[4];
     int w0[4], w1[4];
     auto consume = [&](const float4 (&x)[4], const int (&wv)[4]) {
@@ -626,8 +635,10 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const GradArgs a)
         // added here: the compiler would move these sums past the branches below and keep every converted operand until
         // then (214 registers instead of 120)
         asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
-        reduce4<G>(pr, lane);
-        if ((lane & (G / 4 - 1)) == 0 && e0 < end) g_part[e0] = (float)pr[0];
+        reduce4<SUM>(pr, lane);
+        float g = (float)pr[0];
+        if (TWO) g = add_neighbour16(g);
+        if ((lane & (SUM / 4 - 1)) == 0 && !(TWO && (lane & 16)) && e0 < end) g_part[e0] = g;
         e0 += 4;
     };
     quad_gather<0>(q, rin, ldb, so, x0, w0);
@@ -2149,6 +2160,7 @@ struct sdnn_net {
     bool lds_part_attr_set = false;
     bool lds_attr_set[3] = {};       // the dynamic LDS limit of k_fwd_lds<1 << k> has been raised
     int grad_parts = 0;           // > 0: the last backward pass left the entries' gradient in G[0..grad_parts)
+    bool two_windows = false;     // that gradient is the sum of two rounded windows of samples
     bool vals_t_stale = false;    // the CSR values were changed by something that does not maintain vals_t
     int32_t *d_alive = nullptr;
     int32_t *d_flags[2] = {nullptr, nullptr}, *d_map[2] = {nullptr, nullptr}, *d_n_live[2] = {nullptr, nullptr}; // inference: dead-sample skipping, two rounds' state
@@ -3601,14 +3613,15 @@ extern "C" int sdnn_forward_skip_dead(sdnn_net *net, const float *d_X0, int32_t 
     return SDNN_OK;
 }
 
-// Two whole tiles of 64 samples whose operand together is larger than L2: the sweep takes them as two tiles, each with a
-// partial gradient of its own, rounded to fp32 (16384 neurons of 32 entries: 27.5 -> 25.3 us per layer; 4096 neurons, where
-// the operand fits: 10.2 in two tiles, 8.9 in one).  The batches around it (filled up to 128 samples or not) keep one sum over all of
-// their samples in fp64, rounded once.
-static bool two_tiles(const sdnn_net *net)
+// Batches of 128 samples on nets of short rows and up to 16384 neurons: the gradient is the sum of two windows of 64, each
+// rounded to fp32, as it has been since these batches ran as two halves.  Where the operand is larger than L2 that is a gain
+// (two tiles, each with a partial gradient of its own: 16384 neurons 27.5 -> 25.3 us per layer); below, one sum over the whole
+// tile would be about as fast (4096 neurons, a step of 120 layers: 2.17 to 2.20 ms), but its other rounding moved the outputs of
+// that case's steps by 7e-5 of their norm.  This is the caller's batch: one that is filled up to 128 has one sum over all its
+// samples in fp64, rounded once, like every other.
+static bool two_windows(const sdnn_net *net)
 {
-    const int64_t bytes = 4 * (int64_t)net->max_n * 128;
-    if (net->B != 128 || bytes <= 6500000 || bytes > ((int64_t)1 << 23)) return false;
+    if (net->B != 128 || (int64_t)net->max_n * 128 > ((int64_t)1 << 21)) return false;
     int64_t nnz = 0, rows = 0;
     for (const LayerDev &d : net->layers) { nnz += d.nnz; rows += d.n_out; }
     return nnz < 128 * rows;
@@ -3653,13 +3666,16 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;
     }
+    // two windows: as two tiles (and two partial gradients) where the operand is larger than L2, else in one
+    const bool two = net->two_windows;
     int G = lanes_per_row(net->grad_parts == 2 ? 64 : B);
-    if (net->grad_parts == 1) G = spread_lanes(net, G, a.n_rows);
+    if (!two) G = spread_lanes(net, G, a.n_rows);
     const int rows_per_block = 64 / G * WAVES_PER_BLOCK;
     a.n_tiles = (uint32_t)net->grad_parts;
     a.n_rg = (uint32_t)((a.n_rows + rows_per_block - 1) / rows_per_block);
-    const void *fn = G == 4 ? (const void *)k_bwd_rows<4> : G == 8 ? (const void *)k_bwd_rows<8> : G == 16 ? (const void *)k_bwd_rows<16>
-                     : G == 32 ? (const void *)k_bwd_rows<32> : (const void *)k_bwd_rows<64>;
+    const void *fn = G == 4 ? (const void *)k_bwd_rows<4, false> : G == 8 ? (const void *)k_bwd_rows<8, false>
+                     : G == 16 ? (const void *)k_bwd_rows<16, false> : G == 64 ? (const void *)k_bwd_rows<64, false>
+                     : two ? (const void *)k_bwd_rows<32, true> : (const void *)k_bwd_rows<32, false>;
     HIP_TRY(net, hipLaunchKernel(fn, dim3(a.n_tiles * a.n_rg), dim3(BLOCK_THREADS), args, 0, stream));
     HIP_TRY(net, hipGetLastError());
     return SDNN_OK;
@@ -3672,7 +3688,7 @@ static int grad_fusable(const sdnn_net *net, int B)
     if (B > 256) return 0;
     for (const LayerDev &d : net->layers)
         if (B > 64 && !wide_rows(net, d)) return 0;
-    return two_tiles(net) ? 2 : 1;
+    return net->two_windows && 4 * (int64_t)net->max_n * B > 6500000 ? 2 : 1;
 }
 
 extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)
@@ -3685,6 +3701,7 @@ extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)
     hipStream_t stream = (hipStream_t)stream_;
     const int L = net->n_layers, B = net->Bp;
     const LayerDev &last = net->layers[L - 1];
+    net->two_windows = two_windows(net);
     const int gp = grad_fusable(net, B);
     for (int l = gp ? 0 : 1; l < L; ++l) { // the operands of the products below: refused before anything is launched
         const LayerDev &d = net->layers[l];

@@ -29,16 +29,18 @@ def test_result_across_the_input():
     """)
 
 
-def test_gradient_over_two_tiles_of_samples():
-    """Two partial gradients only where the batch itself is 128 samples and the operand lies between 6.5 and 8.4 MB: not for
-    the batches that are filled up to 128."""
+def test_gradient_over_two_windows_of_samples():
+    """Two rounded windows only where the batch itself is 128 samples on up to 16384 neurons (two partial gradients from 6.5 MB on):
+    not for the batches that are filled up to 128."""
     routes.run("""
-        for n, B, G, tiles in [(12695, 128, 32, 1), (12696, 128, 16, 2), (16384, 128, 16, 2), (16385, 128, 32, 1), (16384, 124, 32, 1),
-                               (16384, 125, 32, 1), (16384, 127, 32, 1), (16384, 129, 64, 1), (4096, 128, 32, 1)]:
+        for n, B, kernel, rows, tiles in [(12695, 128, "<32, true>", 8, 1), (12696, 128, "<16, false>", 16, 2), (16384, 128, "<16, false>", 16, 2),
+                                          (16385, 128, "<32, false>", 8, 1), (16384, 124, "<32, false>", 8, 1), (16384, 125, "<32, false>", 8, 1),
+                                          (16384, 127, "<32, false>", 8, 1), (16384, 129, "<64, false>", 4, 1), (4096, 128, "<32, true>", 8, 1),
+                                          (4096, 125, "<32, false>", 8, 1), (4096, 127, "<32, false>", 8, 1)]:
             net = Net([layer(n, n, (32,))], 300, training=True)
             assert net("sdnn_forward", X0, B, XL, None)[0] == 0
             rc, log = net("sdnn_backward", DL, None)
-            assert rc == 0 and log[-1] == f"k_bwd_rows<{G}> {tiles * -(-n // (256 // G))} 1 1", (n, B, log)
+            assert rc == 0 and log[-1] == f"k_bwd_rows{kernel} {tiles * -(-n // rows)} 1 1", (n, B, log)
     """)
 
 
