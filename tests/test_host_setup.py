@@ -111,8 +111,8 @@ def test_workspace_bytes_and_argument_errors_without_gpu():
     cfg_inf = sdnn.sdnn_config(float("inf"), 16, 0, 1, 0, 0, 0, 0, sdnn.SDNN_LDS_OFF)
     assert l.sdnn_workspace_bytes(arr, 3, C.byref(cfg_inf), C.byref(n)) == 0
     assert 0 < n.value < train_bytes
-    # an inference net of narrow layers also holds the lane-major copy for the LDS-resident forward:
-    # 8 bytes per entry of the 64-row blocks, each as deep as its longest row
+    # an inference net of narrow layers also holds the lane-major copy for the LDS-resident forward: 6 bytes per entry of
+    # the 64-row blocks, each as deep as its longest row filled up to whole chunks of sixteen (here more than 8 per entry)
     plain_inf = n.value
     cfg_lds = sdnn.sdnn_config(float("inf"), 16, 0, 1, 0)
     assert l.sdnn_workspace_bytes(arr, 3, C.byref(cfg_lds), C.byref(n)) == 0
