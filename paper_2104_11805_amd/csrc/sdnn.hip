@@ -178,16 +178,21 @@ struct SpmmArgs {
     int32_t n_cols;
     float *out;           // [n_rows][ld_out]
     const float *aux;     // MODE 0: bias [n_rows] (may be NULL); MODE 1: Xprev [n_rows][ld_out]
-    int32_t n_rows, B;    // B: samples (columns that matter)
+    int32_t n_rows, B;    // B: samples (columns that matter); fills_up(B, ld_out): zeros are stored up to a group of four
     int32_t ld_in, ld_out; // floats per activation row
     uint32_t n_tiles, n_rg, n_vblocks, tile_base;
     float cap;
-    int16_t act;
-    int16_t n_pad;         // the last n_pad of the B samples only fill up a group of four: whatever the kernel computes for them, zeros are stored
+    int32_t act;
     const int32_t *n_live; // NULL, or the number of leading columns of the block that still matter (device)
     int32_t *flags;        // NULL, or MODE 0: flags[s] is set to 1 for every sample s with a non-zero output
     const int32_t *row_ptr;
 };
+// Whether the rows of an output have room for whole groups of four samples (the library's own arrays) and B leaves the last one
+// part-filled: its other columns are stored as zeros, which the kernels with four samples per lane rely on.  (Uniform, from
+// what a kernel has loaded anyway: as an argument of its own, masked value by value, it took 0.7 % of the products.)
+__device__ __forceinline__ bool fills_up(int B, int ld_out) { return (B & 3) != 0 && ld_out > B; }
+__device__ __forceinline__ bool is_fill(int s, int B) { return s >= B && s < ((B + 3) & ~3); }
+
 struct GradArgs : SpmmArgs {
     float *g_part[2];  // gradient of the stored entries over the samples of the first / second tile, in the order of the
                        // transposed index [nnz]
@@ -242,7 +247,7 @@ __device__ __forceinline__ RowMeta load_meta(const int4 *sched, const int32_t *i
 template <int V, int MODE, int U, int ACT>
 __device__ __forceinline__ void spmm_row(RowMeta m, const int32_t *idx, const float *vals,
                                          const int32_t *perm, const float *in, size_t in_bytes,
-                                         float *out, const float *aux, int B, int n_pad, int ld_in, int ld_out, float capf,
+                                         float *out, const float *aux, int B, int ld_in, int ld_out, float capf,
                                          int act, unsigned tile, int lane, int32_t *flags)
 {
     const int s_own = (int)tile * (64 * V) + lane * V;
@@ -367,10 +372,16 @@ __device__ __forceinline__ void spmm_row(RowMeta m, const int32_t *idx, const fl
 #pragma unroll
         for (int v = 0; v < V; ++v) o[v] = act_backprop(act, acc[v], xp[v], capf);
     }
+    if (V > 1 && s + V > B) { // the batch's last piece
 #pragma unroll
-    for (int v = 0; v < V; ++v)
-        if (s + v >= B - n_pad) o[v] = 0.0f;
+        for (int v = 0; v < V; ++v)
+            if (s + v >= B) o[v] = 0.0f;
+    }
     if (live) stv<V>(out + (size_t)m.row * ld + s, o);
+    if (V < 4 && fills_up(B, ld_out) && is_fill(s_own, B)) {
+        const float zero[V] = {};
+        stv<V>(out + (size_t)m.row * ld + s_own, zero);
+    }
     if (MODE == 0 && flags != nullptr && live) { // other rows store the same 1: no ordering needed
 #pragma unroll
         for (int v = 0; v < V; ++v)
@@ -403,7 +414,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
             if (r >= a.n_rows) continue;
             const RowMeta m = load_meta<MODE>(a.sched, a.idx, a.vals, a.perm, r, lane);
             for (unsigned tile = 0; tile < n_tiles; ++tile)
-                spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.n_pad, a.ld_in, a.ld_out, a.cap, a.act,
+                spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.ld_in, a.ld_out, a.cap, a.act,
                                           tile + a.tile_base, lane, a.flags);
         }
         return;
@@ -414,7 +425,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
         const int r = __builtin_amdgcn_readfirstlane((int)(rg * WAVES_PER_BLOCK + wave));
         if (r >= a.n_rows) continue;
         const RowMeta m = load_meta<MODE>(a.sched, a.idx, a.vals, a.perm, r, lane);
-        spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.n_pad, a.ld_in, a.ld_out, a.cap, a.act, tile + a.tile_base, lane, a.flags);
+        spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.ld_in, a.ld_out, a.cap, a.act, tile + a.tile_base, lane, a.flags);
     }
 }
 
@@ -520,7 +531,12 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_rows(const SpmmArgs a)
     if (r >= a.n_rows || !live) return;
     float o[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) o[v] = s + v < a.B - a.n_pad ? act_apply(ACT, acc[v] + b, a.cap) : 0.0f;
+    for (int v = 0; v < 4; ++v) o[v] = act_apply(ACT, acc[v] + b, a.cap);
+    if (s + 4 > a.B) { // the batch's last group
+#pragma unroll
+        for (int v = 1; v < 4; ++v)
+            if (s + v >= a.B) o[v] = 0.0f;
+    }
     float *dst = a.out + (size_t)row * a.ld_out + s;
     if ((a.ld_out & 3) == 0 && ((size_t)a.out & 15) == 0) {
         stv<4>(dst, o);
@@ -662,7 +678,12 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const GradArgs a)
     if (!a.store_out || !live) return;
     float o[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) o[v] = s + v < a.B - a.n_pad ? act_backprop(a.act, acc[v], xp[v], a.cap) : 0.0f;
+    for (int v = 0; v < 4; ++v) o[v] = act_backprop(a.act, acc[v], xp[v], a.cap);
+    if (s + 4 > a.B) { // the batch's last group
+#pragma unroll
+        for (int v = 1; v < 4; ++v)
+            if (s + v >= a.B) o[v] = 0.0f;
+    }
     stv<4>(a.out + (size_t)row * a.ld_out + s, o);
 }
 
@@ -795,7 +816,12 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm_panel(const SpmmArgs a, 
             float o;
             if (MODE == 0) o = act_apply(ACT, acc[r] + (a.aux ? (double)a.aux[row[r]] : 0.0), a.cap);
             else o = act_backprop(a.act, acc[r], xp[r], a.cap);
-            if (live) a.out[(size_t)row[r] * ld + s] = s < B - a.n_pad ? o : 0.0f;
+            if (live) a.out[(size_t)row[r] * ld + s] = o;
+        }
+        if (fills_up(B, a.ld_out) && is_fill(s_own, B)) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (row[r] >= 0) a.out[(size_t)row[r] * ld + s_own] = 0.0f;
         }
     }
 }
@@ -1261,7 +1287,9 @@ __device__ __forceinline__ void spmm_row_grad(RowMeta m, const GradArgs &a, int 
             wave_lds_sync(); // the next group's rows are parked over the ones just read
         }
     }
-    if (a.store_out && live) a.out[(size_t)m.row * ld + s] = s < B - a.n_pad ? act_backprop(a.act, acc, xp, a.cap) : 0.0f;
+    if (!a.store_out) return;
+    if (live) a.out[(size_t)m.row * ld + s] = act_backprop(a.act, acc, xp, a.cap);
+    else if (fills_up(B, a.ld_out) && is_fill(lane, B)) a.out[(size_t)m.row * ld + lane] = 0.0f;
 }
 template <int U>
 __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_grad(const GradArgs a)
@@ -3106,11 +3134,11 @@ static const void *rows_fn(int G, int act)
 
 // in / out: rows of ld_in / ld_out floats.  sub_begin .. sub_end: the launch covers these samples only (sub_begin a
 // multiple of SUB_ALIGN, or of 64 where every layer takes the panel sweep for all but the narrowest blocks; sub_end == 0: all
-// of them).  n_pad: see SpmmArgs.
+// of them).
 template <int MODE>
 static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld_in, float *out, int ld_out,
                        const float *aux, int B, hipStream_t stream, const int32_t *n_live = nullptr, int32_t *flags = nullptr,
-                       int sub_begin = 0, int sub_end = 0, int n_pad = 0)
+                       int sub_begin = 0, int sub_end = 0)
 {
     if (sub_end == 0) sub_end = B;
     SpmmArgs a;
@@ -3124,7 +3152,7 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
         a.n_rows = d.n_in;
     }
     a.vals = d.vals; a.in = in; a.out = out; a.aux = aux; a.B = B; a.ld_in = ld_in; a.ld_out = ld_out;
-    a.cap = net->cfg.act_cap; a.act = (int16_t)net->cfg.activation; a.n_pad = (int16_t)n_pad;
+    a.cap = net->cfg.act_cap; a.act = net->cfg.activation;
     if (a.n_rows == 0) return SDNN_OK;
     const int n_cols = MODE == 0 ? d.n_in : d.n_out;
     a.n_cols = n_cols;
@@ -3440,8 +3468,7 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
         const LayerDev &d = net->layers[l];
         float *out = training ? d.X : (l == L - 1 ? d_XL : ((l & 1) ? pong : ping));
         const int ld_out = !training && l == L - 1 ? B : ld;
-        const int rc = training ? launch_spmm<0>(net, d, in, ld_in, out, ld_out, d.bias, Bp, stream, nullptr, nullptr, 0, 0, Bp - B)
-                                : launch_spmm<0>(net, d, in, ld_in, out, ld_out, d.bias, B, stream);
+        const int rc = launch_spmm<0>(net, d, in, ld_in, out, ld_out, d.bias, B, stream);
         if (rc) return rc;
         in = out;
         ld_in = ld_out;
@@ -3637,12 +3664,12 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
     const int B = net->Bp;
     GradArgs a;
     a.row_ptr = d.t_row_ptr; a.idx = d.t_row_idx; a.perm = nullptr; a.sched = d.t_sched; a.n_rows = d.n_in;
-    a.vals = d.vals_t; a.in = d.D; a.out = out; a.aux = d.X_prev; a.B = B; a.ld_in = a.ld_out = net->ld; a.cap = net->cfg.act_cap;
-    a.act = (int16_t)net->cfg.activation; a.n_pad = (int16_t)(net->Bp - net->B); a.n_live = nullptr; a.flags = nullptr;
+    a.vals = d.vals_t; a.in = d.D; a.out = out; a.aux = d.X_prev; a.B = net->B; a.ld_in = a.ld_out = net->ld; a.cap = net->cfg.act_cap;
+    a.act = net->cfg.activation; a.n_live = nullptr; a.flags = nullptr;
     a.g_part[0] = d.G[0]; a.g_part[1] = d.G[1]; a.store_out = store_out;
     if (a.n_rows == 0 || d.nnz == 0) {
         if (d.nnz == 0 && store_out && a.n_rows > 0) // no entries: Delta_{l-1} = 0, nothing to differentiate
-            return launch_spmm<1>(net, d, d.D, net->ld, out, net->ld, d.X_prev, B, stream, nullptr, nullptr, 0, 0, a.n_pad);
+            return launch_spmm<1>(net, d, d.D, net->ld, out, net->ld, d.X_prev, net->B, stream);
         return SDNN_OK;
     }
     a.n_cols = d.n_out;
@@ -3732,7 +3759,7 @@ extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)
         // Delta_{l} (0-based l-1) = (W^T Delta_{l+1}) masked by X_{l}
         float *dprev = l >= 1 ? net->layers[l - 1].D : nullptr;
         const int rc = gp ? launch_bwd_grad(net, d, dprev, stream, l >= 1)
-                          : launch_spmm<1>(net, d, d.D, net->ld, dprev, net->ld, d.X_prev, B, stream, nullptr, nullptr, 0, 0, B - net->B);
+                          : launch_spmm<1>(net, d, d.D, net->ld, dprev, net->ld, d.X_prev, net->B, stream);
         if (rc) return rc;
     }
     net->state = ST_BACKWARD;
