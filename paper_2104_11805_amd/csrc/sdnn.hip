@@ -192,6 +192,15 @@ struct SpmmArgs {
 // what a kernel has loaded anyway: as an argument of its own, masked value by value, it took 0.7 % of the products.)
 __device__ __forceinline__ bool fills_up(int B, int ld_out) { return (B & 3) != 0 && ld_out > B; }
 __device__ __forceinline__ bool is_fill(int s, int B) { return s >= B && s < ((B + 3) & ~3); }
+// The lane's number, made where it is used: as a value that the compiler may keep or move ahead of the loops, the rare store
+// of zeros costs k_spmm 2 to 8 registers throughout, and some of its variants a wavefront per SIMD.  (Not in the panel sweep:
+// there it took the forward of 65536 neurons from 20.4 to 27.3 ms.)
+__device__ __forceinline__ int lane_number()
+{
+    int n;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(n));
+    return n;
+}
 
 struct GradArgs : SpmmArgs {
     float *g_part[2];  // gradient of the stored entries over the samples of the first / second tile, in the order of the
@@ -378,14 +387,20 @@ __device__ __forceinline__ void spmm_row(RowMeta m, const int32_t *idx, const fl
             if (s + v >= B) o[v] = 0.0f;
     }
     if (live) stv<V>(out + (size_t)m.row * ld + s, o);
-    if (V < 4 && fills_up(B, ld_out) && is_fill(s_own, B)) {
-        const float zero[V] = {};
-        stv<V>(out + (size_t)m.row * ld + s_own, zero);
-    }
     if (MODE == 0 && flags != nullptr && live) { // other rows store the same 1: no ordering needed
 #pragma unroll
         for (int v = 0; v < V; ++v)
             if (o[v] != 0.0f) flags[s + v] = 1;
+    }
+}
+
+// Zeros after a row's last sample, by the wavefront of its last tile.  (In spmm_row itself they take 2 to 6 more registers
+// where a wavefront walks the tiles, and a wavefront per SIMD with them.)
+template <int V> __device__ __forceinline__ void fill_row(const SpmmArgs &a, int row, unsigned tile)
+{
+    if (V < 4 && fills_up(a.B, a.ld_out) && (tile + 1) * (64 * V) >= (unsigned)a.B) {
+        const int s = a.B + lane_number();
+        if (is_fill(s, a.B)) a.out[(size_t)row * a.ld_out + s] = 0.0f;
     }
 }
 
@@ -413,6 +428,8 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
             const int r = __builtin_amdgcn_readfirstlane((int)(rg * WAVES_PER_BLOCK + wave));
             if (r >= a.n_rows) continue;
             const RowMeta m = load_meta<MODE>(a.sched, a.idx, a.vals, a.perm, r, lane);
+            // (one sample per lane comes here only where an operand's rows are not filled up: nobody reads the zeros)
+            if constexpr (V > 1) fill_row<V>(a, m.row, n_tiles - 1 + a.tile_base);
             for (unsigned tile = 0; tile < n_tiles; ++tile)
                 spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.ld_in, a.ld_out, a.cap, a.act,
                                           tile + a.tile_base, lane, a.flags);
@@ -426,6 +443,7 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm(const SpmmArgs a)
         if (r >= a.n_rows) continue;
         const RowMeta m = load_meta<MODE>(a.sched, a.idx, a.vals, a.perm, r, lane);
         spmm_row<V, MODE, U, ACT>(m, a.idx, a.vals, a.perm, a.in, a.in_bytes, a.out, a.aux, a.B, a.ld_in, a.ld_out, a.cap, a.act, tile + a.tile_base, lane, a.flags);
+        fill_row<V>(a, m.row, tile + a.tile_base);
     }
 }
 
@@ -1287,9 +1305,8 @@ __device__ __forceinline__ void spmm_row_grad(RowMeta m, const GradArgs &a, int 
             wave_lds_sync(); // the next group's rows are parked over the ones just read
         }
     }
-    if (!a.store_out) return;
-    if (live) a.out[(size_t)m.row * ld + s] = act_backprop(a.act, acc, xp, a.cap);
-    else if (fills_up(B, a.ld_out) && is_fill(lane, B)) a.out[(size_t)m.row * ld + lane] = 0.0f;
+    if (a.store_out && lane < (fills_up(B, a.ld_out) ? (B + 3) & ~3 : B))
+        a.out[(size_t)m.row * ld + lane] = live ? act_backprop(a.act, acc, xp, a.cap) : 0.0f;
 }
 template <int U>
 __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_grad(const GradArgs a)
