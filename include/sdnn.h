@@ -132,7 +132,11 @@ typedef struct {
  * workspace per stored entry; sdnn_set_weights keeps it current; not built from 4 GiB on).  Every row still
  * adds its terms in storage order: same bits as the per-layer kernels.  AUTO builds the copy and uses the
  * launch where it is faster (enough samples to fill the chip, or layers so small that per-layer launches
- * are bound by their latency); ON uses it whenever the copy exists; OFF never builds it. */
+ * are bound by their latency); ON uses it whenever the copy exists; OFF never builds it.
+ * Inference nets of at least three layers, wider than 16384 neurons and made for more than 64 samples, have a second such copy
+ * (up to 10.5 more bytes per stored entry) for a pass with a launch per layer in which a workgroup carries two samples through
+ * a layer with a panel of up to 16384 neurons at a time in LDS: same bits again.  AUTO and ON use it where it is the faster way;
+ * OFF, a positive panel_cols and reorder_rows = 1 never build it. */
 #define SDNN_LDS_AUTO 0
 #define SDNN_LDS_ON 1
 #define SDNN_LDS_OFF (-1)

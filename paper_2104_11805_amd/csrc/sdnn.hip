@@ -22,6 +22,8 @@
 //     (k_spread_vals).
 //   * inference on layers of up to 32768 neurons: one launch, activations in LDS
 //     (k_fwd_lds).
+//   * inference on wider layers: a launch per layer, a panel of the activations in LDS
+//     at a time (k_fwd_pan).
 //   * inference on large activation blocks goes through all layers in
 //     sub-blocks of samples, so that a layer's output is still in the
 //     memory-side cache when the next layer gathers it.
@@ -1212,6 +1214,282 @@ __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ lay
 }
 
 // ---------------------------------------------------------------------------
+// K1p: Eq. 3 for one layer whose operand does not fit LDS: a workgroup of 16 wavefronts takes two samples and one range of up
+// to 16384 of the layer's rows, and walks the operand in panels of up to 16384 neurons that it holds in LDS one after the other.
+// A lane owns a row per block of 64 (up to 16 blocks per wavefront) and keeps their fp64 sums in registers across the
+// panels.  Column indices ascend inside a row and panels are column ranges, so every sum keeps its storage order.
+//
+// Copy of W: for every range and wavefront one stream of slots (a slot: 64 lanes, a 16-bit position in the panel and a weight
+// each; halves of eight slots as in k_fwd_lds), panel by panel, in a panel block by block.  A block is as deep in a panel as its
+// fullest row there; the rows of a block are chosen with about equal numbers of entries in every panel (sdnn_pan_layout).
+// `ends` has a bit for every slot after which the next block's turn follows.  A panel's slots are filled up to a whole half.
+// Activations between the layers: [pair of samples][position][2], a panel is one contiguous piece, brought into LDS
+// without passing through registers.
+//
+// What bounds it: the stream of W from L2 (384 bytes a slot), with two samples to share it; a slot takes 11 clocks of a CU
+// (vector instructions 6.5, LDS reads at random positions 7, W 6 at the L1's 64 bytes per clock, 9 at what an L2 delivers to 32
+// CUs at once).  Per panel 1.6 us to load it and 1.4 us until the last wavefront is done with the one before: 65536 neurons, 55 us
+// per workgroup.  Four samples and panels of 8192 neurons share W better, but 32 entries are then too few for eight panels
+// (1.64 slots per entry instead of 1.10; 65536 neurons, 1024 samples 583 against 476 us per layer; 20001 neurons 110 against 121).
+// Against k_spmm_panel and k_fwd_lds<1> (24 layers of 32 entries per row, us per layer, before / with it): 65536 neurons, 1024
+// samples 849 / 476; 40000 neurons, 1024 samples 618 / 270; 32768 neurons, 512 samples 123 / 96; 65536 neurons, 64 samples
+// 53 / 65 (half of the CUs: not taken).
+// ---------------------------------------------------------------------------
+static_assert(PAN_WAVES == LDS_WAVES, "the same halves, the same workgroups");
+struct PanForward {
+    const uint4 *stream;   // halves of LDS_HALF_BYTES
+    const int32_t *seg;    // [range][wavefront][panels + 1]: where the panels' slots start, in halves
+    const uint32_t *ends;  // a byte per half
+    const float *bias;     // by position
+    const float2 *in;      // [pairs][in_pos]
+    float2 *out;           // [pairs][out_pos]
+    uint32_t stream_bytes;
+    int32_t in_pos, out_pos; // positions of a sample's activations
+    int32_t panel, n_panels; // positions per panel
+    int32_t range, n_ranges, nb; // positions per range, and blocks per wavefront
+    int32_t n_pairs;
+    float cap;
+};
+// Registers v64 .. v127 of k_fwd_pan are an array of two doubles per block, reached by index: the multiply-adds name the first
+// block's registers and `at` (four words per block) is added to them.  The compiler has the 64 below (amdgpu_num_vgpr counts half
+// of them) and knows nothing of these: as a variable that is indexed by the block they would be copied, or go through memory, at
+// every block.
+// Four slots: w[u] x[u][t] is added to the current block's sums; where bit u of `ends` is set, the next block's turn follows.
+__device__ __forceinline__ void add_four(int &at, unsigned ends, const double (&w)[4], const double (&x)[4][2])
+{
+    unsigned s;
+#define PAN_ADD(w, x0, x1, bit)                                                                              \
+    "v_fma_f64 v[64:65], " w ", " x0 ", v[64:65]\n\tv_fma_f64 v[66:67], " w ", " x1 ", v[66:67]\n\t"           \
+    "s_bfe_u32 %1, %2, " bit "\n\ts_lshl2_add_u32 %0, %1, %0\n\t"
+    asm volatile("s_set_gpr_idx_on %0, gpr_idx(SRC2,DST)\n\t"
+                 PAN_ADD("%3", "%4", "%5", "0x10000") "s_set_gpr_idx_idx %0\n\t"
+                 PAN_ADD("%6", "%7", "%8", "0x10001") "s_set_gpr_idx_idx %0\n\t"
+                 PAN_ADD("%9", "%10", "%11", "0x10002") "s_set_gpr_idx_idx %0\n\t"
+                 PAN_ADD("%12", "%13", "%14", "0x10003")
+                 "s_set_gpr_idx_off"
+                 : "+s"(at), "=&s"(s)
+                 : "s"(ends), "v"(w[0]), "v"(x[0][0]), "v"(x[0][1]), "v"(w[1]), "v"(x[1][0]), "v"(x[1][1]), "v"(w[2]), "v"(x[2][0]), "v"(x[2][1]),
+                   "v"(w[3]), "v"(x[3][0]), "v"(x[3][1])
+                 : "m0", "scc");
+#undef PAN_ADD
+}
+// All of them to zero; naming the last one as written makes the kernel have them.
+__device__ __forceinline__ void clear_sums()
+{
+    asm volatile("v_mov_b32 v127, 0" ::: "v127");
+#pragma unroll
+    for (int at = 0; at < 64; at += 4)
+        asm volatile("s_set_gpr_idx_on %0, gpr_idx(DST)\n\tv_mov_b32 v64, 0\n\tv_mov_b32 v65, 0\n\tv_mov_b32 v66, 0\n\tv_mov_b32 v67, 0\n\ts_set_gpr_idx_off" ::"s"(at) : "m0");
+}
+__device__ __forceinline__ void get_sums(int at, double &v0, double &v1)
+{
+    int w[4];
+    asm volatile("s_set_gpr_idx_on %4, gpr_idx(SRC0)\n\t"
+                 "v_mov_b32 %0, v64\n\tv_mov_b32 %1, v65\n\tv_mov_b32 %2, v66\n\tv_mov_b32 %3, v67\n\t"
+                 "s_set_gpr_idx_off"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+                 : "s"(at)
+                 : "m0");
+    v0 = __hiloint2double(w[1], w[0]);
+    v1 = __hiloint2double(w[3], w[2]);
+}
+
+template <int ACT>
+__global__ void __launch_bounds__(64 * LDS_WAVES) __attribute__((amdgpu_num_vgpr(32))) k_fwd_pan(const PanForward a)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds_act[];
+    typedef float pair __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) pair *lds_ptr;
+    typedef __attribute__((address_space(3))) char *lds_bytes;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the ranges of a pair run side by side on one XCD: they read the same panels (one range of all pairs after the other, so
+    // that all the workgroups of an XCD share one stream of W: 602 against 511 us at 65536 neurons, 1024 samples)
+    const unsigned k = blockIdx.x >> 3;
+    const int q = (int)(k % (unsigned)a.n_ranges), g = (int)(k / (unsigned)a.n_ranges) * 8 + (int)(blockIdx.x & 7u);
+    if (g >= a.n_pairs) return;
+    unsigned shift = 3;
+    asm("" : "+v"(shift)); // kept in a register for lds_address
+    if (tid < 2) lds_act[2 * a.panel + tid] = 0.0f; // where the slots past a row's entries point
+
+    typedef const int32_t __attribute__((address_space(4))) *seg_ptr;
+    const seg_ptr seg = (seg_ptr)a.seg + (q * LDS_WAVES + wave) * (a.n_panels + 1);
+    const int first = seg[0];
+    const __amdgpu_buffer_rsrc_t rst = make_rsrc((const float *)a.stream, a.stream_bytes);
+    const __amdgpu_buffer_rsrc_t rin = make_rsrc((const float *)(a.in + (size_t)g * a.in_pos), (size_t)a.in_pos * 8);
+    const __amdgpu_buffer_rsrc_t ren = make_rsrc((const float *)a.ends, (size_t)a.stream_bytes / LDS_HALF_BYTES);
+    unsigned at = (unsigned)first * LDS_HALF_BYTES;
+    const int lane16 = 16 * lane;
+    struct Half { u32x4 c, wa, wb; } ha, hb;
+    auto request = [&](Half &h) {
+        h.c = __builtin_amdgcn_raw_buffer_load_b128(rst, lane16, (int)at, 0);
+        h.wa = __builtin_amdgcn_raw_buffer_load_b128(rst, lane16 + 1024, (int)at, 0);
+        h.wb = __builtin_amdgcn_raw_buffer_load_b128(rst, lane16 + 2048, (int)at, 0);
+        at += LDS_HALF_BYTES;
+    };
+    clear_sums();
+    int block = 0, p = 0, left = seg[1] - first, half = 0; // block: the current one's words
+    unsigned four_ends = 0, word = 0;                      // the ends of four halves per lane, of the current four
+    auto load_panel = [&](auto more) {
+        const int bytes = min(a.panel, a.in_pos - p * a.panel) * 8;
+        for (int i = 1024 * wave; i < bytes; i += 1024 * LDS_WAVES)
+            if (i + lane16 < bytes)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rin, (__attribute__((address_space(3))) void *)((lds_bytes)0 + i), 16, lane16, p * a.panel * 8 + i, 0, 0);
+        more();
+        __builtin_amdgcn_s_waitcnt(0xf70); // vmcnt(0): the panel is there
+        lds_barrier();
+    };
+    // The next panel into LDS, once every wavefront is done with the one before.
+    auto advance = [&]() {
+        if (++p >= a.n_panels) return;
+        left = seg[p + 1] - seg[p];
+        block = 0;
+        lds_barrier();
+        load_panel([]() {});
+    };
+    auto take = [&](Half &h) { // eight slots; then their registers are free for the half after next
+        unsigned ad[8];
+        pair x[8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            ad[2 * u] = lds_address<0>(h.c[u], shift);
+            ad[2 * u + 1] = lds_address<1>(h.c[u], shift);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = *(lds_ptr)((lds_bytes)0 + ad[u]);
+#pragma unroll
+        for (int v = 0; v < 8; v += 4) {
+            double w[4], xd[4][2];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) w[u] = (double)__uint_as_float(v ? h.wb[u] : h.wa[u]);
+            if (v) request(h);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                xd[u][0] = (double)x[v + u][0];
+                xd[u][1] = (double)x[v + u][1];
+            }
+            add_four(block, word >> v, w, xd);
+        }
+        if (--left == 0) advance();
+    };
+    load_panel([&]() { request(ha); request(hb); });
+    for (const int n = seg[a.n_panels] - first; half < n; half += 2) { // a stream has an even number of halves
+        if ((half & 255) == 0) {
+            four_ends = __builtin_amdgcn_raw_buffer_load_b32(ren, 4 * lane, first + half, 0); // a stream starts on a multiple of four halves
+            __builtin_amdgcn_s_waitcnt(0xf70);
+        }
+        if ((half & 3) == 0) word = (unsigned)__builtin_amdgcn_readlane((int)four_ends, (half >> 2) & 63);
+        if ((half & 6) == 0) { // the hardware serves the oldest wavefront first: turns, or the youngest finish a panel late
+            switch ((wave / 4 + (half >> 3)) & 3) {
+            case 0: __builtin_amdgcn_s_setprio(0); break;
+            case 1: __builtin_amdgcn_s_setprio(1); break;
+            case 2: __builtin_amdgcn_s_setprio(2); break;
+            default: __builtin_amdgcn_s_setprio(3);
+            }
+        }
+        take(ha);
+        word >>= 8;
+        take(hb);
+        word >>= 8;
+    }
+    const int at0 = q * a.range + 64 * wave + lane;
+    pair *out = (pair *)(a.out + (size_t)g * a.out_pos + (size_t)at0);
+    float bias[16];
+#pragma unroll
+    for (int b = 0; b < 16; ++b) bias[b] = a.bias[at0 + 1024 * min(b, a.nb - 1)];
+#pragma unroll
+    for (int b = 0; b < 16; ++b) {
+        if (b >= a.nb) break;
+        double s0, s1;
+        get_sums(4 * b, s0, s1);
+        pair v;
+        v[0] = act_apply(ACT, s0 + (double)bias[b], a.cap);
+        v[1] = act_apply(ACT, s1 + (double)bias[b], a.cap);
+        out[1024 * b] = v;
+    }
+}
+
+// Writes the slots of one block in one panel (grid: blocks per wavefront x ranges, wavefronts, panels), and in panel 0 its biases.
+__global__ void __launch_bounds__(64) k_pan_fill(const LayerDev *__restrict__ layer, uint4 *__restrict__ stream,
+                                                 const int32_t *__restrict__ slot, const int32_t *__restrict__ rows,
+                                                 float *__restrict__ bias, int nb, int panel_cols, int panel_pos,
+                                                 const int32_t *__restrict__ prev_pos)
+{
+    const LayerDev &L = *layer;
+    const int j = blockIdx.x % nb, q = blockIdx.x / nb, w = blockIdx.y, p = blockIdx.z, lane = threadIdx.x, np = gridDim.z;
+    const int at = 1024 * nb * q + 64 * (LDS_WAVES * j + w) + lane;
+    const int row = rows[at];
+    const int32_t *sl = slot + (size_t)((q * LDS_WAVES + w) * np + p) * (nb + 1) + j;
+    const int s0 = sl[0], s1 = sl[1];
+    int beg = 0, end = 0;
+    if (row >= 0) {
+        beg = L.row_ptr[row];
+        end = L.row_ptr[row + 1];
+    }
+    if (p == 0) bias[at] = row >= 0 ? L.bias[row] : 0.0f;
+    // the row's entries in this panel: its columns ascend
+    auto below = [&](int64_t col) {
+        int lo = beg, hi = end;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (L.col_idx[mid] < col) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo;
+    };
+    const int e0 = below((int64_t)p * panel_cols), n = below((int64_t)(p + 1) * panel_cols) - e0;
+    for (int s = s0; s < s1; ++s) {
+        char *half = (char *)stream + (size_t)(s >> 3) * LDS_HALF_BYTES;
+        unsigned pos = (unsigned)panel_pos;
+        float wt = 0.0f;
+        if (s - s0 < n) {
+            const int e = e0 + s - s0, c = L.col_idx[e];
+            wt = L.vals[e];
+            pos = (unsigned)((prev_pos ? prev_pos[c] : c) - p * panel_pos);
+        }
+        *(uint16_t *)(half + 16 * lane + 2 * (s & 7)) = (uint16_t)pos;
+        *(float *)(half + 1024 + ((s & 4) << 8) + 16 * lane + 4 * (s & 3)) = wt;
+    }
+}
+
+// Between [neuron][sample] and [pair of samples][position][2]: tiles of 64 neurons and 64 samples through LDS.
+// IN: rows of X (row r at position r) to pairs, a zero past the last sample; else pairs to the rows that `rows` names.
+template <bool IN>
+__global__ void __launch_bounds__(256) k_pan_turn(float *__restrict__ x, int ld, int n, int B, float2 *__restrict__ pairs, int n_pos,
+                                                  const int32_t *__restrict__ rows)
+{
+    __shared__ float tile[64][65];
+    const int tid = threadIdx.x, p0 = 64 * blockIdx.x, s0 = 64 * blockIdx.y;
+    const int n_pairs = (B + 1) / 2;
+    if constexpr (IN) {
+        for (int i = tid; i < 4096; i += 256) {
+            const int r = i >> 6, s = i & 63;
+            tile[r][s] = p0 + r < n && s0 + s < B ? x[(size_t)(p0 + r) * ld + s0 + s] : 0.0f;
+        }
+        __syncthreads();
+        for (int i = tid; i < 2048; i += 256) {
+            const int r = i & 63, g = i >> 6;
+            if (s0 / 2 + g < n_pairs && p0 + r < n_pos) pairs[(size_t)(s0 / 2 + g) * n_pos + p0 + r] = make_float2(tile[r][2 * g], tile[r][2 * g + 1]);
+        }
+    } else {
+        for (int i = tid; i < 2048; i += 256) {
+            const int r = i & 63, g = i >> 6;
+            if (s0 / 2 + g < n_pairs && p0 + r < n_pos) {
+                const float2 v = pairs[(size_t)(s0 / 2 + g) * n_pos + p0 + r];
+                tile[r][2 * g] = v.x;
+                tile[r][2 * g + 1] = v.y;
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < 4096; i += 256) {
+            const int r = i >> 6, s = i & 63;
+            const int row = p0 + r < n_pos ? rows[p0 + r] : -1;
+            if (row >= 0 && s0 + s < B) x[(size_t)row * ld + s0 + s] = tile[r][s];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // K2 + K4a: back-propagation through W_l fused with the gradient of W_l's stored entries, for
 // launches of at most 64 samples (one sample per lane).  The wavefront of row i of W_l^T gathers
 // Delta_l(j, :) for every stored entry (j, i) anyway and holds X_{l-1}(i, :), the two operands of
@@ -2203,6 +2481,16 @@ struct sdnn_net {
     size_t lm_chunks = 0;
     int32_t lm_max_pos = 0;
     bool lds_part_attr_set = false;
+    bool pan_attr_set = false;
+    struct Pan {                     // a layer's copy of W for k_fwd_pan
+        PanLayer g{};
+        uint4 *stream = nullptr;
+        int32_t *seg = nullptr, *slot = nullptr, *rows = nullptr, *pos = nullptr;
+        uint32_t *ends = nullptr;
+        float *bias = nullptr;
+        double depth = 0;
+    };
+    std::vector<Pan> pan;            // empty: the net has no such copy
     bool lds_attr_set[3] = {};       // the dynamic LDS limit of k_fwd_lds<1 << k> has been raised
     int grad_parts = 0;           // > 0: the last backward pass left the entries' gradient in G[0..grad_parts)
     bool two_windows = false;     // that gradient is the sum of two rounded windows of samples
@@ -2274,7 +2562,10 @@ struct Plan {
         size_t row_ptr, col_idx, vals, bias, t_row_ptr, t_row_idx, t_perm, sched, t_sched, X, D, G[2], vals_t, mid_slot, mid_dst, mid_loc, mid, b1_cs[2], b1_row[2], b1_lm[2];
         int32_t b1_blocks[2];
         size_t b1_chunks[2];
+        PanLayer pan;
+        size_t pan_stream, pan_seg, pan_slot, pan_rows, pan_pos, pan_ends, pan_bias;
     };
+    bool pan = false;            // a copy of W for k_fwd_pan
     std::vector<PerLayer> pl;
     size_t b1_chunk_bytes = 0;   // 0: no lane-major copies for one sample per step
     std::vector<LmLayer> lm_tab; // empty: no lane-major copy
@@ -2499,6 +2790,29 @@ static void plan_b1(const sdnn_layer *layers, int32_t n_layers, const sdnn_confi
     if (fits) pl.b1_chunk_bytes = wide ? 4096 : 3072;
 }
 
+// The forward in panels (k_fwd_pan) is set up for inference nets wider than a panel, of at least three layers (the two passes that
+// turn the samples around take about as long as a layer), with at least four entries per row and panel in the mean, made for
+// batches that can fill the chip (pan_forward_pays).  Fills in the layers' geometry.
+static bool pan_wanted(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, std::vector<Plan::PerLayer> &pl)
+{
+    if (cfg->training || cfg->lds_forward == SDNN_LDS_OFF || cfg->panel_cols > 0 || cfg->reorder_rows || n_layers < 3 || cfg->max_batch <= 64) return false;
+    int64_t nnz = 0, rows = 0, widest = 0;
+    for (int32_t l = 0; l < n_layers; ++l) {
+        if (layers[l].n_out == 0 || layers[l].n_in == 0) return false;
+        nnz += layers[l].row_ptr[layers[l].n_out];
+        rows += layers[l].n_out;
+        widest = std::max<int64_t>(widest, std::max(layers[l].n_out, layers[l].n_in));
+    }
+    const int64_t n_panels = (widest + PAN_POS - 1) / PAN_POS;
+    if (n_panels < 2 || n_panels > PAN_MAX || nnz < 4 * rows * n_panels || cfg->max_batch * widest < 3200000) return false;
+    for (int32_t l = 0; l < n_layers; ++l) {
+        PanLayer &g = pl[l].pan;
+        sdnn_pan_geometry(layers[l], l > 0 ? &pl[l - 1].pan : nullptr, g);
+        if (g.halves * LDS_HALF_BYTES >= ((size_t)1 << 32)) return false; // the kernel addresses a layer's copy with 32-bit offsets
+    }
+    return true;
+}
+
 static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, Plan &pl)
 {
     // Arrays of 1 MiB and more start on a multiple of their size rounded down to a power of two, at most
@@ -2551,6 +2865,12 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
     const size_t mb = (size_t)cfg->max_batch, mld = (size_t)row_pitch((int64_t)max_n, cfg->max_batch);
     plan_b1(layers, n_layers, cfg, pl);
     const bool b1 = pl.b1_chunk_bytes != 0;
+    pl.pan = pan_wanted(layers, n_layers, cfg, pl.pl);
+    size_t paired = 0; // floats of the largest block of activations between its layers
+    if (pl.pan) {
+        for (int32_t l = 0; l < n_layers; ++l) paired = std::max(paired, (size_t)std::max(pl.pl[l].pan.in_pos, pl.pl[l].pan.out_pos));
+        paired *= (mb + 1) / 2 * 2;
+    }
 #define PLAN_KIND(field, bytes_expr)                                   \
     for (int32_t l = 0; l < n_layers; ++l) {                           \
         const sdnn_layer &y = layers[l];                               \
@@ -2570,6 +2890,15 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
         pl.lm_row = take(4 * pl.lm_n_pos);
         pl.lm_bias = take(4 * pl.lm_n_pos);
         pl.lm_pos = take(4 * pl.lm_n_rows);
+    }
+    if (pl.pan) {
+        PLAN_KIND(pan_stream, LDS_HALF_BYTES * q.pan.halves)
+        PLAN_KIND(pan_ends, q.pan.halves)
+        PLAN_KIND(pan_seg, 4 * (size_t)q.pan.n_ranges * LDS_WAVES * (size_t)(q.pan.n_panels + 1))
+        PLAN_KIND(pan_slot, 4 * (size_t)q.pan.n_ranges * LDS_WAVES * (size_t)q.pan.n_panels * (size_t)(q.pan.nb + 1))
+        PLAN_KIND(pan_rows, 4 * (size_t)q.pan.out_pos)
+        PLAN_KIND(pan_bias, 4 * (size_t)q.pan.out_pos)
+        PLAN_KIND(pan_pos, 4 * (size_t)y.n_out)
     }
     if (cfg->training) {
         PLAN_KIND(t_row_ptr, 4 * ((size_t)y.n_in + 1))
@@ -2597,8 +2926,9 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
             PLAN_KIND(b1_lm[1], pl.b1_chunk_bytes * q.b1_chunks[1])
         }
     } else {
-        pl.ping = take(4 * std::max(max_n * mld, max_pos)); // one sample on the lane-major copy: a float per position
-        pl.pong = take(4 * std::max(max_n * mld, max_pos));
+        const size_t buffer = 4 * std::max({max_n * mld, max_pos, paired}); // one sample on the lane-major copy: a float per position
+        pl.ping = take(buffer);
+        pl.pong = take(buffer);
         pl.alive = take(4 * mb);
         for (int k = 0; k < 2; ++k) {
             pl.flags[k] = take(4 * mb);
@@ -2643,6 +2973,17 @@ static int launch_lm_fill(sdnn_net *net, int l, const int32_t *prev_pos, int wit
     if (net->lm_tab[l].nb == 0) return SDNN_OK;
     hipLaunchKernelGGL(k_lm_fill, dim3((unsigned)net->lm_tab[l].nb, LDS_WAVES, fill_parts(net->max_len[0][l])), dim3(64), 0, stream, net->d_layers + l, net->lm_layers + l,
                        net->lm_cs, net->lm, net->lm_bias, net->lm_row, prev_pos, with_cols, net->lm_max_pos);
+    HIP_TRY(net, hipGetLastError());
+    return SDNN_OK;
+}
+
+// (Re)writes layer l's copy for k_fwd_pan from its CSR arrays.
+static int launch_pan_fill(sdnn_net *net, int l, hipStream_t stream)
+{
+    const sdnn_net::Pan &f = net->pan[l];
+    hipLaunchKernelGGL(k_pan_fill, dim3((unsigned)(f.g.nb * f.g.n_ranges), LDS_WAVES, (unsigned)f.g.n_panels), dim3(64), 0, stream,
+                       net->d_layers + l, f.stream, f.slot, f.rows, f.bias, f.g.nb, f.g.panel_cols, f.g.panel,
+                       l > 0 ? (const int32_t *)net->pan[l - 1].pos : nullptr);
     HIP_TRY(net, hipGetLastError());
     return SDNN_OK;
 }
@@ -2694,6 +3035,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
     net->cfg = *cfg;
     try {
         net->layers.resize(n_layers);
+        net->pan.resize(pl.pan ? n_layers : 0);
         net->max_len[0].resize(n_layers);
         net->max_len[1].resize(n_layers);
         net->clustered[0].resize(n_layers);
@@ -2715,6 +3057,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
         std::vector<uint16_t> mid_slot, mid_loc;
         std::vector<int32_t> b1_cs[2];
         std::vector<int2> b1_row[2];
+        PanLayout pan;
         int32_t max_len = 0, t_max_len = 0;
         bool clustered = false, t_clustered = false; // reorder_rows found rows that share columns
         int rc = SDNN_OK;
@@ -2830,6 +3173,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 const LmLayer &t = pl.lm_tab[l];
                 lm_deal_blocks(y, t, lm_row.data() + t.pos, lm_pos.data() + lm_first_row[l], lm_cs.data() + t.cs);
             }
+            if (pl.pan) sdnn_pan_layout(y, pl.pl[l].pan, h.pan);
             h.max_len = h.t_max_len = 0;
             for (int32_t r = 0; r < y.n_out; ++r) h.max_len = std::max(h.max_len, y.row_ptr[r + 1] - y.row_ptr[r]);
             if (training)
@@ -2857,6 +3201,8 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
         int32_t max_out = 0;
         for (int32_t l = 0; l < n_layers; ++l) max_out = std::max(max_out, layers[l].n_out);
         const std::vector<float> zeros((size_t)max_out, 0.0f); // stands in for a NULL bias
+        bool pan_fits = pl.pan;
+        double pan_fullest = 0.0, pan_mean = 0.0;
         unsigned hw = std::thread::hardware_concurrency();
         const int32_t group = (int32_t)std::max(1u, std::min({hw ? hw : 1u, 16u, (unsigned)n_layers}));
         std::vector<HostIdx> idx((size_t)group);
@@ -2930,6 +3276,24 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                     UP(d.t_perm, h.t_perm.data(), 4 * nnz);
                     UP(d.t_sched, h.t_sched.data(), 16 * (size_t)y.n_in);
                 }
+                if (pl.pan) {
+                    sdnn_net::Pan &f = net->pan[l];
+                    f.g = q.pan;
+                    f.depth = h.pan.depth;
+                    f.stream = (uint4 *)(base + q.pan_stream); f.ends = (uint32_t *)(base + q.pan_ends);
+                    f.seg = (int32_t *)(base + q.pan_seg); f.slot = (int32_t *)(base + q.pan_slot);
+                    f.rows = (int32_t *)(base + q.pan_rows); f.pos = (int32_t *)(base + q.pan_pos); f.bias = (float *)(base + q.pan_bias);
+                    pan_fits &= h.pan.ends.size() <= q.pan.halves;
+                    pan_fullest += (double)h.pan.fullest;
+                    pan_mean += (double)nnz / q.pan.n_panels;
+                    if (pan_fits) {
+                        UP(f.ends, h.pan.ends.data(), h.pan.ends.size());
+                        UP(f.seg, h.pan.seg.data(), 4 * h.pan.seg.size());
+                        UP(f.slot, h.pan.slot.data(), 4 * h.pan.slot.size());
+                        UP(f.rows, h.pan.rows.data(), 4 * h.pan.rows.size());
+                        UP(f.pos, h.pan.pos.data(), 4 * h.pan.pos.size());
+                    }
+                }
                 if (gw) UP(d.vals_t, h.vals_t.data(), 4 * nnz);
                 if (gw) UP(d.mid_slot, h.mid_slot.data(), 2 * nnz);
                 if (gw) UP(d.mid_dst, h.mid_dst.data(), 4 * nnz);
@@ -2944,6 +3308,13 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 const int rc_fill = launch_b1_fill(net, l, 1, stream);
                 if (rc_fill) return fail_free(rc_fill);
             }
+        // not where a layout took too many slots, or where the links stay within few panels: the operand of the other kernels is
+        // on chip then
+        if (!pan_fits || pan_fullest > 1.5 * pan_mean) net->pan.clear();
+        for (int32_t l = 0; l < (int32_t)net->pan.size(); ++l) {
+            const int rc_fill = launch_pan_fill(net, l, stream);
+            if (rc_fill) return fail_free(rc_fill);
+        }
         if (want_lm) {
             // from the blocks' depths to where their chunks lie: one wavefront's chunks follow each other through all layers
             int64_t at = 0;
@@ -3305,7 +3676,11 @@ static double per_layer_forward_seconds(const sdnn_net *net, int B)
         }
         double rate, chain;
         int width;
-        if ((int64_t)d.nnz >= 128 * (int64_t)d.n_out) { // a wavefront per row
+        if (net->cfg.panel_cols >= 0 && B > PANEL_MIN_SAMPLES && (int64_t)d.n_in * 256 >= ((int64_t)8 << 20) && longest <= 64 && !net->clustered[0][l]) {
+            width = (B + 63) & ~63; // k_spmm_panel (40000, 50000, 65536 neurons: 9.6, 9.6, 11.3e12)
+            rate = 10e12;
+            chain = 28e-9;
+        } else if ((int64_t)d.nnz >= 128 * (int64_t)d.n_out) { // a wavefront per row
             width = B > 128 ? (B + 255) & ~255 : B > 64 ? 128 : 64;
             rate = B > 128 ? 22e12 : B > 64 ? 17e12 : 14e12;
             chain = B > 64 ? 50e-9 : 28e-9;
@@ -3333,8 +3708,11 @@ static double per_layer_forward_seconds(const sdnn_net *net, int B)
 // 3001 neurons 141 / 153 (64 samples), 169 / 150 (100); 8000 neurons 311 / 358 (150), 388 / 359 (200); 16384 neurons 668 / 717
 // (200), 948 / 793 (300); 32000 neurons 1197 / 1382 (150), 1604 / 1385 (200), 2374 / 2987 (300: a second round), 3526 / 2907 (450);
 // uneven rows, 1024 neurons 107 / 49 (100), 2000 neurons 129 / 143 (64), 172 / 140 (100).
-static int lds_forward_samples(const sdnn_net *net, int B)
+// *seconds (not NULL): what the faster one of the two takes.
+static int lds_forward_samples(const sdnn_net *net, int B, double *seconds = nullptr)
 {
+    const double per_layer = seconds || net->cfg.lds_forward == SDNN_LDS_AUTO ? per_layer_forward_seconds(net, B) : 0.0;
+    if (seconds) *seconds = per_layer;
     if (!net->lm || net->cfg.lds_forward == SDNN_LDS_OFF) return 0;
     for (const LayerDev &d : net->layers)
         if (d.n_out == 0) return 0; // an empty layer: leave it to the general path
@@ -3349,8 +3727,28 @@ static int lds_forward_samples(const sdnn_net *net, int B)
         const double t = rounds * (L * 0.8e-6 + entries * entry[k]) + std::max(0.0, 1.0 - last / 96.0) * (L * 1e-6 + entries * 0.35e-9);
         if (!best || t < t_best) { best = T; t_best = t; }
     }
+    if (!best) return 0;
+    if (seconds) *seconds = net->cfg.lds_forward == SDNN_LDS_ON ? 0.0 : std::min(t_best, per_layer);
     if (net->cfg.lds_forward == SDNN_LDS_ON) return best;
-    return t_best < per_layer_forward_seconds(net, B) ? best : 0;
+    return t_best < per_layer ? best : 0;
+}
+
+// Whether the pass in panels (k_fwd_pan) is the faster way to run B samples than one that takes `other` seconds.  Per layer 3.5 us
+// to launch and, for every round of workgroups, 6 us plus 1.1 us per panel and range (they share an XCD's L2) plus 4.2 ns
+// per wavefront-wide slot; and the two passes that turn the samples around.  Measured, us per layer without / in panels (24 layers of 32 entries):
+// 20001 neurons 23.3 / 28.3 (100 samples), 37.1 / 30.4 (200), 52.9 / 53.8 (300: a second round), 110 / 90 (700); 32768 neurons
+// 27.9 / 45.8 (64), 62.8 / 46.8 (100), 123 / 96 (512); 40000 neurons 38.7 / 42.5 (64), 73.1 / 45.7 (100), 309 / 131 (512);
+// 65536 neurons 53.0 / 64.5 (64), 136 / 66.4 (100), 137 / 114 (150), 849 / 476 (1024).
+static bool pan_forward_pays(const sdnn_net *net, int B, double other)
+{
+    if (net->pan.empty() || B < 2) return false;
+    const int n_cu = std::max(net->n_cu, 1);
+    double t = 10e-6 + 8.0 * (net->pan.front().g.in_pos + (double)net->pan.back().g.out_pos) * B / 4e12;
+    for (const sdnn_net::Pan &f : net->pan) {
+        const int64_t wgs = (int64_t)((B + 15) / 16 * 8) * f.g.n_ranges, rounds = (wgs + n_cu - 1) / n_cu;
+        t += 3.5e-6 + (double)rounds * (6e-6 + 1.1e-6 * f.g.n_panels * f.g.n_ranges + 4.2e-9 * LDS_WAVES * f.depth);
+    }
+    return t < other;
 }
 
 static LdsForward lds_args(const sdnn_net *net, int l0, int l1, const float *in, int ld_in, float *out, int ld_out, int B)
@@ -3398,6 +3796,38 @@ static int sub_block_width(const sdnn_net *net, int B)
     return w >= B ? 0 : (int)w;
 }
 
+// The pass in panels: samples turned to pairs, a launch per layer, and back.
+static int forward_pan(sdnn_net *net, const float *d_X0, int B, float *d_XL, hipStream_t stream, float *ping, float *pong)
+{
+    const void *fn = net->cfg.activation == ACT_SIGMOID ? (const void *)k_fwd_pan<ACT_SIGMOID> : (const void *)k_fwd_pan<ACT_RELU_CAP>;
+    if (!net->pan_attr_set) { // more than the default 64 KiB of dynamic LDS per workgroup
+        HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (PAN_POS + 1)));
+        net->pan_attr_set = true;
+    }
+    const int n_pairs = (B + 1) / 2, tiles = (B + 63) / 64;
+    const PanLayer &g0 = net->pan.front().g, &gl = net->pan.back().g;
+    hipLaunchKernelGGL(k_pan_turn<true>, dim3((unsigned)((g0.in_pos + 63) / 64), (unsigned)tiles), dim3(256), 0, stream,
+                       (float *)d_X0, B, net->layers[0].n_in, B, (float2 *)ping, g0.in_pos, (const int32_t *)nullptr);
+    HIP_TRY(net, hipGetLastError());
+    for (const sdnn_net::Pan &f : net->pan) {
+        PanForward a;
+        a.stream = f.stream; a.seg = f.seg; a.ends = f.ends; a.bias = f.bias; a.in = (const float2 *)ping; a.out = (float2 *)pong;
+        a.stream_bytes = (uint32_t)(f.g.halves * LDS_HALF_BYTES);
+        a.in_pos = f.g.in_pos; a.out_pos = f.g.out_pos; a.panel = f.g.panel; a.n_panels = f.g.n_panels;
+        a.range = f.g.range; a.n_ranges = f.g.n_ranges; a.nb = f.g.nb; a.n_pairs = n_pairs; a.cap = net->cfg.act_cap;
+        void *args[] = {(void *)&a};
+        HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)((n_pairs + 7) / 8 * 8 * f.g.n_ranges)), dim3(64 * LDS_WAVES), args,
+                                     8 * ((size_t)f.g.panel + 1), stream));
+        std::swap(ping, pong);
+    }
+    hipLaunchKernelGGL(k_pan_turn<false>, dim3((unsigned)((gl.out_pos + 63) / 64), (unsigned)tiles), dim3(256), 0, stream,
+                       d_XL, B, net->layers.back().n_out, B, (float2 *)ping, gl.out_pos, (const int32_t *)net->pan.back().rows);
+    HIP_TRY(net, hipGetLastError());
+    net->B = B;
+    net->state = ST_FORWARD;
+    return SDNN_OK;
+}
+
 // `ld`: floats per row of the activations between the layers.
 static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL, void *stream_, float *ping,
                         float *pong, int ld)
@@ -3408,7 +3838,11 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
     const int L = net->n_layers;
     // a workgroup reads and writes columns of its own: d_XL may be d_X0 itself, but not lie across it
     const bool shifted = d_XL && d_XL != d_X0 && overlap(d_X0, net->layers[0].n_in, d_XL, net->layers[L - 1].n_out, B);
-    if (const int T = shifted ? 0 : lds_forward_samples(net, B)) {
+    double other = 0.0;
+    const int T = lds_forward_samples(net, B, net->pan.empty() ? nullptr : &other);
+    if (ping == net->d_ping && pan_forward_pays(net, B, other)) // (in the workspace's buffers: what it keeps there is larger than X)
+        return forward_pan(net, d_X0, B, d_XL, stream, ping, pong);
+    if (T && !shifted) {
         const bool sig = net->cfg.activation == ACT_SIGMOID;
         const int ti = T == 1 ? 0 : T == 2 ? 1 : 2;
         static const void *const fns[2][3] = {
@@ -3982,6 +4416,7 @@ extern "C" int sdnn_set_weights(sdnn_net *net, int32_t layer, const float *d_val
     if (!rc && d_values && net->b1) rc = launch_b1_fill(net, layer - 1, 0, (hipStream_t)stream_);
     if (!rc && (d_values || d_bias) && net->lm) // keep the lane-major copy current
         rc = launch_lm_fill(net, layer - 1, nullptr, 0, (hipStream_t)stream_);
+    if (!rc && (d_values || d_bias) && !net->pan.empty()) rc = launch_pan_fill(net, layer - 1, (hipStream_t)stream_);
     return rc;
 }
 

@@ -2,6 +2,7 @@
 #pragma once
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 #include "../../include/sdnn.h"
 
@@ -46,3 +47,26 @@ struct LayerDev {
     const int2 *b1_row[2];    // [64 b1_blocks]: {row, entries} of a lane, row -1 past the last row
     int4 *b1_lm[2];
 };
+
+// One layer as k_fwd_pan walks it: its operand in panels, its rows in ranges.
+struct PanLayer {
+    int32_t panel_cols, panel, n_panels, in_pos;      // neurons and positions per panel; positions of the operand
+    int32_t range_rows, range, n_ranges, nb, out_pos; // rows and positions per range; blocks of 64 rows per wavefront
+    size_t halves;                                    // room for the stream, in halves of eight slots
+};
+#define PAN_WAVES 16
+#define PAN_POS 16384  // positions of a panel (two samples: 128 KiB of LDS) and of a range (64 registers per lane)
+#define PAN_MAX 16     // panels at most
+#define PAN_SLOTS 1.75 // room for so many slots per entry; a layout that needs more is not used
+// below: the layer before this one, NULL for the first (its operand is stored in the order of its neurons)
+void sdnn_pan_geometry(const sdnn_layer &y, const PanLayer *below, PanLayer &g);
+// Which row sits where in that layer's stream, see k_fwd_pan.  rows [out_pos]: row or -1; pos [n_out]; seg [ranges][wavefronts]
+// [panels + 1] and slot [ranges][wavefronts][panels][nb + 1]: where panels (in halves) and blocks (in slots) start; ends: a byte
+// per half.  fullest: entries in the fullest panel; depth: slots of the deepest wavefront, panel by panel.
+struct PanLayout {
+    std::vector<int32_t> rows, pos, seg, slot;
+    std::vector<uint8_t> ends;
+    int64_t fullest = 0;
+    double depth = 0;
+};
+void sdnn_pan_layout(const sdnn_layer &y, const PanLayer &g, PanLayout &out);

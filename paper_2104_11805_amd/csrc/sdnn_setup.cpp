@@ -208,4 +208,154 @@ extern "C" int sdnn_deal_rows_to_xcds(int32_t n_rows, const int32_t *row_ptr, co
     return SDNN_OK;
 }
 
+void sdnn_pan_geometry(const sdnn_layer &y, const PanLayer *below, PanLayer &g)
+{
+    auto cut = [](int32_t n, int32_t &parts, int32_t &each) {
+        parts = (n + PAN_POS - 1) / PAN_POS;
+        each = ((n + parts - 1) / parts + 63) & ~63;
+    };
+    if (below) { // a panel is what one range of the layer below has written
+        g.n_panels = below->n_ranges;
+        g.panel_cols = below->range_rows;
+        g.panel = below->range;
+        g.in_pos = below->out_pos;
+    } else {
+        cut(y.n_in, g.n_panels, g.panel_cols);
+        g.panel = g.panel_cols;
+        g.in_pos = y.n_in;
+    }
+    cut(y.n_out, g.n_ranges, g.range_rows);
+    g.nb = (g.range_rows + 64 * PAN_WAVES - 1) / (64 * PAN_WAVES);
+    g.range = 64 * PAN_WAVES * g.nb;
+    g.out_pos = g.n_ranges * g.range;
+    const size_t streams = (size_t)g.n_ranges * PAN_WAVES;
+    g.halves = (size_t)(PAN_SLOTS * (double)y.row_ptr[y.n_out] / 512.0) + streams * ((size_t)g.n_panels * (size_t)(g.nb + 8) / 8 + 7) + 4;
+    g.halves = (g.halves + 3) & ~(size_t)3;
+}
+
+// A wavefront's lanes walk their rows in step, so a block of 64 rows costs as many slots in a panel as its fullest row has
+// entries there.  The rows of a range are halved, again and again, at the median of the panel in which their counts spread most,
+// until 64 are left: their counts are then about equal in every panel (32 entries per row over four panels: 1.10 slots per entry,
+// against 1.76 for rows as they come).
+void sdnn_pan_layout(const sdnn_layer &y, const PanLayer &g, PanLayout &out)
+{
+    const int32_t P = g.n_panels, nb = g.nb;
+    std::vector<int32_t> count((size_t)y.n_out * P, 0), order, len;
+    std::vector<int64_t> per_panel((size_t)P, 0), keys;
+    for (int32_t r = 0; r < y.n_out; ++r) { // columns ascend: a panel's entries end where the next one's begin
+        const int32_t *c = y.col_idx + y.row_ptr[r], *const end = y.col_idx + y.row_ptr[r + 1];
+        for (int32_t p = 0; p < P; ++p) {
+            const int64_t bound = (int64_t)(p + 1) * g.panel_cols;
+            const int32_t *const from = c;
+            while (c < end && *c < bound) ++c;
+            count[(size_t)r * P + p] = (int32_t)(c - from);
+            per_panel[(size_t)p] += c - from;
+        }
+    }
+    out.fullest = *std::max_element(per_panel.begin(), per_panel.end());
+    out.rows.assign((size_t)g.out_pos, -1);
+    out.pos.assign((size_t)y.n_out, 0);
+    out.seg.assign((size_t)g.n_ranges * PAN_WAVES * (P + 1), 0);
+    out.slot.assign((size_t)g.n_ranges * PAN_WAVES * P * (nb + 1), 0);
+    out.ends.clear();
+    out.depth = 0;
+    int32_t at = 0; // slots so far
+    struct Block { int32_t first, n; int64_t slots; };
+    std::vector<Block> blocks;
+    std::vector<int32_t> members[PAN_WAVES];
+    std::vector<int32_t> depth; // [block][panel]
+    for (int32_t q = 0; q < g.n_ranges; ++q) {
+        const int32_t r0 = std::min(y.n_out, q * g.range_rows), r1 = std::min(y.n_out, r0 + g.range_rows);
+        order.resize((size_t)(r1 - r0));
+        std::iota(order.begin(), order.end(), r0);
+        blocks.clear();
+        std::vector<std::pair<int32_t, int32_t>> todo(1, {0, r1 - r0});
+        while (!todo.empty()) {
+            const int32_t a = todo.back().first, b = todo.back().second;
+            todo.pop_back();
+            if (b - a <= 64) {
+                if (b > a) blocks.push_back({a, b - a, 0});
+                continue;
+            }
+            int32_t by = 0;
+            int64_t sum[PAN_MAX] = {}, sq[PAN_MAX] = {};
+            for (int32_t k = a; k < b; ++k) {
+                const int32_t *c = count.data() + (size_t)order[(size_t)k] * P;
+                for (int32_t p = 0; p < P; ++p) {
+                    sum[p] += c[p];
+                    sq[p] += (int64_t)c[p] * c[p];
+                }
+            }
+            double most = -1;
+            for (int32_t p = 0; p < P; ++p) {
+                const double spread = (double)sq[p] - (double)sum[p] * (double)sum[p] / (b - a);
+                if (spread > most) { most = spread; by = p; }
+            }
+            const int32_t m = a + ((b - a + 63) / 64 + 1) / 2 * 64;
+            keys.resize((size_t)(b - a)); // fullest first, ties by row
+            for (int32_t k = a; k < b; ++k) keys[(size_t)(k - a)] = (int64_t)-count[(size_t)order[(size_t)k] * P + by] * ((int64_t)1 << 32) + order[(size_t)k];
+            std::nth_element(keys.begin(), keys.begin() + (m - a), keys.end());
+            for (int32_t k = a; k < b; ++k) order[(size_t)k] = (int32_t)(uint32_t)keys[(size_t)(k - a)];
+            todo.push_back({m, b});
+            todo.push_back({a, m});
+        }
+        depth.assign(blocks.size() * P, 1); // every block has a slot in every panel, after which the next one's turn follows
+        for (size_t k = 0; k < blocks.size(); ++k)
+            for (int32_t p = 0; p < P; ++p) {
+                int32_t &d = depth[k * P + p];
+                for (int32_t i = 0; i < blocks[k].n; ++i) d = std::max(d, count[(size_t)order[(size_t)(blocks[k].first + i)] * P + p]);
+                blocks[k].slots += d;
+            }
+        // dealt to the wavefronts, the deepest first, each to the one with the fewest slots so far
+        std::vector<int32_t> by_depth(blocks.size());
+        std::iota(by_depth.begin(), by_depth.end(), 0);
+        std::stable_sort(by_depth.begin(), by_depth.end(), [&](int32_t u, int32_t v) { return blocks[u].slots > blocks[v].slots; });
+        int64_t load[PAN_WAVES] = {};
+        for (auto &m : members) m.clear();
+        for (int32_t k : by_depth) {
+            int w = -1;
+            for (int i = 0; i < PAN_WAVES; ++i)
+                if ((int32_t)members[i].size() < nb && (w < 0 || load[i] < load[w])) w = i;
+            load[w] += blocks[k].slots;
+            members[w].push_back(k);
+        }
+        std::vector<int64_t> deepest((size_t)P, 0);
+        for (int w = 0; w < PAN_WAVES; ++w) {
+            at = (at + 31) & ~31; // a multiple of four halves
+            for (size_t j = 0; j < members[w].size(); ++j) {
+                const Block &b = blocks[members[w][j]];
+                for (int32_t i = 0; i < b.n; ++i) {
+                    const int32_t local = 64 * (PAN_WAVES * (int32_t)j + w) + i, row = order[(size_t)(b.first + i)];
+                    out.rows[(size_t)(q * g.range + local)] = row;
+                    out.pos[(size_t)row] = q * g.range + local;
+                }
+            }
+            int32_t *seg = out.seg.data() + (size_t)(q * PAN_WAVES + w) * (P + 1);
+            for (int32_t p = 0; p < P; ++p) {
+                const int32_t from = at;
+                int32_t *slot = out.slot.data() + ((size_t)(q * PAN_WAVES + w) * P + p) * (nb + 1);
+                seg[p] = at / 8;
+                out.ends.resize((size_t)at / 8 + 1, 0);
+                for (int32_t j = 0; j < nb; ++j) {
+                    slot[j] = at;
+                    if (j >= (int32_t)members[w].size()) continue;
+                    at += depth[(size_t)members[w][j] * P + p];
+                    out.ends.resize((size_t)(at - 1) / 8 + 1, 0);
+                    if (j + 1 < (int32_t)members[w].size()) out.ends[(size_t)(at - 1) / 8] |= (uint8_t)(1u << ((at - 1) & 7));
+                }
+                if (members[w].empty()) at += 1; // a wavefront without rows takes part in the barriers
+                const int32_t used = std::max<int32_t>(1, (int32_t)members[w].size());
+                at = p < P - 1 ? (at + 7) & ~7 : (at + 15) & ~15; // a whole half; at the end an even number of them
+                for (int32_t j = used; j <= nb; ++j) slot[j] = at; // the last block's slots are filled up to a batch
+                deepest[(size_t)p] = std::max<int64_t>(deepest[(size_t)p], at - from);
+            }
+            seg[P] = at / 8;
+        }
+        double d = 0;
+        for (int64_t v : deepest) d += (double)v;
+        out.depth = std::max(out.depth, d);
+    }
+    out.ends.resize(((size_t)at + 31) / 32 * 4, 0);
+}
+
 extern "C" const char *sdnn_version(void) { return "sdnn 0.1 (gfx950)"; }

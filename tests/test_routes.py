@@ -140,3 +140,35 @@ def test_more_results_than_a_launch_has_threads():
             rc, log = net("sdnn_forward", X0, B, XL, None)
             assert rc == 0 and len(log) == 1 and log[0].startswith(kernel), (B, log, sdnn.last_error(net.h))
     """)
+
+
+def test_forward_in_panels():
+    """Which passes go in panels: those of tests/test_gpu_pan_forward.py, and where that path was measured faster than the others
+    by 7 % and more (32 entries per row, 24 layers); not with links that stay within one panel, over two layers, in the fixed
+    staging array, where the caller asks for other layouts, or with one sample."""
+    routes.run("""
+        from tests import pan_nets
+        def spread(n, n_in, links):
+            ci = np.sort((np.arange(links) * (n_in // links) + np.random.default_rng(n).integers(0, n_in // links, (n, links))), axis=1)
+            return n, n_in, np.arange(0, n * links + 1, links, dtype=np.int32), ci.astype(np.int32).ravel(), np.ones(n * links, np.float32), None
+        def pans(net, B, call="sdnn_forward"):
+            rc, log = net(call, X0, B, XL, None)
+            assert rc == 0, sdnn.last_error(net.h)
+            n = sum(l.startswith("k_fwd_pan<") for l in log)
+            assert n in (0, len(net.keep)) and (n == 0 or (len(log) == n + 2 and log[0].startswith("k_pan_turn<true>"))), log
+            return n > 0
+        for widths, b, lengths in pan_nets.NETS:
+            net = Net([(y.n_out, y.n_in, y.row_ptr, y.col_idx, y.values, y.bias) for y in pan_nets.layers(widths, lengths)], b)
+            assert pans(net, b) and not pans(net, 1)
+            lib.sdnn_destroy(net.h)
+        for n, yes, no in [(16384, (), (512, 1024)), (20001, (512, 700, 1024), (1, 33, 64, 100)), (25000, (200, 512, 700, 1024), (33, 64)),
+                           (32768, (100, 150, 256, 300, 400, 512, 1024), (33, 64)), (40000, (100, 200, 512, 1024), (33, 64)), (65536, (100, 150, 256, 1024), (33, 64))]:
+            net = Net([spread(n, n, 32)] * 24, 1024)
+            assert [pans(net, B) for B in yes + no] == [True] * len(yes) + [False] * len(no), (n, [(B, pans(net, B)) for B in yes + no])
+            lib.sdnn_destroy(net.h)
+        assert not pans(Net([layer(40000, 40000, (32,))] * 4, 512), 512)
+        assert not pans(Net([spread(40000, 40000, 32)] * 2, 512), 512)
+        assert not pans(Net([spread(40000, 40000, 32)] * 4, 512), 50, "sdnn_forward_noalloc")
+        for options in (dict(lds_forward=-1), dict(panel_cols=8192), dict(reorder_rows=1), dict(training=True)):
+            assert not pans(Net([spread(40000, 40000, 32)] * 3, 512, **options), 512)
+    """)
