@@ -22,6 +22,8 @@
 //     (k_spread_vals).
 //   * inference on layers of up to 32768 neurons: one launch, activations in LDS
 //     (k_fwd_lds).
+//   * training on narrow layers: one launch per pass, activations in LDS
+//     (k_train_lds).
 //   * inference on wider layers: a launch per layer, a panel of the activations in LDS
 //     at a time (k_fwd_pan).
 //   * inference on large activation blocks goes through all layers in
@@ -1228,6 +1230,207 @@ __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ lay
             else pk[k >> 1] = pos;
         }
         if (with_cols) o[0] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+        o[64] = make_uint4(wt[0], wt[1], wt[2], wt[3]);
+        o[128] = make_uint4(wt[4], wt[5], wt[6], wt[7]);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// K1t / K2t: training on nets so narrow that a launch per layer is bound by its chain of dependent loads: the whole forward pass
+// (MODE 0, Eq. 3 for l = 1..L) or the whole back-propagation (MODE 1, Eq. 7 for l = L..2) in one launch.  A workgroup of
+// 16 wavefronts takes one sample through all layers as k_fwd_lds<1> does, over lane-major copies of W and of W^T that follow the
+// stepped values (k_train_fill); the gradient is formed by k_update as before.  The activations of up to 2048 neurons lie in LDS
+// twice, so a layer's results replace nothing that is still read and one barrier ends a layer (the positions of every other step
+// are stored 2048 higher).  Both passes keep a layer's neurons in the same order, that of the rows of W_{l+1}^T by length, so that
+// a sample's X_l and Delta_l are stored and read back in whole lines [step][sample][position]; k_train_turn then brings them to where
+// the other kernels expect them.  (Stored there at once, four bytes a line, the passes took 3.5 and 4.6 us per layer.)  Every
+// lane adds its row's terms in storage order: same bits as k_spmm.
+//
+// What bounds it: per layer of 1024 neurons of 32 entries 1.5 us of LDS reads, 1.3 us of the stream of W, and the barrier; 2.4 us
+// forward, 3.0 back (columns of 16 to 50 entries in chunks of sixteen), where a launch per layer took 4.8 and 5.7.  The copies come
+// from HBM, and a workgroup that waits for a line holds up everyone on its XCD: workgroups on the compute units that the samples
+// leave idle read the copy through once as fast as they can, so that it comes from the memory-side cache (a step of 120 layers whose
+// arrays are not on chip, 64 samples: 1277 -> 970 us; 1400 with a launch per layer).
+// ---------------------------------------------------------------------------
+#define TRAIN_LDS_POS 2048 // neurons at most: two blocks per wavefront
+struct TrainLds {
+    const LayerDev *layers;
+    const LmLayer *tab, *tab_x; // per step: layer 1.. (MODE 0), layer L.. down to 2 (MODE 1); and those of MODE 0
+    const int32_t *cs;
+    const uint4 *lm;
+    const float *bias;          // MODE 0: by position
+    float *out;                 // [step][max_batch][position]
+    const float *x;             // MODE 1: what MODE 0 has stored there
+    unsigned lm_bytes;
+    int32_t n_steps, n_layers, max_batch, ld, B;
+    float cap;
+};
+template <int MODE, int ACT>
+__global__ void __launch_bounds__(64 * LDS_WAVES) k_train_lds(const TrainLds a)
+{
+    __shared__ float act[2 * TRAIN_LDS_POS + 1];
+    typedef __attribute__((address_space(3))) float *lds_ptr;
+    typedef __attribute__((address_space(3))) char *lds_bytes;
+    const lds_bytes base = (lds_bytes)(lds_ptr)act;
+    typedef const LmLayer __attribute__((address_space(4))) *tab_ptr;
+    typedef const int32_t __attribute__((address_space(4))) *cs_ptr;
+    const tab_ptr tab = (tab_ptr)a.tab, tab_x = (tab_ptr)a.tab_x;
+    const cs_ptr cs = (cs_ptr)a.cs;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if ((int)blockIdx.x >= a.B) { // on compute units that the samples leave idle: the copy of W into the memory-side cache at once
+        const uint4 *p = a.lm;
+        const size_t n = a.lm_bytes / 16, stride = (size_t)(gridDim.x - a.B) * blockDim.x;
+        for (size_t i = (size_t)(blockIdx.x - a.B) * blockDim.x + tid; i < n; i += 8 * stride) {
+            unsigned t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = i + u * stride < n ? p[i + u * stride].x : 0u;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) asm volatile("" ::"v"(t[u]));
+        }
+        return;
+    }
+    // neighbouring samples share cache lines of the input: an XCD takes a contiguous stretch of them
+    const int nwg = a.B, per = nwg >> 3, wg = (int)blockIdx.x;
+    const int s = wg < 8 * per ? (wg & 7) * per + (wg >> 3) : wg;
+    unsigned shift = 2;
+    asm("" : "+v"(shift)); // kept in a register for lds_address
+    const __amdgpu_buffer_rsrc_t rlm = make_rsrc((const float *)a.lm, a.lm_bytes);
+    unsigned at = (unsigned)cs[tab[0].cs + wave * (tab[0].nb + 1)] * LDS_CHUNK_BYTES;
+    const int lane16 = 16 * lane;
+    struct Half { u32x4 c, wa, wb; } ha, hb;
+    auto request = [&](Half &h) {
+        h.c = __builtin_amdgcn_raw_buffer_load_b128(rlm, lane16, (int)at, 0);
+        h.wa = __builtin_amdgcn_raw_buffer_load_b128(rlm, lane16 + 1024, (int)at, 0);
+        h.wb = __builtin_amdgcn_raw_buffer_load_b128(rlm, lane16 + 2048, (int)at, 0);
+        at += LDS_HALF_BYTES;
+    };
+    request(ha);
+    request(hb);
+    {
+        const LayerDev &L = a.layers[MODE == 0 ? 0 : a.n_layers - 1];
+        const int n = MODE == 0 ? L.n_in : L.n_out;
+        const float *in = MODE == 0 ? L.X_prev : L.D;
+        for (int i = tid; i < n; i += 64 * LDS_WAVES) act[i] = in[(size_t)i * a.ld + s];
+    }
+    if (tid == 0) act[2 * TRAIN_LDS_POS] = 0.0f; // where the slots past the end of a row point
+    __syncthreads();
+    for (int k = 0; k < a.n_steps; ++k) {
+        const int nb = tab[k].nb, cs0 = tab[k].cs + wave * (nb + 1), pos0 = 64 * wave + lane;
+        // what this lane's results wait for: biases, or the X_l that the derivative is taken from (step a.n_layers - 2 - k of MODE 0)
+        const float *aux = MODE == 0 ? a.bias + tab[k].pos : a.x + (size_t)tab_x[a.n_layers - 2 - k].pos * a.max_batch + (size_t)s * tab[k].n_pos;
+        float *out = a.out + (size_t)tab[k].pos * a.max_batch + (size_t)s * tab[k].n_pos;
+        float *next = act + ((k + 1) & 1) * TRAIN_LDS_POS;
+        for (int j = 0; j < nb; ++j) {
+            const float e = aux[pos0 + 1024 * j];
+            double acc = 0.0;
+            auto take = [&](Half &h) { // eight entries; then their registers are free for the half after next
+                unsigned ad[8];
+                double w[8];
+                float x[8];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    ad[2 * u] = lds_address<0>(h.c[u], shift);
+                    ad[2 * u + 1] = lds_address<1>(h.c[u], shift);
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = *(lds_ptr)(base + ad[u]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    w[u] = (double)__uint_as_float(h.wa[u]);
+                    w[u + 4] = (double)__uint_as_float(h.wb[u]);
+                }
+                request(h);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc = fma(w[u], (double)x[u], acc);
+            };
+            for (int i = cs[cs0 + j + 1] - cs[cs0 + j]; i > 0; --i) {
+                take(ha);
+                __builtin_amdgcn_sched_barrier(0);
+                take(hb);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const float r = MODE == 0 ? act_apply(ACT, acc + (double)e, a.cap) : act_backprop(ACT, acc, e, a.cap);
+            next[pos0 + 1024 * j] = r;
+            out[pos0 + 1024 * j] = r;
+        }
+        lds_barrier(); // the layer is complete before anyone reads it
+    }
+}
+
+// From [step][max_batch][position] to X_l (MODE 0) or Delta_{l-1} (MODE 1), [neuron][ld]: tiles of 64 positions and 64 samples
+// through LDS, zeros for the samples that fill up the batch.  grid = (tiles of positions, tiles of samples, steps).
+template <int MODE>
+__global__ void __launch_bounds__(256) k_train_turn(const LayerDev *__restrict__ layers, int n_layers, int step0, const LmLayer *__restrict__ tab,
+                                                    const int32_t *__restrict__ rows, const float *__restrict__ from, int max_batch, int ld, int B, int Bp)
+{
+    __shared__ float tile[64][65];
+    const int k = step0 + (int)blockIdx.z, tid = threadIdx.x, p0 = 64 * blockIdx.x, s0 = 64 * blockIdx.y;
+    const LmLayer t = tab[k];
+    if (p0 >= t.n_pos) return;
+    float *out = MODE == 0 ? layers[k].X : layers[n_layers - 2 - k].D;
+    const float *in = from + (size_t)t.pos * max_batch;
+    for (int i = tid; i < 4096; i += 256) {
+        const int p = i & 63, s = i >> 6;
+        tile[s][p] = s0 + s < B ? in[(size_t)(s0 + s) * t.n_pos + p0 + p] : 0.0f;
+    }
+    __syncthreads();
+    for (int i = tid; i < 4096; i += 256) {
+        const int s = i & 63, p = i >> 6, row = rows[t.pos + p0 + p];
+        if (row >= 0 && s0 + s < Bp) out[(size_t)row * ld + s0 + s] = tile[s][p];
+    }
+}
+
+// Writes the weights of the steps' copies from the CSR values (COLS: and the positions of the operand), and the biases by position:
+// steps step0 .. step0 + n_steps - 1, eight steps to a row of the grid, each on an XCD of its own (MODE 1 reads a layer's values in
+// any order: by all XCDs 77 us for 120 layers of 1024 neurons).  grid = (8 max_nb wavefronts, eights of steps).  pos: the positions of every step's rows, step after step; first[k]: where
+// step k's start.
+template <int MODE, bool COLS>
+__global__ void __launch_bounds__(256) k_train_fill(const LayerDev *__restrict__ layers, int n_layers, int step0, int n_steps, const LmLayer *__restrict__ tab,
+                                                    const int32_t *__restrict__ cs, uint4 *__restrict__ lm, const int32_t *__restrict__ rows,
+                                                    const int32_t *__restrict__ pos, const int32_t *__restrict__ first, float *__restrict__ bias)
+{
+    const int step = 8 * (int)blockIdx.y + (int)(blockIdx.x & 7u), k = step0 + step, w = (int)(blockIdx.x >> 3) & (LDS_WAVES - 1);
+    const int j = (int)(blockIdx.x >> 3) / LDS_WAVES, lane = threadIdx.x & 63;
+    if (step >= n_steps) return;
+    const int nb = tab[k].nb;
+    if (j >= nb) return;
+    const LayerDev &L = layers[MODE == 0 ? k : n_layers - 1 - k];
+    const int at = tab[k].pos + 64 * (LDS_WAVES * j + w) + lane, row = rows[at];
+    const int c0 = cs[tab[k].cs + w * (nb + 1) + j], c1 = cs[tab[k].cs + w * (nb + 1) + j + 1];
+    const int32_t *ptr = MODE == 0 ? L.row_ptr : L.t_row_ptr, *idx = MODE == 0 ? L.col_idx : L.t_row_idx;
+    int beg = 0, end = 0;
+    if (row >= 0) {
+        beg = ptr[row];
+        end = ptr[row + 1];
+    }
+    if (MODE == 0 && threadIdx.x < 64) bias[at] = row >= 0 ? L.bias[row] : 0.0f;
+    for (int hf = threadIdx.x >> 6; hf < 2 * (c1 - c0); hf += 4) {
+        uint4 *o = lm + ((size_t)c0 * LDS_CHUNK_BYTES + (size_t)hf * LDS_HALF_BYTES) / 16 + lane;
+        unsigned pk[4], wt[8];
+        int from[8]; // where the values are
+        const int e0 = beg + hf * 8;
+        if (MODE == 1 && e0 + 8 <= end) {
+            const I4 a = *(const I4 *)(L.t_perm + e0), b = *(const I4 *)(L.t_perm + e0 + 4);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { from[u] = a.v[u]; from[u + 4] = b.v[u]; }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) from[u] = e0 + u >= end ? 0 : MODE == 0 ? e0 + u : L.t_perm[e0 + u];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int e = e0 + u;
+            unsigned p = 2 * TRAIN_LDS_POS;
+            wt[u] = 0;
+            if (e < end) {
+                wt[u] = __float_as_uint(L.vals[from[u]]);
+                if (COLS) p = (unsigned)((k & 1) * TRAIN_LDS_POS + (k > 0 ? pos[first[k - 1] + idx[e]] : idx[e]));
+            }
+            if (u & 1) pk[u >> 1] |= p << 16;
+            else pk[u >> 1] = p;
+        }
+        if (COLS) o[0] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
         o[64] = make_uint4(wt[0], wt[1], wt[2], wt[3]);
         o[128] = make_uint4(wt[4], wt[5], wt[6], wt[7]);
     }
@@ -2494,6 +2697,15 @@ struct sdnn_net {
     size_t lm_chunks = 0;
     int32_t lm_max_pos = 0;
     bool lds_part_attr_set = false;
+    struct Train {                   // a copy of W (0) or W^T (1) for k_train_lds
+        std::vector<LmLayer> tab;    // empty: there is none
+        LmLayer *d_tab = nullptr;
+        int32_t *cs = nullptr, *row = nullptr, *pos = nullptr, *first = nullptr;
+        uint4 *lm = nullptr;
+        float *bias = nullptr, *out = nullptr;
+        size_t chunks = 0;
+        int32_t max_nb = 0;
+    } train[2];
     bool pan_attr_set = false;
     struct Pan {                     // a layer's copy of W for k_fwd_pan
         PanLayer g{};
@@ -2579,6 +2791,11 @@ struct Plan {
         size_t pan_stream, pan_seg, pan_slot, pan_rows, pan_pos, pan_ends, pan_bias;
     };
     bool pan = false;            // a copy of W for k_fwd_pan
+    struct Train {               // the copies of W and W^T for k_train_lds
+        std::vector<LmLayer> tab;
+        size_t n_cs = 0, n_pos = 0, n_rows = 0, n_chunks = 0, d_tab = 0, cs = 0, row = 0, pos = 0, first = 0, lm = 0, bias = 0, out = 0;
+    } train[2];
+    bool train_lds = false;
     std::vector<PerLayer> pl;
     size_t b1_chunk_bytes = 0;   // 0: no lane-major copies for one sample per step
     std::vector<LmLayer> lm_tab; // empty: no lane-major copy
@@ -2803,6 +3020,52 @@ static void plan_b1(const sdnn_layer *layers, int32_t n_layers, const sdnn_confi
     if (fits) pl.b1_chunk_bytes = wide ? 4096 : 3072;
 }
 
+// Training with a launch per pass (k_train_lds): narrow nets of short rows, whose gradient is not formed in the backward sweep; four
+// layers and more (a step launches two kernels more, to bring the copies up to date).
+// Fills in the tables' sizes; the chunks are a bound (the columns may not be known here): the first block of a copy is no deeper
+// than its longest row, every later one no deeper than the mean of the 64 rows before it.
+#define TRAIN_LDS_MAX_ROW 512
+// Seconds a layer: a launch per layer and pass takes 4.2 (forward) and 5.0 us (back-propagation) besides its gathers; a step of a
+// single launch 1.9 besides its entries (barrier, turning the samples around, bringing the copies up to date).  Measured, us per
+// training step, 48 layers of 32 entries per row, a launch per layer / single: 1024 neurons 535 / 396 (2 samples), 569 / 388 (64), 809 / 539
+// (256); 1201 neurons 599 / 459 (64); 1450 neurons 582 / 536 (2), 615 / 523 (64), 952 / 899 (256); 1800 neurons 594 / 622 (2),
+// 631 / 600 (64); 2048 neurons 604 / 671 (2), 631 / 647 (64).
+#define TRAIN_PER_LAYER(o) ((o) ? 5.0e-6 : 4.2e-6)
+#define TRAIN_STEP 1.9e-6
+static void plan_train(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, Plan &pl)
+{
+    pl.train_lds = false;
+    if (!cfg->training || cfg->max_batch < 2 || cfg->max_batch > 256 || n_layers < 4 || cfg->lds_forward == SDNN_LDS_OFF || cfg->panel_cols > 0 ||
+        cfg->reorder_rows || grad_buffers_wanted(layers, n_layers, cfg))
+        return;
+    for (int32_t l = 0; l < n_layers; ++l) {
+        const sdnn_layer &y = layers[l];
+        if (y.n_out < 1 || y.n_in < 1 || y.n_out > TRAIN_LDS_POS || y.n_in > TRAIN_LDS_POS) return;
+        for (int32_t r = 0; r < y.n_out; ++r)
+            if (y.row_ptr[r + 1] - y.row_ptr[r] > TRAIN_LDS_MAX_ROW) return;
+    }
+    for (int o = 0; o < 2; ++o) {
+        Plan::Train &t = pl.train[o];
+        for (int32_t k = 0; k < n_layers - o; ++k) {
+            const sdnn_layer &y = layers[o ? n_layers - 1 - k : k];
+            const int32_t n = o ? y.n_in : y.n_out;
+            LmLayer e;
+            e.nb = (n + 64 * LDS_WAVES - 1) / (64 * LDS_WAVES);
+            e.n_pos = 64 * LDS_WAVES * e.nb;
+            e.cs = (int32_t)t.n_cs;
+            e.pos = (int32_t)t.n_pos;
+            t.tab.push_back(e);
+            t.n_cs += (size_t)LDS_WAVES * (size_t)(e.nb + 1);
+            t.n_pos += (size_t)e.n_pos;
+            t.n_rows += (size_t)n;
+            const size_t nnz = (size_t)y.row_ptr[y.n_out], blocks = ((size_t)n + 63) / 64;
+            t.n_chunks += TRAIN_LDS_MAX_ROW / LDS_CHUNK + (nnz / 64 + 15 * blocks) / LDS_CHUNK + 1;
+        }
+        if (t.n_chunks * LDS_CHUNK_BYTES >= ((size_t)1 << 32)) return; // the kernel addresses a copy with 32-bit offsets
+    }
+    pl.train_lds = true;
+}
+
 // The forward in panels (k_fwd_pan) is set up for inference nets wider than a panel, of at least three layers (the two passes that
 // turn the samples around take about as long as a layer), with at least four entries per row and panel in the mean, made for
 // batches that can fill the chip (pan_forward_pays).  Fills in the layers' geometry.
@@ -2879,6 +3142,7 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
     plan_b1(layers, n_layers, cfg, pl);
     const bool b1 = pl.b1_chunk_bytes != 0;
     pl.pan = pan_wanted(layers, n_layers, cfg, pl.pl);
+    plan_train(layers, n_layers, cfg, pl);
     size_t paired = 0; // floats of the largest block of activations between its layers
     if (pl.pan) {
         for (int32_t l = 0; l < n_layers; ++l) paired = std::max(paired, (size_t)std::max(pl.pl[l].pan.in_pos, pl.pl[l].pan.out_pos));
@@ -2929,6 +3193,17 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
             PLAN_KIND(mid_dst, 4 * nnz[l])
             PLAN_KIND(mid_loc, 2 * nnz[l])
             PLAN_KIND(mid, 4 * nnz[l])
+        }
+        for (Plan::Train &t : pl.train) {
+            if (!pl.train_lds) break;
+            t.lm = take(LDS_CHUNK_BYTES * (t.n_chunks + 1)); // a wavefront requests one chunk past its last
+            t.cs = take(4 * t.n_cs);
+            t.d_tab = take(sizeof(LmLayer) * t.tab.size());
+            t.row = take(4 * t.n_pos);
+            t.pos = take(4 * t.n_rows);
+            t.first = take(4 * t.tab.size());
+            t.bias = take(4 * t.n_pos);
+            t.out = take(4 * t.n_pos * mb);
         }
         if (b1) {
             PLAN_KIND(b1_cs[0], 4 * ((size_t)q.b1_blocks[0] + 1))
@@ -2987,6 +3262,49 @@ static int launch_lm_fill(sdnn_net *net, int l, const int32_t *prev_pos, int wit
     hipLaunchKernelGGL(k_lm_fill, dim3((unsigned)net->lm_tab[l].nb, LDS_WAVES, fill_parts(net->max_len[0][l])), dim3(64), 0, stream, net->d_layers + l, net->lm_layers + l,
                        net->lm_cs, net->lm, net->lm_bias, net->lm_row, prev_pos, with_cols, net->lm_max_pos);
     HIP_TRY(net, hipGetLastError());
+    return SDNN_OK;
+}
+
+// (Re)writes the copies for k_train_lds from the CSR arrays: those of layer l, or of all (l < 0).
+static int launch_train_fill(sdnn_net *net, int l, bool cols, hipStream_t stream)
+{
+    for (int o = 0; o < 2; ++o) {
+        const sdnn_net::Train &t = net->train[o];
+        const int n = (int)t.tab.size(), from = l < 0 ? 0 : o ? net->n_layers - 1 - l : l, to = l < 0 ? n : std::min(n, from + 1);
+        const void *fn = o ? cols ? (const void *)k_train_fill<1, true> : (const void *)k_train_fill<1, false>
+                           : cols ? (const void *)k_train_fill<0, true> : (const void *)k_train_fill<0, false>;
+        for (int k0 = from; k0 < to; k0 += 65536) {
+            const int n_steps = std::min(65536, to - k0);
+            void *args[] = {(void *)&net->d_layers, (void *)&net->n_layers, (void *)&k0, (void *)&n_steps, (void *)&t.d_tab, (void *)&t.cs, (void *)&t.lm, (void *)&t.row,
+                            (void *)&t.pos, (void *)&t.first, (void *)&t.bias};
+            HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)(8 * LDS_WAVES * t.max_nb), (unsigned)((n_steps + 7) / 8)), dim3(256), args, 0, stream));
+        }
+    }
+    return SDNN_OK;
+}
+
+// Whether the passes over B samples go through k_train_lds.
+static bool train_lds(const sdnn_net *net, int B) { return B > 1 && B <= net->n_cu && !net->train[0].tab.empty(); }
+
+static int launch_train_lds(sdnn_net *net, int o, int B, int Bp, int ld, hipStream_t stream)
+{
+    const sdnn_net::Train &t = net->train[o];
+    TrainLds a;
+    a.layers = net->d_layers; a.tab = t.d_tab; a.tab_x = net->train[0].d_tab; a.cs = t.cs; a.lm = t.lm; a.bias = t.bias; a.out = t.out;
+    a.x = net->train[0].out; a.lm_bytes = (unsigned)(LDS_CHUNK_BYTES * (t.chunks + 1));
+    a.n_steps = (int)t.tab.size(); a.n_layers = net->n_layers; a.max_batch = net->cfg.max_batch; a.ld = ld; a.B = B; a.cap = net->cfg.act_cap;
+    const bool sig = net->cfg.activation == ACT_SIGMOID;
+    const void *fn = o ? sig ? (const void *)k_train_lds<1, ACT_SIGMOID> : (const void *)k_train_lds<1, ACT_RELU_CAP>
+                       : sig ? (const void *)k_train_lds<0, ACT_SIGMOID> : (const void *)k_train_lds<0, ACT_RELU_CAP>;
+    void *args[] = {(void *)&a};
+    HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)(B + std::min(128, std::max(0, net->n_cu - B)))), dim3(64 * LDS_WAVES), args, 0, stream));
+    fn = o ? (const void *)k_train_turn<1> : (const void *)k_train_turn<0>;
+    for (int k0 = 0; k0 < a.n_steps; k0 += 65535) {
+        void *targs[] = {(void *)&net->d_layers, (void *)&net->n_layers, (void *)&k0, (void *)&t.d_tab, (void *)&t.row, (void *)&t.out,
+                         (void *)&net->cfg.max_batch, (void *)&ld, (void *)&B, (void *)&Bp};
+        HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)(LDS_WAVES * t.max_nb), (unsigned)((Bp + 63) / 64), (unsigned)std::min(65535, a.n_steps - k0)),
+                                     dim3(256), targs, 0, stream));
+    }
     return SDNN_OK;
 }
 
@@ -3076,12 +3394,24 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
         int rc = SDNN_OK;
     };
     const bool want_lm = !pl.lm_tab.empty();
+    struct { std::vector<int32_t> cs, row, pos, first; } tl[2];
     std::vector<int32_t> lm_cs, lm_row, lm_pos;
     std::vector<size_t> lm_first_row((size_t)n_layers, 0); // where a layer's part of lm_pos starts
     try {
         lm_cs.resize(pl.lm_n_cs);
         lm_row.resize(pl.lm_n_pos);
         lm_pos.resize(pl.lm_n_rows);
+        for (int o = 0; o < (pl.train_lds ? 2 : 0); ++o) {
+            const Plan::Train &t = pl.train[o];
+            tl[o].cs.resize(t.n_cs);
+            tl[o].row.resize(t.n_pos);
+            tl[o].pos.resize(t.n_rows);
+            tl[o].first.resize(t.tab.size(), 0);
+            for (size_t k = 1; k < t.tab.size(); ++k) {
+                const sdnn_layer &y = layers[o ? n_layers - (int32_t)k : (int32_t)k - 1];
+                tl[o].first[k] = tl[o].first[k - 1] + (o ? y.n_in : y.n_out);
+            }
+        }
     } catch (...) {
         return fail_free(fail(nullptr, SDNN_ENOMEM, "host allocation failed"));
     }
@@ -3185,6 +3515,16 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
             if (want_lm) {
                 const LmLayer &t = pl.lm_tab[l];
                 lm_deal_blocks(y, t, lm_row.data() + t.pos, lm_pos.data() + lm_first_row[l], lm_cs.data() + t.cs);
+            }
+            if (pl.train_lds) { // the rows of W_l^T by length (l > 1), and those of the last W; the others follow them (below)
+                const int32_t o = l > 0, k = o ? n_layers - 1 - l : n_layers - 1;
+                const LmLayer &t = pl.train[o].tab[(size_t)k];
+                sdnn_layer v = o ? y : layers[n_layers - 1];
+                if (o) {
+                    v.n_out = y.n_in;
+                    v.row_ptr = h.t_row_ptr.data();
+                }
+                lm_deal_blocks(v, t, tl[o].row.data() + t.pos, tl[o].pos.data() + tl[o].first[(size_t)k], tl[o].cs.data() + t.cs);
             }
             if (pl.pan) sdnn_pan_layout(y, pl.pl[l].pan, h.pan);
             h.max_len = h.t_max_len = 0;
@@ -3321,6 +3661,67 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 const int rc_fill = launch_b1_fill(net, l, 1, stream);
                 if (rc_fill) return fail_free(rc_fill);
             }
+        if (pl.train_lds) {
+            // layer l's neurons in the order of the rows of W_{l+1}^T in both passes
+            for (int32_t k = 0; k + 1 < n_layers; ++k) {
+                const LmLayer &t = pl.train[0].tab[(size_t)k], &u = pl.train[1].tab[(size_t)(n_layers - 2 - k)];
+                std::copy_n(tl[1].row.data() + u.pos, t.n_pos, tl[0].row.data() + t.pos);
+                std::copy_n(tl[1].pos.data() + tl[1].first[(size_t)(n_layers - 2 - k)], layers[k].n_out, tl[0].pos.data() + tl[0].first[(size_t)k]);
+                for (int32_t w = 0; w < LDS_WAVES; ++w)
+                    for (int32_t j = 0; j < t.nb; ++j) {
+                        int32_t len = 0;
+                        for (int32_t i = 0; i < 64; ++i) {
+                            const int32_t r = tl[0].row[(size_t)(t.pos + 64 * (LDS_WAVES * j + w) + i)];
+                            if (r >= 0) len = std::max(len, layers[k].row_ptr[r + 1] - layers[k].row_ptr[r]);
+                        }
+                        tl[0].cs[(size_t)(t.cs + w * (t.nb + 1) + j)] = (len + LDS_CHUNK - 1) / LDS_CHUNK;
+                    }
+            }
+            double launches = 0.0, single = 0.0; // what the two passes take with a launch per layer, and with one each
+            bool fits = true;
+            for (int o = 0; o < 2; ++o) {
+                int64_t chunks = 0;
+                for (const int32_t depth : tl[o].cs) chunks += depth;
+                fits &= (size_t)chunks <= pl.train[o].n_chunks;
+                single += (double)pl.train[o].tab.size() * TRAIN_STEP + 3.5e-9 * LDS_CHUNK * (double)chunks;
+                for (int32_t l = o; l < n_layers; ++l) {
+                    launches += TRAIN_PER_LAYER(o) + std::max(4.0 * 64 * net->layers[l].nnz / 20e12, 28e-9 * net->max_len[o][l]);
+                    fits &= net->max_len[o][l] <= TRAIN_LDS_MAX_ROW;
+                }
+            }
+            for (int o = 0; o < (fits && single < launches ? 2 : 0); ++o) {
+                const Plan::Train &t = pl.train[o];
+                sdnn_net::Train &n = net->train[o];
+                int64_t at = 0; // as for the LDS-resident forward below
+                for (int w = 0; w < LDS_WAVES; ++w)
+                    for (const LmLayer &e : t.tab) {
+                        int32_t *c = tl[o].cs.data() + e.cs + w * (e.nb + 1);
+                        for (int32_t j = 0; j <= e.nb; ++j) {
+                            const int32_t depth = c[j];
+                            c[j] = (int32_t)at;
+                            if (j < e.nb) at += depth;
+                        }
+                    }
+                for (const LmLayer &e : t.tab) n.max_nb = std::max(n.max_nb, e.nb);
+                n.d_tab = (LmLayer *)(base + t.d_tab);
+                n.cs = (int32_t *)(base + t.cs);
+                n.row = (int32_t *)(base + t.row);
+                n.pos = (int32_t *)(base + t.pos);
+                n.first = (int32_t *)(base + t.first);
+                n.lm = (uint4 *)(base + t.lm);
+                n.bias = (float *)(base + t.bias);
+                n.out = (float *)(base + t.out);
+                n.chunks = (size_t)at;
+                n.tab = t.tab;
+                UP(n.cs, tl[o].cs.data(), 4 * tl[o].cs.size());
+                UP(n.d_tab, t.tab.data(), sizeof(LmLayer) * t.tab.size());
+                UP(n.row, tl[o].row.data(), 4 * tl[o].row.size());
+                UP(n.pos, tl[o].pos.data(), 4 * tl[o].pos.size());
+                UP(n.first, tl[o].first.data(), 4 * tl[o].first.size());
+            }
+            const int rc_fill = launch_train_fill(net, -1, true, stream);
+            if (rc_fill) return fail_free(rc_fill);
+        }
         // not where a layout took too many slots, or where the links stay within few panels: the operand of the other kernels is
         // on chip then
         if (!pan_fits || pan_fullest > 1.5 * pan_mean) net->pan.clear();
@@ -3929,7 +4330,12 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
         net->state = ST_FORWARD;
         return SDNN_OK;
     }
-    for (int l = 0; l < L; ++l) {
+    const bool single = training && train_lds(net, B);
+    if (single) {
+        const int rc = launch_train_lds(net, 0, B, Bp, ld, stream);
+        if (rc) return rc;
+    }
+    for (int l = 0; l < (single ? 0 : L); ++l) {
         const LayerDev &d = net->layers[l];
         float *out = training ? d.X : (l == L - 1 ? d_XL : ((l & 1) ? pong : ping));
         const int ld_out = !training && l == L - 1 ? B : ld;
@@ -4220,7 +4626,12 @@ extern "C" int sdnn_backward(sdnn_net *net, const float *d_dLoss, void *stream_)
         }
         net->vals_t_stale = false;
     }
-    for (int l = L - 1; l >= (gp ? 0 : 1); --l) {
+    const bool single = !gp && train_lds(net, net->B);
+    if (single) {
+        const int rc = launch_train_lds(net, 1, net->B, net->Bp, net->ld, stream);
+        if (rc) return rc;
+    }
+    for (int l = L - 1; l >= (gp ? 0 : 1) && !single; --l) {
         const LayerDev &d = net->layers[l];
         // Delta_{l} (0-based l-1) = (W^T Delta_{l+1}) masked by X_{l}
         float *dprev = l >= 1 ? net->layers[l - 1].D : nullptr;
@@ -4329,6 +4740,7 @@ extern "C" int sdnn_sgd_step(sdnn_net *net, float lr, void *stream_)
     } else {
         rc = launch_update(net, 0, net->n_layers, lr, 0, nullptr, nullptr, (hipStream_t)stream_);
         if (net->layers[0].vals_t) net->vals_t_stale = true; // this kernel steps the CSR copy only
+        if (!rc) rc = launch_train_fill(net, -1, false, (hipStream_t)stream_); // the copies of narrow nets follow
     }
     if (rc) return rc;
     net->state = ST_IDLE;
@@ -4431,6 +4843,7 @@ extern "C" int sdnn_set_weights(sdnn_net *net, int32_t layer, const float *d_val
     if (!rc && d_values && net->b1) rc = launch_b1_fill(net, layer - 1, 0, (hipStream_t)stream_);
     if (!rc && (d_values || d_bias) && net->lm) // keep the lane-major copy current
         rc = launch_lm_fill(net, layer - 1, nullptr, 0, (hipStream_t)stream_);
+    if (!rc && (d_values || d_bias)) rc = launch_train_fill(net, layer - 1, false, (hipStream_t)stream_);
     if (!rc && (d_values || d_bias) && !net->pan.empty()) rc = launch_pan_fill(net, layer - 1, (hipStream_t)stream_);
     return rc;
 }

@@ -172,3 +172,33 @@ def test_forward_in_panels():
         for options in (dict(lds_forward=-1), dict(panel_cols=8192), dict(reorder_rows=1), dict(training=True)):
             assert not pans(Net([spread(40000, 40000, 32)] * 3, 512, **options), 512)
     """)
+
+
+def test_training_with_one_launch_per_pass():
+    """Narrow nets of short rows and at least four layers: not with one sample, more samples than compute units, long rows or
+    columns, the gradient formed in the sweep, or lds_forward off."""
+    routes.run("""
+        from tests import pan_nets
+        def nets(widths, lengths, max_batch, **options):
+            ls = pan_nets.layers(widths, lengths, seed=8100)
+            return Net([(y.n_out, y.n_in, y.row_ptr, y.col_idx, y.values, y.bias) for y in ls], max_batch, training=True, **options)
+        def passes(net, B):
+            rc, f = net("sdnn_forward", X0, B, XL, None)
+            assert rc == 0
+            rc, b = net("sdnn_backward", DL, None)
+            assert rc == 0
+            rc, u = net("sdnn_sgd_step", C.c_float(0.1), None)
+            assert rc == 0
+            n = sum(l.startswith("k_train_fill") for l in u)
+            return any("k_train_lds<0" in l for l in f), any("k_train_lds<1" in l for l in b), n
+        for widths, b, lengths in [((1024,) * 5, 64, (32,)), ((50, 1025, 63, 1000, 7), 5, (0, 1, 16, 17, 33)), ((300, 1400, 1300, 64, 1), 255, (7, 8, 9)),
+                                   ((1024, 65, 1023, 129, 1024, 40), 2, (15, 31, 64)), ((200, 900, 800, 700, 100), 9, (20, 40)), ((300, 1024, 1024, 1024, 50), 5, (0, 5, 17, 40))]:
+            assert passes(nets(widths, lengths, b), b) == (True, True, 2), widths
+        n = (1024,) * 5
+        assert passes(nets(n, (32,), 64), 1)[:2] == (False, False)
+        for net, B in [(nets(n[:4], (32,), 64), 64), (nets(n, (32,), 64, lds_forward=-1), 64), (nets(n, (32,), 64, fuse_gradient=1), 64), (nets(n, (32,), 300), 64),
+                       (nets((2049,) + n, (32,), 64), 64), (nets((1024,) * 5, (1, 600), 64, fuse_gradient=-1), 64)]:
+            assert passes(net, B) == (False, False, 0), (net.keep[0][0], passes(net, B))
+        rc, log = nets(n, (32,), 64)("sdnn_set_weights", 2, X0, XL, None)
+        assert rc == 0 and sum(l.startswith("k_train_fill") for l in log) == 2
+    """)
