@@ -1991,7 +1991,6 @@ __global__ void __launch_bounds__(64) k_spmv_stage(const SpmmArgs a, int R)
 // 6.1 / 8.7 / 3.9 -> 3.7 / 5.5 / 1.9; 65536 neurons 14.9 / 22.3 / 15.7 -> 10.5 / 10.7 / 19.5.
 // ---------------------------------------------------------------------------
 #define B1_MAX_LDS (160 * 1024) // bytes of the step's LDS copy of a vector
-#define B1_LOAD 4 // chunks requested together
 template <bool WIDE> struct B1 { // columns of 2 bytes, or (more than 65536 of them) 4
     static constexpr unsigned CHUNK_BYTES = WIDE ? 4096 : 3072, WEIGHTS = WIDE ? 2048 : 1024;
 };
@@ -2015,6 +2014,10 @@ __global__ void __launch_bounds__(64) k_spmv_lm(const SpmvLmArgs a)
     const int lane = threadIdx.x, b = blockIdx.x;
     typedef const int32_t __attribute__((address_space(4))) *cs_ptr;
     const cs_ptr scs = (cs_ptr)a.cs;
+    // Chunks requested together.  Back-propagation: the longest of a few thousand random columns with 32 entries in the mean have about
+    // sixty, and a second round of loads and gathers for them is what the whole layer would wait for.  Step, us per layer, four
+    // chunks / eight: 1024 neurons 6.92 / 6.70, 4096 7.53 / 7.25, 8192 9.51 / 9.12, 16384 11.66 / 11.22, 32768 17.33 / 17.08, 50001 the same.
+    constexpr int LOAD = TRAIN && MODE == 1 && !WIDE ? 8 : 4;
     int c0, n, place; // first chunk, chunks, where the result goes
     [[maybe_unused]] int len = 0; // TRAIN: entries of the lane's row
     if constexpr (TRAIN) {
@@ -2040,11 +2043,11 @@ __global__ void __launch_bounds__(64) k_spmv_lm(const SpmvLmArgs a)
     }
     double acc = 0.0;
     unsigned at = (unsigned)c0 * B1<WIDE>::CHUNK_BYTES;
-    for (int i = 0; i < n; i += B1_LOAD, at += B1_LOAD * B1<WIDE>::CHUNK_BYTES) {
-        u32x4 c[B1_LOAD], ch[B1_LOAD], wa[B1_LOAD], wb[B1_LOAD];
-        float x[B1_LOAD][8];
+    for (int i = 0; i < n; i += LOAD, at += LOAD * B1<WIDE>::CHUNK_BYTES) {
+        u32x4 c[LOAD], ch[LOAD], wa[LOAD], wb[LOAD];
+        float x[LOAD][8];
 #pragma unroll
-        for (int u = 0; u < B1_LOAD; ++u)
+        for (int u = 0; u < LOAD; ++u)
             if (i + u < n) {
                 const int o = (int)(at + u * B1<WIDE>::CHUNK_BYTES);
                 c[u] = __builtin_amdgcn_raw_buffer_load_b128(rlm, 16 * lane, o, 0);
@@ -2053,7 +2056,7 @@ __global__ void __launch_bounds__(64) k_spmv_lm(const SpmvLmArgs a)
                 wb[u] = __builtin_amdgcn_raw_buffer_load_b128(rlm, 16 * lane + B1<WIDE>::WEIGHTS + 1024, o, 0);
             }
 #pragma unroll
-        for (int u = 0; u < B1_LOAD; ++u)
+        for (int u = 0; u < LOAD; ++u)
             if (i + u < n) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
@@ -2063,13 +2066,13 @@ __global__ void __launch_bounds__(64) k_spmv_lm(const SpmvLmArgs a)
             }
         if (TRAIN && !WIDE && a.in_bytes > 4u * 0xffffu) { // 65536 columns: no 2-byte column is outside the operand
 #pragma unroll
-            for (int u = 0; u < B1_LOAD; ++u)
+            for (int u = 0; u < LOAD; ++u)
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
                     if (i + u < n && 8 * (i + u) + k >= len) x[u][k] = 0.0f;
         }
 #pragma unroll
-        for (int u = 0; u < B1_LOAD; ++u)
+        for (int u = 0; u < LOAD; ++u)
             if (i + u < n) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k)

@@ -1,5 +1,5 @@
 """Nets made for one sample per step (lane-major copies of W and W^T) at the edges of their layout: blocks of 64 rows, chunks
-of eight entries and rounds of four chunks, the longest row they take and the first they do not, more than 65536 neurons
+of eight entries and rounds of four chunks (back: eight), the longest row they take and the first they do not, more than 65536 neurons
 (4-byte columns), vectors that do and do not fit LDS in the step; weights replaced in between and read back."""
 import numpy as np
 import pytest
@@ -55,6 +55,13 @@ def test_blocks_and_chunks(n, activation):
 def test_longest_row(longest):
     """513 entries in one row: the net takes the kernels that share a row among lanes."""
     _steps([_layer(9520, 600, 700, (longest,) + (3,) * 599), _layer(9521, 40, 600, (9, 30))], 9530)
+
+
+@pytest.mark.parametrize("rows", [200, 360, 435, 900, 1300])
+def test_long_columns(rows):
+    """Columns of about 30, 54, 65, 135 and 195 entries: one round of eight chunks in the backward pass, and several; layers
+    whose numbers of blocks of 64 rows (4 to 21, and 1) do not fit each other's."""
+    _steps([_layer(9590, rows, 20, (3,)), _layer(9591, 20, rows, (9, 1)), _layer(9592, rows, 20, (3,)), _layer(9593, 5, rows, (40,))], 9595)
 
 
 def test_wide_layers():
