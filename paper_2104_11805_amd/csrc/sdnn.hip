@@ -1989,6 +1989,7 @@ __global__ void __launch_bounds__(64) k_spmv_stage(const SpmmArgs a, int R)
 // every gathered activation.  Forward / backward / step, us per layer, before (products staged in LDS, a gradient array, the
 // values moved from the transposed to the CSR order) and after: 1024 neurons 4.6 / 4.8 / 0.2 -> 3.2 / 3.7 / 0.1; 16384 neurons
 // 6.1 / 8.7 / 3.9 -> 3.7 / 5.5 / 1.9; 65536 neurons 14.9 / 22.3 / 15.7 -> 10.5 / 10.7 / 19.5.
+// (Rounds of eight chunks going back have since taken 0.2 us off 1024 and 0.4 off 16384 neurons.)
 // ---------------------------------------------------------------------------
 #define B1_MAX_LDS (160 * 1024) // bytes of the step's LDS copy of a vector
 template <bool WIDE> struct B1 { // columns of 2 bytes, or (more than 65536 of them) 4
