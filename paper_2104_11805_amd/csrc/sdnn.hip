@@ -1982,7 +1982,7 @@ __global__ void __launch_bounds__(64) k_spmv_stage(const SpmmArgs a, int R)
 // ---------------------------------------------------------------------------
 // Nets made for one sample per step (max_batch == 1, rows of moderate length), and inference calls with one sample on
 // nets that hold the lane-major copy of k_fwd_lds: a lane per row over a lane-major copy, so that columns and weights come
-// in coalesced 16-byte loads and nothing is parked or exchanged; up to 32 gathers of single activations are in flight per
+// in coalesced 16-byte loads and nothing is parked or exchanged; up to 32 gathers of single activations (back: 64) are in flight per
 // lane.  Training nets keep one copy of W and one of W^T and step both (no gradient of the entries is stored and no value
 // moves from one order to the other); the CSR values are written out when they are asked for.
 // What bounds them: a launch and its chain of dependent loads (3.2 us) plus, on wide layers, a 128-byte line from L2 for
