@@ -897,7 +897,7 @@ __device__ __forceinline__ void lds_barrier()
 // The hardware serves the oldest wavefront of a SIMD first, so that of four with equal work the youngest is done a third later,
 // and everyone waits for it at the next barrier.  With a priority that goes round, block by block, they end closer together
 // (16384 neurons, 256 samples 35.4 -> 33.6 us per layer; 4096 neurons, 1024 samples 14.6 -> 14.1; 8192 neurons with 820 entries
-// per row, 1024 samples 640 -> 617).  Up to two rounds of workgroups only: in later ones the workgroups of an XCD are further
+// per row, 1024 samples 640 -> 617).  In which layers: lm_turns.  Up to two rounds of workgroups only: in later ones the workgroups of an XCD are further
 // apart in the stream of W that they share, and the turns made that worse (16384 neurons, 4096 samples, eight rounds, 48 layers
 // 13.8 -> 14.4 ms; four rounds 6.85 -> 6.97; two rounds 605 -> 587 us per 8 layers).
 __device__ __forceinline__ void take_turns(int turn)
@@ -941,7 +941,7 @@ struct LdsForward {
     int32_t ld_in, ld_out;
     int32_t B;             // samples
     int32_t vec_io;        // rows of in and out are whole T-float pieces
-    int32_t turns;         // the wavefronts take turns, see take_turns
+    int32_t turns;         // whether the wavefronts take turns, see take_turns (k_fwd_lds_part: with how many samples, lm_turns)
     float cap;
     // parts of a pass that drops dead samples (k_fwd_lds_part)
     const int32_t *n_live; // samples that are left; workgroups past them end at once
@@ -1020,6 +1020,7 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
     // All the workgroups of an XCD stream through the same copy of W at about the same time, and whoever comes first to a
     // line waits for memory.  So they share that out: before a layer's last block each wavefront touches one line in so many
     // of the next layer's stream (3001 neurons, 120 layers, copies of W that come from HBM: 1.08 -> 0.92 ms).
+    const bool turns = PART ? (a.turns & T) != 0 : a.turns != 0;
     const unsigned xcd_wg = (blockIdx.x >> 3) % max(1u, min(32u, gridDim.x >> 3));
     unsigned touched = 0;
     lds_barrier();
@@ -1066,7 +1067,7 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
                         acc[t] = fma(w[u], (double)xv, acc[t]);
                     }
             };
-            if (a.turns) take_turns(wave / 4 + j);
+            if (turns) take_turns(wave / 4 + j);
             for (int i = 0; i < n; ++i) { // (nothing moves across: the loads would be requested late, with those of the other half)
                 take(ha);
                 __builtin_amdgcn_sched_barrier(0);
@@ -2700,6 +2701,7 @@ struct sdnn_net {
     std::vector<LmLayer> lm_tab;     // host copy of lm_layers
     size_t lm_chunks = 0;
     int32_t lm_max_pos = 0;
+    int32_t turns = 0;               // lm_turns of three quarters of its chunks and more
     bool lds_part_attr_set = false;
     struct Train {                   // a copy of W (0) or W^T (1) for k_train_lds
         std::vector<LmLayer> tab;    // empty: there is none
@@ -2933,6 +2935,37 @@ static void lm_deal_blocks(const sdnn_layer &y, const LmLayer &tab, int32_t *row
             pos[order[(size_t)(r0 + k)]] = at;
         }
     }
+}
+
+// With how many samples per workgroup (bits 1, 2 and 4) the wavefronts take turns at priority in a layer whose blocks have the
+// depths that lm_deal_blocks left in cs: where their shares of the layer, in chunks, are about equal.  The first wavefronts have the
+// deepest blocks and those left over; by age they are served first, and turns hold them up.  Later rounds of blocks make up for a
+// share that is a little longer, with four samples sooner.  us per layer, 32 entries per row, by age / in turns, with 1, 2 and 4
+// samples: 300 neurons (a round: nobody is later than the others) 1.55 / 1.66, 1.76 / 1.87, 2.38 / 2.55; 1089 (two rounds, the longest
+// share 1.78 of the mean one) 2.88 / 3.28, 3.15 / 3.56, 4.82 / 5.08; 1792 (1.14) 3.74 / 3.80, 4.04 / 4.19, 6.07 / 6.23; 1856 (1.10)
+// 4.01 / 3.89, 4.38 / 4.26, 6.65 / 6.31; 2112 (three rounds, 1.45) 4.66 / 4.91, 5.14 / 5.34, 7.87 / 7.58; 2432 (1.26) 5.02 / 5.06,
+// 5.61 / 5.55, 8.60 / 8.26; 3136 (four, 1.31) 6.46 / 6.31, 7.27 / 6.99, 11.00 / 10.88.
+// Not on rows of 28 chunks and more in the mean with one sample, nor, where all blocks are about as deep, with two: the workgroups of
+// an XCD come apart in the stream of W by deep blocks, which its L2 then fetches again and again (820 entries per row, 8192 neurons,
+// 220 and 500 samples 390 / 473, 477 / 570; a tenth of the columns with a heavy tail, 220 samples, 4097 neurons 92.3 / 87.5, 5000
+// neurons 132 / 142, 6000 neurons 187 / 232, 8192 neurons 397 / 567; 500 samples, 8192 neurons 465 / 446).
+static int lm_turns(int32_t nb, const int32_t *cs)
+{
+    int64_t longest = 0, all = 0, blocks = 0, deepest = 0;
+    for (int w = 0; w < LDS_WAVES; ++w) {
+        int64_t share = 0;
+        for (int32_t j = 0; j < nb; ++j) {
+            const int64_t depth = cs[w * (nb + 1) + j];
+            share += depth;
+            blocks += depth > 0;
+            deepest = std::max(deepest, depth);
+        }
+        longest = std::max(longest, share);
+        all += share;
+    }
+    if (nb < 2) return 0;
+    const bool equal = (double)longest * LDS_WAVES <= (1.0 + 0.13 * (nb - 1)) * (double)all, deep = all >= 28 * blocks;
+    return (equal && !deep ? 1 : 0) | (equal && !(deep && 2 * all > deepest * blocks) ? 2 : 0) | (equal || nb > 2 ? 4 : 0);
 }
 
 // Runs fn(0 .. n - 1) on up to 16 host threads (here if there are no more threads); fn must not throw.
@@ -3734,6 +3767,15 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
             if (rc_fill) return fail_free(rc_fill);
         }
         if (want_lm) {
+            int64_t in_turns[5] = {};
+            for (const LmLayer &t : pl.lm_tab) {
+                const int32_t *c = lm_cs.data() + t.cs, mask = lm_turns(t.nb, c);
+                int64_t chunks = 0;
+                for (int32_t k = 0; k < LDS_WAVES * (t.nb + 1); ++k) chunks += c[k];
+                for (int T = 1; T <= 4; T *= 2) in_turns[T] += mask & T ? chunks : 0;
+            }
+            for (int T = 1; T <= 4; T *= 2)
+                if (4 * in_turns[T] >= 3 * (int64_t)pl.lm_n_chunks) net->turns |= T;
             // from the blocks' depths to where their chunks lie: one wavefront's chunks follow each other through all layers
             int64_t at = 0;
             for (int w = 0; w < LDS_WAVES; ++w)
@@ -4274,7 +4316,7 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
         }
         LdsForward a = lds_args(net, 0, L, d_X0, B, d_XL, B, B);
         a.vec_io = (B % T == 0 && aligned(d_X0, 4 * T) && aligned(d_XL, 4 * T)) ? 1 : 0;
-        a.turns = (B + T - 1) / T <= 2 * net->n_cu;
+        a.turns = (net->turns & T) && (B + T - 1) / T <= 2 * net->n_cu;
         void *args[] = {(void *)&a};
         HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)((B + T - 1) / T)), dim3(64 * LDS_WAVES), args, lds_bytes, stream));
         HIP_TRY(net, hipGetLastError());
@@ -4438,7 +4480,7 @@ static int skip_dead_lds(sdnn_net *net, const float *d_X0, int B, float *d_XL, i
         if (last && k > 0) // the samples that have died (a pass of one stretch stores every column)
             hipLaunchKernelGGL(k_fill_f32, dim3(ew_blocks((size_t)n_last * B)), dim3(256), 0, stream, d_XL, (size_t)n_last * B, 0.0f);
         LdsForward a = lds_args(net, l0, l1, in, ld_in, out, last ? B : ld, B);
-        a.turns = 1;
+        a.turns = net->turns;
         a.n_live = net->d_n_live[k & 1];
         a.src_col = net->d_flags[k & 1];
         a.dst_col = last ? net->d_map[k & 1] : nullptr;

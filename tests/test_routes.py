@@ -202,3 +202,37 @@ def test_training_with_one_launch_per_pass():
         rc, log = nets(n, (32,), 64)("sdnn_set_weights", 2, X0, XL, None)
         assert rc == 0 and sum(l.startswith("k_train_fill") for l in log) == 2
     """)
+
+
+def test_turns_at_priority_between_equal_shares():
+    """With 1, 2 and 4 samples per workgroup of the LDS forward: the wavefronts do not take turns where the blocks left over, or one
+    deep block, make the shares of a few of them longer than the others', nor on the longest rows."""
+    routes.run("""
+        def turns(deg):
+            n = len(deg)
+            net = Net([layer(n, n, deg)] * 2, 1024, lds_forward=1)
+            out = {}
+            for B in (200, 500, 1000):
+                rc, log = net("sdnn_forward", X0, B, XL, None)
+                assert rc == 0 and len(log) == 1
+                out[int(log[0][10])] = stub.stub_arg()[22]           # LdsForward::turns
+            return out
+        def uneven(n):
+            # a tenth of the columns in the mean, at most a quarter
+            tail, lo, hi = ((np.arange(n) + 0.5) / n) ** (-1 / 1.2), 0.0, n
+            while hi - lo > 1e-6:
+                mid = (lo + hi) / 2
+                lo, hi = (mid, hi) if np.clip(np.round(tail * mid), 1, n // 4).mean() < 0.1 * n else (lo, mid)
+            return np.clip(np.round(tail * hi), 1, n // 4).astype(int)
+        none, every, four = {1: 0, 2: 0, 4: 0}, {1: 1, 2: 1, 4: 1}, {1: 0, 2: 0, 4: 1}
+        for n, want in [(300, none), (1024, none), (1025, none), (1089, none), (1565, none), (1792, none), (1793, every), (2048, every),
+                        (2100, four), (2432, four), (2433, every), (3001, every), (3100, every), (4096, every), (7000, every)]:
+            assert turns([32] * n) == want, (n, turns([32] * n))
+        for n, want in [(1300, none), (2000, none), (3001, every), (4097, every), (6000, {1: 0, 2: 1, 4: 1}), (8192, {1: 0, 2: 1, 4: 1})]:
+            assert turns(uneven(n)) == want, (n, turns(uneven(n)))
+        assert turns([820] * 8192) == four
+        net = Net([layer(4096, 4096, (32,)), layer(10, 4096, (32,))], 1024, lds_forward=1) # a narrow layer does not matter
+        assert net("sdnn_forward", X0, 1000, XL, None)[0] == 0 and stub.stub_arg()[22] == 1
+        net = Net([layer(1300, 1300, (32,))] * 3, 1024, act_cap=32.0, lds_forward=1)
+        assert net("sdnn_forward_skip_dead", X0, 1000, XL, 1, DL, None)[0] == 0 and stub.stub_arg()[22] == 0
+    """)
