@@ -951,8 +951,9 @@ struct LdsForward {
     int32_t max_pos;       // positions of the LDS buffer; one more follows, which holds zeros
 };
 
-// PART: a stretch of layers for the samples that are still alive.
-template <int T, int ACT, bool PART>
+// PART: a stretch of layers for the samples that are still alive.  ORDER: a wavefront requests its halves of W strictly one after the
+// other (see take, below).
+template <int T, int ACT, bool PART, bool ORDER>
 __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_samples)
 {
     extern __shared__ __attribute__((aligned(16))) float lds_act[];
@@ -1068,11 +1069,11 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
                     }
             };
             if (turns) take_turns(wave / 4 + j);
-            for (int i = 0; i < n; ++i) { // (nothing moves across: the loads would be requested late, with those of the other half)
+            for (int i = 0; i < n; ++i) { // (ORDER: nothing moves across; else the loads are requested with those of the other half)
                 take(ha);
-                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (ORDER) __builtin_amdgcn_sched_barrier(0);
                 take(hb);
-                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (ORDER) __builtin_amdgcn_sched_barrier(0);
             }
             const double bd = (double)bias;
 #pragma unroll
@@ -1138,12 +1139,12 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
     }
 }
 
-template <int T, int ACT>
+template <int T, int ACT, bool ORDER>
 __global__ void __launch_bounds__(64 * LDS_WAVES) k_fwd_lds(const LdsForward a)
 {
     // neighbouring samples share cache lines of X: an XCD takes a contiguous stretch of them
     const int nwg = (int)gridDim.x, per = nwg >> 3, wg = (int)blockIdx.x;
-    lds_forward<T, ACT, false>(a, wg < 8 * per ? (wg & 7) * per + (wg >> 3) : wg, a.B);
+    lds_forward<T, ACT, false, ORDER>(a, wg < 8 * per ? (wg & 7) * per + (wg >> 3) : wg, a.B);
 }
 
 // A stretch of layers for the samples that are still alive, as many per workgroup as it takes to give every CU one (the
@@ -1152,11 +1153,11 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) k_fwd_lds_part(const LdsForwar
 {
     const int n = *a.n_live, wg = (int)blockIdx.x;
     if (4 * a.max_pos <= LDS_MAX_FLOATS && n > 2 * n_cu) {
-        if (4 * wg < n) lds_forward<4, ACT_RELU_CAP, true>(a, wg, n);
+        if (4 * wg < n) lds_forward<4, ACT_RELU_CAP, true, true>(a, wg, n);
     } else if (2 * a.max_pos <= LDS_MAX_FLOATS && n > n_cu) {
-        if (2 * wg < n) lds_forward<2, ACT_RELU_CAP, true>(a, wg, n);
+        if (2 * wg < n) lds_forward<2, ACT_RELU_CAP, true, true>(a, wg, n);
     } else {
-        if (wg < n) lds_forward<1, ACT_RELU_CAP, true>(a, wg, n);
+        if (wg < n) lds_forward<1, ACT_RELU_CAP, true, true>(a, wg, n);
     }
 }
 
@@ -2949,6 +2950,12 @@ static void lm_deal_blocks(const sdnn_layer &y, const LmLayer &tab, int32_t *row
 // an XCD come apart in the stream of W by deep blocks, which its L2 then fetches again and again (820 entries per row, 8192 neurons,
 // 220 and 500 samples 390 / 473, 477 / 570; a tenth of the columns with a heavy tail, 220 samples, 4097 neurons 92.3 / 87.5, 5000
 // neurons 132 / 142, 6000 neurons 187 / 232, 8192 neurons 397 / 567; 500 samples, 8192 neurons 465 / 446).
+// LM_IN_ORDER: whether with one sample (and the ReLU) the loads of W are requested strictly in their order, as with more samples they
+// always are.  Not on blocks of two chunks and fewer in five rounds and more, nor in three without turns.  us per layer, 64 / 200 samples, in order and
+// then in the compiler's: 300 neurons of 32 entries 1.51 / 1.53, 1300 3.08 / 3.13 (200), 1856 4.03 / 4.13, 2112 4.89 / 4.81, 2304 5.13 / 5.02,
+// 3500 6.64 / 6.78 (200), 4300 8.59 / 8.42, 8192 14.97 / 14.79, 16384 30.0 / 29.6; 2048 neurons of 64 entries 8.48 / 8.67 (220), 8192
+// neurons of 128 entries 62.4 / 65.0, of 256 123 / 147.
+#define LM_IN_ORDER 8
 static int lm_turns(int32_t nb, const int32_t *cs)
 {
     int64_t longest = 0, all = 0, blocks = 0, deepest = 0;
@@ -2963,9 +2970,10 @@ static int lm_turns(int32_t nb, const int32_t *cs)
         longest = std::max(longest, share);
         all += share;
     }
-    if (nb < 2) return 0;
     const bool equal = (double)longest * LDS_WAVES <= (1.0 + 0.13 * (nb - 1)) * (double)all, deep = all >= 28 * blocks;
-    return (equal && !deep ? 1 : 0) | (equal && !(deep && 2 * all > deepest * blocks) ? 2 : 0) | (equal || nb > 2 ? 4 : 0);
+    const int order = nb <= 2 || (nb <= 4 && equal) || all >= 3 * blocks ? LM_IN_ORDER : 0;
+    if (nb < 2) return order;
+    return order | (equal && !deep ? 1 : 0) | (equal && !(deep && 2 * all > deepest * blocks) ? 2 : 0) | (equal || nb > 2 ? 4 : 0);
 }
 
 // Runs fn(0 .. n - 1) on up to 16 host threads (here if there are no more threads); fn must not throw.
@@ -3767,15 +3775,15 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
             if (rc_fill) return fail_free(rc_fill);
         }
         if (want_lm) {
-            int64_t in_turns[5] = {};
+            int64_t of_bit[LM_IN_ORDER + 1] = {};
             for (const LmLayer &t : pl.lm_tab) {
                 const int32_t *c = lm_cs.data() + t.cs, mask = lm_turns(t.nb, c);
                 int64_t chunks = 0;
                 for (int32_t k = 0; k < LDS_WAVES * (t.nb + 1); ++k) chunks += c[k];
-                for (int T = 1; T <= 4; T *= 2) in_turns[T] += mask & T ? chunks : 0;
+                for (int bit = 1; bit <= LM_IN_ORDER; bit *= 2) of_bit[bit] += mask & bit ? chunks : 0;
             }
-            for (int T = 1; T <= 4; T *= 2)
-                if (4 * in_turns[T] >= 3 * (int64_t)pl.lm_n_chunks) net->turns |= T;
+            for (int bit = 1; bit <= LM_IN_ORDER; bit *= 2)
+                if (4 * of_bit[bit] >= 3 * (int64_t)pl.lm_n_chunks) net->turns |= bit;
             // from the blocks' depths to where their chunks lie: one wavefront's chunks follow each other through all layers
             int64_t at = 0;
             for (int w = 0; w < LDS_WAVES; ++w)
@@ -4306,9 +4314,9 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
         const bool sig = net->cfg.activation == ACT_SIGMOID;
         const int ti = T == 1 ? 0 : T == 2 ? 1 : 2;
         static const void *const fns[2][3] = {
-            {(const void *)k_fwd_lds<1, ACT_RELU_CAP>, (const void *)k_fwd_lds<2, ACT_RELU_CAP>, (const void *)k_fwd_lds<4, ACT_RELU_CAP>},
-            {(const void *)k_fwd_lds<1, ACT_SIGMOID>, (const void *)k_fwd_lds<2, ACT_SIGMOID>, (const void *)k_fwd_lds<4, ACT_SIGMOID>}};
-        const void *fn = fns[sig ? 1 : 0][ti];
+            {(const void *)k_fwd_lds<1, ACT_RELU_CAP, true>, (const void *)k_fwd_lds<2, ACT_RELU_CAP, true>, (const void *)k_fwd_lds<4, ACT_RELU_CAP, true>},
+            {(const void *)k_fwd_lds<1, ACT_SIGMOID, true>, (const void *)k_fwd_lds<2, ACT_SIGMOID, true>, (const void *)k_fwd_lds<4, ACT_SIGMOID, true>}};
+        const void *fn = T == 1 && !sig && !(net->turns & LM_IN_ORDER) ? (const void *)k_fwd_lds<1, ACT_RELU_CAP, false> : fns[sig ? 1 : 0][ti];
         const size_t lds_bytes = sizeof(float) * (size_t)T * ((size_t)net->lm_max_pos + 1);
         if (!net->lds_attr_set[ti]) { // more than the default 64 KiB of dynamic LDS per workgroup
             HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (LDS_MAX_FLOATS + 4)));

@@ -234,5 +234,17 @@ def test_turns_at_priority_between_equal_shares():
         net = Net([layer(4096, 4096, (32,)), layer(10, 4096, (32,))], 1024, lds_forward=1) # a narrow layer does not matter
         assert net("sdnn_forward", X0, 1000, XL, None)[0] == 0 and stub.stub_arg()[22] == 1
         net = Net([layer(1300, 1300, (32,))] * 3, 1024, act_cap=32.0, lds_forward=1)
-        assert net("sdnn_forward_skip_dead", X0, 1000, XL, 1, DL, None)[0] == 0 and stub.stub_arg()[22] == 0
+        assert net("sdnn_forward_skip_dead", X0, 1000, XL, 1, DL, None)[0] == 0 and stub.stub_arg()[22] & 7 == 0
+    """)
+
+
+def test_order_of_the_loads_with_one_sample():
+    """The LDS forward with one sample per workgroup requests its loads strictly in order on long rows and where there are few
+    rounds of blocks."""
+    routes.run("""
+        for n, links, order in [(300, 32, "true"), (2048, 32, "true"), (2049, 32, "false"), (2049, 33, "true"), (2500, 32, "true"), (4096, 32, "true"), (4097, 32, "false"), (4097, 33, "true"), (16384, 16, "false"), (9000, 256, "true")]:
+            for activation in (0, 1):
+                net = Net([layer(n, n, (links,))] * 2, 1024, lds_forward=1, activation=activation)
+                rc, log = net("sdnn_forward", X0, 1 if n == 16384 else 2, XL, None)
+                assert rc == 0 and log == [f"k_fwd_lds<1, {activation}, {'true' if activation else order}> {1 if n == 16384 else 2} 1 1"], (n, links, log)
     """)
