@@ -897,9 +897,12 @@ __device__ __forceinline__ void lds_barrier()
 // The hardware serves the oldest wavefront of a SIMD first, so that of four with equal work the youngest is done a third later,
 // and everyone waits for it at the next barrier.  With a priority that goes round, block by block, they end closer together
 // (16384 neurons, 256 samples 35.4 -> 33.6 us per layer; 4096 neurons, 1024 samples 14.6 -> 14.1; 8192 neurons with 820 entries
-// per row, 1024 samples 640 -> 617).  In which layers: lm_turns.  Up to two rounds of workgroups only: in later ones the workgroups of an XCD are further
-// apart in the stream of W that they share, and the turns made that worse (16384 neurons, 4096 samples, eight rounds, 48 layers
-// 13.8 -> 14.4 ms; four rounds 6.85 -> 6.97; two rounds 605 -> 587 us per 8 layers).
+// per row, 1024 samples 640 -> 617).  In which layers: lm_turns.  A launch through the whole net: up to two rounds of workgroups only.
+// In later ones the workgroups of an XCD are further apart in the stream of W that they share, and the turns made that worse (16384
+// neurons, 4096 samples, eight rounds, 48 layers 13.8 -> 14.4 ms; four rounds 6.85 -> 6.97; two rounds 605 -> 587 us per 8 layers).
+// The stretches of a pass that drops dead samples are launches of their own, at whose starts the workgroups are together again: turns
+// in any number of rounds (us per pass of 48 layers without turns / in up to two rounds / in all: 16384 neurons, 4096 samples, eight
+// rounds at first 6873 / 6750 / 6600; 2048 samples, four rounds 3364 / 3335 / 3321; 9973 neurons, 3000 samples 3245 / 3151 / 3125).
 __device__ __forceinline__ void take_turns(int turn)
 {
     switch (turn & 3) {
