@@ -2716,6 +2716,9 @@ struct sdnn_net {
         size_t chunks = 0;
         int32_t max_nb = 0;
     } train[2];
+    // seconds that both passes take with a launch per layer, their gathers of one sample, those with a single launch, and what is
+    // added where the samples leave no compute unit idle (train_lds_pays)
+    double train_per_layer = 0, train_gathers = 0, train_single = 0, train_cold = 0;
     bool pan_attr_set = false;
     struct Pan {                     // a layer's copy of W for k_fwd_pan
         PanLayer g{};
@@ -3073,13 +3076,6 @@ static void plan_b1(const sdnn_layer *layers, int32_t n_layers, const sdnn_confi
 // Fills in the tables' sizes; the chunks are a bound (the columns may not be known here): the first block of a copy is no deeper
 // than its longest row, every later one no deeper than the mean of the 64 rows before it.
 #define TRAIN_LDS_MAX_ROW 512
-// Seconds a layer: a launch per layer and pass takes 4.2 (forward) and 5.0 us (back-propagation) besides its gathers; a step of a
-// single launch 1.9 besides its entries (barrier, turning the samples around, bringing the copies up to date).  Measured, us per
-// training step, 48 layers of 32 entries per row, a launch per layer / single: 1024 neurons 535 / 396 (2 samples), 569 / 388 (64), 809 / 539
-// (256); 1201 neurons 599 / 459 (64); 1450 neurons 582 / 536 (2), 615 / 523 (64), 952 / 899 (256); 1800 neurons 594 / 622 (2),
-// 631 / 600 (64); 2048 neurons 604 / 671 (2), 631 / 647 (64).
-#define TRAIN_PER_LAYER(o) ((o) ? 5.0e-6 : 4.2e-6)
-#define TRAIN_STEP 1.9e-6
 static void plan_train(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, Plan &pl)
 {
     pl.train_lds = false;
@@ -3331,8 +3327,21 @@ static int launch_train_fill(sdnn_net *net, int l, bool cols, hipStream_t stream
     return SDNN_OK;
 }
 
-// Whether the passes over B samples go through k_train_lds.
-static bool train_lds(const sdnn_net *net, int B) { return B > 1 && B <= net->n_cu && !net->train[0].tab.empty(); }
+// Whether the passes over B samples go through k_train_lds: where both together are done sooner than with a launch per layer.
+// A launch per layer takes 3.2 us forward and 4.0 us back, 28 ns per entry of its longest row and its gathers, at 20 TB/s.  A step of a
+// single launch takes 1.9 us (barrier, turning the samples around, bringing the copies up to date) and 56 ns per chunk of a wavefront;
+// with a sample on every compute unit nobody reads ahead, and the copies take 39 ns per chunk more to come from HBM.  us per layer of a
+// training step, 48 layers of 32 entries per row, a launch per layer / single: 300 neurons 8.9 / 4.2 (2 samples), 12.8 / 7.2 (256); 1024
+// neurons 9.6 / 7.6 (2), 10.6 / 7.6 (64), 16.6 / 10.4 (200), 16.9 / 11.0 (248), 16.5 / 13.3 (256); 1450 neurons 10.6 / 10.6 (2), 11.4 /
+// 10.6 (64), 19.6 / 14.6 (200), 19.7 / 19.2 (256); 1800 neurons 10.9 / 12.4 (2), 11.1 / 12.4 (16), 12.4 / 12.3 (64); 2048 neurons 11.0 /
+// 13.5 (2), 12.5 / 13.2 (64), 14.4 / 14.3 (96), 15.4 / 14.8 (127); of 8 entries 8.6 / 8.0 (2), 14.6 / 14.4 (256); 1024 neurons of 64
+// entries 13.0 / 12.2 (2); 512 neurons of 160 entries 20.9 / 14.6 (2).
+static bool train_lds_pays(const sdnn_net *net, int B)
+{
+    const int width = B <= 64 ? B : (B + 63) & ~63;
+    return net->train_single + (B >= net->n_cu ? net->train_cold : 0.0) < net->train_per_layer + net->train_gathers * width;
+}
+static bool train_lds(const sdnn_net *net, int B) { return B > 1 && B <= net->n_cu && !net->train[0].tab.empty() && train_lds_pays(net, B); }
 
 static int launch_train_lds(sdnn_net *net, int o, int B, int Bp, int ld, hipStream_t stream)
 {
@@ -3425,6 +3434,13 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
     }
     char *base = (char *)d_workspace;
     auto fail_free = [&](int code) { sdnn_destroy(net); return code; };
+    {
+        int devid = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDevice(&devid) != hipSuccess || hipGetDeviceProperties(&prop, devid) != hipSuccess)
+            return fail_free(fail(nullptr, SDNN_EHIP, "cannot query the device"));
+        net->n_cu = prop.multiProcessorCount;
+    }
 
     // Host part of the setup (transposed index, row schedules): independent per layer, so a group of layers is
     // prepared by one host thread each, then uploaded with one synchronisation for the whole group.
@@ -3725,19 +3741,21 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                         tl[0].cs[(size_t)(t.cs + w * (t.nb + 1) + j)] = (len + LDS_CHUNK - 1) / LDS_CHUNK;
                     }
             }
-            double launches = 0.0, single = 0.0; // what the two passes take with a launch per layer, and with one each
-            bool fits = true;
+            bool fits = true, pays = false;
             for (int o = 0; o < 2; ++o) {
                 int64_t chunks = 0;
                 for (const int32_t depth : tl[o].cs) chunks += depth;
                 fits &= (size_t)chunks <= pl.train[o].n_chunks;
-                single += (double)pl.train[o].tab.size() * TRAIN_STEP + 3.5e-9 * LDS_CHUNK * (double)chunks;
+                net->train_single += 1.9e-6 * (double)pl.train[o].tab.size() + 56e-9 * (double)chunks;
+                net->train_cold += 39e-9 * (double)chunks;
                 for (int32_t l = o; l < n_layers; ++l) {
-                    launches += TRAIN_PER_LAYER(o) + std::max(4.0 * 64 * net->layers[l].nnz / 20e12, 28e-9 * net->max_len[o][l]);
+                    net->train_per_layer += (o ? 4.0e-6 : 3.2e-6) + 28e-9 * net->max_len[o][l];
+                    net->train_gathers += 4.0 * net->layers[l].nnz / 20e12;
                     fits &= net->max_len[o][l] <= TRAIN_LDS_MAX_ROW;
                 }
             }
-            for (int o = 0; o < (fits && single < launches ? 2 : 0); ++o) {
+            for (int32_t B = 2; B <= std::min(cfg->max_batch, net->n_cu); ++B) pays |= train_lds_pays(net, B);
+            for (int o = 0; o < (fits && pays ? 2 : 0); ++o) {
                 const Plan::Train &t = pl.train[o];
                 sdnn_net::Train &n = net->train[o];
                 int64_t at = 0; // as for the LDS-resident forward below
@@ -3827,11 +3845,6 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
 #undef UP
 #undef SYNC
     {
-        int devid = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&devid) != hipSuccess || hipGetDeviceProperties(&prop, devid) != hipSuccess)
-            return fail_free(fail(nullptr, SDNN_EHIP, "cannot query the device"));
-        net->n_cu = prop.multiProcessorCount;
         void *scratch_dev = nullptr; // this GPU's copy of the fixed staging array of sdnn_forward_noalloc
         if (scratch_address(nullptr, &scratch_dev) != SDNN_OK) return fail_free(SDNN_EHIP);
     }

@@ -60,7 +60,9 @@ hipError_t hipMemcpyAsync(void *, const void *, size_t bytes, hipMemcpyKind, hip
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
-hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) { p->multiProcessorCount = 256; return hipSuccess; } // the header appends the version
+static int cus = 256;
+void stub_cus(int n) { cus = n; } // nets that are created from now on
+hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) { p->multiProcessorCount = cus; return hipSuccess; } // the header appends the version
 const char *hipGetErrorString(hipError_t e) { return e == hipErrorInvalidConfiguration ? "invalid configuration" : "no error"; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *) { *p = (void *)((size_t)1 << 44); return hipSuccess; }

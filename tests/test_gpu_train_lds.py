@@ -40,6 +40,29 @@ def test_single_launch_passes_against_a_launch_per_layer(widths, b, lengths):
     assert float(single[len(widths) - 1].abs().max()) > 0
 
 
+def _steps(layers, max_batch, batches, **options):
+    """X_l, Delta_l and the weights of one net after each of its steps over so many samples."""
+    net = sdnn.Net(layers, 2.0, max_batch, training=True, **options)
+    out = []
+    for step, b in enumerate(batches):
+        xl = torch.empty(layers[-1].n_out, b, device=P.DEV)
+        net.sdnn_forward(P.dev(wl.normal_inputs(8600 + step, layers[0].n_in, b)), xl)
+        net.sdnn_backward(sdnn.sdnn_mse_dloss(xl, P.dev(np.abs(wl.normal_inputs(8700 + step, layers[-1].n_out, b)))))
+        out += [xl.clone()] + [net.sdnn_get_activation(k, b) for k in range(1, len(layers) + 1)] + [net.sdnn_get_delta(k, b) for k in range(1, len(layers) + 1)]
+        net.sdnn_sgd_step(0.05)
+        out += [t for k in range(1, len(layers) + 1) for t in net.sdnn_get_weights(k)]
+    net.close()
+    return out
+
+
+def test_steps_of_different_batches():
+    """A net whose steps over 2 and 1 samples take a launch per layer, those over 33 and 64 a single one (tests/test_routes.py)."""
+    layers = pan_nets.layers((1600,) * 13, (32,), seed=8400)
+    batches = (64, 2, 33, 1, 64, 2)
+    single, per_layer = (_steps(layers, 64, batches, lds_forward=o) for o in (sdnn.SDNN_LDS_AUTO, sdnn.SDNN_LDS_OFF))
+    assert all(torch.equal(u, v) for u, v in zip(single, per_layer))
+
+
 def test_single_launch_passes_sigmoid():
     layers = pan_nets.layers((200, 900, 800, 700, 100), (20, 40), seed=8200)
     single, per_layer = (_two_steps(layers, 9, np.inf, activation="sigmoid", lds_forward=o) for o in (sdnn.SDNN_LDS_AUTO, sdnn.SDNN_LDS_OFF))

@@ -204,6 +204,38 @@ def test_training_with_one_launch_per_pass():
     """)
 
 
+def test_training_with_one_launch_per_pass_by_the_batch():
+    """The same net steps in either way: with a launch per layer where wide layers meet few samples, or more samples than compute
+    units; on half of a chip's compute units they are not idle while the copies come."""
+    routes.run("""
+        from tests import pan_nets
+        def batches(n, links, max_batch, cus=256, **options):
+            stub.stub_cus(cus)
+            ls = pan_nets.layers((n,) * 13, (links,), seed=8400)
+            net = Net([(y.n_out, y.n_in, y.row_ptr, y.col_idx, y.values, y.bias) for y in ls], max_batch, training=True, **options)
+            single = []
+            for B in (2, 16, 33, 64, 96, 127, 128, 200, 256):
+                if B > max_batch:
+                    break
+                rc, f = net("sdnn_forward", X0, B, XL, None)
+                assert rc == 0
+                rc, b = net("sdnn_backward", DL, None)
+                assert rc == 0
+                f, b = ([l.startswith("k_train_lds") for l in log] for log in (f, b))
+                assert any(f) == any(b), (n, B)
+                single += [B] * any(f)
+            lib.sdnn_destroy(net.h)
+            return single
+        every = [2, 16, 33, 64, 96, 127, 128, 200, 256]
+        for n, links, max_batch, want in [(300, 32, 256, every), (1024, 32, 256, every), (1201, 32, 256, every), (1600, 32, 64, [33, 64]), (1800, 32, 64, []),
+                                          (2048, 32, 64, []), (1024, 64, 64, every[:4]), (512, 160, 64, every[:4]), (2048, 8, 200, every[:-1])]:
+            got = batches(n, links, max_batch)
+            assert got == want, (n, links, max_batch, got)
+        assert batches(2048, 32, 127, fuse_gradient=-1) == [96, 127]
+        assert batches(300, 32, 256, cus=128) == every[:7]
+    """)
+
+
 def test_turns_at_priority_between_equal_shares():
     """With 1, 2 and 4 samples per workgroup of the LDS forward: the wavefronts do not take turns where the blocks left over, or one
     deep block, make the shares of a few of them longer than the others', nor on the longest rows."""
