@@ -58,6 +58,13 @@ hipError_t hipMemcpyAsync(void *, const void *, size_t bytes, hipMemcpyKind, hip
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+static int capture;
+void stub_capture(int on) { capture = on; } // every stream is being captured
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s)
+{
+    *s = capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 static int cus = 256;

@@ -63,6 +63,44 @@ def test_steps_of_different_batches():
     assert all(torch.equal(u, v) for u, v in zip(single, per_layer))
 
 
+def test_captured_steps_between_steps_of_few_samples():
+    """A graph of a step over 64 samples (the copies are read) and steps over 2 (they are not), in turn, against a net that runs all
+    of them eagerly with a launch per layer."""
+    layers = pan_nets.layers((1600,) * 13, (32,), seed=8400)
+    nets = [sdnn.Net(layers, 2.0, 64, training=True, lds_forward=o) for o in (sdnn.SDNN_LDS_AUTO, sdnn.SDNN_LDS_OFF)]
+    data = {b: [P.dev(wl.normal_inputs(8800 + b, 1600, b)), P.dev(np.abs(wl.normal_inputs(8900 + b, 1600, b))), torch.empty(1600, b, device=P.DEV),
+                torch.empty(1600, b, device=P.DEV)] for b in (2, 64)}
+
+    def step(net, b):
+        x, y, xl, dl = data[b]
+        net.sdnn_forward(x, xl)
+        sdnn.sdnn_mse_dloss(xl, y, out=dl)
+        net.sdnn_backward(dl)
+        net.sdnn_sgd_step(0.05)
+
+    for net in nets:
+        step(net, 2)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step(nets[0], 64)
+    for b in (64, 2, 64, 64, 2):
+        if b == 64:
+            graph.replay()
+        else:
+            step(nets[0], b)
+        step(nets[1], b)
+        torch.cuda.synchronize()
+        for k in (1, 7, 12):
+            assert all(torch.equal(u, v) for u, v in zip(*(net.sdnn_get_weights(k) for net in nets))), (b, k)
+    step(nets[0], 64)
+    step(nets[1], 64)
+    assert torch.equal(nets[0].sdnn_get_activation(12, 64), nets[1].sdnn_get_activation(12, 64))
+    for net in nets:
+        net.close()
+
+
 def test_single_launch_passes_sigmoid():
     layers = pan_nets.layers((200, 900, 800, 700, 100), (20, 40), seed=8200)
     single, per_layer = (_two_steps(layers, 9, np.inf, activation="sigmoid", lds_forward=o) for o in (sdnn.SDNN_LDS_AUTO, sdnn.SDNN_LDS_OFF))

@@ -236,6 +236,36 @@ def test_training_with_one_launch_per_pass_by_the_batch():
     """)
 
 
+def test_copies_of_narrow_training_nets_follow_when_they_are_read():
+    """A step that does not read the copies leaves them behind; the next pass that reads them brings them up to date first.  Not in
+    a graph, and not once a graph reads them: its replays have to find them current."""
+    routes.run("""
+        from tests import pan_nets
+        def net(n=1600, max_batch=64):
+            ls = pan_nets.layers((n,) * 13, (32,), seed=8400)
+            return Net([(y.n_out, y.n_in, y.row_ptr, y.col_idx, y.values, y.bias) for y in ls], max_batch, training=True)
+        def fills(net, B, capture=()):
+            out = []
+            for k, (name, args) in enumerate([("sdnn_forward", (X0, B, XL, None)), ("sdnn_backward", (DL, None)), ("sdnn_sgd_step", (C.c_float(0.1), None))]):
+                stub.stub_capture(k in capture)
+                rc, log = net(name, *args)
+                assert rc == 0
+                out.append(sum(l.startswith("k_train_fill") for l in log))
+                assert not out[-1] or k == 2 or log[0].startswith("k_train_fill") or log[1].startswith("k_train_fill"), log
+            stub.stub_capture(0)
+            return out
+        a = net()
+        assert [fills(a, B) for B in (64, 2, 1, 2, 64, 64)] == [[0, 0, 2], [0, 0, 0], [0, 0, 0], [0, 0, 0], [2, 0, 2], [0, 0, 2]]
+        for B in (1, 2):                               # a captured step, and what follows it
+            b = net()
+            assert [fills(b, B, (0, 1, 2)), fills(b, B), fills(b, 64), fills(b, B)] == [[0, 0, 2], [0, 0, 0], [2, 0, 2], [0, 0, 0]]
+        c = net()                                      # a graph that reads copies which are behind, and a pass after it
+        assert [fills(c, 2), fills(c, 64, (0, 1)), fills(c, 2), fills(c, 64), fills(c, 2), fills(c, 64)] == [[0, 0, 0], [2, 2, 2], [0, 0, 2], [2, 0, 2], [0, 0, 2], [0, 0, 2]]
+        d = net()
+        assert [fills(d, 64, (0, 1, 2)), fills(d, 1), fills(d, 64)] == [[0, 0, 2], [0, 0, 2], [0, 0, 2]]
+    """)
+
+
 def test_turns_at_priority_between_equal_shares():
     """With 1, 2 and 4 samples per workgroup of the LDS forward: the wavefronts do not take turns where the blocks left over, or one
     deep block, make the shares of a few of them longer than the others', nor on the longest rows."""
