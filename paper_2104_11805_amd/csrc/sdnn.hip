@@ -3075,8 +3075,10 @@ static void plan_b1(const sdnn_layer *layers, int32_t n_layers, const sdnn_confi
 
 // Training with a launch per pass (k_train_lds): narrow nets of short rows, whose gradient is not formed in the backward sweep; four
 // layers and more (a step launches two kernels more, to bring the copies up to date).
-// Fills in the tables' sizes; the chunks are a bound (the columns may not be known here): the first block of a copy is no deeper
-// than its longest row, every later one no deeper than the mean of the 64 rows before it.
+// Fills in the tables' sizes; the chunks are a bound, from the lengths of the rows of W alone (the columns may not be known here).
+// W_L, by the length of its rows: as many as there are.  The other W follow the rows of the W^T above, in any order for all that
+// is known here: no more than if every block had one of their longest rows.  W^T: its first block is no deeper than the most entries
+// a column can have, every later one no deeper than the mean of the 64 rows before it.
 #define TRAIN_LDS_MAX_ROW 512
 static void plan_train(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, Plan &pl)
 {
@@ -3105,7 +3107,16 @@ static void plan_train(const sdnn_layer *layers, int32_t n_layers, const sdnn_co
             t.n_pos += (size_t)e.n_pos;
             t.n_rows += (size_t)n;
             const size_t nnz = (size_t)y.row_ptr[y.n_out], blocks = ((size_t)n + 63) / 64;
-            t.n_chunks += TRAIN_LDS_MAX_ROW / LDS_CHUNK + (nnz / 64 + 15 * blocks) / LDS_CHUNK + 1;
+            if (o) {
+                t.n_chunks += (size_t)(std::min(y.n_out, TRAIN_LDS_MAX_ROW) + LDS_CHUNK - 1) / LDS_CHUNK + (nnz / 64 + (LDS_CHUNK - 1) * blocks) / LDS_CHUNK;
+            } else if (k == n_layers - 1) {
+                t.n_chunks += lm_chunks(y);
+            } else {
+                std::vector<int32_t> chunks((size_t)n);
+                for (int32_t r = 0; r < n; ++r) chunks[(size_t)r] = (y.row_ptr[r + 1] - y.row_ptr[r] + LDS_CHUNK - 1) / LDS_CHUNK;
+                std::partial_sort(chunks.begin(), chunks.begin() + (ptrdiff_t)blocks, chunks.end(), std::greater<int32_t>());
+                for (size_t b = 0; b < blocks; ++b) t.n_chunks += (size_t)chunks[b];
+            }
         }
         if (t.n_chunks * LDS_CHUNK_BYTES >= ((size_t)1 << 32)) return; // the kernel addresses a copy with 32-bit offsets
     }

@@ -211,7 +211,7 @@ def test_training_with_one_launch_per_pass_by_the_batch():
         from tests import pan_nets
         def batches(n, links, max_batch, cus=256, **options):
             stub.stub_cus(cus)
-            ls = pan_nets.layers((n,) * 13, (links,), seed=8400)
+            ls = pan_nets.layers((n,) * 13, links if isinstance(links, tuple) else (links,), seed=8400)
             net = Net([(y.n_out, y.n_in, y.row_ptr, y.col_idx, y.values, y.bias) for y in ls], max_batch, training=True, **options)
             single = []
             for B in (2, 16, 33, 64, 96, 127, 128, 200, 256):
@@ -232,6 +232,9 @@ def test_training_with_one_launch_per_pass_by_the_batch():
             got = batches(n, links, max_batch)
             assert got == want, (n, links, max_batch, got)
         assert batches(2048, 32, 127, fuse_gradient=-1) == [96, 127]
+        # a longer row in every block of 64: W follows the order of the rows of the W^T above, and the room for it is not that of sorted rows
+        for n, links in [(700, (16,) * 20 + (100,)), (512, (8,) * 63 + (200,)), (300, (4,) * 60 + (500,))]:
+            assert batches(n, links, 64) == every[:4], (n, links)
         assert batches(300, 32, 256, cus=128) == every[:7]
     """)
 
