@@ -1,5 +1,5 @@
 """Training on narrow nets with one launch per pass: widths around the blocks of 64 rows and the 1024 and 2048 positions, rows of
-W and of W^T around the chunks of sixteen entries, batches that are filled up.  Forward and deltas the same bits as the oracle's,
+W and of W^T around the chunks of sixteen entries and up to 512, batches that are filled up and batches of a net made for more.  Forward and deltas the same bits as the oracle's,
 over two steps, so that the copies have followed the first one's values."""
 import numpy as np
 import pytest
@@ -61,6 +61,14 @@ def test_steps_of_different_batches():
     batches = (64, 2, 33, 1, 64, 2)
     single, per_layer = (_steps(layers, 64, batches, lds_forward=o) for o in (sdnn.SDNN_LDS_AUTO, sdnn.SDNN_LDS_OFF))
     assert all(torch.equal(u, v) for u, v in zip(single, per_layer))
+
+
+@pytest.mark.parametrize("widths,max_batch,lengths,full,batches", pan_nets.TRAIN_NETS)
+def test_single_launch_passes_at_their_limits(widths, max_batch, lengths, full, batches):
+    layers = pan_nets.layers(widths, lengths, seed=8500, full=full)
+    single, per_layer = (_steps(layers, max_batch, batches, lds_forward=o) for o in (sdnn.SDNN_LDS_AUTO, sdnn.SDNN_LDS_OFF))
+    assert all(torch.equal(u, v) for u, v in zip(single, per_layer))
+    assert all(float(t.abs().max()) > 0 for t in single[:2 * len(layers) + 1])
 
 
 def test_captured_steps_between_steps_of_few_samples():

@@ -239,6 +239,30 @@ def test_training_with_one_launch_per_pass_by_the_batch():
     """)
 
 
+def test_training_with_one_launch_per_pass_at_its_limits():
+    """The nets of tests/test_gpu_train_lds.py go through it; a row or a column of 513 entries, and more samples than compute units,
+    do not."""
+    routes.run("""
+        from tests import pan_nets
+        def single(widths, max_batch, lengths, full, batches):
+            ls = pan_nets.layers(widths, lengths, seed=8500, full=full)
+            net = Net([(y.n_out, y.n_in, y.row_ptr, y.col_idx, y.values, y.bias) for y in ls], max_batch, training=True)
+            out = []
+            for B in batches:
+                rc, log = net("sdnn_forward", X0, B, XL, None)
+                assert rc == 0
+                out.append(any(l.startswith("k_train_lds") for l in log))
+            return out
+        for case in pan_nets.TRAIN_NETS:
+            assert single(*case) == [B > 1 for B in case[4]], (case, single(*case))
+        assert single((600,) * 6, 33, (1, 6, 2, 5), 0, (33,)) == [True]
+        assert single((600,) * 6, 33, (1, 6, 2, 5), 1, (33,)) == [False]
+        assert single((513,) * 6, 33, (1, 6, 2, 513), 0, (33,)) == [False]
+        stub.stub_cus(128)
+        assert single((300,) * 6, 256, (8,), 0, (127, 128, 129, 256)) == [True, True, False, False]
+    """)
+
+
 def test_copies_of_narrow_training_nets_follow_when_they_are_read():
     """A step that does not read the copies leaves them behind; the next pass that reads them brings them up to date first.  Not in
     a graph, and not once a graph reads them: its replays have to find them current."""
