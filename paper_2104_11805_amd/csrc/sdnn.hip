@@ -4412,7 +4412,8 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
     // cache (what a layer wrote is what the next one gathers): measured on 65536-neuron layers, blocks of 1024
     // samples: 179 ms per 24 layers in one piece, 161 ms in sub-blocks of 64; 16384 neurons, 4096 samples: 41.5 ms
     // per 48 layers in one piece, 39.1 in sub-blocks of 256.
-    const int sub_w = training ? 0 : sub_block_width(net, B);
+    // (Not where d_XL lies across d_X0: a sub-block's results would replace inputs of the later ones.)
+    const int sub_w = training || shifted ? 0 : sub_block_width(net, B);
     if (sub_w > 0) {
         for (int s0 = 0; s0 < B; s0 += sub_w) {
             const int s1 = std::min(B, s0 + sub_w);

@@ -62,3 +62,18 @@ def test_lds_forward_over_its_input(shift):
     net.sdnn_forward(x0, out)
     assert np.array_equal(P.host(out), ref)
     net.close()
+
+
+@pytest.mark.parametrize("shift", [1, 2100 * 3 + 2])
+def test_forward_across_a_large_input(shift):
+    """Blocks that a launch per layer takes through the net in sub-blocks of samples where the result does not lie across the input."""
+    layers = [_ragged(9300 + l, 5000, 5000, (3, 20)) for l in range(2)]
+    x = wl.normal_inputs(9310, 5000, 2100)
+    net = sdnn.Net(layers, 1.5, 2100, training=False, lds_forward=sdnn.SDNN_LDS_OFF)
+    ref = net.sdnn_forward(P.dev(x), torch.empty(5000, 2100, device=P.DEV)).clone()
+    room = torch.empty(x.size + 2 * 8192, device=P.DEV)
+    x0, out = room[8192:8192 + x.size].view(-1, 2100), room[8192 + shift:8192 + shift + x.size].view(-1, 2100)
+    x0.copy_(P.dev(x))
+    net.sdnn_forward(x0, out)
+    assert torch.equal(out, ref)
+    net.close()

@@ -29,6 +29,17 @@ def test_result_across_the_input():
     """)
 
 
+def test_result_across_the_input_in_one_piece():
+    """Blocks of activations past the memory-side cache go through all layers in sub-blocks of samples, whose results must not replace
+    inputs of the later ones."""
+    routes.run("""
+        net = Net([layer(5000, 5000, (8,))] * 3, 2000, lds_forward=-1)
+        for shift, pieces in [(0, 3), (4, 1), (-4, 1), (4 * 5000 * 2000 - 4, 1), (4 * 5000 * 2000, 3)]:
+            rc, log = net("sdnn_forward", X0, 2000, X0 + shift, None)
+            assert rc == 0 and len(log) == 3 * pieces, (shift, log)
+    """)
+
+
 def test_gradient_over_two_windows_of_samples():
     """Two rounded windows only where the batch itself is 128 samples on up to 16384 neurons (two partial gradients from 6.5 MB on):
     not for the batches that are filled up to 128."""
