@@ -135,8 +135,8 @@ typedef struct {
  * are bound by their latency); ON uses it whenever the copy exists; OFF never builds it.
  * Inference nets of at least three layers, wider than 16384 neurons and made for more than 64 samples, have a second such copy
  * (up to 10.5 more bytes per stored entry) for a pass with a launch per layer in which a workgroup carries two samples through
- * a layer with a panel of up to 16384 neurons at a time in LDS: same bits again.  AUTO and ON use it where it is the faster way;
- * OFF, a positive panel_cols and reorder_rows = 1 never build it.
+ * a layer with a panel of up to 16384 neurons at a time in LDS: same bits again.  AUTO uses it where it is the faster way, and so does
+ * ON where the layers are too wide for the launch above; OFF, ON up to that width, a positive panel_cols and reorder_rows = 1 never build it.
  * Training nets of at least four layers of up to 2048 neurons, rows and columns of up to 512 entries, 2 <= max_batch <= 256 and no gradient
  * formed in the backward sweep have lane-major copies of W and of W^T (at most 200 KB and 6.5 bytes per stored entry each, and
  * another X_l and Delta_l): sdnn_forward and sdnn_backward are then one such launch each where that is faster than a launch per

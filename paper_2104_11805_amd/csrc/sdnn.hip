@@ -3125,9 +3125,11 @@ static void plan_train(const sdnn_layer *layers, int32_t n_layers, const sdnn_co
 
 // The forward in panels (k_fwd_pan) is set up for inference nets wider than a panel, of at least three layers (the two passes that
 // turn the samples around take about as long as a layer), with at least four entries per row and panel in the mean, made for
-// batches that can fill the chip (pan_forward_pays).  Fills in the layers' geometry.
-static bool pan_wanted(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, std::vector<Plan::PerLayer> &pl)
+// batches that can fill the chip (pan_forward_pays); not where lds_forward = ON takes k_fwd_lds with every batch (`lm`: the net has its copy).
+// Fills in the layers' geometry.
+static bool pan_wanted(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, bool lm, std::vector<Plan::PerLayer> &pl)
 {
+    if (lm && cfg->lds_forward == SDNN_LDS_ON) return false;
     if (cfg->training || cfg->lds_forward == SDNN_LDS_OFF || cfg->panel_cols > 0 || cfg->reorder_rows || n_layers < 3 || cfg->max_batch <= 64) return false;
     int64_t nnz = 0, rows = 0, widest = 0;
     for (int32_t l = 0; l < n_layers; ++l) {
@@ -3198,7 +3200,7 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
     const size_t mb = (size_t)cfg->max_batch, mld = (size_t)row_pitch((int64_t)max_n, cfg->max_batch);
     plan_b1(layers, n_layers, cfg, pl);
     const bool b1 = pl.b1_chunk_bytes != 0;
-    pl.pan = pan_wanted(layers, n_layers, cfg, pl.pl);
+    pl.pan = pan_wanted(layers, n_layers, cfg, lm, pl.pl);
     plan_train(layers, n_layers, cfg, pl);
     size_t paired = 0; // floats of the largest block of activations between its layers
     if (pl.pan) {
@@ -4221,12 +4223,12 @@ static double per_layer_forward_seconds(const sdnn_net *net, int B)
 // 3001 neurons 141 / 153 (64 samples), 169 / 150 (100); 8000 neurons 311 / 358 (150), 388 / 359 (200); 16384 neurons 668 / 717
 // (200), 948 / 793 (300); 32000 neurons 1197 / 1382 (150), 1604 / 1385 (200), 2374 / 2987 (300: a second round), 3526 / 2907 (450);
 // uneven rows, 1024 neurons 107 / 49 (100), 2000 neurons 129 / 143 (64), 172 / 140 (100).
-// *seconds (not NULL): what the faster one of the two takes.
-static int lds_forward_samples(const sdnn_net *net, int B, double *seconds = nullptr)
+// shifted: the single launch cannot run, d_XL lies across d_X0.  *seconds (not NULL): what the faster one of those that can run takes.
+static int lds_forward_samples(const sdnn_net *net, int B, bool shifted = false, double *seconds = nullptr)
 {
     const double per_layer = seconds || net->cfg.lds_forward == SDNN_LDS_AUTO ? per_layer_forward_seconds(net, B) : 0.0;
     if (seconds) *seconds = per_layer;
-    if (!net->lm || net->cfg.lds_forward == SDNN_LDS_OFF) return 0;
+    if (shifted || !net->lm || net->cfg.lds_forward == SDNN_LDS_OFF) return 0;
     for (const LayerDev &d : net->layers)
         if (d.n_out == 0) return 0; // an empty layer: leave it to the general path
     static const double entry[3] = {3.5e-9, 3.9e-9, 6.2e-9};
@@ -4241,7 +4243,7 @@ static int lds_forward_samples(const sdnn_net *net, int B, double *seconds = nul
         if (!best || t < t_best) { best = T; t_best = t; }
     }
     if (!best) return 0;
-    if (seconds) *seconds = net->cfg.lds_forward == SDNN_LDS_ON ? 0.0 : std::min(t_best, per_layer);
+    if (seconds) *seconds = std::min(t_best, per_layer);
     if (net->cfg.lds_forward == SDNN_LDS_ON) return best;
     return t_best < per_layer ? best : 0;
 }
@@ -4352,10 +4354,10 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
     // a workgroup reads and writes columns of its own: d_XL may be d_X0 itself, but not lie across it
     const bool shifted = d_XL && d_XL != d_X0 && overlap(d_X0, net->layers[0].n_in, d_XL, net->layers[L - 1].n_out, B);
     double other = 0.0;
-    const int T = lds_forward_samples(net, B, net->pan.empty() ? nullptr : &other);
+    const int T = lds_forward_samples(net, B, shifted, net->pan.empty() ? nullptr : &other);
     if (ping == net->d_ping && pan_forward_pays(net, B, other)) // (in the workspace's buffers: what it keeps there is larger than X)
         return forward_pan(net, d_X0, B, d_XL, stream, ping, pong);
-    if (T && !shifted) {
+    if (T) {
         const bool sig = net->cfg.activation == ACT_SIGMOID;
         const int ti = T == 1 ? 0 : T == 2 ? 1 : 2;
         static const void *const fns[2][3] = {

@@ -185,6 +185,30 @@ def test_forward_in_panels():
     """)
 
 
+def test_forward_in_panels_beside_the_single_launch():
+    """A result that lies across the input cannot take the single launch: what the panels are compared with is a launch per layer.
+    lds_forward = ON takes the single launch with every batch and holds no copy for panels; layers too wide for it still do."""
+    routes.run("""
+        def spread(n, n_in, links):
+            ci = np.sort((np.arange(links) * (n_in // links) + np.random.default_rng(n).integers(0, n_in // links, (n, links))), axis=1)
+            return n, n_in, np.arange(0, n * links + 1, links, dtype=np.int32), ci.astype(np.int32).ravel(), np.ones(n * links, np.float32), None
+        def kernel(net, B, xl=XL):
+            rc, log = net("sdnn_forward", X0, B, xl, None)
+            assert rc == 0
+            return log[len(log) // 2].split("<")[0]
+        net = Net([spread(18000, 18000, 32)] * 24, 1024)
+        for B in (507, 729, 951):
+            assert [kernel(net, B), kernel(net, B, X0 + 4)] == ["k_fwd_lds", "k_fwd_pan"], B
+        auto, on, off = (Net([spread(32768, 32768, 32)] * 4, 1024, lds_forward=o) for o in (0, 1, -1))
+        assert [kernel(n, 512) for n in (auto, on)] == ["k_fwd_pan", "k_fwd_lds"]
+        entries = 4 * 32 * 32768
+        assert on.bytes - off.bytes < 7 * entries and auto.bytes - on.bytes > 6 * entries
+        rc, log = on("sdnn_set_weights", 2, X0, XL, None)
+        assert rc == 0 and not any(l.startswith("k_pan") for l in log), (rc, log)
+        assert kernel(Net([spread(40000, 40000, 32)] * 4, 1024, lds_forward=1), 512) == "k_fwd_pan"
+    """)
+
+
 def test_training_with_one_launch_per_pass():
     """Narrow nets of short rows and at least four layers: not with one sample, more samples than compute units, long rows or
     columns, the gradient formed in the sweep, or lds_forward off."""
