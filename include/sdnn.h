@@ -133,15 +133,21 @@ typedef struct {
  * adds its terms in storage order: same bits as the per-layer kernels.  AUTO builds the copy and uses the
  * launch where it is faster (enough samples to fill the chip, or layers so small that per-layer launches
  * are bound by their latency); ON uses it whenever the copy exists; OFF never builds it.
- * Inference nets of at least three layers, wider than 16384 neurons and made for more than 64 samples, have a second such copy
- * (up to 10.5 more bytes per stored entry) for a pass with a launch per layer in which a workgroup carries two samples through
- * a layer with a panel of up to 16384 neurons at a time in LDS: same bits again.  AUTO uses it where it is the faster way, and so does
- * ON where the layers are too wide for the launch above; OFF, ON up to that width, a positive panel_cols and reorder_rows = 1 never build it.
+ * Inference nets of at least three layers, wider than 16384 neurons (at most 262144), of four entries and more per row and panel in
+ * the mean, and made for more than 64 samples and for 3200000 activations and more a layer, have a second such copy for a pass with a
+ * launch per layer in which a workgroup carries two samples through a layer with a panel of up to 16384 neurons at a time in LDS: same
+ * bits again.  Its room: 10.5 bytes per stored entry, 12 per neuron, and for every layer and 16384 of its rows 0.34 MB and 0.15 MB per
+ * panel (13.4 bytes per entry in all with 65536 neurons of 32 entries, 18.9 with 33000 of 12).  AUTO uses it where it is the faster
+ * way, and so does ON where the layers are too wide for the launch above; OFF, ON up to that width, a positive panel_cols and
+ * reorder_rows = 1 never build it.
  * Training nets of at least four layers of up to 2048 neurons, rows and columns of up to 512 entries, 2 <= max_batch <= 256 and no gradient
- * formed in the backward sweep have lane-major copies of W and of W^T (at most 200 KB and 6.5 bytes per stored entry each, and
- * another X_l and Delta_l): sdnn_forward and sdnn_backward are then one such launch each where that is faster than a launch per
- * layer, with the same bits; sdnn_sgd_step and sdnn_set_weights keep the copies current.  OFF, a positive panel_cols and
- * reorder_rows = 1 never build them. */
+ * formed in the backward sweep have lane-major copies of W and of W^T: sdnn_forward and sdnn_backward are then one such launch each
+ * where that is faster than a launch per layer for the pass's samples, with the same bits; sdnn_sgd_step and sdnn_set_weights keep
+ * the copies current, or the next pass that reads them does.  Their room, for every layer: 6 bytes per entry of W where every row
+ * is filled up to a multiple of 16 and blocks of 64 rows to their longest one; for W^T 6 bytes per entry, 90 per neuron and 0.2 MB; another
+ * X_l and Delta_l, of max_batch samples and a multiple of 1024 neurons (in all 1.2 MB a layer of 1024 neurons of 32 entries with 64
+ * samples; it is reserved from the lengths of the rows alone, also where the columns then make a launch per layer the faster way).
+ * OFF, a positive panel_cols and reorder_rows = 1 never build them. */
 #define SDNN_LDS_AUTO 0
 #define SDNN_LDS_ON 1
 #define SDNN_LDS_OFF (-1)
