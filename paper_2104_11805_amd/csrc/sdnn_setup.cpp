@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cstdarg>
 #include <cstdio>
+#include <cstring>
 #include <numeric>
 #include <vector>
 
@@ -233,23 +234,41 @@ void sdnn_pan_geometry(const sdnn_layer &y, const PanLayer *below, PanLayer &g)
     g.halves = (g.halves + 3) & ~(size_t)3;
 }
 
+// How many of a row's columns are below `bound`: four at a time, without branches on them.
+static int32_t entries_below(const int32_t *c, int32_t len, int32_t bound)
+{
+    typedef int32_t four __attribute__((vector_size(16)));
+    const four bounds = {bound, bound, bound, bound};
+    four sum = {0, 0, 0, 0};
+    int32_t e = 0;
+    for (; e + 4 <= len; e += 4) {
+        four v;
+        std::memcpy(&v, c + e, sizeof v);
+        sum -= v < bounds; // -1 where it holds
+    }
+    int32_t n = sum[0] + sum[1] + sum[2] + sum[3];
+    for (; e < len; ++e) n += c[e] < bound;
+    return n;
+}
+
 // A wavefront's lanes walk their rows in step, so a block of 64 rows costs as many slots in a panel as its fullest row has
 // entries there.  The rows of a range are halved, again and again, at the median of the panel in which their counts spread most,
 // until 64 are left: their counts are then about equal in every panel (32 entries per row over four panels: 1.10 slots per entry,
 // against 1.76 for rows as they come).
 void sdnn_pan_layout(const sdnn_layer &y, const PanLayer &g, PanLayout &out)
 {
-    const int32_t P = g.n_panels, nb = g.nb;
-    std::vector<int32_t> count((size_t)y.n_out * P, 0), order, len;
-    std::vector<int64_t> per_panel((size_t)P, 0), keys;
-    for (int32_t r = 0; r < y.n_out; ++r) { // columns ascend: a panel's entries end where the next one's begin
-        const int32_t *c = y.col_idx + y.row_ptr[r], *const end = y.col_idx + y.row_ptr[r + 1];
+    const int32_t P = g.n_panels, S = (P + 3) & ~3, nb = g.nb; // a row's counts: P, and zeros up to a multiple of four
+    std::vector<int32_t> count((size_t)y.n_out * S, 0), order, of_row, rows_of_count, second;
+    std::vector<int64_t> per_panel((size_t)P, 0);
+    for (int32_t r = 0; r < y.n_out; ++r) {
+        const int32_t *const c = y.col_idx + y.row_ptr[r], len = y.row_ptr[r + 1] - y.row_ptr[r];
+        int32_t before = 0;
         for (int32_t p = 0; p < P; ++p) {
-            const int64_t bound = (int64_t)(p + 1) * g.panel_cols;
-            const int32_t *const from = c;
-            while (c < end && *c < bound) ++c;
-            count[(size_t)r * P + p] = (int32_t)(c - from);
-            per_panel[(size_t)p] += c - from;
+            int32_t below = len; // entries of this panel and those before it
+            if (p < P - 1) below = before + entries_below(c + before, len - before, (p + 1) * g.panel_cols); // columns ascend
+            count[(size_t)r * S + p] = below - before;
+            per_panel[(size_t)p] += below - before;
+            before = below;
         }
     }
     out.fullest = *std::max_element(per_panel.begin(), per_panel.end());
@@ -277,25 +296,50 @@ void sdnn_pan_layout(const sdnn_layer &y, const PanLayer &g, PanLayout &out)
                 if (b > a) blocks.push_back({a, b - a, 0});
                 continue;
             }
-            int32_t by = 0;
-            int64_t sum[PAN_MAX] = {}, sq[PAN_MAX] = {};
-            for (int32_t k = a; k < b; ++k) {
-                const int32_t *c = count.data() + (size_t)order[(size_t)k] * P;
-                for (int32_t p = 0; p < P; ++p) {
-                    sum[p] += c[p];
-                    sq[p] += (int64_t)c[p] * c[p];
+            int32_t by = 0, sum[PAN_MAX] = {};   // (at most PAN_POS rows of at most PAN_POS entries)
+            double sq[PAN_MAX] = {}, most = -1;
+            for (int32_t p0 = 0; p0 < S; p0 += 4) {
+                int32_t s4[4] = {};
+                double q4[4] = {};
+                for (int32_t k = a; k < b; ++k) {
+                    const int32_t *c = count.data() + (size_t)order[(size_t)k] * S + p0;
+                    for (int i = 0; i < 4; ++i) {
+                        s4[i] += c[i];
+                        q4[i] += (double)c[i] * c[i];
+                    }
                 }
+                std::copy_n(s4, 4, sum + p0);
+                std::copy_n(q4, 4, sq + p0);
             }
-            double most = -1;
             for (int32_t p = 0; p < P; ++p) {
-                const double spread = (double)sq[p] - (double)sum[p] * (double)sum[p] / (b - a);
+                const double spread = sq[p] - (double)sum[p] * (double)sum[p] / (b - a);
                 if (spread > most) { most = spread; by = p; }
             }
+            // the fullest rows first, ties by row: `order` ascends in every part, so a pass that keeps it that way does both
             const int32_t m = a + ((b - a + 63) / 64 + 1) / 2 * 64;
-            keys.resize((size_t)(b - a)); // fullest first, ties by row
-            for (int32_t k = a; k < b; ++k) keys[(size_t)(k - a)] = (int64_t)-count[(size_t)order[(size_t)k] * P + by] * ((int64_t)1 << 32) + order[(size_t)k];
-            std::nth_element(keys.begin(), keys.begin() + (m - a), keys.end());
-            for (int32_t k = a; k < b; ++k) order[(size_t)k] = (int32_t)(uint32_t)keys[(size_t)(k - a)];
+            of_row.resize((size_t)(b - a));
+            int32_t fullest = 0;
+            for (int32_t k = a; k < b; ++k) {
+                const int32_t c = count[(size_t)order[(size_t)k] * S + by];
+                of_row[(size_t)(k - a)] = c;
+                fullest = std::max(fullest, c);
+            }
+            rows_of_count.assign((size_t)fullest + 1, 0);
+            for (int32_t k = 0; k < b - a; ++k) rows_of_count[(size_t)of_row[(size_t)k]]++;
+            int32_t median = fullest, left = m - a; // rows of more than `median` entries go first, and `left` of just so many
+            while (rows_of_count[(size_t)median] < left) left -= rows_of_count[(size_t)median--];
+            second.resize((size_t)(b - a));
+            int32_t n0 = a, n1 = 0;
+            for (int32_t k = a; k < b; ++k) {
+                const int32_t c = of_row[(size_t)(k - a)], row = order[(size_t)k];
+                const int32_t tie = c == median && left > 0, first = (c > median) | tie;
+                left -= tie;
+                order[(size_t)n0] = row; // (both are written, one counts)
+                second[(size_t)n1] = row;
+                n0 += first;
+                n1 += !first;
+            }
+            std::copy_n(second.begin(), n1, order.begin() + m);
             todo.push_back({m, b});
             todo.push_back({a, m});
         }
@@ -303,7 +347,7 @@ void sdnn_pan_layout(const sdnn_layer &y, const PanLayer &g, PanLayout &out)
         for (size_t k = 0; k < blocks.size(); ++k)
             for (int32_t p = 0; p < P; ++p) {
                 int32_t &d = depth[k * P + p];
-                for (int32_t i = 0; i < blocks[k].n; ++i) d = std::max(d, count[(size_t)order[(size_t)(blocks[k].first + i)] * P + p]);
+                for (int32_t i = 0; i < blocks[k].n; ++i) d = std::max(d, count[(size_t)order[(size_t)(blocks[k].first + i)] * S + p]);
                 blocks[k].slots += d;
             }
         // dealt to the wavefronts, the deepest first, each to the one with the fewest slots so far
