@@ -265,7 +265,10 @@ void sdnn_pan_layout(const sdnn_layer &y, const PanLayer &g, PanLayout &out)
         int32_t before = 0;
         for (int32_t p = 0; p < P; ++p) {
             int32_t below = len; // entries of this panel and those before it
-            if (p < P - 1) below = before + entries_below(c + before, len - before, (p + 1) * g.panel_cols); // columns ascend
+            if (p < P - 1) { // columns ascend; of short rows all entries are looked at, the same number for every panel and row
+                const int32_t from = len > 128 ? before : 0;
+                below = from + entries_below(c + from, len - from, (p + 1) * g.panel_cols);
+            }
             count[(size_t)r * S + p] = below - before;
             per_panel[(size_t)p] += below - before;
             before = below;
