@@ -2008,7 +2008,7 @@ struct SpmvLmArgs {
     unsigned lm_bytes;
     const float *in;
     unsigned in_bytes;
-    const float *aux;    // MODE 0: biases, MODE 1: X_{l-1}; in the order of the results' places
+    const float *aux;    // MODE 0: biases, MODE 1 and 2: X_{l-1}; in the order of the results' places
     float *out;
     float cap;
     int32_t act;
@@ -2020,9 +2020,11 @@ __global__ void __launch_bounds__(64) k_spmv_lm(const SpmvLmArgs a)
     const int lane = threadIdx.x, b = blockIdx.x;
     typedef const int32_t __attribute__((address_space(4))) *cs_ptr;
     const cs_ptr scs = (cs_ptr)a.cs;
-    // Chunks requested together.  Back-propagation: the longest of a few thousand random columns with 32 entries in the mean have about
-    // sixty, and a second round of loads and gathers for them is what the whole layer would wait for.  Step, us per layer, four
-    // chunks / eight: 1024 neurons 6.92 / 6.70, 4096 7.53 / 7.25, 8192 9.51 / 9.12, 16384 11.66 / 11.22, 32768 17.33 / 17.08, 50001 the same.
+    // Chunks requested together.  Back-propagation (MODE 1): the longest of a few thousand random columns with 32 entries in the mean
+    // have about sixty, and a second round of loads and gathers for them is what the whole layer would wait for.  Not in layers of more
+    // than three wavefronts per CU, which the L2 is busy with (MODE 2).  Step, us per layer, four chunks / eight: 1024 neurons 6.92 /
+    // 6.70, 4096 7.53 / 7.25, 8192 9.51 / 9.12, 16384 11.66 / 11.22, 32768 17.33 / 17.08; forward and back-propagation 40001 neurons
+    // 14.81 / 14.69, 49000 16.87 / 16.82, 49200 17.10 / 17.17, 60000 19.95 / 20.05, 65504 21.31 / 21.51, 65536 22.45 / 22.75.
     constexpr int LOAD = TRAIN && MODE == 1 && !WIDE ? 8 : 4;
     int c0, n, place; // first chunk, chunks, where the result goes
     [[maybe_unused]] int len = 0; // TRAIN: entries of the lane's row
@@ -2073,9 +2075,11 @@ __global__ void __launch_bounds__(64) k_spmv_lm(const SpmvLmArgs a)
         if (TRAIN && !WIDE && a.in_bytes > 4u * 0xffffu) { // 65536 columns: no 2-byte column is outside the operand
 #pragma unroll
             for (int u = 0; u < LOAD; ++u)
+                if (i + u < n) {
 #pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (i + u < n && 8 * (i + u) + k >= len) x[u][k] = 0.0f;
+                    for (int k = 0; k < 8; ++k)
+                        if (8 * (i + u) + k >= len) x[u][k] = 0.0f;
+                }
         }
 #pragma unroll
         for (int u = 0; u < LOAD; ++u)
@@ -4071,6 +4075,8 @@ static int launch_spmm(sdnn_net *net, const LayerDev &d, const float *in, int ld
         b.lm_bytes = 0xffffffffu; // every chunk that the table names is there
         b.cap = a.cap; b.act = a.act;
         if (net->b1_wide) hipLaunchKernelGGL((k_spmv_lm<MODE, true, true>), dim3((unsigned)d.b1_blocks[o]), dim3(64), 0, stream, b);
+        else if (MODE == 1 && d.b1_blocks[o] > 3 * net->n_cu)
+            hipLaunchKernelGGL((k_spmv_lm<2 * MODE, false, true>), dim3((unsigned)d.b1_blocks[o]), dim3(64), 0, stream, b);
         else hipLaunchKernelGGL((k_spmv_lm<MODE, false, true>), dim3((unsigned)d.b1_blocks[o]), dim3(64), 0, stream, b);
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;

@@ -69,6 +69,16 @@ def test_wide_layers():
     _steps([_layer(9542, 41000, 60, (1, 3)), _layer(9543, 50, 41000, (2, 9, 33))], 9560, n_steps=2, replace=False)
 
 
+@pytest.mark.parametrize("n,long_columns", [(49152, 300), (49153, 300), (65536, 300), (65536, 33)])
+def test_long_columns_of_wide_layers(n, long_columns):
+    """On both sides of three wavefronts per CU: the first 64 columns have an entry in every row, the others one or none."""
+    rng = np.random.default_rng(9545)
+    cols = np.concatenate([np.tile(np.arange(64), (long_columns, 1)), 64 + np.sort(rng.choice(n - 64, (long_columns, 9), replace=False), axis=1)], axis=1)
+    y = wl.Layer(long_columns, n, np.arange(0, cols.size + 1, 73, dtype=np.int32), cols.astype(np.int32).ravel(),
+                 (rng.standard_normal(cols.size) * 0.1).astype(np.float32), (rng.standard_normal(long_columns) * 0.1).astype(np.float32))
+    _steps([_layer(9546, n, 60, (1, 3)), y], 9565, n_steps=2, replace=False)
+
+
 @pytest.mark.parametrize("n", [64, 1025, 16400])
 def test_one_sample_inference_on_the_lane_major_copy(n):
     layers = [_layer(9570, n, 90, (0, 1, 9, 16, 17, 33)), _layer(9571, n, n, (3, 16, 33)), _layer(9572, 70, n, (5, 40))]

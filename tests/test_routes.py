@@ -328,6 +328,18 @@ def test_copies_of_narrow_training_nets_follow_when_they_are_read():
     """)
 
 
+def test_back_propagation_of_one_sample():
+    """In rounds of eight chunks up to three wavefronts per CU, of four in wider layers and with 4-byte columns."""
+    routes.run("""
+        for n, kernel in [(3000, "<1, false, true>"), (49152, "<1, false, true>"), (49153, "<2, false, true>"), (65536, "<2, false, true>"), (65537, "<1, true, true>")]:
+            ci = np.sort((np.arange(n)[:, None] + 17 * np.arange(8)) % n, axis=1).astype(np.int32).ravel()
+            net = Net([(n, n, np.arange(0, 8 * n + 1, 8, dtype=np.int32), ci, np.ones(8 * n, np.float32), None)] * 2, 1, training=True)
+            assert net("sdnn_forward", X0, 1, XL, None)[0] == 0
+            rc, log = net("sdnn_backward", DL, None)
+            assert rc == 0 and [l for l in log if l.startswith("k_spmv_lm")] == [f"k_spmv_lm{kernel} {-(-n // 64)} 1 1"], (n, log)
+    """)
+
+
 def test_turns_at_priority_between_equal_shares():
     """With 1, 2 and 4 samples per workgroup of the LDS forward: the wavefronts do not take turns where the blocks left over, or one
     deep block, make the shares of a few of them longer than the others', nor on the longest rows."""
