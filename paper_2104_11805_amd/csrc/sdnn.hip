@@ -929,6 +929,8 @@ template <> struct LdsPiece<1> { typedef float type; };
 template <> struct LdsPiece<2> { typedef float type __attribute__((ext_vector_type(2))); };
 template <> struct LdsPiece<4> { typedef float type __attribute__((ext_vector_type(4))); };
 
+#define LM_IN_ORDER 8          // a bit of sdnn_net::turns beside those of 1, 2 and 4 samples, see lm_turns
+
 // What a launch takes through which layers.
 struct LdsForward {
     const LmLayer *tab;
@@ -1160,7 +1162,9 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) k_fwd_lds_part(const LdsForwar
     } else if (2 * a.max_pos <= LDS_MAX_FLOATS && n > n_cu) {
         if (2 * wg < n) lds_forward<2, ACT_RELU_CAP, true, true>(a, wg, n);
     } else {
-        if (wg < n) lds_forward<1, ACT_RELU_CAP, true, true>(a, wg, n);
+        if (wg >= n) return;
+        if (a.turns & LM_IN_ORDER) lds_forward<1, ACT_RELU_CAP, true, true>(a, wg, n);
+        else lds_forward<1, ACT_RELU_CAP, true, false>(a, wg, n);
     }
 }
 
@@ -2962,12 +2966,15 @@ static void lm_deal_blocks(const sdnn_layer &y, const LmLayer &tab, int32_t *row
 // an XCD come apart in the stream of W by deep blocks, which its L2 then fetches again and again (820 entries per row, 8192 neurons,
 // 220 and 500 samples 390 / 473, 477 / 570; a tenth of the columns with a heavy tail, 220 samples, 4097 neurons 92.3 / 87.5, 5000
 // neurons 132 / 142, 6000 neurons 187 / 232, 8192 neurons 397 / 567; 500 samples, 8192 neurons 465 / 446).
-// LM_IN_ORDER: whether with one sample (and the ReLU) the loads of W are requested strictly in their order, as with more samples they
-// always are.  Not on blocks of two chunks and fewer in five rounds and more, nor in three without turns.  us per layer, 64 / 200 samples, in order and
-// then in the compiler's: 300 neurons of 32 entries 1.51 / 1.53, 1300 3.08 / 3.13 (200), 1856 4.03 / 4.13, 2112 4.89 / 4.81, 2304 5.13 / 5.02,
-// 3500 6.64 / 6.78 (200), 4300 8.59 / 8.42, 8192 14.97 / 14.79, 16384 30.0 / 29.6; 2048 neurons of 64 entries 8.48 / 8.67 (220), 8192
-// neurons of 128 entries 62.4 / 65.0, of 256 123 / 147.
-#define LM_IN_ORDER 8
+// Nor with one sample on half of that in a layer of more than 12 MB (8192 neurons of 256 entries, 16 / 64 / 200 samples 125 / 116 / 110 by age,
+// 127 / 117 / 113 in turns).
+// LM_IN_ORDER: whether with one sample the loads of W are requested strictly in their order, as with more samples they always are.
+// Without turns: with one round of blocks, and with short rows or fewer second blocks than SIMDs in two.  With turns: in up to three
+// rounds, and where the layer is larger than an L2, whose misses hold up loads that are requested late (6 MB; it is 4 MB, shared).
+// us per layer, 32 entries per row and 200 samples (else: entries x samples), in order / in the compiler's: by age 300 neurons 1.51 / 1.53 (64), 1300
+// 3.08 / 3.13, 2112 4.89 / 4.81 (64); a tenth of the columns with a heavy tail, 64 samples 1024 neurons 7.85 / 8.24, 1180 9.51 / 9.65 (100),
+// 1249 10.6 / 10.5, 2000 24.6 / 23.8, 6000 244 / 254; in turns 2048 neurons 5.10 / 5.13, x 64 8.16 / 8.18 (64), 3001 6.91 / 6.90, 4096 9.15 /
+// 8.98, x 64 15.9 / 15.2 (64), x 128 28.3 / 27.1, 8192 16.4 / 16.2, x 64 29.0 / 28.6, x 128 55.0 / 57.1, 16384 31.7 / 31.3, x 128 117 / 138.
 static int lm_turns(int32_t nb, const int32_t *cs)
 {
     int64_t longest = 0, all = 0, blocks = 0, deepest = 0;
@@ -2983,9 +2990,12 @@ static int lm_turns(int32_t nb, const int32_t *cs)
         all += share;
     }
     const bool equal = (double)longest * LDS_WAVES <= (1.0 + 0.13 * (nb - 1)) * (double)all, deep = all >= 28 * blocks;
-    const int order = nb <= 2 || (nb <= 4 && equal) || all >= 3 * blocks ? LM_IN_ORDER : 0;
+    const bool deep_1 = deep || (all >= 14 * blocks && all * LDS_CHUNK_BYTES > 12000000), beyond_l2 = all * LDS_CHUNK_BYTES > 6000000;
+    const bool in_turns = nb > 1 && equal && !deep_1;
+    const bool in_order = in_turns ? nb <= 3 || beyond_l2 : nb == 1 || deep_1 || (nb == 2 && (all < 3 * blocks || blocks < LDS_WAVES + 4));
+    const int order = in_order ? LM_IN_ORDER : 0;
     if (nb < 2) return order;
-    return order | (equal && !deep ? 1 : 0) | (equal && !(deep && 2 * all > deepest * blocks) ? 2 : 0) | (equal || nb > 2 ? 4 : 0);
+    return order | (in_turns ? 1 : 0) | (equal && !(deep && 2 * all > deepest * blocks) ? 2 : 0) | (equal || nb > 2 ? 4 : 0);
 }
 
 // Runs fn(0 .. n - 1) on up to 16 host threads (here if there are no more threads); fn must not throw.
@@ -4366,10 +4376,12 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
     if (T) {
         const bool sig = net->cfg.activation == ACT_SIGMOID;
         const int ti = T == 1 ? 0 : T == 2 ? 1 : 2;
-        static const void *const fns[2][3] = {
-            {(const void *)k_fwd_lds<1, ACT_RELU_CAP, true>, (const void *)k_fwd_lds<2, ACT_RELU_CAP, true>, (const void *)k_fwd_lds<4, ACT_RELU_CAP, true>},
-            {(const void *)k_fwd_lds<1, ACT_SIGMOID, true>, (const void *)k_fwd_lds<2, ACT_SIGMOID, true>, (const void *)k_fwd_lds<4, ACT_SIGMOID, true>}};
-        const void *fn = T == 1 && !sig && !(net->turns & LM_IN_ORDER) ? (const void *)k_fwd_lds<1, ACT_RELU_CAP, false> : fns[sig ? 1 : 0][ti];
+        static const void *const fns[2][4] = {
+            {(const void *)k_fwd_lds<1, ACT_RELU_CAP, true>, (const void *)k_fwd_lds<2, ACT_RELU_CAP, true>, (const void *)k_fwd_lds<4, ACT_RELU_CAP, true>,
+             (const void *)k_fwd_lds<1, ACT_RELU_CAP, false>},
+            {(const void *)k_fwd_lds<1, ACT_SIGMOID, true>, (const void *)k_fwd_lds<2, ACT_SIGMOID, true>, (const void *)k_fwd_lds<4, ACT_SIGMOID, true>,
+             (const void *)k_fwd_lds<1, ACT_SIGMOID, false>}};
+        const void *fn = fns[sig ? 1 : 0][T == 1 && !(net->turns & LM_IN_ORDER) ? 3 : ti]; // (a net has one of the two)
         const size_t lds_bytes = sizeof(float) * (size_t)T * ((size_t)net->lm_max_pos + 1);
         if (!net->lds_attr_set[ti]) { // more than the default 64 KiB of dynamic LDS per workgroup
             HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (LDS_MAX_FLOATS + 4)));

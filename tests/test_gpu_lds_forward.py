@@ -49,6 +49,25 @@ def test_lds_forward_samples_per_workgroup(b):
     net.close()
 
 
+@pytest.mark.parametrize("activation", ["relu", "sigmoid"])
+@pytest.mark.parametrize("n", [2100, 4200, 2048])
+def test_lds_forward_with_loads_in_either_order(n, activation):
+    """One sample per workgroup on layers whose loads of W are in the compiler's order (2100: by age, 4200: in turns) and in their own."""
+    layers = [_ragged(9400 + n + l, n, n, (3, 20, 34)) for l in range(3)]
+    for y in layers[1:]:
+        y.bias = -np.abs(y.bias)
+    x = wl.normal_inputs(9410, n, 5)
+    nets = [sdnn.Net(layers, 1.5, 5, training=False, activation=activation, lds_forward=o) for o in (sdnn.SDNN_LDS_ON, sdnn.SDNN_LDS_OFF)]
+    outs = [net.sdnn_forward(P.dev(x), torch.empty(n, 5, device=P.DEV)) for net in nets]
+    assert torch.equal(outs[0], outs[1]) and float(outs[0].std()) > 0
+    if activation == "relu":
+        skip = torch.full_like(outs[0], -1.0)
+        nets[0].sdnn_forward_skip_dead(P.dev(x), skip, check_every=1)
+        assert torch.equal(skip, outs[1])
+    for net in nets:
+        net.close()
+
+
 @pytest.mark.parametrize("shift", [0, 1, -5, 600 * 3 + 2, -(600 * 2 + 1)])
 def test_lds_forward_over_its_input(shift):
     """The result over the input, or shifted against it by some floats, as the per-layer launches take it."""

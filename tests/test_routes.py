@@ -375,12 +375,25 @@ def test_turns_at_priority_between_equal_shares():
 
 
 def test_order_of_the_loads_with_one_sample():
-    """The LDS forward with one sample per workgroup requests its loads strictly in order on long rows and where there are few
-    rounds of blocks."""
+    """The LDS forward with one sample per workgroup requests its loads strictly in order where there are few rounds of blocks or the
+    layers are larger than an L2."""
     routes.run("""
-        for n, links, order in [(300, 32, "true"), (2048, 32, "true"), (2049, 32, "false"), (2049, 33, "true"), (2500, 32, "true"), (4096, 32, "true"), (4097, 32, "false"), (4097, 33, "true"), (16384, 16, "false"), (9000, 256, "true")]:
+        def order(deg, activation=0):
+            n = len(deg)
+            net = Net([layer(n, n, deg)] * 2, 1024, lds_forward=1, activation=activation)
+            rc, log = net("sdnn_forward", X0, 1 if n == 16384 else 2, XL, None)
+            assert rc == 0 and len(log) == 1 and log[0].startswith(f"k_fwd_lds<1, {activation}, "), (n, log)
+            return log[0].split(", ")[2].startswith("true")
+        def uneven(n):
+            tail, lo, hi = ((np.arange(n) + 0.5) / n) ** (-1 / 1.2), 0.0, n
+            while hi - lo > 1e-6:
+                mid = (lo + hi) / 2
+                lo, hi = (mid, hi) if np.clip(np.round(tail * mid), 1, n // 4).mean() < 0.1 * n else (lo, mid)
+            return np.clip(np.round(tail * hi), 1, n // 4).astype(int)
+        for n, links, want in [(300, 32, True), (1024, 200, True), (1025, 33, True), (1216, 33, True), (1217, 33, False), (1300, 32, True), (1856, 64, True),
+                               (2048, 32, True), (2049, 32, False), (2500, 32, True), (3072, 64, True), (3500, 32, False), (4096, 32, False), (4096, 128, False),
+                               (4097, 33, False), (8192, 96, False), (8192, 128, True), (16384, 16, False), (16384, 64, True), (9000, 256, True)]:
             for activation in (0, 1):
-                net = Net([layer(n, n, (links,))] * 2, 1024, lds_forward=1, activation=activation)
-                rc, log = net("sdnn_forward", X0, 1 if n == 16384 else 2, XL, None)
-                assert rc == 0 and log == [f"k_fwd_lds<1, {activation}, {'true' if activation else order}> {1 if n == 16384 else 2} 1 1"], (n, links, log)
+                assert order([links] * n, activation) == want, (n, links, activation)
+        assert [order(uneven(n)) for n in (1000, 1180, 1249, 2000, 6000, 8192)] == [True, True, False, False, True, True]
     """)
