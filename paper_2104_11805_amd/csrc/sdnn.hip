@@ -1255,11 +1255,12 @@ __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ lay
 // the other kernels expect them.  (Stored there at once, four bytes a line, the passes took 3.5 and 4.6 us per layer.)  Every
 // lane adds its row's terms in storage order: same bits as k_spmm.
 //
-// What bounds it: per layer of 1024 neurons of 32 entries 1.5 us of LDS reads, 1.3 us of the stream of W, and the barrier; 2.4 us
-// forward, 3.0 back (columns of 16 to 50 entries in chunks of sixteen), where a launch per layer took 4.8 and 5.7.  The copies come
+// What bounds it: per layer of 1024 neurons of 32 entries 1.6 us of LDS reads (back 1.8), 1.35 us of the stream of W (1.75), 1.0 us of
+// vector instructions (1.2) by their counters, and the chain between two barriers; 2.4 us forward, 3.0 back (columns of 16 to 50
+// entries in chunks of sixteen), where a launch per layer takes 4.5 and 5.8.  The copies come
 // from HBM, and a workgroup that waits for a line holds up everyone on its XCD: workgroups on the compute units that the samples
 // leave idle read the copy through once as fast as they can, so that it comes from the memory-side cache (a step of 120 layers whose
-// arrays are not on chip, 64 samples: 1277 -> 970 us; 1400 with a launch per layer).
+// arrays are not on chip, 64 samples: 950 us, 300 more without them; 1390 with a launch per layer).
 // ---------------------------------------------------------------------------
 #define TRAIN_LDS_POS 2048 // neurons at most: two blocks per wavefront
 struct TrainLds {
@@ -1458,10 +1459,11 @@ __global__ void __launch_bounds__(256) k_train_fill(const LayerDev *__restrict__
 // Activations between the layers: [pair of samples][position][2], a panel is one contiguous piece, brought into LDS
 // without passing through registers.
 //
-// What bounds it: the stream of W from L2 (384 bytes a slot), with two samples to share it; a slot takes 11 clocks of a CU
-// (vector instructions 6.5, LDS reads at random positions 7, W 6 at the L1's 64 bytes per clock, 9 at what an L2 delivers to 32
-// CUs at once).  Per panel 1.6 us to load it and 1.4 us until the last wavefront is done with the one before: 65536 neurons, 55 us
-// per workgroup.  Four samples and panels of 8192 neurons share W better, but 32 entries are then too few for eight panels
+// What bounds it: the stream of W from L2 (384 bytes a slot), with two samples to share it; a slot takes 10.7 clocks of a CU
+// (counted: 6.95 vector instructions, that is 7 clocks of the four SIMDs; LDS reads at random positions 7.8, 4.8 of them conflicts; W 6
+// at the L1's 64 bytes per clock, 9 at what an L2 delivers to 32 CUs at once; over the whole launch, panels included, none of them is
+// busy for more than 58 % of the time).  Per panel 1.6 us to load it and 1.4 us until the last wavefront is done with the one before:
+// 65536 neurons, 55 us per workgroup.  Four samples and panels of 8192 neurons share W better, but 32 entries are then too few for eight panels
 // (1.64 slots per entry instead of 1.10; 65536 neurons, 1024 samples 583 against 476 us per layer; 20001 neurons 110 against 121).
 // Against k_spmm_panel and k_fwd_lds<1> (24 layers of 32 entries per row, us per layer, before / with it): 65536 neurons, 1024
 // samples 849 / 476; 40000 neurons, 1024 samples 618 / 270; 32768 neurons, 512 samples 123 / 96; 65536 neurons, 64 samples
@@ -1994,11 +1996,11 @@ __global__ void __launch_bounds__(64) k_spmv_stage(const SpmmArgs a, int R)
 // in coalesced 16-byte loads and nothing is parked or exchanged; up to 32 gathers of single activations (back: 64) are in flight per
 // lane.  Training nets keep one copy of W and one of W^T and step both (no gradient of the entries is stored and no value
 // moves from one order to the other); the CSR values are written out when they are asked for.
-// What bounds them: a launch and its chain of dependent loads (3.2 us) plus, on wide layers, a 128-byte line from L2 for
-// every gathered activation.  Forward / backward / step, us per layer, before (products staged in LDS, a gradient array, the
-// values moved from the transposed to the CSR order) and after: 1024 neurons 4.6 / 4.8 / 0.2 -> 3.2 / 3.7 / 0.1; 16384 neurons
-// 6.1 / 8.7 / 3.9 -> 3.7 / 5.5 / 1.9; 65536 neurons 14.9 / 22.3 / 15.7 -> 10.5 / 10.7 / 19.5.
-// (Rounds of eight chunks going back have since taken 0.2 us off 1024 and 0.4 off 16384 neurons.)
+// What bounds them: a launch and its chain of dependent loads (3.3 us at 1024 neurons) plus, on wide layers, a 128-byte line from L2
+// for every gathered activation (with it 4.3 and 4.5 us at 16384).  Forward / backward / step, us per layer, before (products staged in
+// LDS, a gradient array, the values moved from the transposed to the CSR order; arrays partly on chip) and now (three nets in turn, their
+// arrays from HBM): 1024 neurons 4.6 / 4.8 / 0.2, 3.3 / 3.4 / 0.1; 16384 neurons 6.1 / 8.7 / 3.9, 4.3 / 4.5 / 2.4; 65536 neurons 14.9 /
+// 22.3 / 15.7, 11.0 / 11.1 / 20.8.
 // ---------------------------------------------------------------------------
 #define B1_MAX_LDS (160 * 1024) // bytes of the step's LDS copy of a vector
 template <bool WIDE> struct B1 { // columns of 2 bytes, or (more than 65536 of them) 4
