@@ -3359,14 +3359,17 @@ static int launch_train_fill(sdnn_net *net, int l, bool cols, hipStream_t stream
 }
 
 // Whether the passes over B samples go through k_train_lds: where both together are done sooner than with a launch per layer.
-// A launch per layer takes 3.2 us forward and 4.0 us back, 28 ns per entry of its longest row and its gathers, at 20 TB/s.  A step of a
+// A launch per layer takes 3.2 us forward and 4.0 us back, 28 ns per entry of its longest row and its gathers, at 20 TB/s; 0.2 us more
+// where the entries of W no longer stay in the L2s (4 MB each) from one pass to the next, since nothing reads ahead.  A step of a
 // single launch takes 1.9 us (barrier, turning the samples around, bringing the copies up to date) and 56 ns per chunk of a wavefront;
 // with a sample on every compute unit nobody reads ahead, and the copies take 39 ns per chunk more to come from HBM.  us per layer of a
 // training step, 48 layers of 32 entries per row, a launch per layer / single: 300 neurons 8.9 / 4.2 (2 samples), 12.8 / 7.2 (256); 1024
 // neurons 9.6 / 7.6 (2), 10.6 / 7.6 (64), 16.6 / 10.4 (200), 16.9 / 11.0 (248), 16.5 / 13.3 (256); 1450 neurons 10.6 / 10.6 (2), 11.4 /
 // 10.6 (64), 19.6 / 14.6 (200), 19.7 / 19.2 (256); 1800 neurons 10.9 / 12.4 (2), 11.1 / 12.4 (16), 12.4 / 12.3 (64); 2048 neurons 11.0 /
 // 13.5 (2), 12.5 / 13.2 (64), 14.4 / 14.3 (96), 15.4 / 14.8 (127); of 8 entries 8.6 / 8.0 (2), 14.6 / 14.4 (256); 1024 neurons of 64
-// entries 13.0 / 12.2 (2); 512 neurons of 160 entries 20.9 / 14.6 (2).
+// entries 13.0 / 12.2 (2); 512 neurons of 160 entries 20.9 / 14.6 (2).  120 layers, one net over and over and (three in turn): 1536 neurons
+// 10.81 / 10.77 (11.50 / 11.34) with 2 samples, 1600 10.83 / 11.19 (11.63 / 11.78) with 2 and 11.08 / 11.02 (11.86 / 11.49) with 16, 1850 11.95 /
+// 12.05 (12.88 / 12.23) with 64, 2048 12.11 / 13.01 (12.93 / 13.14) with 64.
 static bool train_lds_pays(const sdnn_net *net, int B)
 {
     const int width = B <= 64 ? B : (B + 63) & ~63;
@@ -3795,8 +3798,10 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 fits &= (size_t)chunks <= pl.train[o].n_chunks;
                 net->train_single += 1.9e-6 * (double)pl.train[o].tab.size() + 56e-9 * (double)chunks;
                 net->train_cold += 39e-9 * (double)chunks;
+                size_t entries = 0;
+                for (int32_t l = 0; l < n_layers; ++l) entries += (size_t)net->layers[l].nnz;
                 for (int32_t l = o; l < n_layers; ++l) {
-                    net->train_per_layer += (o ? 4.0e-6 : 3.2e-6) + 28e-9 * net->max_len[o][l];
+                    net->train_per_layer += (o ? 4.0e-6 : 3.2e-6) + (8 * entries > ((size_t)32 << 20) ? 0.2e-6 : 0.0) + 28e-9 * net->max_len[o][l];
                     net->train_gathers += 4.0 * net->layers[l].nnz / 20e12;
                     fits &= net->max_len[o][l] <= TRAIN_LDS_MAX_ROW;
                 }

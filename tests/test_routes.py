@@ -244,10 +244,10 @@ def test_training_with_one_launch_per_pass_by_the_batch():
     units; on half of a chip's compute units they are not idle while the copies come."""
     routes.run("""
         from tests import pan_nets
-        def batches(n, links, max_batch, cus=256, **options):
+        def batches(n, links, max_batch, cus=256, depth=12, **options):
             stub.stub_cus(cus)
             ls = pan_nets.layers((n,) * 13, links if isinstance(links, tuple) else (links,), seed=8400)
-            net = Net([(y.n_out, y.n_in, y.row_ptr, y.col_idx, y.values, y.bias) for y in ls], max_batch, training=True, **options)
+            net = Net([(y.n_out, y.n_in, y.row_ptr, y.col_idx, y.values, y.bias) for y in ls * (depth // 12)], max_batch, training=True, **options)
             single = []
             for B in (2, 16, 33, 64, 96, 127, 128, 200, 256):
                 if B > max_batch:
@@ -267,6 +267,9 @@ def test_training_with_one_launch_per_pass_by_the_batch():
             got = batches(n, links, max_batch)
             assert got == want, (n, links, max_batch, got)
         assert batches(2048, 32, 127, fuse_gradient=-1) == [96, 127]
+        for n, want in [(1500, [2, 16, 33, 64]), (1600, [16, 33, 64]), (1850, [64]), (2048, [])]: # W does not stay in the L2s
+            got = batches(n, 32, 64, depth=120)
+            assert got == want, (n, got)
         # a longer row in every block of 64: W follows the order of the rows of the W^T above, and the room for it is not that of sorted rows
         for n, links in [(700, (16,) * 20 + (100,)), (512, (8,) * 63 + (200,)), (300, (4,) * 60 + (500,))]:
             assert batches(n, links, 64) == every[:4], (n, links)
