@@ -1260,7 +1260,7 @@ __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ lay
 // entries in chunks of sixteen), where a launch per layer takes 4.5 and 5.8.  The copies come
 // from HBM, and a workgroup that waits for a line holds up everyone on its XCD: workgroups on the compute units that the samples
 // leave idle read the copy through once as fast as they can, so that it comes from the memory-side cache (a step of 120 layers whose
-// arrays are not on chip, 64 samples: 950 us, 300 more without them; 1390 with a launch per layer).
+// arrays are not on chip, 64 samples: 910 us, 300 more without them; 1406 with a launch per layer).
 // ---------------------------------------------------------------------------
 #define TRAIN_LDS_POS 2048 // neurons at most: two blocks per wavefront
 struct TrainLds {
@@ -2729,7 +2729,8 @@ struct sdnn_net {
     // seconds that both passes take with a launch per layer, their gathers of one sample, those with a single launch, and what is
     // added where the samples leave no compute unit idle (train_lds_pays)
     double train_per_layer = 0, train_gathers = 0, train_single = 0, train_cold = 0;
-    bool train_stale = false;     // the values were stepped and the copies did not follow
+    bool train_stale = false;     // the values were stepped or replaced and the copies did not follow
+    bool train_replaced = false;  // a layer's values were replaced since the last pass that reads the copies
     bool train_kept = false;      // a captured graph reads the copies: they always follow
     bool pan_attr_set = false;
     struct Pan {                     // a layer's copy of W for k_fwd_pan
@@ -3395,6 +3396,7 @@ static int launch_train_lds(sdnn_net *net, int o, int B, int Bp, int ld, hipStre
         if (rc) return rc;
         net->train_stale = captured;
     }
+    net->train_replaced &= captured;
     const sdnn_net::Train &t = net->train[o];
     TrainLds a;
     a.layers = net->d_layers; a.tab = t.d_tab; a.tab_x = net->train[0].d_tab; a.cs = t.cs; a.lm = t.lm; a.bias = t.bias; a.out = t.out;
@@ -4974,7 +4976,11 @@ extern "C" int sdnn_set_weights(sdnn_net *net, int32_t layer, const float *d_val
     if (!rc && d_values && net->b1) rc = launch_b1_fill(net, layer - 1, 0, (hipStream_t)stream_);
     if (!rc && (d_values || d_bias) && net->lm) // keep the lane-major copy current
         rc = launch_lm_fill(net, layer - 1, nullptr, 0, (hipStream_t)stream_);
-    if (!rc && (d_values || d_bias)) rc = launch_train_fill(net, layer - 1, false, (hipStream_t)stream_);
+    if (!rc && (d_values || d_bias) && !net->train[0].tab.empty()) { // the first layer's copies follow at once, all others' in one go with the next pass
+        if (!net->train_replaced || net->train_kept || capturing((hipStream_t)stream_)) rc = launch_train_fill(net, layer - 1, false, (hipStream_t)stream_);
+        else net->train_stale = true;
+        net->train_replaced = true;
+    }
     if (!rc && (d_values || d_bias) && !net->pan.empty()) rc = launch_pan_fill(net, layer - 1, (hipStream_t)stream_);
     return rc;
 }

@@ -71,6 +71,24 @@ def test_single_launch_passes_at_their_limits(widths, max_batch, lengths, full, 
     assert all(float(t.abs().max()) > 0 for t in single[:2 * len(layers) + 1])
 
 
+def test_all_weights_replaced_before_a_step():
+    layers, other = (pan_nets.layers((700,) * 7, (16, 40), seed=s) for s in (8900, 8950))
+    x, y = P.dev(wl.normal_inputs(8960, 700, 9)), P.dev(np.abs(wl.normal_inputs(8961, 700, 9)))
+    outs = []
+    for o in (sdnn.SDNN_LDS_AUTO, sdnn.SDNN_LDS_OFF):
+        net = sdnn.Net(layers, 2.0, 9, training=True, lds_forward=o)
+        xl = torch.empty(700, 9, device=P.DEV)
+        for rounds in range(2):
+            for k, (l, v) in enumerate(zip(layers, other), 1):
+                net.sdnn_set_weights(k, P.dev(np.resize(v.values, l.nnz) * (0.5 + rounds)), P.dev(v.bias))
+            net.sdnn_forward(x, xl)
+            net.sdnn_backward(sdnn.sdnn_mse_dloss(xl, y))
+            outs.append([xl.clone()] + [net.sdnn_get_delta(k, 9) for k in range(1, 7)])
+            net.sdnn_sgd_step(0.05)
+        net.close()
+    assert all(torch.equal(u, v) for u, v in zip(outs[0] + outs[1], outs[2] + outs[3])) and not torch.equal(outs[0][0], outs[1][0])
+
+
 def test_captured_steps_between_steps_of_few_samples():
     """A graph of a step over 64 samples (the copies are read) and steps over 2 (they are not), in turn, against a net that runs all
     of them eagerly with a launch per layer."""

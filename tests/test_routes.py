@@ -328,6 +328,19 @@ def test_copies_of_narrow_training_nets_follow_when_they_are_read():
         assert [fills(c, 2), fills(c, 64, (0, 1)), fills(c, 2), fills(c, 64), fills(c, 2), fills(c, 64)] == [[0, 0, 0], [2, 2, 2], [0, 0, 2], [2, 0, 2], [0, 0, 2], [0, 0, 2]]
         d = net()
         assert [fills(d, 64, (0, 1, 2)), fills(d, 1), fills(d, 64)] == [[0, 0, 2], [0, 0, 2], [0, 0, 2]]
+        def replaced(net, layers, capture=0):
+            stub.stub_capture(capture)
+            out = []
+            for k in layers:
+                rc, log = net("sdnn_set_weights", k, X0, XL, None)
+                assert rc == 0
+                out.append(sum(l.startswith("k_train_fill") for l in log))
+            stub.stub_capture(0)
+            return out
+        e = net()                                      # all layers replaced: the first one's copy (W_1^T has none) at once, the others' with the next pass
+        assert replaced(e, range(1, 5)) == [1, 0, 0, 0] and fills(e, 64) == [2, 0, 2] and replaced(e, (3,)) == [2] and fills(e, 64) == [0, 0, 2]
+        assert replaced(e, (2, 3)) == [2, 0] and replaced(e, (3, 4), 1) == [2, 2] and fills(e, 64, (0, 1)) == [2, 2, 2]
+        assert replaced(e, (2, 3)) == [2, 2] and fills(e, 64) == [2, 0, 2] and replaced(e, (2, 3)) == [2, 2] and fills(e, 64) == [0, 0, 2]
     """)
 
 
