@@ -1,7 +1,7 @@
 // libsdnn: HIP kernels (gfx950) and the C-ABI entry points that launch them.
 //
-// Mapping to the hardware (64-wide wavefronts, no matrix cores: none of the
-// three passes is a dense contraction):
+// Mapping to the hardware (64-wide wavefronts; none of the three passes is a
+// dense contraction: matrix cores only add up lanes, in k_bwd_long):
 //   * forward / backward product: one wavefront per matrix row, the 64 lanes
 //     walk the row together and each lane owns V consecutive samples, so the
 //     row's column indices and weights are wave-uniform (scalar loads) and each
@@ -15,8 +15,8 @@
 //     positions of the values in the CSR array.
 //   * short rows: several rows per wavefront, four samples per lane (k_rows).
 //   * nets with enough entries per layer: the backward sweep also forms the
-//     gradient of the stored entries (k_bwd_rows; few short rows: k_bwd_grad,
-//     gathered rows parked in LDS) and reads the values from a copy in the order
+//     gradient of the stored entries (k_bwd_rows; long rows and many samples:
+//     k_bwd_long; few short rows: k_bwd_grad, gathered rows parked in LDS) and reads the values from a copy in the order
 //     of the transposed index; the descent step is then a streaming pass over
 //     that copy (k_apply) and a second one that rebuilds the CSR copy
 //     (k_spread_vals).
@@ -578,6 +578,13 @@ template <int BIT> __device__ __forceinline__ double lane_exchange(double v)
     const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
 }
+// The value of the lane N places on in its group of sixteen.
+template <int N> __device__ __forceinline__ double row_rotate(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x120 + N, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x120 + N, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
 // One halving step of a sum over lanes of N values: the lane keeps the half of the values whose number has the bit that
 // its own number has in place BIT, and adds its partner's share of them.
 template <int N, int BIT> __device__ __forceinline__ void halve(double (&p)[4], int lane)
@@ -696,6 +703,131 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_rows(const GradArgs a)
             quad_gather<0>(q, rin, ldb, so, x0, w0);
         }
         consume(x1, w1);
+    }
+    if (!a.store_out || !live) return;
+    float o[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[v] = act_backprop(a.act, acc[v], xp[v], a.cap);
+    if (s + 4 > a.B) { // the batch's last group
+#pragma unroll
+        for (int v = 1; v < 4; ++v)
+            if (s + v >= a.B) o[v] = 0.0f;
+    }
+    stv<4>(a.out + (size_t)row * a.ld_out + s, o);
+}
+
+// The same sweep for long rows and more than 128 samples: a wavefront per row.  k_bwd_rows<64> keeps the vector units issuing in
+// 91 % of its clocks there (23 instructions per entry, 6.5 of them the sum over the lanes, 3 to hand the entries round).  Here a
+// row's entries come through the scalar cache, a group of sixteen ahead, and the sums over the lanes are products with ones on the
+// matrix cores (4x4x4, fp64), which run beside the vector units: 15 vector and 1.25 matrix instructions per entry.
+//   The product of lanes (16 k + 4 b + i) with B[k][j] = [j == u] leaves the sums over k of entry u in the lanes (16 i + 4 b + u) and
+//   adds nothing to the others; the sums of four entries, as the right operand of A[i][k] = [i == q], go to the lanes (16 q + 4 b + u).
+//   Sixteen entries end up in sixteen lanes, and two rotations add the four b.
+// 0 times infinity is NaN, so where one of the sixteen sums is not finite they are formed one by one instead.
+// Per layer of 8192 neurons of 820 entries, 256 samples, between other kernels 344 -> 291 us: 6.9 GB of gathered rows at 24 TB/s, where
+// a stream of such gathers alone reaches 26 to 31.  (Eight to sixteen gathers in flight, four or five wavefronts per SIMD: the same.)
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+__global__ void __launch_bounds__(BLOCK_THREADS) k_bwd_long(const GradArgs a)
+{
+    typedef const int __attribute__((address_space(4))) *int_ptr;
+    typedef const float __attribute__((address_space(4))) *float_ptr;
+    const int lane = threadIdx.x & 63;
+    const int r = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6)));
+    if (r >= a.n_rows) return;
+    const int_ptr task = (int_ptr)(const int *)(a.sched + r);
+    const int row = task[0], beg = task[1], end = task[2];
+    const int_ptr idx = (int_ptr)a.idx;
+    const float_ptr vals = (float_ptr)a.vals;
+    const unsigned ldb = 4u * (unsigned)a.ld_in;
+    const int s_own = 4 * lane;
+    const bool live = s_own < a.B;
+    const int s = live ? s_own : 0;
+    const unsigned so = 4u * (unsigned)s;
+    const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
+    float *__restrict__ g_part = a.g_part[0];
+    float xp[4] = {0.0f, 0.0f, 0.0f, 0.0f}; // lanes outside the batch add nothing to the gradient
+    if (live) ldv<4>(a.aux + (size_t)row * a.ld_out + s, xp);
+    double xd[4], acc[4] = {0.0, 0.0, 0.0, 0.0}, one_at[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        xd[v] = (double)xp[v];
+        one_at[v] = (lane & 3) == v ? 1.0 : 0.0;
+    }
+    // sixteen entries: past the end of the row, zero weights at a column outside the operand
+    auto fetch = [&](int g, i32x16 &c, f32x16 &w) {
+        if (g + 16 <= end) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) { c[k] = idx[g + k]; w[k] = vals[g + k]; }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int e = min(g + k, end - 1);
+                const int ck = idx[e];
+                const float wk = vals[e];
+                c[k] = g + k < end ? ck : a.n_cols;
+                w[k] = g + k < end ? wk : 0.0f;
+            }
+        }
+    };
+    float4 x0[4], x1[4];
+    auto gather = [&](const i32x16 &c, int k, float4 (&x)[4]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = as_f4(__builtin_amdgcn_raw_buffer_load_b128(rin, (int)so, (int)((unsigned)c[k + u] * ldb), 0));
+    };
+    auto consume = [&](const float4 (&x)[4], const f32x16 &w, int k, double &sums) {
+        double pr[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double wk = (double)w[k + u];
+            const double d0 = (double)x[u].x, d1 = (double)x[u].y, d2 = (double)x[u].z, d3 = (double)x[u].w;
+            acc[0] = fma(wk, d0, acc[0]);
+            acc[1] = fma(wk, d1, acc[1]);
+            acc[2] = fma(wk, d2, acc[2]);
+            acc[3] = fma(wk, d3, acc[3]);
+            pr[u] = fma(d3, xd[3], fma(d2, xd[2], fma(d1, xd[1], d0 * xd[0])));
+        }
+        asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])); // see k_bwd_rows
+        sums = 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sums = __builtin_amdgcn_mfma_f64_4x4x4f64(pr[u], one_at[u], sums, 0, 0, 0);
+    };
+    i32x16 c, cn;
+    f32x16 w, wn;
+    if (beg < end) {
+        fetch(beg, c, w);
+        gather(c, 0, x0);
+    }
+    for (int g = beg; g < end; g += 16) {
+        const bool more = g + 16 < end;
+        if (more) fetch(g + 16, cn, wn);
+        double part[4];
+        gather(c, 4, x1);
+        consume(x0, w, 0, part[0]);
+        gather(c, 8, x0);
+        consume(x1, w, 4, part[1]);
+        gather(c, 12, x1);
+        consume(x0, w, 8, part[2]);
+        if (more) gather(cn, 0, x0);
+        consume(x1, w, 12, part[3]);
+        double sum = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sum = __builtin_amdgcn_mfma_f64_4x4x4f64(one_at[q], part[q], sum, 0, 0, 0);
+        sum += row_rotate<8>(sum);
+        sum += row_rotate<4>(sum);
+        const int e = g + 4 * (lane >> 4) + (lane & 3);
+        if (__ballot(!(fabs(sum) < HUGE_VAL)) == 0) {
+            if ((lane & 12) == 0 && e < end) g_part[e] = (float)sum;
+        } else { // an infinity or NaN is in all the sums: one by one
+            for (int k = g; k < min(g + 16, end); ++k) {
+                const float4 x = as_f4(__builtin_amdgcn_raw_buffer_load_b128(rin, (int)so, (int)((unsigned)idx[k] * ldb), 0));
+                double pr[4] = {fma((double)x.w, xd[3], fma((double)x.z, xd[2], fma((double)x.y, xd[1], (double)x.x * xd[0]))), 0.0, 0.0, 0.0};
+                reduce4<64>(pr, lane);
+                if (lane == 0) g_part[k] = (float)pr[0];
+            }
+        }
+        c = cn;
+        w = wn;
     }
     if (!a.store_out || !live) return;
     float o[4];
@@ -4694,6 +4826,9 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;
     }
+    // More than 128 samples: a wavefront per row either way.  From 128 entries per row on (what counts as long elsewhere too) by scalar
+    // loads and matrix products; shorter rows would wait for the two dependent scalar loads at their start (step of 6 layers, 256
+    // samples, k_bwd_rows / k_bwd_long: 1300 neurons of 130 entries 291 / 280 us, 3001 of 300 730 / 678, 8192 of 820 4030 / 3680).
     // two windows: as two tiles (and two partial gradients) where the operand is larger than L2, else in one
     const bool two = net->two_windows;
     int G = lanes_per_row(net->grad_parts == 2 ? 64 : B);
@@ -4702,7 +4837,8 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
     a.n_tiles = (uint32_t)net->grad_parts;
     a.n_rg = (uint32_t)((a.n_rows + rows_per_block - 1) / rows_per_block);
     const void *fn = G == 4 ? (const void *)k_bwd_rows<4, false> : G == 8 ? (const void *)k_bwd_rows<8, false>
-                     : G == 16 ? (const void *)k_bwd_rows<16, false> : G == 64 ? (const void *)k_bwd_rows<64, false>
+                     : G == 16 ? (const void *)k_bwd_rows<16, false>
+                     : G == 64 ? ((int64_t)d.nnz >= 128 * (int64_t)a.n_rows ? (const void *)k_bwd_long : (const void *)k_bwd_rows<64, false>)
                      : two ? (const void *)k_bwd_rows<32, true> : (const void *)k_bwd_rows<32, false>;
     HIP_TRY(net, hipLaunchKernel(fn, dim3(a.n_tiles * a.n_rg), dim3(BLOCK_THREADS), args, 0, stream));
     HIP_TRY(net, hipGetLastError());

@@ -108,6 +108,31 @@ def test_backward(b):
     assert not np.isfinite(deltas[1][touched]).any()
 
 
+@pytest.mark.parametrize("b", [130, 256])
+def test_gradient_on_long_columns(b):
+    """An infinite delta is in the gradient of its own row's entries and in no other: the others' sums differ from those of the
+    run without it by the order of fp64 additions at most, i.e. by no more than their last bit."""
+    lay = _layer(9514, 900, 120)
+    rng = np.random.default_rng(9515)
+    cols = np.stack([np.sort(rng.choice(120, 30, replace=False)) for _ in range(900)]).astype(np.int32)
+    lay = wl.Layer(900, 120, np.arange(0, 900 * 30 + 1, 30, dtype=np.int32), cols.ravel(), rng.standard_normal(27000).astype(np.float32), lay.bias)
+    x = wl.normal_inputs(9516, 120, b)
+    grads = []
+    for bad in (0.0, np.inf, np.nan):
+        d = wl.normal_inputs(9517, 900, b)
+        d[[0, 9, 500], 3] += bad
+        net = sdnn.Net([lay], 1e30, b, training=True, fuse_gradient=1, activation="sigmoid")
+        net.sdnn_forward(P.dev(x), torch.empty(900, b, device=P.DEV))
+        net.sdnn_backward(P.dev(d))
+        grads.append(P.host(net.sdnn_weight_grad(1)[0]).reshape(900, 30))
+        net.close()
+    touched = np.zeros(900, bool)
+    touched[[0, 9, 500]] = True
+    for g in grads[1:]:
+        assert not np.isfinite(g[touched]).any()
+        assert (np.abs(g[~touched] - grads[0][~touched]) <= 2.0 ** -23 * np.abs(grads[0][~touched])).all()
+
+
 def _hot_and_cold(n, degree, n_layers):
     """The first half of the neurons is exactly zero for inputs of 1 and grows without bound for inputs of 0; the other half
     stays alive.  A row's links lie in its own half."""

@@ -38,6 +38,24 @@ def test_batch_sizes_around_the_lanes_per_row(b):
     _step(layers, b, 9310, fuse=1)
 
 
+def _turned(lay):
+    """The layer whose W is the other one's W^T."""
+    rows = np.repeat(np.arange(lay.n_out), np.diff(lay.row_ptr))
+    order = np.lexsort((rows, lay.col_idx))
+    row_ptr = np.zeros(lay.n_in + 1, np.int32)
+    np.cumsum(np.bincount(lay.col_idx, minlength=lay.n_in), out=row_ptr[1:])
+    return wl.Layer(lay.n_in, lay.n_out, row_ptr, rows[order].astype(np.int32), lay.values[order], np.linspace(-0.5, 0.5, lay.n_in, dtype=np.float32))
+
+
+@pytest.mark.parametrize("b,activation", [(129, "relu"), (130, "sigmoid"), (192, "relu"), (255, "relu"), (256, "relu"), (256, "sigmoid")])
+def test_long_columns_and_more_than_128_samples(b, activation):
+    """The sweep with a wavefront per row: columns of W around its groups of sixteen entries, empty ones and very long ones;
+    layers whose columns have just under and just over 128 entries on average."""
+    layers = [_turned(_layer(9430, 301, 1700, (0, 1, 15, 16, 17, 31, 33, 250, 1700))), _turned(_layer(9431, 1700, 203, (126, 127, 129, 129))),
+              _turned(_layer(9432, 203, 150, (127, 126)))]
+    _step(layers, b, 9440, 1, activation)
+
+
 @pytest.mark.parametrize("b,fuse,activation", [(5, -1, "relu"), (99, -1, "relu"), (30, 1, "sigmoid"), (99, 1, "sigmoid")])
 def test_separate_update_and_sigmoid(b, fuse, activation):
     layers = [_layer(9320, 2113, 250, (2, 9, 16, 40)), _layer(9321, 75, 2113, (70, 16, 5, 90))]
