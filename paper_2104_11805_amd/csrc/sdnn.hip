@@ -2536,6 +2536,8 @@ k_update(const LayerDev *__restrict__ layers, int layer0, int n_layers, int inte
 // over the entries of every layer (grid = (chunks of entries, layers)); k_apply_bias forms the bias
 // gradient sum_s Delta(row, s).
 // ---------------------------------------------------------------------------
+// GRAD: no step, the gradient itself goes that way, through G[1] instead of mid (n_parts == 1: nothing else uses it).
+template <bool GRAD>
 __global__ void __launch_bounds__(TR_THREADS) k_apply(const LayerDev *__restrict__ layers, int n_parts, float lr)
 {
     // The gradient and one copy of the values are in the order of the transposed index: this pass is a stream over
@@ -2557,24 +2559,30 @@ __global__ void __launch_bounds__(TR_THREADS) k_apply(const LayerDev *__restrict
     const uint16_t *__restrict__ slot = L.mid_slot + q0;
     const int32_t *__restrict__ dst = L.mid_dst + q0;
     float *__restrict__ vals_t = L.vals_t + q0;
-    float *__restrict__ mid = L.mid;
+    float *__restrict__ mid = GRAD ? L.G[1] : L.mid;
     const int tid = (int)threadIdx.x;
 #define APPLY_ONE(G0, G1, W) (float)((double)(W) - dlr * (double)(float)(n_parts == 2 ? (double)(G0) + (double)(G1) : (double)(G0)))
     for (int k = tid; k < cnt4; k += TR_THREADS) { // q0 is a multiple of 4 and the arrays are 16-byte aligned
         const float4 a = reinterpret_cast<const float4 *>(g0)[k];
-        float4 b = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (n_parts == 2) b = reinterpret_cast<const float4 *>(g1)[k];
-        float4 w = reinterpret_cast<const float4 *>(vals_t)[k];
         const ushort4 o = reinterpret_cast<const ushort4 *>(slot)[k];
-        w.x = APPLY_ONE(a.x, b.x, w.x); w.y = APPLY_ONE(a.y, b.y, w.y);
-        w.z = APPLY_ONE(a.z, b.z, w.z); w.w = APPLY_ONE(a.w, b.w, w.w);
-        reinterpret_cast<float4 *>(vals_t)[k] = w;
+        float4 w = a;
+        if constexpr (!GRAD) {
+            float4 b = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (n_parts == 2) b = reinterpret_cast<const float4 *>(g1)[k];
+            w = reinterpret_cast<const float4 *>(vals_t)[k];
+            w.x = APPLY_ONE(a.x, b.x, w.x); w.y = APPLY_ONE(a.y, b.y, w.y);
+            w.z = APPLY_ONE(a.z, b.z, w.z); w.w = APPLY_ONE(a.w, b.w, w.w);
+            reinterpret_cast<float4 *>(vals_t)[k] = w;
+        }
         stage[o.x] = w.x; stage[o.y] = w.y; stage[o.z] = w.z; stage[o.w] = w.w;
     }
     if (tid < (cnt & 3)) {
         const int k = 4 * cnt4 + tid;
-        const float w = APPLY_ONE(g0[k], n_parts == 2 ? g1[k] : 0.0f, vals_t[k]);
-        vals_t[k] = w;
+        float w = g0[k];
+        if constexpr (!GRAD) {
+            w = APPLY_ONE(w, n_parts == 2 ? g1[k] : 0.0f, vals_t[k]);
+            vals_t[k] = w;
+        }
         stage[slot[k]] = w;
     }
 #undef APPLY_ONE
@@ -2583,17 +2591,18 @@ __global__ void __launch_bounds__(TR_THREADS) k_apply(const LayerDev *__restrict
 }
 
 // Chunk c of the CSR values from entries [c TR_CHUNK, (c+1) TR_CHUNK) of mid: placed in LDS by mid_loc, then
-// written out in order.  grid = (chunks, layers).
-__global__ void __launch_bounds__(TR_THREADS) k_spread_vals(const LayerDev *__restrict__ layers)
+// written out in order.  grid = (chunks, layers).  GRAD: chunk c of the gradient `g` of one layer, from G[1].
+template <bool GRAD>
+__global__ void __launch_bounds__(TR_THREADS) k_spread_vals(const LayerDev *__restrict__ layers, float *__restrict__ g)
 {
     __shared__ __attribute__((aligned(16))) float chunk[TR_CHUNK];
     const LayerDev &L = layers[blockIdx.y];
     const int64_t c0 = (int64_t)blockIdx.x * TR_CHUNK;
     if (c0 >= L.nnz) return;
     const int cnt = (int)min((int64_t)TR_CHUNK, (int64_t)L.nnz - c0), cnt4 = cnt >> 2;
-    const float *__restrict__ mid = L.mid + c0;
+    const float *__restrict__ mid = (GRAD ? L.G[1] : L.mid) + c0;
     const uint16_t *__restrict__ loc = L.mid_loc + c0;
-    float *__restrict__ vals = L.vals + c0;
+    float *__restrict__ vals = (GRAD ? g : L.vals) + c0;
     for (int k = (int)threadIdx.x; k < cnt4; k += TR_THREADS) { // c0 is a multiple of 4 and the arrays are 16-byte aligned
         const float4 v = reinterpret_cast<const float4 *>(mid)[k];
         const ushort4 o = reinterpret_cast<const ushort4 *>(loc)[k];
@@ -2601,6 +2610,10 @@ __global__ void __launch_bounds__(TR_THREADS) k_spread_vals(const LayerDev *__re
     }
     if ((int)threadIdx.x < (cnt & 3)) chunk[loc[4 * cnt4 + (int)threadIdx.x]] = mid[4 * cnt4 + (int)threadIdx.x];
     __syncthreads();
+    if (GRAD && ((size_t)g & 15) != 0) { // the caller's array
+        for (int k = (int)threadIdx.x; k < cnt; k += TR_THREADS) vals[k] = chunk[k];
+        return;
+    }
     for (int k = (int)threadIdx.x; k < cnt4; k += TR_THREADS)
         reinterpret_cast<float4 *>(vals)[k] = reinterpret_cast<const float4 *>(chunk)[k];
     if ((int)threadIdx.x < (cnt & 3)) vals[4 * cnt4 + (int)threadIdx.x] = chunk[4 * cnt4 + (int)threadIdx.x];
@@ -4971,10 +4984,10 @@ extern "C" int sdnn_sgd_step(sdnn_net *net, float lr, void *stream_)
             const int nl = std::min(65535, net->n_layers - l0);
             if (max_nnz > 0) { // a span per workgroup, a multiple of 8 workgroups per layer
                 const unsigned gx = (unsigned)((((int64_t)max_nnz + TR_SPAN - 1) / TR_SPAN + 7) & ~(int64_t)7);
-                hipLaunchKernelGGL(k_apply, dim3(gx, (unsigned)nl), dim3(TR_THREADS), 0, (hipStream_t)stream_,
+                hipLaunchKernelGGL(k_apply<false>, dim3(gx, (unsigned)nl), dim3(TR_THREADS), 0, (hipStream_t)stream_,
                                    net->d_layers + l0, net->grad_parts, lr);
-                hipLaunchKernelGGL(k_spread_vals, dim3((unsigned)((max_nnz + TR_CHUNK - 1) / TR_CHUNK), (unsigned)nl),
-                                   dim3(TR_THREADS), 0, (hipStream_t)stream_, net->d_layers + l0);
+                hipLaunchKernelGGL(k_spread_vals<false>, dim3((unsigned)((max_nnz + TR_CHUNK - 1) / TR_CHUNK), (unsigned)nl),
+                                   dim3(TR_THREADS), 0, (hipStream_t)stream_, net->d_layers + l0, (float *)nullptr);
             }
             if (max_rows > 0 && net->cfg.update_bias)
                 hipLaunchKernelGGL(k_apply_bias, dim3((unsigned)((max_rows + 16 * WAVES_PER_BLOCK - 1) / (16 * WAVES_PER_BLOCK)), (unsigned)nl),
@@ -5016,6 +5029,10 @@ extern "C" int sdnn_sgd_step(sdnn_net *net, float lr, void *stream_)
     return SDNN_OK;
 }
 
+// From so many entries on the gradient is brought into CSR order in the two passes that the stepped values go through, else by
+// a scatter of single values (with the bias, scatter / two passes: 0.77e6 entries 14.6 / 15.8 us, 1.02e6 16.8 / 17.3, 1.28e6 20.4 / 18.2,
+// 2.1e6 30.1 / 20.5, 6.7e6 83.6 / 36.1).
+#define GRAD_SPREAD_MIN (1 << 20)
 extern "C" int sdnn_weight_grad(sdnn_net *net, int32_t layer, float *d_g, float *d_gb, void *stream_)
 {
     if (!net) return fail(nullptr, SDNN_EINVAL, "net is NULL");
@@ -5028,7 +5045,12 @@ extern "C" int sdnn_weight_grad(sdnn_net *net, int32_t layer, float *d_g, float 
         // the backward sweep has already formed the gradient that sdnn_sgd_step will apply: hand out that one
         const LayerDev &d = net->layers[layer - 1];
         hipStream_t stream = (hipStream_t)stream_;
-        if (d_g && d.nnz > 0)
+        if (d_g && d.nnz >= GRAD_SPREAD_MIN && net->grad_parts == 1) {
+            const unsigned gx = (unsigned)((((int64_t)d.nnz + TR_SPAN - 1) / TR_SPAN + 7) & ~(int64_t)7);
+            hipLaunchKernelGGL(k_apply<true>, dim3(gx), dim3(TR_THREADS), 0, stream, net->d_layers + (layer - 1), 1, 0.0f);
+            hipLaunchKernelGGL(k_spread_vals<true>, dim3((unsigned)(((int64_t)d.nnz + TR_CHUNK - 1) / TR_CHUNK)), dim3(TR_THREADS), 0, stream,
+                               net->d_layers + (layer - 1), d_g);
+        } else if (d_g && d.nnz > 0)
             hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)std::min(4096, (d.nnz + 2047) / 2048)), dim3(256), 0, stream,
                                (const float *)d.G[0], net->grad_parts == 2 ? (const float *)d.G[1] : (const float *)nullptr,
                                d.t_perm, d_g, d.nnz);

@@ -91,6 +91,37 @@ def test_gradient_is_rounded_once(b):
     net.close()
 
 
+@pytest.mark.parametrize("n_out,offset", [(2097, 0), (2097, 1), (2098, 3), (2100, 2)])
+def test_gradient_of_a_million_entries_in_csr_order(n_out, offset):
+    """Entries just under 2^20 (a scatter), and just over (two passes; the last chunk and span part-filled), into an array that
+    starts at any float; what lies before and after it stays."""
+    import ctypes as C
+    import torch
+    from paper_2104_11805_amd import sdnn
+    lay = _layer(9395, n_out, 600, (500,))
+    nnz, b = lay.col_idx.size, 5
+    assert (nnz >= 1 << 20) == (n_out > 2097)
+    x, d = wl.normal_inputs(9396, 600, b), wl.normal_inputs(9397, n_out, b)
+    lay.values[:], lay.bias[:] = 0.0, 1.0          # every neuron is active: Delta is the loss gradient
+    net = sdnn.Net([lay], float("inf"), b, training=True, fuse_gradient=1)
+    net.sdnn_forward(P.dev(x), torch.empty(n_out, b, device=P.DEV))
+    net.sdnn_backward(P.dev(d))
+    out = torch.full((nnz + 16,), 7.0, device=P.DEV)
+    for _ in range(2):
+        rc = sdnn.lib().sdnn_weight_grad(net._handle, 1, C.c_void_p(out.data_ptr() + 4 * offset), None, None)
+        assert rc == 0
+    torch.cuda.synchronize()
+    got = P.host(out)
+    assert (got[:offset] == 7.0).all() and (got[offset + nnz:] == 7.0).all()
+    rows = np.repeat(np.arange(n_out), 500)
+    terms = d[rows].astype(np.float64) * x[lay.col_idx].astype(np.float64)
+    assert (np.abs(got[offset:offset + nnz] - terms.sum(axis=1)) <= 2.0 ** -24 * np.abs(terms.sum(axis=1)) + 2 * b * 2.0 ** -53 * np.abs(terms).sum(axis=1)).all()
+    new = lay.values.astype(np.float64) - 0.5 * got[offset:offset + nnz]
+    net.sdnn_sgd_step(0.5)
+    assert np.array_equal(P.host(net.sdnn_get_weights(1)[0]), new.astype(np.float32))
+    net.close()
+
+
 def test_a_smaller_batch_after_a_larger_one():
     """The arrays' row pitch follows the batch: nothing of the earlier, wider batch may show."""
     import torch
