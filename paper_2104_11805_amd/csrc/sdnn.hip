@@ -24,6 +24,8 @@
 //     (k_fwd_lds).
 //   * training on narrow layers: one launch per pass, activations in LDS
 //     (k_train_lds).
+//   * training on layers of long rows: the forward pass with four samples of a
+//     layer's whole operand in LDS (k_fwd_long).
 //   * inference on wider layers: a launch per layer, a panel of the activations in LDS
 //     at a time (k_fwd_pan).
 //   * inference on large activation blocks goes through all layers in
@@ -1579,6 +1581,147 @@ __global__ void __launch_bounds__(256) k_train_fill(const LayerDev *__restrict__
 }
 
 // ---------------------------------------------------------------------------
+// K1l: Eq. 3 for one layer of long rows in training: a workgroup of 16 wavefronts holds four samples of the whole operand in LDS and
+// takes every n_ranges-th block of 64 rows, a lane per row, over a lane-major copy of W that follows the stepped values
+// (k_long_fill).  The blocks, longest first, are handed to whichever wavefront is free.  Every lane adds its row's terms in storage
+// order: same bits as k_spmm.
+//
+// What bounds it: per wavefront-wide entry LDS returns 1024 bytes at 128 a clock and the L1 384 bytes of W at 64 a clock, by the same way
+// into the registers: 14 clocks of a CU, of which vector instructions take 10.  A gather through the L1 returns the same 1024 bytes in
+// 16 clocks, and 24 where half of them miss L2 (an operand of 8 MB).  8192 neurons of 820 entries, 256 samples, us per layer: k_spmm
+// 280, this 182, and k_long_fill 18.
+// ---------------------------------------------------------------------------
+#define LONG_MIN_BATCH 65 // see long_forward
+#define LONG_POS 8192 // neurons of the operand at most: four samples in 128 KiB
+struct FwdLong {
+    const int32_t *cs;  // [blocks + 1]: first half of a block
+    const int2 *row;    // [64 blocks]: {row, entries}, row -1 past the last
+    const uint4 *lm;    // halves of LDS_HALF_BYTES
+    const float *bias;
+    const float *in;    // [n_in][ld]
+    float *out;         // [n_out][ld]
+    uint32_t lm_bytes;
+    int32_t blocks, n_in, ld, B;
+    int32_t groups, n_ranges; // groups of four samples
+    float cap;
+};
+template <int ACT>
+__global__ void __launch_bounds__(64 * LDS_WAVES) k_fwd_long(const FwdLong a)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds_act[];
+    typedef float piece __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) piece *lds_ptr;
+    typedef __attribute__((address_space(3))) char *lds_bytes;
+    const lds_ptr act = (lds_ptr)(__attribute__((address_space(3))) float *)lds_act; // the kernel's only LDS: at address 0
+    int *next = (int *)(lds_act + 4 * (a.n_in + 1)); // the next block of this workgroup's that nobody has taken
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // An XCD takes a stretch of the samples, whose rows of X share cache lines, and all ranges of W side by side.
+    const int per = (a.groups + 7) >> 3, k = (int)(blockIdx.x >> 3), q = k / per, g = (int)(blockIdx.x & 7u) * per + k % per;
+    if (g >= a.groups) return;
+    for (int i = tid; i < a.n_in; i += 64 * LDS_WAVES) act[i] = *(const piece *)(a.in + (size_t)i * a.ld + 4 * g);
+    if (tid == 0) {
+        act[a.n_in] = piece{0.0f, 0.0f, 0.0f, 0.0f}; // where the slots past the end of a row point
+        *next = LDS_WAVES;
+    }
+    unsigned shift = 4;
+    asm("" : "+v"(shift)); // kept in a register for lds_address
+    const __amdgpu_buffer_rsrc_t rlm = make_rsrc((const float *)a.lm, a.lm_bytes);
+    const int lane16 = 16 * lane;
+    unsigned at = 0;
+    struct Half { u32x4 c, wa, wb; } ha, hb;
+    auto request = [&](Half &h) {
+        h.c = __builtin_amdgcn_raw_buffer_load_b128(rlm, lane16, (int)at, 0);
+        h.wa = __builtin_amdgcn_raw_buffer_load_b128(rlm, lane16 + 1024, (int)at, 0);
+        h.wb = __builtin_amdgcn_raw_buffer_load_b128(rlm, lane16 + 2048, (int)at, 0);
+        at += LDS_HALF_BYTES;
+    };
+    __syncthreads();
+    for (int b = q + a.n_ranges * wave; b < a.blocks;) {
+        const int c0 = a.cs[b];
+        int n = a.cs[b + 1] - c0;
+        const int row = a.row[64 * b + lane].x;
+        at = (unsigned)c0 * LDS_HALF_BYTES;
+        request(ha);
+        request(hb);
+        const double bias = a.bias && row >= 0 ? (double)a.bias[row] : 0.0;
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        auto take = [&](Half &h) { // eight entries; then their registers are free for the half after next
+            unsigned ad[8];
+            double w[8];
+            piece x[8];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                ad[2 * u] = lds_address<0>(h.c[u], shift);
+                ad[2 * u + 1] = lds_address<1>(h.c[u], shift);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = *(lds_ptr)((lds_bytes)0 + ad[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                w[u] = (double)__uint_as_float(h.wa[u]);
+                w[u + 4] = (double)__uint_as_float(h.wb[u]);
+            }
+            request(h);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[t] = fma(w[u], (double)x[u][t], acc[t]);
+        };
+        while (n > 0) {
+            take(ha);
+            __builtin_amdgcn_sched_barrier(0);
+            if (--n == 0) break;
+            take(hb);
+            __builtin_amdgcn_sched_barrier(0);
+            --n;
+        }
+        piece o;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) o[t] = 4 * g + t < a.B ? act_apply(ACT, acc[t] + bias, a.cap) : 0.0f;
+        if (row >= 0) *(piece *)(a.out + (size_t)row * a.ld + 4 * g) = o;
+        int take_next = 0;
+        if (lane == 0) take_next = __hip_atomic_fetch_add(next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        b = q + a.n_ranges * __builtin_amdgcn_readfirstlane(take_next);
+    }
+}
+
+// Writes the weights of those copies from the CSR values (COLS: and the columns).  grid = (blocks, parts, layers): a workgroup's
+// wavefronts take neighbouring halves, so that a line of the values is read once.
+template <bool COLS>
+__global__ void __launch_bounds__(256) k_long_fill(const LayerDev *__restrict__ layers)
+{
+    const LayerDev &L = layers[blockIdx.z];
+    const int b = blockIdx.x, lane = threadIdx.x & 63;
+    if (b >= L.b1_blocks[0]) return;
+    const int c0 = L.b1_cs[0][b], n = L.b1_cs[0][b + 1] - c0, parts = gridDim.y;
+    const int from = (int)((int64_t)n * blockIdx.y / parts), to = (int)((int64_t)n * (blockIdx.y + 1) / parts);
+    const int2 r = L.b1_row[0][64 * b + lane];
+    const int beg = r.x >= 0 ? L.row_ptr[r.x] : 0;
+    for (int i = from + (int)(threadIdx.x >> 6); i < to; i += 4) {
+        const int e = beg + 8 * i, left = r.y - 8 * i;
+        uint4 *dst = (uint4 *)L.b1_lm[0] + (size_t)(c0 + i) * (LDS_HALF_BYTES / 16) + lane;
+        float w[8];
+        if (left >= 8) {
+            const F4 u = *(const F4 *)(L.vals + e), v = *(const F4 *)(L.vals + e + 4);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { w[k] = u.v[k]; w[k + 4] = v.v[k]; }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = k < left ? L.vals[e + k] : 0.0f;
+        }
+        if constexpr (COLS) {
+            unsigned c[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) c[k] = k < left ? (unsigned)L.col_idx[e + k] : (unsigned)L.n_in;
+            dst[0] = make_uint4(c[0] | c[1] << 16, c[2] | c[3] << 16, c[4] | c[5] << 16, c[6] | c[7] << 16);
+        }
+        dst[64] = make_uint4(__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3]));
+        dst[128] = make_uint4(__float_as_uint(w[4]), __float_as_uint(w[5]), __float_as_uint(w[6]), __float_as_uint(w[7]));
+    }
+}
+
+// ---------------------------------------------------------------------------
 // K1p: Eq. 3 for one layer whose operand does not fit LDS: a workgroup of 16 wavefronts takes two samples and one range of up
 // to 16384 of the layer's rows, and walks the operand in panels of up to 16384 neurons that it holds in LDS one after the other.
 // A lane owns a row per block of 64 (up to 16 blocks per wavefront) and keeps their fp64 sums in registers across the
@@ -2877,6 +3020,8 @@ struct sdnn_net {
     bool train_stale = false;     // the values were stepped or replaced and the copies did not follow
     bool train_replaced = false;  // a layer's values were replaced since the last pass that reads the copies
     bool train_kept = false;      // a captured graph reads the copies: they always follow
+    bool long_lm = false, long_attr_set = false; // copies of W for k_fwd_long
+    bool long_stale = false, long_kept = false;  // as train_stale and train_kept
     bool pan_attr_set = false;
     struct Pan {                     // a layer's copy of W for k_fwd_pan
         PanLayer g{};
@@ -2967,6 +3112,7 @@ struct Plan {
         size_t n_cs = 0, n_pos = 0, n_rows = 0, n_chunks = 0, d_tab = 0, cs = 0, row = 0, pos = 0, first = 0, lm = 0, bias = 0, out = 0;
     } train[2];
     bool train_lds = false;
+    bool long_lm = false;        // copies of W for k_fwd_long (in the places of b1_*[0])
     std::vector<PerLayer> pl;
     size_t b1_chunk_bytes = 0;   // 0: no lane-major copies for one sample per step
     std::vector<LmLayer> lm_tab; // empty: no lane-major copy
@@ -3044,7 +3190,7 @@ static bool grad_buffers_wanted(const sdnn_layer *layers, int32_t n_layers, cons
 }
 
 // Chunks of a layer's lane-major copy: its rows, longest first, in blocks of 64, each as deep as its first row.
-static size_t lm_chunks(const sdnn_layer &y)
+static size_t lm_chunks(const sdnn_layer &y, size_t per = LDS_CHUNK)
 {
     std::vector<int32_t> rows_of_len; // a histogram is enough: the first rows of the blocks are rows 0, 64, 128, ... by length
     for (int32_t r = 0; r < y.n_out; ++r) {
@@ -3057,7 +3203,7 @@ static size_t lm_chunks(const sdnn_layer &y)
     for (size_t len = rows_of_len.size(); len-- > 0;) {
         const int64_t after = before + rows_of_len[len];
         const int64_t firsts = (after + 63) / 64 - (before + 63) / 64; // multiples of 64 in [before, after)
-        total += (size_t)firsts * ((len + LDS_CHUNK - 1) / LDS_CHUNK);
+        total += (size_t)firsts * ((len + per - 1) / per);
         before = after;
     }
     return total;
@@ -3285,6 +3431,34 @@ static void plan_train(const sdnn_layer *layers, int32_t n_layers, const sdnn_co
     pl.train_lds = true;
 }
 
+// The copies for k_fwd_long: training nets of long rows whose operands fit its LDS, made for batches that take it (long_forward), with
+// enough entries per layer to pay for bringing the copies up to date after a step (a step of two layers of 1000 neurons of 130 entries
+// takes 77 us without them and 82 with).
+static void plan_long(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg, Plan &pl)
+{
+    pl.long_lm = false;
+    if (!cfg->training || cfg->max_batch < LONG_MIN_BATCH || cfg->lds_forward == SDNN_LDS_OFF || cfg->panel_cols > 0 || cfg->reorder_rows ||
+        pl.train_lds)
+        return;
+    int64_t nnz = 0;
+    for (int32_t l = 0; l < n_layers; ++l) {
+        const sdnn_layer &y = layers[l];
+        if (y.n_out < 1 || y.n_in < 1 || y.n_in > LONG_POS || (int64_t)y.row_ptr[y.n_out] < 128 * (int64_t)y.n_out) return;
+        nnz += y.row_ptr[y.n_out];
+    }
+    if (nnz < (int64_t)150000 * n_layers) return;
+    for (int32_t l = 0; l < n_layers; ++l) {
+        Plan::PerLayer &q = pl.pl[l];
+        q.b1_blocks[0] = (layers[l].n_out + 63) / 64;
+        q.b1_chunks[0] = lm_chunks(layers[l], LDS_CHUNK / 2);
+        if (q.b1_chunks[0] * LDS_HALF_BYTES >= ((size_t)1 << 32) - 65536) { // the kernel addresses a copy with 32-bit offsets
+            for (int32_t k = 0; k <= l; ++k) pl.pl[k].b1_blocks[0] = 0;
+            return;
+        }
+    }
+    pl.long_lm = true;
+}
+
 // The forward in panels (k_fwd_pan) is set up for inference nets wider than a panel, of at least three layers (the two passes that
 // turn the samples around take about as long as a layer), with at least four entries per row and panel in the mean, made for
 // batches that can fill the chip (pan_forward_pays); not where lds_forward = ON takes k_fwd_lds with every batch (`lm`: the net has its copy).
@@ -3364,6 +3538,7 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
     const bool b1 = pl.b1_chunk_bytes != 0;
     pl.pan = pan_wanted(layers, n_layers, cfg, lm, pl.pl);
     plan_train(layers, n_layers, cfg, pl);
+    plan_long(layers, n_layers, cfg, pl);
     size_t paired = 0; // floats of the largest block of activations between its layers
     if (pl.pan) {
         for (int32_t l = 0; l < n_layers; ++l) paired = std::max(paired, (size_t)std::max(pl.pl[l].pan.in_pos, pl.pl[l].pan.out_pos));
@@ -3425,6 +3600,11 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
             t.first = take(4 * t.tab.size());
             t.bias = take(4 * t.n_pos);
             t.out = take(4 * t.n_pos * mb);
+        }
+        if (pl.long_lm) {
+            PLAN_KIND(b1_cs[0], 4 * ((size_t)q.b1_blocks[0] + 1))
+            PLAN_KIND(b1_row[0], 8 * 64 * (size_t)q.b1_blocks[0])
+            PLAN_KIND(b1_lm[0], LDS_HALF_BYTES * q.b1_chunks[0])
         }
         if (b1) {
             PLAN_KIND(b1_cs[0], 4 * ((size_t)q.b1_blocks[0] + 1))
@@ -3587,6 +3767,25 @@ static int launch_b1_fill(sdnn_net *net, int l, int with_cols, hipStream_t strea
     return SDNN_OK;
 }
 
+// Brings the copies for k_fwd_long of layers l0 .. l0 + n - 1 up to date with the CSR values (cols: and writes their columns).
+static int launch_long_fill(sdnn_net *net, int l0, int n, bool cols, hipStream_t stream)
+{
+    int blocks = 1;
+    for (int l = l0; l < l0 + n; ++l) blocks = std::max(blocks, net->layers[l].b1_blocks[0]);
+    for (int k = 0; k < n; k += 65535) {
+        const dim3 grid((unsigned)blocks, 8, (unsigned)std::min(65535, n - k));
+        if (cols) hipLaunchKernelGGL(k_long_fill<true>, grid, dim3(256), 0, stream, net->d_layers + l0 + k);
+        else hipLaunchKernelGGL(k_long_fill<false>, grid, dim3(256), 0, stream, net->d_layers + l0 + k);
+        HIP_TRY(net, hipGetLastError());
+    }
+    return SDNN_OK;
+}
+// From 65 samples on: narrower batches are gathered in rows of 256 bytes by k_spmm<1>, where a step is 4 to 12 % slower with the copies
+// (step of 6 layers, a tenth of the columns with a heavy tail, us without / with, 64, 66, 128 and 256 samples: 1301 neurons 218 / 227, 268 /
+// 255, 268 / 255, 279 / 262; 3001 neurons 487 / 534, 600 / 569, 588 / 562, 667 / 611; 8192 neurons 1803 / 1948, 2639 / 2236, 2644 / 2299,
+// 3602 / 3090).
+static bool long_forward(const sdnn_net *net, int B) { return net->long_lm && B >= LONG_MIN_BATCH; }
+
 extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg,
                            void *d_workspace, size_t workspace_bytes, void *stream_,
                            sdnn_net **out)
@@ -3681,6 +3880,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
     const bool gw_ = grad_buffers_wanted(layers, n_layers, cfg);
     const bool b1 = pl.b1_chunk_bytes != 0;
     net->b1_wide = pl.b1_chunk_bytes == 4096;
+    net->long_lm = pl.long_lm;
     net->b1 = b1;
     auto prepare = [&](int32_t l, HostIdx &h) {
         try {
@@ -3727,7 +3927,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 h.sched[r] = make_int4(h.order[r], y.row_ptr[h.order[r]], y.row_ptr[h.order[r] + 1], 0);
             for (size_t r = 0; r < h.t_sched.size(); ++r)
                 h.t_sched[r] = make_int4(h.t_order[r], h.t_row_ptr[h.t_order[r]], h.t_row_ptr[h.t_order[r] + 1], 0);
-            for (int o = 0; o < (b1 ? 2 : 0); ++o) { // blocks of 64 rows, longest first, whatever the row schedule is
+            for (int o = 0; o < (b1 ? 2 : pl.long_lm ? 1 : 0); ++o) { // blocks of 64 rows, longest first, whatever the row schedule is
                 const int32_t n = o ? y.n_in : y.n_out, *ptr = o ? h.t_row_ptr.data() : y.row_ptr;
                 std::vector<int32_t> by_len((size_t)n);
                 sdnn_row_schedule(n, ptr, by_len.data());
@@ -3863,10 +4063,11 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 d.mid = gw ? (float *)(base + q.mid) : nullptr;
                 for (int o = 0; o < 2; ++o) {
                     d.b1_blocks[o] = q.b1_blocks[o];
-                    d.b1_cs[o] = b1 ? (const int32_t *)(base + q.b1_cs[o]) : nullptr;
-                    d.b1_row[o] = b1 ? (const int2 *)(base + q.b1_row[o]) : nullptr;
-                    d.b1_lm[o] = b1 ? (int4 *)(base + q.b1_lm[o]) : nullptr;
-                    if (b1) {
+                    const bool copied = b1 || (pl.long_lm && o == 0);
+                    d.b1_cs[o] = copied ? (const int32_t *)(base + q.b1_cs[o]) : nullptr;
+                    d.b1_row[o] = copied ? (const int2 *)(base + q.b1_row[o]) : nullptr;
+                    d.b1_lm[o] = copied ? (int4 *)(base + q.b1_lm[o]) : nullptr;
+                    if (copied) {
                         UP(d.b1_cs[o], h.b1_cs[o].data(), 4 * h.b1_cs[o].size());
                         UP(d.b1_row[o], h.b1_row[o].data(), 8 * h.b1_row[o].size());
                     }
@@ -3922,6 +4123,10 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 const int rc_fill = launch_b1_fill(net, l, 1, stream);
                 if (rc_fill) return fail_free(rc_fill);
             }
+        if (net->long_lm) {
+            const int rc_fill = launch_long_fill(net, 0, n_layers, true, stream);
+            if (rc_fill) return fail_free(rc_fill);
+        }
         if (pl.train_lds) {
             // layer l's neurons in the order of the rows of W_{l+1}^T in both passes
             for (int32_t k = 0; k + 1 < n_layers; ++k) {
@@ -4513,6 +4718,36 @@ static int forward_pan(sdnn_net *net, const float *d_X0, int B, float *d_XL, hip
     return SDNN_OK;
 }
 
+// The forward pass of a training net through k_fwd_long, from d_x0.
+static int forward_long(sdnn_net *net, int B, int Bp, int ld, hipStream_t stream)
+{
+    const void *fn = net->cfg.activation == ACT_SIGMOID ? (const void *)k_fwd_long<ACT_SIGMOID> : (const void *)k_fwd_long<ACT_RELU_CAP>;
+    if (!net->long_attr_set) { // more than the default 64 KiB of dynamic LDS per workgroup
+        HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 16 * (LONG_POS + 2)));
+        net->long_attr_set = true;
+    }
+    const bool captured = capturing(stream);
+    net->long_kept |= captured;
+    if (net->long_stale) {
+        const int rc = launch_long_fill(net, 0, net->n_layers, false, stream);
+        if (rc) return rc;
+        net->long_stale = captured;
+    }
+    for (int l = 0; l < net->n_layers; ++l) {
+        const LayerDev &d = net->layers[l];
+        FwdLong a;
+        a.cs = d.b1_cs[0]; a.row = d.b1_row[0]; a.lm = (const uint4 *)d.b1_lm[0]; a.bias = d.bias; a.in = d.X_prev; a.out = d.X;
+        a.lm_bytes = 0xffffffffu; // every half that the table names is there
+        a.blocks = d.b1_blocks[0]; a.n_in = d.n_in; a.ld = ld; a.B = B; a.cap = net->cfg.act_cap;
+        a.groups = Bp / 4;
+        const int per = (a.groups + 7) / 8;
+        a.n_ranges = std::max(1, std::min(net->n_cu / 8 / per, a.blocks));
+        void *args[] = {(void *)&a};
+        HIP_TRY(net, hipLaunchKernel(fn, dim3((unsigned)(8 * per * a.n_ranges)), dim3(64 * LDS_WAVES), args, 16 * ((size_t)d.n_in + 2), stream));
+    }
+    return SDNN_OK;
+}
+
 // `ld`: floats per row of the activations between the layers.
 static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL, void *stream_, float *ping,
                         float *pong, int ld)
@@ -4609,7 +4844,12 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
         const int rc = launch_train_lds(net, 0, B, Bp, ld, stream);
         if (rc) return rc;
     }
-    for (int l = 0; l < (single ? 0 : L); ++l) {
+    const bool by_four = training && !single && (ld & 3) == 0 && long_forward(net, B);
+    if (by_four) {
+        const int rc = forward_long(net, B, Bp, ld, stream);
+        if (rc) return rc;
+    }
+    for (int l = 0; l < (single || by_four ? 0 : L); ++l) {
         const LayerDev &d = net->layers[l];
         float *out = training ? d.X : (l == L - 1 ? d_XL : ((l & 1) ? pong : ping));
         const int ld_out = !training && l == L - 1 ? B : ld;
@@ -5024,6 +5264,10 @@ extern "C" int sdnn_sgd_step(sdnn_net *net, float lr, void *stream_)
             else net->train_stale = true;
         }
     }
+    if (!rc && net->long_lm) { // the copies for k_fwd_long follow, or do so when a pass needs them
+        if (long_forward(net, net->B) || net->long_kept || capturing((hipStream_t)stream_)) rc = launch_long_fill(net, 0, net->n_layers, false, (hipStream_t)stream_);
+        else net->long_stale = true;
+    }
     if (rc) return rc;
     net->state = ST_IDLE;
     return SDNN_OK;
@@ -5132,6 +5376,7 @@ extern "C" int sdnn_set_weights(sdnn_net *net, int32_t layer, const float *d_val
         if (layer > 1) net->bias_nonpos = false; // device data: its signs are not inspected
     }
     if (!rc && d_values && net->b1) rc = launch_b1_fill(net, layer - 1, 0, (hipStream_t)stream_);
+    if (!rc && d_values && net->long_lm) rc = launch_long_fill(net, layer - 1, 1, false, (hipStream_t)stream_);
     if (!rc && (d_values || d_bias) && net->lm) // keep the lane-major copy current
         rc = launch_lm_fill(net, layer - 1, nullptr, 0, (hipStream_t)stream_);
     if (!rc && (d_values || d_bias) && !net->train[0].tab.empty()) { // the first layer's copies follow at once, all others' in one go with the next pass
