@@ -3773,7 +3773,7 @@ static int launch_long_fill(sdnn_net *net, int l0, int n, bool cols, hipStream_t
     int blocks = 1;
     for (int l = l0; l < l0 + n; ++l) blocks = std::max(blocks, net->layers[l].b1_blocks[0]);
     for (int k = 0; k < n; k += 65535) {
-        const dim3 grid((unsigned)blocks, 8, (unsigned)std::min(65535, n - k));
+        const dim3 grid((unsigned)blocks, 16, (unsigned)std::min(65535, n - k)); // (8 parts: 105 us for six layers of 8192 neurons of 820 entries, 16: 97)
         if (cols) hipLaunchKernelGGL(k_long_fill<true>, grid, dim3(256), 0, stream, net->d_layers + l0 + k);
         else hipLaunchKernelGGL(k_long_fill<false>, grid, dim3(256), 0, stream, net->d_layers + l0 + k);
         HIP_TRY(net, hipGetLastError());
@@ -5079,9 +5079,10 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;
     }
-    // More than 128 samples: a wavefront per row either way.  From 128 entries per row on (what counts as long elsewhere too) by scalar
-    // loads and matrix products; shorter rows would wait for the two dependent scalar loads at their start (step of 6 layers, 256
-    // samples, k_bwd_rows / k_bwd_long: 1300 neurons of 130 entries 291 / 280 us, 3001 of 300 730 / 678, 8192 of 820 4030 / 3680).
+    // More than 128 samples: a wavefront per row either way.  From 64 entries per row on by scalar loads and matrix products, whose
+    // start takes a row longer (step with 256 samples, k_bwd_rows / k_bwd_long: 4096 neurons of 32 entries, 120 layers 2954 / 2983 us, 8001
+    // of 32, 48 layers 2255 / 2239; 6 layers of 1024 neurons of 102 entries 250 / 241, 1300 of 130 291 / 280, 3001 of 300 730 / 678, 8192
+    // of 820 4030 / 3680).
     // two windows: as two tiles (and two partial gradients) where the operand is larger than L2, else in one
     const bool two = net->two_windows;
     int G = lanes_per_row(net->grad_parts == 2 ? 64 : B);
@@ -5091,7 +5092,7 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
     a.n_rg = (uint32_t)((a.n_rows + rows_per_block - 1) / rows_per_block);
     const void *fn = G == 4 ? (const void *)k_bwd_rows<4, false> : G == 8 ? (const void *)k_bwd_rows<8, false>
                      : G == 16 ? (const void *)k_bwd_rows<16, false>
-                     : G == 64 ? ((int64_t)d.nnz >= 128 * (int64_t)a.n_rows ? (const void *)k_bwd_long : (const void *)k_bwd_rows<64, false>)
+                     : G == 64 ? ((int64_t)d.nnz >= 64 * (int64_t)a.n_rows ? (const void *)k_bwd_long : (const void *)k_bwd_rows<64, false>)
                      : two ? (const void *)k_bwd_rows<32, true> : (const void *)k_bwd_rows<32, false>;
     HIP_TRY(net, hipLaunchKernel(fn, dim3(a.n_tiles * a.n_rg), dim3(BLOCK_THREADS), args, 0, stream));
     HIP_TRY(net, hipGetLastError());

@@ -50,9 +50,9 @@ def _turned(lay):
 @pytest.mark.parametrize("b,activation", [(129, "relu"), (130, "sigmoid"), (192, "relu"), (255, "relu"), (256, "relu"), (256, "sigmoid")])
 def test_long_columns_and_more_than_128_samples(b, activation):
     """The sweep with a wavefront per row: columns of W around its groups of sixteen entries, empty ones and very long ones;
-    layers whose columns have just under and just over 128 entries on average."""
-    layers = [_turned(_layer(9430, 301, 1700, (0, 1, 15, 16, 17, 31, 33, 250, 1700))), _turned(_layer(9431, 1700, 203, (126, 127, 129, 129))),
-              _turned(_layer(9432, 203, 150, (127, 126)))]
+    layers whose columns have just under and just over 64 entries on average."""
+    layers = [_turned(_layer(9430, 301, 1700, (0, 1, 15, 16, 17, 31, 33, 250, 1700))), _turned(_layer(9431, 1700, 203, (62, 64, 65, 66))),
+              _turned(_layer(9432, 203, 150, (63, 64)))]
     _step(layers, b, 9440, 1, activation)
 
 
