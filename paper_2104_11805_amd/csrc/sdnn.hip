@@ -580,6 +580,24 @@ template <int BIT> __device__ __forceinline__ double lane_exchange(double v)
     const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
 }
+// The value of the lane whose number differs in exactly that bit (bits 0 to 3), and the sum with it (bits 4 and 5).
+template <int BIT> __device__ __forceinline__ double lane_xor(double v)
+{
+    if constexpr (BIT != 2) {
+        return lane_exchange<BIT>(v);
+    } else { // lane ^ 7, then ^ 3
+        const int lo = __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(__double2loint(v), 0x141, 0xf, 0xf, true), 0x1b, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x141, 0xf, 0xf, true), 0x1b, 0xf, 0xf, true);
+        return __hiloint2double(hi, lo);
+    }
+}
+template <int BIT> __device__ __forceinline__ double add_lane_xor(double v)
+{
+    const unsigned l = (unsigned)__double2loint(v), h = (unsigned)__double2hiint(v);
+    const auto lo = BIT == 5 ? __builtin_amdgcn_permlane32_swap(l, l, false, false) : __builtin_amdgcn_permlane16_swap(l, l, false, false);
+    const auto hi = BIT == 5 ? __builtin_amdgcn_permlane32_swap(h, h, false, false) : __builtin_amdgcn_permlane16_swap(h, h, false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
 // The value of the lane N places on in its group of sixteen.
 template <int N> __device__ __forceinline__ double row_rotate(double v)
 {
@@ -2616,8 +2634,11 @@ k_update(const LayerDev *__restrict__ layers, int layer0, int n_layers, int inte
 #pragma unroll
             for (int v = 0; v < V; ++v) sum += (double)d[v];
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+        sum = add_lane_xor<4>(add_lane_xor<5>(sum));
+        sum += lane_xor<3>(sum);
+        sum += lane_xor<2>(sum);
+        sum += lane_xor<1>(sum);
+        sum += lane_xor<0>(sum);
         if (lane == 0) {
             const float gb = (float)sum;
             if (emit) gb_out[row] = gb;
@@ -2685,21 +2706,21 @@ k_update(const LayerDev *__restrict__ layers, int layer0, int n_layers, int inte
             for (int j = 0; j < 4; ++j) {
                 const double send = up8 ? a[j] : a[j + 4];
                 const double keep = up8 ? a[j + 4] : a[j];
-                a[j] = keep + __shfl_xor(send, 8);
+                a[j] = keep + lane_xor<3>(send);
             }
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const double send = up4 ? a[j] : a[j + 2];
                 const double keep = up4 ? a[j + 2] : a[j];
-                a[j] = keep + __shfl_xor(send, 4);
+                a[j] = keep + lane_xor<2>(send);
             }
             {
                 const double send = up2 ? a[0] : a[1];
                 const double keep = up2 ? a[1] : a[0];
-                a[0] = keep + __shfl_xor(send, 2);
+                a[0] = keep + lane_xor<1>(send);
             }
         }
-        a[0] += __shfl_xor(a[0], 1);
+        a[0] += lane_xor<0>(a[0]);
         if (writer) {
             const float g = (float)a[0];
             if (emit) g_out[p0 + kw] = g;
