@@ -1016,7 +1016,10 @@ __global__ void __launch_bounds__(BLOCK_THREADS) k_spmm_panel(const SpmmArgs a, 
 // Activations: row (block j of wavefront w, lane r) of a layer sits at position 64 (16 j + w) + r; the columns of
 // the next layer are stored as those positions.  Every lane adds its row's terms in storage order in fp64 (the
 // same sums as k_spmm).  A layer's results wait in registers until every wavefront has read its operands, and
-// then replace them: one buffer instead of two, i.e. twice the samples or twice the width per CU.
+// then replace them: one buffer instead of two, i.e. twice the samples or twice the width per CU.  Where four samples fit twice (up to
+// 4096 positions) every other layer has its operand max_pos positions higher (the copy's positions say so): results are stored as they
+// come, and one barrier ends a layer (us per pass of 120 layers, one buffer / two: 1024 neurons, 64 samples 306 / 295; 2001, 100 samples
+// 493 / 480; 4096, 200 samples 880 / 866, 1024 samples 1633 / 1600; 3001 with 777 samples of which some die 799 / 781).
 //
 // What bounds it, in clocks of a CU per wavefront-wide entry (T = 1 / 2 / 4): vector instructions 4 / 6.5 / 10.5 (one
 // address, one weight conversion, T conversions and T multiply-adds), LDS reads at random positions 7 / 7 / 13 (measured
@@ -1105,8 +1108,9 @@ struct LdsForward {
     const int32_t *src_col; // the column of `in` that holds sample k of them
     const int32_t *dst_col; // the column of `out` that sample k goes to (NULL: k)
     int32_t *alive;        // alive[k] = whether sample k has a non-zero activation at the end (NULL: not wanted)
-    int32_t max_pos;       // positions of the LDS buffer; one more follows, which holds zeros
-};
+    int32_t max_pos;       // positions of the LDS buffer
+    int32_t two;           // max_pos, where odd layers (l0 and so on: 0-based) have their operand in a second buffer behind the first, else 0
+};                         // one more position follows, which holds zeros
 
 // PART: a stretch of layers for the samples that are still alive.  ORDER: a wavefront requests its halves of W strictly one after the
 // other (see take, below).
@@ -1158,9 +1162,9 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
 #pragma unroll
             for (int t = 0; t < T; ++t) v[t] = s0 + t < n_samples ? p[s0 + t] : 0.0f;
         }
-        act[i] = v;
+        act[(PART && (a.l0 & 1) ? a.two : 0) + i] = v;
     }
-    if (tid < T) lds_act[T * a.max_pos + tid] = 0.0f; // where the slots past the end of a row point
+    if (tid < T) lds_act[T * (a.max_pos + a.two) + tid] = 0.0f; // where the slots past the end of a row point
 
     // the wavefront's place in the copy of W, in bytes (the copy is smaller than 4 GiB), goes into the loads as a scalar
     const __amdgpu_buffer_rsrc_t rlm = make_rsrc((const float *)a.lm, a.lm_bytes);
@@ -1186,6 +1190,15 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
     for (int l = a.l0; l < a.l1; ++l) {
         const int nb = stab[l].nb, cs0 = stab[l].cs + wave * (nb + 1), pos0 = stab[l].pos + 64 * wave + lane;
         f32x32 res;
+        auto result = [&](int j) {
+            piece v;
+            if constexpr (T == 1) v = res[j];
+            else {
+#pragma unroll
+                for (int t = 0; t < T; ++t) v[t] = res[j * T + t];
+            }
+            return v;
+        };
         for (int j = 0; j < nb; ++j) {
             if (j > 0 && j == nb - 1 && l + 1 < a.l1) { // see above (one block per layer: it would only hold the wavefront up)
                 asm volatile("" ::"v"(touched));
@@ -1235,16 +1248,8 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
             const double bd = (double)bias;
 #pragma unroll
             for (int t = 0; t < T; ++t) res[j * T + t] = act_apply(ACT, acc[t] + bd, a.cap);
+            if (a.two && l < a.l1 - 1) act[(l & 1 ? 0 : a.two) + 64 * (LDS_WAVES * j + wave) + lane] = result(j);
         }
-        auto result = [&](int j) {
-            piece v;
-            if constexpr (T == 1) v = res[j];
-            else {
-#pragma unroll
-                for (int t = 0; t < T; ++t) v[t] = res[j * T + t];
-            }
-            return v;
-        };
         if (l == a.l1 - 1) {
             unsigned nz = 0; // bit t: this lane has a non-zero result for sample t
             for (int j = 0; j < nb; ++j) {
@@ -1290,8 +1295,10 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
             }
             return;
         }
-        lds_barrier(); // every wavefront has read its operands
-        for (int j = 0; j < nb; ++j) act[64 * (LDS_WAVES * j + wave) + lane] = result(j);
+        if (!a.two) {
+            lds_barrier(); // every wavefront has read its operands
+            for (int j = 0; j < nb; ++j) act[64 * (LDS_WAVES * j + wave) + lane] = result(j);
+        }
         lds_barrier(); // the layer is complete before anyone reads it
     }
 }
@@ -1360,7 +1367,7 @@ __global__ void __launch_bounds__(1024) k_live_columns(const int32_t *__restrict
 __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ layer, const LmLayer *__restrict__ tab,
                                                 const int32_t *__restrict__ lm_cs, uint4 *__restrict__ lm,
                                                 float *__restrict__ lm_bias, const int32_t *__restrict__ lm_row,
-                                                const int32_t *__restrict__ prev_pos, int with_cols, int pad_pos)
+                                                const int32_t *__restrict__ prev_pos, int with_cols, int pad_pos, int first_pos)
 {
     const LayerDev &L = *layer;
     const int j = blockIdx.x, w = blockIdx.y, lane = threadIdx.x, nb = tab->nb;
@@ -1385,7 +1392,7 @@ __global__ void __launch_bounds__(64) k_lm_fill(const LayerDev *__restrict__ lay
             wt[k] = 0;
             if (e < end) {
                 wt[k] = __float_as_uint(L.vals[e]);
-                if (with_cols) pos = (unsigned)(prev_pos ? prev_pos[L.col_idx[e]] : L.col_idx[e]);
+                if (with_cols) pos = (unsigned)(first_pos + (prev_pos ? prev_pos[L.col_idx[e]] : L.col_idx[e]));
             }
             if (k & 1) pk[k >> 1] |= pos << 16;
             else pk[k >> 1] = pos;
@@ -3059,7 +3066,7 @@ struct sdnn_net {
     LmLayer *lm_layers = nullptr;
     std::vector<LmLayer> lm_tab;     // host copy of lm_layers
     size_t lm_chunks = 0;
-    int32_t lm_max_pos = 0;
+    int32_t lm_max_pos = 0, lm_two = 0; // see LdsForward
     int32_t turns = 0;               // lm_turns of three quarters of its chunks and more
     bool lds_part_attr_set = false;
     struct Train {                   // a copy of W (0) or W^T (1) for k_train_lds
@@ -3718,7 +3725,7 @@ static int launch_lm_fill(sdnn_net *net, int l, const int32_t *prev_pos, int wit
 {
     if (net->lm_tab[l].nb == 0) return SDNN_OK;
     hipLaunchKernelGGL(k_lm_fill, dim3((unsigned)net->lm_tab[l].nb, LDS_WAVES, fill_parts(net->max_len[0][l])), dim3(64), 0, stream, net->d_layers + l, net->lm_layers + l,
-                       net->lm_cs, net->lm, net->lm_bias, net->lm_row, prev_pos, with_cols, net->lm_max_pos);
+                       net->lm_cs, net->lm, net->lm_bias, net->lm_row, prev_pos, with_cols, net->lm_max_pos + net->lm_two, l & 1 ? net->lm_two : 0);
     HIP_TRY(net, hipGetLastError());
     return SDNN_OK;
 }
@@ -4289,6 +4296,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
             net->lm_tab = pl.lm_tab;
             net->lm_max_pos = layers[0].n_in;
             for (const LmLayer &t : pl.lm_tab) net->lm_max_pos = std::max(net->lm_max_pos, t.n_pos);
+            net->lm_two = 2 * 4 * net->lm_max_pos <= LDS_MAX_FLOATS ? net->lm_max_pos : 0;
             int32_t *d_pos = (int32_t *)(base + pl.lm_pos);
             UP(net->lm_cs, lm_cs.data(), 4 * lm_cs.size());
             UP(net->lm_layers, pl.lm_tab.data(), sizeof(LmLayer) * (size_t)n_layers);
@@ -4706,7 +4714,7 @@ static LdsForward lds_args(const sdnn_net *net, int l0, int l1, const float *in,
     a.lm_bytes = (unsigned)(LDS_CHUNK_BYTES * (net->lm_chunks + 1));
     a.l0 = l0; a.l1 = l1; a.n_in = net->layers[l0].n_in;
     a.in = in; a.out = out; a.ld_in = ld_in; a.ld_out = ld_out; a.B = B;
-    a.cap = net->cfg.act_cap; a.max_pos = net->lm_max_pos;
+    a.cap = net->cfg.act_cap; a.max_pos = net->lm_max_pos; a.two = net->lm_two;
     return a;
 }
 
@@ -4829,7 +4837,7 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
             {(const void *)k_fwd_lds<1, ACT_SIGMOID, true>, (const void *)k_fwd_lds<2, ACT_SIGMOID, true>, (const void *)k_fwd_lds<4, ACT_SIGMOID, true>,
              (const void *)k_fwd_lds<1, ACT_SIGMOID, false>}};
         const void *fn = fns[sig ? 1 : 0][T == 1 && !(net->turns & LM_IN_ORDER) ? 3 : ti]; // (a net has one of the two)
-        const size_t lds_bytes = sizeof(float) * (size_t)T * ((size_t)net->lm_max_pos + 1);
+        const size_t lds_bytes = sizeof(float) * (size_t)T * ((size_t)net->lm_max_pos + net->lm_two + 1);
         if (!net->lds_attr_set[ti]) { // more than the default 64 KiB of dynamic LDS per workgroup
             HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (LDS_MAX_FLOATS + 4)));
             net->lds_attr_set[ti] = true;
@@ -4853,7 +4861,8 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
             memset(&b, 0, sizeof b);
             b.cs = net->lm_cs; b.lm = net->lm; b.lm_bytes = (unsigned)(LDS_CHUNK_BYTES * (net->lm_chunks + 1));
             b.lm_row = last ? net->lm_row : nullptr; b.aux = net->lm_bias;
-            b.in = in; b.in_bytes = (unsigned)(4 * n_in); b.out = last ? d_XL : ((l & 1) ? pong : ping);
+            const int first = l & 1 ? net->lm_two : 0; // the position that the copy has for the operand's first
+            b.in = in - first; b.in_bytes = (unsigned)(4 * (n_in + first)); b.out = last ? d_XL : ((l & 1) ? pong : ping);
             b.cap = net->cfg.act_cap; b.act = net->cfg.activation;
             b.nb = net->lm_tab[l].nb; b.tab_cs = net->lm_tab[l].cs; b.tab_pos = net->lm_tab[l].pos;
             n_in = (size_t)net->lm_tab[l].n_pos;
@@ -4979,7 +4988,7 @@ static int skip_dead_lds(sdnn_net *net, const float *d_X0, int B, float *d_XL, i
     const int last_check = (L - 1) / check_every * check_every;
     int t_max = 4;
     while (t_max > 1 && t_max * net->lm_max_pos > LDS_MAX_FLOATS) t_max /= 2;
-    const size_t lds_bytes = sizeof(float) * (size_t)t_max * ((size_t)net->lm_max_pos + 1);
+    const size_t lds_bytes = sizeof(float) * (size_t)t_max * ((size_t)net->lm_max_pos + net->lm_two + 1);
     if (!net->lds_part_attr_set) {
         HIP_TRY(net, hipFuncSetAttribute((const void *)k_fwd_lds_part, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (LDS_MAX_FLOATS + 4)));
         net->lds_part_attr_set = true;

@@ -96,3 +96,32 @@ def test_forward_across_a_large_input(shift):
     net.sdnn_forward(x0, out)
     assert torch.equal(out, ref)
     net.close()
+
+
+@pytest.mark.parametrize("sizes", [(4096, 4095, 1, 4096, 1025, 3000), (4097, 1024, 1023, 300), (17, 4096, 4097, 40, 40)])
+@pytest.mark.parametrize("b", [1, 70, 300, 1100])
+def test_two_buffers_up_to_4096_positions(sizes, b):
+    """Layers alternate between two LDS buffers where the net's positions fit twice with four samples, and share one beyond: the widest
+    of either kind, odd and even numbers of layers, one, two and four samples per workgroup, stretches that start at either buffer."""
+    rng = np.random.default_rng(9700)
+    layers = []
+    for l, (n_in, n_out) in enumerate(zip(sizes, sizes[1:])):
+        d = min(n_in, 24)
+        cols = np.stack([np.sort(rng.choice(n_in, d, replace=False)) for _ in range(n_out)]).astype(np.int32)
+        layers.append(wl.Layer(n_out, n_in, np.arange(0, n_out * d + 1, d, dtype=np.int32), cols.ravel(), (rng.standard_normal(n_out * d) * 0.4).astype(np.float32),
+                               -0.05 * rng.random(n_out).astype(np.float32)))
+    x = np.maximum(wl.normal_inputs(9701, sizes[0], b), 0.0)
+    ref = P.O32.forward(layers, x, 8.0)[-1]
+    net = sdnn.Net(layers, 8.0, b, training=False, lds_forward=sdnn.SDNN_LDS_ON)
+    out = torch.empty(sizes[-1], b, device=P.DEV)
+    for _ in range(2):
+        assert np.array_equal(P.host(net.sdnn_forward(P.dev(x), out)), ref)
+    for every in (1, 3):
+        n_live = torch.zeros(1, dtype=torch.int32, device=P.DEV)
+        out.fill_(-1.0)
+        net.sdnn_forward_skip_dead(P.dev(x), out, check_every=every, n_live=n_live)
+        assert np.array_equal(P.host(out), ref), every
+    v, bias = net.sdnn_get_weights(2)
+    net.sdnn_set_weights(2, values=v.clone(), bias=bias.clone())
+    assert np.array_equal(P.host(net.sdnn_forward(P.dev(x), out)), ref)
+    net.close()
