@@ -1114,9 +1114,11 @@ struct LdsForward {
 
 // PART: a stretch of layers for the samples that are still alive.  ORDER: a wavefront requests its halves of W strictly one after the
 // other (see take, below).
-template <int T, int ACT, bool PART, bool ORDER>
+// TWO (!PART): a.two != 0; looked at in every block it costs the nets that have one buffer up to 1 %.
+template <int T, int ACT, bool PART, bool ORDER, bool TWO>
 __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_samples)
 {
+    const int second = PART || TWO ? a.two : 0; // where the second buffer starts
     extern __shared__ __attribute__((aligned(16))) float lds_act[];
     typedef typename LdsPiece<T>::type piece; // the T samples of one position: one LDS access
     typedef __attribute__((address_space(3))) piece *lds_ptr;
@@ -1162,9 +1164,9 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
 #pragma unroll
             for (int t = 0; t < T; ++t) v[t] = s0 + t < n_samples ? p[s0 + t] : 0.0f;
         }
-        act[(PART && (a.l0 & 1) ? a.two : 0) + i] = v;
+        act[(PART && (a.l0 & 1) ? second : 0) + i] = v;
     }
-    if (tid < T) lds_act[T * (a.max_pos + a.two) + tid] = 0.0f; // where the slots past the end of a row point
+    if (tid < T) lds_act[T * (a.max_pos + second) + tid] = 0.0f; // where the slots past the end of a row point
 
     // the wavefront's place in the copy of W, in bytes (the copy is smaller than 4 GiB), goes into the loads as a scalar
     const __amdgpu_buffer_rsrc_t rlm = make_rsrc((const float *)a.lm, a.lm_bytes);
@@ -1248,7 +1250,7 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
             const double bd = (double)bias;
 #pragma unroll
             for (int t = 0; t < T; ++t) res[j * T + t] = act_apply(ACT, acc[t] + bd, a.cap);
-            if (a.two && l < a.l1 - 1) act[(l & 1 ? 0 : a.two) + 64 * (LDS_WAVES * j + wave) + lane] = result(j);
+            if (second && l < a.l1 - 1) act[(l & 1 ? 0 : second) + 64 * (LDS_WAVES * j + wave) + lane] = result(j);
         }
         if (l == a.l1 - 1) {
             unsigned nz = 0; // bit t: this lane has a non-zero result for sample t
@@ -1295,7 +1297,7 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
             }
             return;
         }
-        if (!a.two) {
+        if (!second) {
             lds_barrier(); // every wavefront has read its operands
             for (int j = 0; j < nb; ++j) act[64 * (LDS_WAVES * j + wave) + lane] = result(j);
         }
@@ -1303,12 +1305,12 @@ __device__ __forceinline__ void lds_forward(const LdsForward &a, int grp, int n_
     }
 }
 
-template <int T, int ACT, bool ORDER>
+template <int T, int ACT, bool ORDER, bool TWO>
 __global__ void __launch_bounds__(64 * LDS_WAVES) k_fwd_lds(const LdsForward a)
 {
     // neighbouring samples share cache lines of X: an XCD takes a contiguous stretch of them
     const int nwg = (int)gridDim.x, per = nwg >> 3, wg = (int)blockIdx.x;
-    lds_forward<T, ACT, false, ORDER>(a, wg < 8 * per ? (wg & 7) * per + (wg >> 3) : wg, a.B);
+    lds_forward<T, ACT, false, ORDER, TWO>(a, wg < 8 * per ? (wg & 7) * per + (wg >> 3) : wg, a.B);
 }
 
 // A stretch of layers for the samples that are still alive, as many per workgroup as it takes to give every CU one (the
@@ -1317,13 +1319,13 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) k_fwd_lds_part(const LdsForwar
 {
     const int n = *a.n_live, wg = (int)blockIdx.x;
     if (4 * a.max_pos <= LDS_MAX_FLOATS && n > 2 * n_cu) {
-        if (4 * wg < n) lds_forward<4, ACT_RELU_CAP, true, true>(a, wg, n);
+        if (4 * wg < n) lds_forward<4, ACT_RELU_CAP, true, true, true>(a, wg, n);
     } else if (2 * a.max_pos <= LDS_MAX_FLOATS && n > n_cu) {
-        if (2 * wg < n) lds_forward<2, ACT_RELU_CAP, true, true>(a, wg, n);
+        if (2 * wg < n) lds_forward<2, ACT_RELU_CAP, true, true, true>(a, wg, n);
     } else {
         if (wg >= n) return;
-        if (a.turns & LM_IN_ORDER) lds_forward<1, ACT_RELU_CAP, true, true>(a, wg, n);
-        else lds_forward<1, ACT_RELU_CAP, true, false>(a, wg, n);
+        if (a.turns & LM_IN_ORDER) lds_forward<1, ACT_RELU_CAP, true, true, true>(a, wg, n);
+        else lds_forward<1, ACT_RELU_CAP, true, false, true>(a, wg, n);
     }
 }
 
@@ -1838,8 +1840,8 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) __attribute__((amdgpu_num_vgpr
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // A workgroup takes one piece (a range of a pair) after the other: the first panel of the next one comes while the results of this
-    // one are stored, and its first halves of W before that (a workgroup per piece: 11385 against 11227 us per 24 layers of 65536
-    // neurons, 1024 samples, eight pieces for each).
+    // one are stored, and its first halves of W before that (a workgroup per piece / staying, us per pass: 65536 neurons, 1024 samples, 24
+    // layers 11300 / 11165; 50000, 400 samples 4195 / 4081; 40001, 650 samples 3958 / 3911; 80001, 300 samples, 12 layers 2311 / 2220).
     // The ranges of a pair run side by side on one XCD: they read the same panels (one range of all pairs after the other, so
     // that all the workgroups of an XCD share one stream of W: 602 against 511 us at 65536 neurons, 1024 samples)
     const int xcd = (int)(blockIdx.x & 7u), stride = (int)(gridDim.x >> 3);
@@ -1946,7 +1948,7 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) __attribute__((amdgpu_num_vgpr
         }
         const int at0 = q * a.range + 64 * wave + lane;
         pair *out = (pair *)(a.out + (size_t)g * a.out_pos + (size_t)at0);
-        constexpr int K = ACT == ACT_SIGMOID ? 1 : 4; // (exp() takes the registers of the others)
+        constexpr int K = ACT == ACT_SIGMOID ? 1 : 16; // biases at once (exp() takes their registers)
         for (int b0 = 0; b0 < a.nb; b0 += K) {
             float bias[K];
 #pragma unroll
@@ -4814,6 +4816,12 @@ static int forward_long(sdnn_net *net, int B, int Bp, int ld, hipStream_t stream
     return SDNN_OK;
 }
 
+template <int ACT, bool TWO> static const void *lds_fn(int T, int turns)
+{
+    return T == 4 ? (const void *)k_fwd_lds<4, ACT, true, TWO> : T == 2 ? (const void *)k_fwd_lds<2, ACT, true, TWO>
+           : turns & LM_IN_ORDER ? (const void *)k_fwd_lds<1, ACT, true, TWO> : (const void *)k_fwd_lds<1, ACT, false, TWO>;
+}
+
 // `ld`: floats per row of the activations between the layers.
 static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL, void *stream_, float *ping,
                         float *pong, int ld)
@@ -4831,12 +4839,9 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
     if (T) {
         const bool sig = net->cfg.activation == ACT_SIGMOID;
         const int ti = T == 1 ? 0 : T == 2 ? 1 : 2;
-        static const void *const fns[2][4] = {
-            {(const void *)k_fwd_lds<1, ACT_RELU_CAP, true>, (const void *)k_fwd_lds<2, ACT_RELU_CAP, true>, (const void *)k_fwd_lds<4, ACT_RELU_CAP, true>,
-             (const void *)k_fwd_lds<1, ACT_RELU_CAP, false>},
-            {(const void *)k_fwd_lds<1, ACT_SIGMOID, true>, (const void *)k_fwd_lds<2, ACT_SIGMOID, true>, (const void *)k_fwd_lds<4, ACT_SIGMOID, true>,
-             (const void *)k_fwd_lds<1, ACT_SIGMOID, false>}};
-        const void *fn = fns[sig ? 1 : 0][T == 1 && !(net->turns & LM_IN_ORDER) ? 3 : ti]; // (a net has one of the two)
+        const void *const fns[2][2] = {{lds_fn<ACT_RELU_CAP, false>(T, net->turns), lds_fn<ACT_RELU_CAP, true>(T, net->turns)},
+                                       {lds_fn<ACT_SIGMOID, false>(T, net->turns), lds_fn<ACT_SIGMOID, true>(T, net->turns)}};
+        const void *fn = fns[sig ? 1 : 0][net->lm_two ? 1 : 0]; // (a net has one of those for T)
         const size_t lds_bytes = sizeof(float) * (size_t)T * ((size_t)net->lm_max_pos + net->lm_two + 1);
         if (!net->lds_attr_set[ti]) { // more than the default 64 KiB of dynamic LDS per workgroup
             HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (LDS_MAX_FLOATS + 4)));
