@@ -180,8 +180,8 @@ def run_config(cfg, args, steps, warmup, headline):
     # separate backward: layers L..2 only; fused sweep: all layers, the first one without a Delta output
     bb -= (4 * first.n_in * Bt) if fused else layer_bytes(first.n_out, first.nnz, Bt, fused)[1]
     panels = short_rows and N * 256 >= (8 << 20) and (args.panel_cols >= 0 or not headline)   # the library's policy
-    kernels = {"forward": "k_spmm_panel<8,0>" if panels else f"k_spmm<{v},0,{8 if short_rows else 16}>" if not short_rows or (Bt <= 64 and N < 2048) else "k_rows",
-               "backward": ("k_bwd_grad<8>" if Bt <= 64 and short_rows and N <= 6144 else "k_bwd_rows") if fused else f"k_spmm<{v},1,{8 if short_rows else 16}>",
+    kernels = {"forward": "k_spmm_panel<8,0>" if panels else "k_fwd_long" if not short_rows and Bt > 64 and N <= 8192 else f"k_spmm<{v},0,{8 if short_rows else 16}>" if not short_rows or (Bt <= 64 and N < 2048) else "k_rows",
+               "backward": ("k_bwd_grad<8>" if Bt <= 64 and short_rows and N <= 6144 else "k_bwd_rows" if short_rows or Bt <= 128 else "k_bwd_long") if fused else f"k_spmm<{v},1,{8 if short_rows else 16}>",
                "update": "k_apply + k_spread_vals + k_apply_bias" if fused else "k_update<4>"}
     passes = {"forward": (fwd_ms, fb, L), "backward": (bwd_ms, bb, L if fused else L - 1), "update": (upd_ms, ub, 1)}
     dom = max(passes, key=lambda k: passes[k][0])
