@@ -152,8 +152,8 @@ typedef struct {
  * of up to 8192 neurons and max_batch > 64 have a lane-major copy of W for passes of more than 64 samples: sdnn_forward then takes a launch
  * per layer in which a workgroup holds four samples of the operand in LDS, with the same bits; sdnn_sgd_step and sdnn_set_weights keep the
  * copies current, or the next pass that reads them does.  Their room: 6 bytes per entry where every row is filled up to a multiple of 8
- * and blocks of 64 rows, by length, to their longest one, and 8 bytes per row.  OFF, a positive panel_cols and reorder_rows = 1 never build
- * them. */
+ * and blocks of 64 rows, by length, to their longest one, 8 bytes per row and 6 KB a layer.  OFF, a positive panel_cols and
+ * reorder_rows = 1 never build them. */
 #define SDNN_LDS_AUTO 0
 #define SDNN_LDS_ON 1
 #define SDNN_LDS_OFF (-1)

@@ -1623,7 +1623,7 @@ __global__ void __launch_bounds__(256) k_train_fill(const LayerDev *__restrict__
 struct FwdLong {
     const int32_t *cs;  // [blocks + 1]: first half of a block
     const int2 *row;    // [64 blocks]: {row, entries}, row -1 past the last
-    const uint4 *lm;    // halves of LDS_HALF_BYTES
+    const uint4 *lm;    // halves of LDS_HALF_BYTES, and two more: a wavefront requests two past its last
     const float *bias;
     const float *in;    // [n_in][ld]
     float *out;         // [n_out][ld]
@@ -3087,6 +3087,7 @@ struct sdnn_net {
     bool train_replaced = false;  // a layer's values were replaced since the last pass that reads the copies
     bool train_kept = false;      // a captured graph reads the copies: they always follow
     bool long_lm = false, long_attr_set = false; // copies of W for k_fwd_long
+    std::vector<uint32_t> long_bytes;            // their sizes
     bool long_stale = false, long_kept = false;  // as train_stale and train_kept
     bool pan_attr_set = false;
     struct Pan {                     // a layer's copy of W for k_fwd_pan
@@ -3517,7 +3518,7 @@ static void plan_long(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
         Plan::PerLayer &q = pl.pl[l];
         q.b1_blocks[0] = (layers[l].n_out + 63) / 64;
         q.b1_chunks[0] = lm_chunks(layers[l], LDS_CHUNK / 2);
-        if (q.b1_chunks[0] * LDS_HALF_BYTES >= ((size_t)1 << 32) - 65536) { // the kernel addresses a copy with 32-bit offsets
+        if ((q.b1_chunks[0] + 2) * LDS_HALF_BYTES >= ((size_t)1 << 32) - 65536) { // the kernel addresses a copy with 32-bit offsets
             for (int32_t k = 0; k <= l; ++k) pl.pl[k].b1_blocks[0] = 0;
             return;
         }
@@ -3670,7 +3671,7 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
         if (pl.long_lm) {
             PLAN_KIND(b1_cs[0], 4 * ((size_t)q.b1_blocks[0] + 1))
             PLAN_KIND(b1_row[0], 8 * 64 * (size_t)q.b1_blocks[0])
-            PLAN_KIND(b1_lm[0], LDS_HALF_BYTES * q.b1_chunks[0])
+            PLAN_KIND(b1_lm[0], LDS_HALF_BYTES * (q.b1_chunks[0] + 2)) // a wavefront requests two halves past its last
         }
         if (b1) {
             PLAN_KIND(b1_cs[0], 4 * ((size_t)q.b1_blocks[0] + 1))
@@ -4190,6 +4191,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 if (rc_fill) return fail_free(rc_fill);
             }
         if (net->long_lm) {
+            for (const Plan::PerLayer &q : pl.pl) net->long_bytes.push_back((uint32_t)(LDS_HALF_BYTES * (q.b1_chunks[0] + 2)));
             const int rc_fill = launch_long_fill(net, 0, n_layers, true, stream);
             if (rc_fill) return fail_free(rc_fill);
         }
@@ -4805,7 +4807,7 @@ static int forward_long(sdnn_net *net, int B, int Bp, int ld, hipStream_t stream
         const LayerDev &d = net->layers[l];
         FwdLong a;
         a.cs = d.b1_cs[0]; a.row = d.b1_row[0]; a.lm = (const uint4 *)d.b1_lm[0]; a.bias = d.bias; a.in = d.X_prev; a.out = d.X;
-        a.lm_bytes = 0xffffffffu; // every half that the table names is there
+        a.lm_bytes = net->long_bytes[(size_t)l];
         a.blocks = d.b1_blocks[0]; a.n_in = d.n_in; a.ld = ld; a.B = B; a.cap = net->cfg.act_cap;
         a.groups = Bp / 4;
         const int per = (a.groups + 7) / 8;

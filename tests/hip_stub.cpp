@@ -40,13 +40,16 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t 
     return hipSuccess;
 }
 static char arg[92]; // the start of the first argument of the last launch of an LDS forward
+static char long_arg[80]; // the same for k_fwd_long: the whole argument
 const char *stub_arg() { return arg; }
+const char *stub_long_arg() { return long_arg; }
 hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **args, size_t lds, hipStream_t)
 {
     // what the runtime refuses: 2^32 work items in a dimension, more LDS than a workgroup can have
     if ((unsigned long long)g.x * b.x >= 1ull << 32 || g.y > 65535 || g.z > 65535 || g.x == 0 || g.y == 0 || g.z == 0 || lds > 160 * 1024)
         return hipErrorInvalidConfiguration;
     if (names()[fn].compare(0, 9, "k_fwd_lds") == 0) memcpy(arg, args[0], sizeof arg);
+    if (names()[fn].compare(0, 11, "k_fwd_long<") == 0) memcpy(long_arg, args[0], sizeof long_arg);
     char line[512];
     snprintf(line, sizeof line, "%s %u %u %u\n", names()[fn].c_str(), g.x, g.y, g.z);
     text += line;

@@ -18,6 +18,7 @@ lib = sdnn.lib()
 stub = C.CDLL(None)                               # the global scope: preloaded
 stub.stub_log.restype = C.c_char_p
 stub.stub_arg.restype = C.POINTER(C.c_int32)
+stub.stub_long_arg.restype = C.POINTER(C.c_uint64)
 ADDR = 1 << 40                                     # device addresses: never followed on the host
 
 def layer(n_out, n_in, lengths, bias=None):

@@ -413,3 +413,19 @@ def test_order_of_the_loads_with_one_sample():
                 assert order([links] * n, activation) == want, (n, links, activation)
         assert [order(uneven(n)) for n in (1000, 1180, 1249, 2000, 6000, 8192)] == [True, True, False, False, True, True]
     """)
+
+
+def test_long_forward_requests_nothing_past_its_copy():
+    """A wavefront requests two halves of eight slots past the last one of its block: also those of the last layer, whose copy ends the
+    workspace, have room in it."""
+    routes.run("""
+        for widths, lengths in [((1024, 1024, 1024), (256,)), ((8192, 300), (8192, 700, 3)), ((1500, 1089, 1281), (0, 1, 250, 512, 300)), ((8192, 8192), (2048, 64, 20, 8))]:
+            net = Net([layer(o, i, np.minimum(np.resize(lengths, o), i)) for i, o in zip(widths, widths[1:])], 100, training=True)
+            rc, log = net("sdnn_forward", X0, 100, XL, None)
+            assert rc == 0 and sum(l.startswith("k_fwd_long<") for l in log) == len(widths) - 1, log
+            rp = net.keep[-1][2]
+            deg = np.sort(np.diff(rp))[::-1]
+            halves = int(((deg[::64] + 7) // 8).sum())
+            lm, sizes = stub.stub_long_arg()[2], stub.stub_long_arg()[6]
+            assert 3072 * (halves + 2) <= sizes & 0xffffffff and lm + (sizes & 0xffffffff) <= ADDR + net.bytes, (widths, lm - ADDR, net.bytes)
+    """)
