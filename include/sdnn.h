@@ -149,7 +149,8 @@ typedef struct {
  * samples; it is reserved from the lengths of the rows alone, also where the columns then make a launch per layer the faster way).
  * OFF, a positive panel_cols and reorder_rows = 1 never build them.
  * Other training nets with 128 entries and more per row in the mean of every layer, 150000 and more per layer in the mean of all, operands
- * of up to 8192 neurons and max_batch > 64 have a lane-major copy of W for passes of more than 64 samples: sdnn_forward then takes a launch
+ * of up to 8192 neurons and max_batch > 64 have a lane-major copy of W for passes of more than 64 samples (from 1025 on, four for each
+ * compute unit, not with every number of them and every shape): sdnn_forward then takes a launch
  * per layer in which a workgroup holds four samples of the operand in LDS, with the same bits; sdnn_sgd_step and sdnn_set_weights keep the
  * copies current, or the next pass that reads them does.  Their room: 6 bytes per entry where every row is filled up to a multiple of 8
  * and blocks of 64 rows, by length, to their longest one, 8 bytes per row and 6 KB a layer.  OFF, a positive panel_cols and

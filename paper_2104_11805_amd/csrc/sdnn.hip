@@ -3088,6 +3088,7 @@ struct sdnn_net {
     bool train_kept = false;      // a captured graph reads the copies: they always follow
     bool long_lm = false, long_attr_set = false; // copies of W for k_fwd_long
     std::vector<uint32_t> long_bytes;            // their sizes
+    bool long_even = true;                       // every layer has a block for each wavefront, none with more than an eighth of its halves
     bool long_stale = false, long_kept = false;  // as train_stale and train_kept
     bool pan_attr_set = false;
     struct Pan {                     // a layer's copy of W for k_fwd_pan
@@ -3851,7 +3852,18 @@ static int launch_long_fill(sdnn_net *net, int l0, int n, bool cols, hipStream_t
 // (step of 6 layers, a tenth of the columns with a heavy tail, us without / with, 64, 66, 128 and 256 samples: 1301 neurons 218 / 227, 268 /
 // 255, 268 / 255, 279 / 262; 3001 neurons 487 / 534, 600 / 569, 588 / 562, 667 / 611; 8192 neurons 1803 / 1948, 2639 / 2236, 2644 / 2299,
 // 3602 / 3090).
-static bool long_forward(const sdnn_net *net, int B) { return net->long_lm && B >= LONG_MIN_BATCH; }
+// More groups of four samples than compute units take a second round and more: not where the last one leaves more than a quarter of
+// all places empty, nor where a workgroup waits for the deepest block of a layer, which k_spmm's wavefronts of all samples do at the
+// same time (forward pass, us, k_spmm / this; 6 layers of 1024 neurons of 256 entries, 1024 samples 295 / 189, 1028 276 / 296, 1536 342 /
+// 304, 2048 427 / 327; 3 of 8192 neurons of 820, 1536 samples 3613 / 2518, 2048 4253 / 2820; 64 rows of 2400 entries, 1028 samples 156 / 194,
+// 2052 152 / 295; 2 layers of 8192 neurons, 64 rows of all of them, 130 entries else, 2048 samples 1444 / 1505; 6 of 513 neurons of 300, 2304
+// samples 305 / 335).
+static bool long_forward(const sdnn_net *net, int B)
+{
+    if (!net->long_lm || B < LONG_MIN_BATCH) return false;
+    const int groups = padded_batch(B) / 4, n_cu = std::max(net->n_cu, 1), rounds = ((groups + 7) / 8 * 8 + n_cu - 1) / n_cu;
+    return rounds == 1 || (net->long_even && 4 * (int64_t)groups >= 3 * (int64_t)rounds * n_cu);
+}
 
 extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdnn_config *cfg,
                            void *d_workspace, size_t workspace_bytes, void *stream_,
@@ -4191,7 +4203,10 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                 if (rc_fill) return fail_free(rc_fill);
             }
         if (net->long_lm) {
-            for (const Plan::PerLayer &q : pl.pl) net->long_bytes.push_back((uint32_t)(LDS_HALF_BYTES * (q.b1_chunks[0] + 2)));
+            for (const Plan::PerLayer &q : pl.pl) {
+                net->long_bytes.push_back((uint32_t)(LDS_HALF_BYTES * (q.b1_chunks[0] + 2)));
+                net->long_even &= q.b1_blocks[0] >= LDS_WAVES && 8 * (size_t)((net->max_len[0][&q - pl.pl.data()] + 7) / 8) <= q.b1_chunks[0];
+            }
             const int rc_fill = launch_long_fill(net, 0, n_layers, true, stream);
             if (rc_fill) return fail_free(rc_fill);
         }

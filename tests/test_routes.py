@@ -429,3 +429,26 @@ def test_long_forward_requests_nothing_past_its_copy():
             lm, sizes = stub.stub_long_arg()[2], stub.stub_long_arg()[6]
             assert 3072 * (halves + 2) <= sizes & 0xffffffff and lm + (sizes & 0xffffffff) <= ADDR + net.bytes, (widths, lm - ADDR, net.bytes)
     """)
+
+
+def test_long_forward_by_the_batch():
+    """From 65 samples on; more groups of four samples than compute units only where the rounds are three quarters full and every layer
+    has blocks for all wavefronts, none much deeper than the others."""
+    routes.run("""
+        def batches(net):
+            out = []
+            for B in (1, 64, 65, 255, 1024, 1025, 1532, 1533, 2048, 2049, 2300, 2301, 3072, 3073):
+                rc, log = net("sdnn_forward", X0, B, XL, None)
+                n = sum(l.startswith("k_fwd_long<") for l in log)
+                assert rc == 0 and n in (0, len(net.keep)) and all(not l.startswith("k_fwd_long<") or int(l.split()[1]) * 4 >= B for l in log), (B, log)
+                out += [B] * (n > 0)
+            lib.sdnn_destroy(net.h)
+            return out
+        few, many = [65, 255, 1024], [1533, 2048, 2301, 3072, 3073]
+        for widths, lengths, want in [((1024, 1024), (256,), few + many), ((1000, 961), (256,), few + many), ((1000, 960), (256,), few), ((8192, 64), (2400,), few),
+                                      ((2048, 2048), (632,) + (140,) * 63, few + many), ((2048, 2048), (633,) + (140,) * 63, few)]:
+            got = batches(Net([layer(o, i, lengths) for i, o in zip(widths, widths[1:])], 3073, training=True))
+            assert got == want, (widths, got)
+        stub.stub_cus(128)
+        assert batches(Net([layer(1024, 1024, (256,))], 3073, training=True)) == [65, 255, 1024, 1532, 1533, 2048, 2049, 2300, 2301, 3072, 3073]
+    """)
