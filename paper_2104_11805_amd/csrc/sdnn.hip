@@ -4933,7 +4933,8 @@ static int forward_impl(sdnn_net *net, const float *d_X0, int32_t B, float *d_XL
         const int rc = launch_train_lds(net, 0, B, Bp, ld, stream);
         if (rc) return rc;
     }
-    const bool by_four = training && !single && (ld & 3) == 0 && long_forward(net, B);
+    // (operands of 4 GiB, of LONG_POS neurons at most here, are launch_spmm's to refuse)
+    const bool by_four = training && !single && (ld & 3) == 0 && 4 * (int64_t)LONG_POS * ld < ((int64_t)1 << 32) && long_forward(net, B);
     if (by_four) {
         const int rc = forward_long(net, B, Bp, ld, stream);
         if (rc) return rc;

@@ -452,3 +452,14 @@ def test_long_forward_by_the_batch():
         stub.stub_cus(128)
         assert batches(Net([layer(1024, 1024, (256,))], 3073, training=True)) == [65, 255, 1024, 1532, 1533, 2048, 2049, 2300, 2301, 3072, 3073]
     """)
+
+
+def test_long_forward_refuses_an_operand_of_4_gib():
+    """As the kernel that it stands in for does: 8192 neurons, 131072 samples."""
+    routes.run("""
+        for n, B, want in [(8192, 131068, 0), (8192, 131072, sdnn.SDNN_EINVAL), (8191, 131072, 0)]:
+            net = Net([layer(n, n, (128,))], B, training=True)
+            rc, log = net("sdnn_forward", X0, B, None, None)
+            assert rc == want and (rc == 0 or "4 GiB" in sdnn.last_error(net.h)) and (rc == 0) == any(l.startswith(("k_fwd_long", "k_spmm")) for l in log), (n, B, rc, log)
+            lib.sdnn_destroy(net.h)
+    """)
