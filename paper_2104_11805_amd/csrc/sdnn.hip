@@ -5133,6 +5133,20 @@ static bool two_windows(const sdnn_net *net)
 // Whether k_bwd_rows can take this layer's Delta: rows of whole 16-byte pieces, within its offsets.
 static bool wide_rows(const sdnn_net *net, const LayerDev &d) { return (net->ld & 3) == 0 && rows_addressable(d.n_out, net->ld); }
 
+// Whether a sweep of more than 128 samples, with a wavefront per row either way, goes by scalar loads and matrix products (k_bwd_long).  Its
+// start takes a row longer, and it has fewer gathers in flight, which tells where the operand is larger than the L2s: not below 64 entries
+// per row, of operands over 10.7 MB only where the rows are the longer the larger it is, and not over 26 MB (with rows of 1024 bytes 16 MB).
+// Sweep of all layers, us, k_bwd_rows / k_bwd_long, layers of n neurons of k entries, s samples: n = 1024, k = 64, s = 256 132 / 115; 8192, 64, 256
+// 130 / 126; 16000 x 12000, 90, 256 (12.3 MB) 99 / 101; 14000, 64, 224 (12.5 MB) 225 / 231; 14000, 100, 256 (14.3 MB) 267 / 285; 16384, 64, 200 (14.7
+// MB) 291 / 298; 16384, 160, 224 458 / 429; 20000, 200, 224 (17.9 MB) 721 / 691; 20000, 1200, 256 (20.5 MB) 2453 / 3057; 25000, 820, 224 (22.4 MB)
+// 2156 / 1772; 32768, 200, 224 (29.4 MB) 1037 / 1051; 8192, 820, 256 1014 / 818.  (Steps with 32 entries, 4096 neurons 2954 / 2983, 8001 neurons
+// 2255 / 2239.)
+static bool bwd_long(const LayerDev &d, uint32_t in_bytes, int B)
+{
+    const double mb = 1e-6 * in_bytes;
+    return mb <= (B > 224 ? 16.0 : 26.0) && (double)d.nnz >= std::max(64.0, 20.0 * mb - 150.0) * d.n_in;
+}
+
 // Fused back-propagation + entry gradient of one layer.  store_out = 0 for the first layer (gradient only: there is no
 // Delta_0, out may be NULL).
 static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStream_t stream, int store_out)
@@ -5169,10 +5183,6 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
         HIP_TRY(net, hipGetLastError());
         return SDNN_OK;
     }
-    // More than 128 samples: a wavefront per row either way.  From 64 entries per row on by scalar loads and matrix products, whose
-    // start takes a row longer (step with 256 samples, k_bwd_rows / k_bwd_long: 4096 neurons of 32 entries, 120 layers 2954 / 2983 us, 8001
-    // of 32, 48 layers 2255 / 2239; 6 layers of 1024 neurons of 102 entries 250 / 241, 1300 of 130 291 / 280, 3001 of 300 730 / 678, 8192
-    // of 820 4030 / 3680).
     // two windows: as two tiles (and two partial gradients) where the operand is larger than L2, else in one
     const bool two = net->two_windows;
     int G = lanes_per_row(net->grad_parts == 2 ? 64 : B);
@@ -5182,7 +5192,7 @@ static int launch_bwd_grad(sdnn_net *net, const LayerDev &d, float *out, hipStre
     a.n_rg = (uint32_t)((a.n_rows + rows_per_block - 1) / rows_per_block);
     const void *fn = G == 4 ? (const void *)k_bwd_rows<4, false> : G == 8 ? (const void *)k_bwd_rows<8, false>
                      : G == 16 ? (const void *)k_bwd_rows<16, false>
-                     : G == 64 ? ((int64_t)d.nnz >= 64 * (int64_t)a.n_rows ? (const void *)k_bwd_long : (const void *)k_bwd_rows<64, false>)
+                     : G == 64 ? (bwd_long(d, a.in_bytes, B) ? (const void *)k_bwd_long : (const void *)k_bwd_rows<64, false>)
                      : two ? (const void *)k_bwd_rows<32, true> : (const void *)k_bwd_rows<32, false>;
     HIP_TRY(net, hipLaunchKernel(fn, dim3(a.n_tiles * a.n_rg), dim3(BLOCK_THREADS), args, 0, stream));
     HIP_TRY(net, hipGetLastError());

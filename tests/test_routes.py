@@ -463,3 +463,22 @@ def test_long_forward_refuses_an_operand_of_4_gib():
             assert rc == want and (rc == 0 or "4 GiB" in sdnn.last_error(net.h)) and (rc == 0) == any(l.startswith(("k_fwd_long", "k_spmm")) for l in log), (n, B, rc, log)
             lib.sdnn_destroy(net.h)
     """)
+
+
+def test_sweep_of_long_rows():
+    """129 to 256 samples and 64 entries per row of W^T and more; more than that on operands over 10.7 MB, and not over 26 MB (225 samples and
+    more: 16 MB)."""
+    routes.run("""
+        def kernel(n, deg, B):
+            net = Net([layer(n, n, deg)], 256, training=True, fuse_gradient=1)
+            assert net("sdnn_forward", X0, B, XL, None)[0] == 0
+            rc, log = net("sdnn_backward", DL, None)
+            lib.sdnn_destroy(net.h)
+            assert rc == 0 and (not log[-1].startswith("k_bwd_long") or log[-1] == f"k_bwd_long {-(-n // 4)} 1 1"), log
+            return log[-1].split()[0].split("<")[0]
+        for n, k, B, want in [(1000, 64, 128, 0), (1000, 64, 129, 1), (1000, 64, 256, 1), (1000, 63, 256, 0), (10449, 64, 256, 1), (10450, 64, 256, 0), (12000, 95, 256, 0), (12000, 96, 256, 1),
+                              (12000, 64, 192, 1), (15625, 170, 256, 1), (15626, 170, 256, 0), (15626, 170, 225, 0), (15626, 170, 224, 1), (29017, 369, 224, 0), (29017, 370, 224, 1),
+                              (29018, 400, 224, 0)]:
+            assert kernel(n, (k,), B) == ("k_bwd_long" if want else "k_bwd_rows"), (n, k, B)
+        assert [kernel(1000, (64,) * 999 + (c,), 200) for c in (64, 63)] == ["k_bwd_long", "k_bwd_rows"]
+    """)
