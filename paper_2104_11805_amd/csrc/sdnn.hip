@@ -1773,7 +1773,7 @@ __global__ void __launch_bounds__(256) k_long_fill(const LayerDev *__restrict__ 
 // ---------------------------------------------------------------------------
 static_assert(PAN_WAVES == LDS_WAVES, "the same halves, the same workgroups");
 struct PanForward {
-    const uint4 *stream;   // halves of LDS_HALF_BYTES
+    const uint4 *stream;   // halves of LDS_HALF_BYTES, and two more
     const int32_t *seg;    // [range][wavefront][panels + 1]: where the panels' slots start, in halves
     const uint32_t *ends;  // a byte per half
     const float *bias;     // by position
@@ -1830,7 +1830,8 @@ __device__ __forceinline__ void get_sums(int at, double &v0, double &v1)
     v1 = __hiloint2double(w[3], w[2]);
 }
 
-template <int ACT>
+// STAY: a workgroup takes one piece (a range of a pair) after the other; see forward_pan.
+template <int ACT, bool STAY>
 __global__ void __launch_bounds__(64 * LDS_WAVES) __attribute__((amdgpu_num_vgpr(32))) k_fwd_pan(const PanForward a)
 {
     extern __shared__ __attribute__((aligned(16))) float lds_act[];
@@ -1839,9 +1840,6 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) __attribute__((amdgpu_num_vgpr
     typedef __attribute__((address_space(3))) char *lds_bytes;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // A workgroup takes one piece (a range of a pair) after the other: the first panel of the next one comes while the results of this
-    // one are stored, and its first halves of W before that (a workgroup per piece / staying, us per pass: 65536 neurons, 1024 samples, 24
-    // layers 11300 / 11165; 50000, 400 samples 4195 / 4081; 40001, 650 samples 3958 / 3911; 80001, 300 samples, 12 layers 2311 / 2220).
     // The ranges of a pair run side by side on one XCD: they read the same panels (one range of all pairs after the other, so
     // that all the workgroups of an XCD share one stream of W: 602 against 511 us at 65536 neurons, 1024 samples)
     const int xcd = (int)(blockIdx.x & 7u), stride = (int)(gridDim.x >> 3);
@@ -1857,7 +1855,7 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) __attribute__((amdgpu_num_vgpr
     const __amdgpu_buffer_rsrc_t rst = make_rsrc((const float *)a.stream, a.stream_bytes);
     const __amdgpu_buffer_rsrc_t ren = make_rsrc((const float *)a.ends, (size_t)a.stream_bytes / LDS_HALF_BYTES);
     int first = seg[0], n = seg[a.n_panels] - first; // this wavefront's halves
-    unsigned at = (unsigned)first * LDS_HALF_BYTES, at_end = 0xffffffffu, at_next = 0; // at the stream's end the next one's halves follow
+    unsigned at = (unsigned)first * LDS_HALF_BYTES, at_end = 0xffffffffu, at_next = 0; // STAY: at the stream's end the next one's halves follow
     const int lane16 = 16 * lane;
     struct Half { u32x4 c, wa, wb; } ha, hb;
     auto request = [&](Half &h) {
@@ -1865,7 +1863,7 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) __attribute__((amdgpu_num_vgpr
         h.wa = __builtin_amdgcn_raw_buffer_load_b128(rst, lane16 + 1024, (int)at, 0);
         h.wb = __builtin_amdgcn_raw_buffer_load_b128(rst, lane16 + 2048, (int)at, 0);
         at += LDS_HALF_BYTES;
-        at = at == at_end ? at_next : at;
+        if constexpr (STAY) at = at == at_end ? at_next : at;
     };
     clear_sums();
     int block = 0, p = 0, left = 0, half = 0; // block: the current one's words
@@ -1920,16 +1918,17 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) __attribute__((amdgpu_num_vgpr
     request(hb);
     for (;;) {
         const int k_next = k + stride, q_next = k_next % a.n_ranges, g_next = k_next / a.n_ranges * 8 + xcd;
-        const bool more = g_next < a.n_pairs;
-        at_end = (unsigned)(first + n) * LDS_HALF_BYTES;
-        at_next = (unsigned)seg_of(q_next)[0] * LDS_HALF_BYTES;
-        if (at == at_end) at = at_next; // a stream of two halves
+        const bool more = STAY && g_next < a.n_pairs;
         left = seg[1] - first;
-        // (a stream starts on a multiple of four halves and has an even number of them)
-        four_ends = __builtin_amdgcn_raw_buffer_load_b32(ren, 4 * lane, first, 0);
+        if constexpr (STAY) {
+            at_end = (unsigned)(first + n) * LDS_HALF_BYTES;
+            at_next = (unsigned)seg_of(q_next)[0] * LDS_HALF_BYTES;
+            if (at == at_end) at = at_next; // a stream of two halves
+            four_ends = __builtin_amdgcn_raw_buffer_load_b32(ren, 4 * lane, first, 0);
+        }
         panel_there();
-        for (half = 0; half < n; half += 2) {
-            if (half > 0 && (half & 255) == 0) {
+        for (half = 0; half < n; half += 2) { // a stream starts on a multiple of four halves and has an even number of them
+            if ((!STAY || half > 0) && (half & 255) == 0) {
                 four_ends = __builtin_amdgcn_raw_buffer_load_b32(ren, 4 * lane, first + half, 0);
                 __builtin_amdgcn_s_waitcnt(0xf70);
             }
@@ -1948,7 +1947,7 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) __attribute__((amdgpu_num_vgpr
         }
         const int at0 = q * a.range + 64 * wave + lane;
         pair *out = (pair *)(a.out + (size_t)g * a.out_pos + (size_t)at0);
-        constexpr int K = ACT == ACT_SIGMOID ? 1 : 16; // biases at once (exp() takes their registers)
+        constexpr int K = ACT == ACT_SIGMOID ? 4 : 16; // biases at once (exp() takes their registers)
         for (int b0 = 0; b0 < a.nb; b0 += K) {
             float bias[K];
 #pragma unroll
@@ -1964,6 +1963,7 @@ __global__ void __launch_bounds__(64 * LDS_WAVES) __attribute__((amdgpu_num_vgpr
                 out[1024 * (b0 + b)] = v;
             }
         }
+        if constexpr (!STAY) return;
         if (!more) return;
         clear_sums();
         k = k_next; q = q_next; g = g_next;
@@ -3547,7 +3547,7 @@ static bool pan_wanted(const sdnn_layer *layers, int32_t n_layers, const sdnn_co
     for (int32_t l = 0; l < n_layers; ++l) {
         PanLayer &g = pl[l].pan;
         sdnn_pan_geometry(layers[l], l > 0 ? &pl[l - 1].pan : nullptr, g);
-        if (g.halves * LDS_HALF_BYTES >= ((size_t)1 << 32)) return false; // the kernel addresses a layer's copy with 32-bit offsets
+        if ((g.halves + 2) * LDS_HALF_BYTES >= ((size_t)1 << 32)) return false; // the kernel addresses a layer's copy with 32-bit offsets
     }
     return true;
 }
@@ -3633,8 +3633,8 @@ static void make_plan(const sdnn_layer *layers, int32_t n_layers, const sdnn_con
         pl.lm_pos = take(4 * pl.lm_n_rows);
     }
     if (pl.pan) {
-        PLAN_KIND(pan_stream, LDS_HALF_BYTES * q.pan.halves)
-        PLAN_KIND(pan_ends, q.pan.halves)
+        PLAN_KIND(pan_stream, LDS_HALF_BYTES * (q.pan.halves + 2)) // a wavefront requests two halves past its last
+        PLAN_KIND(pan_ends, q.pan.halves + 2)
         PLAN_KIND(pan_seg, 4 * (size_t)q.pan.n_ranges * LDS_WAVES * (size_t)(q.pan.n_panels + 1))
         PLAN_KIND(pan_slot, 4 * (size_t)q.pan.n_ranges * LDS_WAVES * (size_t)q.pan.n_panels * (size_t)(q.pan.nb + 1))
         PLAN_KIND(pan_rows, 4 * (size_t)q.pan.out_pos)
@@ -4773,9 +4773,12 @@ static int sub_block_width(const sdnn_net *net, int B)
 // The pass in panels: samples turned to pairs, a launch per layer, and back.
 static int forward_pan(sdnn_net *net, const float *d_X0, int B, float *d_XL, hipStream_t stream, float *ping, float *pong)
 {
-    const void *fn = net->cfg.activation == ACT_SIGMOID ? (const void *)k_fwd_pan<ACT_SIGMOID> : (const void *)k_fwd_pan<ACT_RELU_CAP>;
+    const bool sig = net->cfg.activation == ACT_SIGMOID;
+    const void *const one = sig ? (const void *)k_fwd_pan<ACT_SIGMOID, false> : (const void *)k_fwd_pan<ACT_RELU_CAP, false>;
+    const void *const stay = (const void *)k_fwd_pan<ACT_RELU_CAP, true>;
     if (!net->pan_attr_set) { // more than the default 64 KiB of dynamic LDS per workgroup
-        HIP_TRY(net, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (PAN_POS + 1)));
+        HIP_TRY(net, hipFuncSetAttribute(one, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (PAN_POS + 1)));
+        HIP_TRY(net, hipFuncSetAttribute(stay, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * (PAN_POS + 1)));
         net->pan_attr_set = true;
     }
     const int n_pairs = (B + 1) / 2, tiles = (B + 63) / 64;
@@ -4786,13 +4789,19 @@ static int forward_pan(sdnn_net *net, const float *d_X0, int B, float *d_XL, hip
     for (const sdnn_net::Pan &f : net->pan) {
         PanForward a;
         a.stream = f.stream; a.seg = f.seg; a.ends = f.ends; a.bias = f.bias; a.in = (const float2 *)ping; a.out = (float2 *)pong;
-        a.stream_bytes = (uint32_t)(f.g.halves * LDS_HALF_BYTES);
+        a.stream_bytes = (uint32_t)((f.g.halves + 2) * LDS_HALF_BYTES);
         a.in_pos = f.g.in_pos; a.out_pos = f.g.out_pos; a.panel = f.g.panel; a.n_panels = f.g.n_panels;
         a.range = f.g.range; a.n_ranges = f.g.n_ranges; a.nb = f.g.nb; a.n_pairs = n_pairs; a.cap = net->cfg.act_cap;
         void *args[] = {(void *)&a};
-        const int pieces = (n_pairs + 7) / 8 * f.g.n_ranges; // of an XCD
-        HIP_TRY(net, hipLaunchKernel(fn, dim3(8u * (unsigned)std::min(pieces, std::max(net->n_cu / 8, 1))), dim3(64 * LDS_WAVES), args,
-                                     8 * ((size_t)f.g.panel + 1), stream));
+        // From eight pieces (a range of a pair) for five places on, a workgroup takes one after the other: the first panel of the next one comes
+        // while the results of this one are stored, and its first halves of W before that.  With fewer, one look more at every half costs
+        // what that gives, and with the sigmoid, whose exp() needs the registers (us per pass, a workgroup per piece / staying: 65536
+        // neurons, 200 samples (13 pieces for 8 places), 8 layers 884 / 860; 40001, 1024 samples 2287 / 2215; 80001, 300 samples 1368 / 1332; 45000,
+        // 257 samples (3 for 2), 6 layers 530 / 557; 32768, 200 samples (a piece each) 350 / 357, 300 (19 for 16) 669 / 677, 1024 1570 / 1584).
+        const int pieces = (n_pairs + 7) / 8 * f.g.n_ranges, places = std::max(net->n_cu / 8, 1); // of an XCD
+        const bool stays = !sig && 5 * (int64_t)pieces >= 8 * (int64_t)places;
+        HIP_TRY(net, hipLaunchKernel(stays ? stay : one, dim3(8u * (unsigned)(stays ? places : pieces)), dim3(64 * LDS_WAVES), args, 8 * ((size_t)f.g.panel + 1),
+                                     stream));
         std::swap(ping, pong);
     }
     hipLaunchKernelGGL(k_pan_turn<false>, dim3((unsigned)((gl.out_pos + 63) / 64), (unsigned)tiles), dim3(256), 0, stream,

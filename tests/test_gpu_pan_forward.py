@@ -37,8 +37,9 @@ def test_pan_forward_after_the_weights_were_replaced():
     net.close()
 
 
-def test_pan_forward_sigmoid():
-    widths, b, lengths = pan_nets.NETS[3]
+@pytest.mark.parametrize("b", [129, 341])
+def test_pan_forward_sigmoid(b):
+    widths, _, lengths = pan_nets.NETS[3]
     layers = pan_nets.layers(widths, lengths)
     x = wl.normal_inputs(7300, widths[0], b)
     nets = [sdnn.Net(layers, np.inf, b, training=False, activation="sigmoid", lds_forward=o) for o in (sdnn.SDNN_LDS_AUTO, sdnn.SDNN_LDS_OFF)]
@@ -61,10 +62,11 @@ def test_pan_forward_over_its_input(shift):
     net.close()
 
 
-@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
-def test_infinities_stay_with_the_rows_that_gather_them(bad):
-    """Slots past a row's entries, and rows of other panels, take nothing from a neuron that is not finite."""
-    widths, b, lengths = pan_nets.NETS[3]
+@pytest.mark.parametrize("bad,b", [(np.inf, 129), (-np.inf, 129), (np.nan, 129), (np.inf, 341), (np.nan, 341)])
+def test_infinities_stay_with_the_rows_that_gather_them(bad, b):
+    """Slots past a row's entries, and rows of other panels, take nothing from a neuron that is not finite, nor does the next piece of a
+    workgroup (341 samples: 171 pairs, of which three XCDs have one more than the others) from one whose sums are not."""
+    widths, _, lengths = pan_nets.NETS[3]
     layers = pan_nets.layers(widths, lengths)
     x = wl.normal_inputs(7500, widths[0], b)
     hit = x.copy()

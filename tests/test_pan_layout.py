@@ -43,12 +43,12 @@ def test_compiler_stays_out_of_the_registers_of_the_sums(tmp_path):
     flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-pthread")]
     subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", "-o", str(asm), os.path.join(build.CSRC, "sdnn.hip")], check=True)
     text = asm.read_text()
-    bodies = re.findall(r"^_Z9k_fwd_panILi[01]EEv10PanForward:.*?s_endpgm", text, re.S | re.M)
-    assert len(bodies) == 2
+    bodies = re.findall(r"^_Z9k_fwd_panILi[01]ELb[01]EEv10PanForward:.*?s_endpgm", text, re.S | re.M)
+    assert len(bodies) == 3
     for body in bodies:
         outside = re.sub(r";;#ASMSTART.*?;;#ASMEND", "", body, flags=re.S)
         named = [int(n) for m in re.findall(r"\bv(\d+)\b|\bv\[(\d+):(\d+)\]", outside) for n in m if n]
         assert named and max(named) < 64, max(named)
         assert "scratch_" not in outside and "accvgpr" not in outside
         assert "v[64:65]" in body
-    assert re.findall(r"k_fwd_panILi[01]EEv10PanForward\.num_vgpr, (\d+)", text) == ["128", "128"]
+    assert re.findall(r"k_fwd_panILi[01]ELb[01]EEv10PanForward\.num_vgpr, (\d+)", text) == ["128"] * 3

@@ -482,3 +482,25 @@ def test_sweep_of_long_rows():
             assert kernel(n, (k,), B) == ("k_bwd_long" if want else "k_bwd_rows"), (n, k, B)
         assert [kernel(1000, (64,) * 999 + (c,), 200) for c in (64, 63)] == ["k_bwd_long", "k_bwd_rows"]
     """)
+
+
+def test_workgroups_that_stay_in_the_forward_in_panels():
+    """With the clamped ReLU and at least eight pieces for five places of an XCD a workgroup takes one piece after the other; else there is
+    a workgroup for every piece.  The nets of tests/test_gpu_pan_forward.py take both."""
+    routes.run("""
+        from tests import pan_nets
+        def pans(widths, lengths, batches, max_batch=800, **options):
+            net = Net([(y.n_out, y.n_in, y.row_ptr, y.col_idx, y.values, y.bias) for y in pan_nets.layers(widths, lengths)], max_batch, **options)
+            out = []
+            for B in batches:
+                rc, log = net("sdnn_forward", X0, B, XL, None)
+                assert rc == 0
+                out.append([l.split("<")[1].replace(">", "").replace(",", "").split()[:3] for l in log if l.startswith("k_fwd_pan<")])
+            return out
+        n = (40000,) * 4                               # three ranges; 256 samples: 16 pairs for an XCD
+        got = pans(n, (32,), (129, 256, 272, 273, 341))
+        assert got == [[["0", "false", "216"]] * 3, [["0", "false", "384"]] * 3, [["0", "false", "408"]] * 3, [["0", "true", "256"]] * 3, [["0", "true", "256"]] * 3], got
+        assert pans(n, (32,), (341,), activation=1) == [[["1", "false", "528"]] * 3]
+        widths, b, lengths = pan_nets.NETS[0]
+        assert [p[1] for p in pans(widths, lengths, (b,), b)[0]] == ["true"] * 3
+    """)
