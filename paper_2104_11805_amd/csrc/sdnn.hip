@@ -3061,6 +3061,7 @@ struct sdnn_net {
     bool b1 = false, b1_wide = false; // made for one sample per step: lane-major copies of W and W^T; with 4-byte columns
     int occ_panel[2][4] = {};     // the same for k_spmm_panel<R,MODE>, R = 1, 2, 4, 8
     std::vector<int32_t> max_len[2]; // per layer: longest row of W (0) and of W^T (1)
+    std::vector<char> grad_spread;   // per layer: sdnn_weight_grad in two passes, where one partial gradient holds it
     std::vector<char> clustered[2];  // per layer: reorder_rows found clusters in W (0), in W^T (1)
     uint4 *lm = nullptr;             // lane-major copy of W for k_fwd_lds, NULL: there is none
     int32_t *lm_cs = nullptr, *lm_row = nullptr;
@@ -3835,6 +3836,19 @@ static int launch_b1_fill(sdnn_net *net, int l, int with_cols, hipStream_t strea
     return SDNN_OK;
 }
 
+// sdnn_weight_grad brings the gradient into CSR order in the two passes that the stepped values go through, or by a scatter of single values,
+// which is the faster way where its lines stay on chip: in small layers, and in layers of short rows whose columns lie close together (few
+// runs per span).  With the bias, us, scatter / two passes: random columns, 32 entries per row, 1.05e6 entries 20 / 23, 1.44e6 23.2 / 24.4, 1.60e6
+// 26.5 / 24.9, 2.10e6 31.9 / 26.4; 64 per row 1.54e6 22.2 / 24.4, 1.79e6 27.0 / 24.6; 820 per row, 6.72e6 77 / 34; columns on a diagonal, 32 per row
+// (2 runs), 2.10e6 16 / 22, 8.39e6 44.5 / 46.3; 64 per row, 4.19e6 32 / 26; in a window of 4096 columns, 32 per row (9 runs), 2.10e6 25.7 / 24.9, 4.19e6
+// 50 / 31; of 512 columns (2 runs), 2.10e6 22.6 / 24.4.
+#define GRAD_SPREAD_MIN (7 << 18)
+static bool grad_spread_pays(const sdnn_layer &y, size_t runs)
+{
+    const int64_t nnz = y.row_ptr[y.n_out];
+    return nnz >= GRAD_SPREAD_MIN && (runs >= 6 * (size_t)((nnz + TR_SPAN - 1) / TR_SPAN) || nnz >= 64 * (int64_t)y.n_out);
+}
+
 // Brings the copies for k_fwd_long of layers l0 .. l0 + n - 1 up to date with the CSR values (cols: and writes their columns).
 static int launch_long_fill(sdnn_net *net, int l0, int n, bool cols, hipStream_t stream)
 {
@@ -3901,6 +3915,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
         net->pan.resize(pl.pan ? n_layers : 0);
         net->max_len[0].resize(n_layers);
         net->max_len[1].resize(n_layers);
+        net->grad_spread.resize(n_layers);
         net->clustered[0].resize(n_layers);
         net->clustered[1].resize(n_layers);
     } catch (...) {
@@ -3929,6 +3944,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
         std::vector<int2> b1_row[2];
         PanLayout pan;
         int32_t max_len = 0, t_max_len = 0;
+        size_t runs = 0; // of entries that k_apply writes one after the other
         bool clustered = false, t_clustered = false; // reorder_rows found rows that share columns
         int rc = SDNN_OK;
     };
@@ -4038,6 +4054,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                         if (in_span[c]++ == 0) touched.push_back((int32_t)c);
                     }
                     std::sort(touched.begin(), touched.end());
+                    h.runs += touched.size();
                     int32_t run = 0; // in_span[c]: from the span's count for chunk c to the rank of its next entry
                     for (int32_t c : touched) { const int32_t n = in_span[c]; in_span[c] = run; run += n; }
                     for (size_t q = s0; q < s1; ++q) {
@@ -4155,6 +4172,7 @@ extern "C" int sdnn_create(const sdnn_layer *layers, int32_t n_layers, const sdn
                            : l == 0       ? (float *)(base + pl.x0)
                                           : net->layers[l - 1].X;
                 net->max_n = std::max(net->max_n, std::max(y.n_out, y.n_in));
+                net->grad_spread[l] = gw && grad_spread_pays(y, h.runs);
                 net->max_len[0][l] = h.max_len;
                 net->max_len[1][l] = h.t_max_len;
                 net->clustered[0][l] = h.clustered;
@@ -5383,10 +5401,6 @@ extern "C" int sdnn_sgd_step(sdnn_net *net, float lr, void *stream_)
     return SDNN_OK;
 }
 
-// From so many entries on the gradient is brought into CSR order in the two passes that the stepped values go through, else by
-// a scatter of single values (with the bias, scatter / two passes: 0.77e6 entries 14.6 / 15.8 us, 1.02e6 16.8 / 17.3, 1.28e6 20.4 / 18.2,
-// 2.1e6 30.1 / 20.5, 6.7e6 83.6 / 36.1).
-#define GRAD_SPREAD_MIN (1 << 20)
 extern "C" int sdnn_weight_grad(sdnn_net *net, int32_t layer, float *d_g, float *d_gb, void *stream_)
 {
     if (!net) return fail(nullptr, SDNN_EINVAL, "net is NULL");
@@ -5399,7 +5413,7 @@ extern "C" int sdnn_weight_grad(sdnn_net *net, int32_t layer, float *d_g, float 
         // the backward sweep has already formed the gradient that sdnn_sgd_step will apply: hand out that one
         const LayerDev &d = net->layers[layer - 1];
         hipStream_t stream = (hipStream_t)stream_;
-        if (d_g && d.nnz >= GRAD_SPREAD_MIN && net->grad_parts == 1) {
+        if (d_g && net->grad_spread[layer - 1] && net->grad_parts == 1) {
             const unsigned gx = (unsigned)((((int64_t)d.nnz + TR_SPAN - 1) / TR_SPAN + 7) & ~(int64_t)7);
             hipLaunchKernelGGL(k_apply<true>, dim3(gx), dim3(TR_THREADS), 0, stream, net->d_layers + (layer - 1), 1, 0.0f);
             hipLaunchKernelGGL(k_spread_vals<true>, dim3((unsigned)(((int64_t)d.nnz + TR_CHUNK - 1) / TR_CHUNK)), dim3(TR_THREADS), 0, stream,

@@ -504,3 +504,25 @@ def test_workgroups_that_stay_in_the_forward_in_panels():
         widths, b, lengths = pan_nets.NETS[0]
         assert [p[1] for p in pans(widths, lengths, (b,), b)[0]] == ["true"] * 3
     """)
+
+
+def test_gradient_in_csr_order():
+    """Large layers in two passes: not where the columns of short rows lie close together, nor with two partial gradients."""
+    routes.run("""
+        def passes(n, k, B, columns, n_in=None):
+            n_in = n_in or n
+            rng = np.random.default_rng(n)
+            step = n_in // k
+            ci = dict(random=lambda: np.arange(k) * step + rng.integers(0, step, (n, k)), diagonal=lambda: np.sort((np.arange(n)[:, None] + np.arange(k)) % n_in, axis=1),
+                      window=lambda: np.sort((np.arange(n)[:, None] + 128 * np.arange(k)) % n_in, axis=1))[columns]()
+            net = Net([(n, n_in, np.arange(0, n * k + 1, k, dtype=np.int32), ci.astype(np.int32).ravel(), np.ones(n * k, np.float32), None)], B, training=True, fuse_gradient=1)
+            assert net("sdnn_forward", X0, B, XL, None)[0] == 0 and net("sdnn_backward", DL, None)[0] == 0
+            rc, log = net("sdnn_weight_grad", 1, X0, None, None)
+            lib.sdnn_destroy(net.h)
+            names = [l.split()[0] for l in log]
+            assert rc == 0 and names in (["k_sum_parts"], ["k_apply<true>", "k_spread_vals<true>"]), log
+            return len(names)
+        for n, k, B, columns, want in [(57343, 32, 64, "random", 1), (57344, 32, 64, "random", 2), (16384, 112, 64, "random", 2), (16384, 112, 128, "random", 1),
+                                       (65536, 32, 64, "diagonal", 1), (65536, 32, 64, "window", 2), (40000, 63, 64, "diagonal", 1), (40000, 64, 64, "diagonal", 2)]:
+            assert passes(n, k, B, columns) == want, (n, k, B, columns)
+    """)
