@@ -526,3 +526,61 @@ def test_gradient_in_csr_order():
                                        (65536, 32, 64, "diagonal", 1), (65536, 32, 64, "window", 2), (40000, 63, 64, "diagonal", 1), (40000, 64, 64, "diagonal", 2)]:
             assert passes(n, k, B, columns) == want, (n, k, B, columns)
     """)
+
+
+def test_long_forward_by_the_net():
+    """Operands of up to 8192 neurons, 128 entries per row in the mean of every layer, 150000 per layer in the mean of all, made for more than
+    64 samples; not for inference or where the caller asks for other layouts.  No copies, no room for them."""
+    routes.run("""
+        def longs(layers, max_batch=65, **options):
+            options = {"training": True, **options}
+            net, off = Net(layers, max_batch, **options), Net(layers, max_batch, **{**options, "lds_forward": -1})
+            rc, log = net("sdnn_forward", X0, max_batch, XL, None)
+            n = sum(l.startswith("k_fwd_long<") for l in log)
+            assert rc == 0 and n in (0, len(layers)) and (net.bytes > off.bytes) == (n > 0), log
+            for h in (net.h, off.h):
+                lib.sdnn_destroy(h)
+            return n > 0
+        one_less = (128,) * 1199 + (127,)
+        for layers, want in [([layer(8192, 8192, (128,))], True), ([layer(8192, 8193, (128,))], False), ([layer(8193, 8192, (128,))], True),
+                             ([layer(1200, 1200, (128,))], True), ([layer(1200, 1200, one_less)], False), ([layer(8192, 1200, (128,) * 8191 + (127,))], False),
+                             ([layer(1171, 1200, (128,))], False), ([layer(1172, 1200, (128,))], True),
+                             ([layer(1200, 1200, (128,)), layer(1144, 1200, (128,))], True), ([layer(1200, 1200, (128,)), layer(1143, 1200, (128,))], False),
+                             ([layer(2000, 2000, (400,)), layer(2000, 2000, (127,))], False), ([layer(2000, 2000, (0, 1, 500)), layer(10, 2000, (128,))], True)]:
+            assert longs(layers) == want, [(l[0], l[1], len(l[3])) for l in layers]
+        net = [layer(2000, 2000, (200,))]
+        assert longs(net, 64) is False and longs(net, 300) and longs(net, fuse_gradient=1) and longs(net, fuse_gradient=-1) and longs(net, lds_forward=1)
+        for options in (dict(training=False, lds_forward=-1), dict(panel_cols=512), dict(reorder_rows=1)):
+            assert not longs(net, **options), options
+    """)
+
+
+def test_copies_for_the_long_forward_follow_when_they_are_read():
+    """After a step whose batch reads them, at once; else before the next pass that does.  In a graph, and once a graph reads
+    them, always.  Replaced values at once, of that layer."""
+    routes.run("""
+        def net():
+            return Net([layer(2000, 2000, (200,))] * 3, 256, training=True)
+        def fills(net, B, capture=()):
+            out = []
+            for k, (name, args) in enumerate([("sdnn_forward", (X0, B, XL, None)), ("sdnn_backward", (DL, None)), ("sdnn_sgd_step", (C.c_float(0.1), None))]):
+                stub.stub_capture(k in capture)
+                rc, log = net(name, *args)
+                assert rc == 0
+                lines = [l for l in log if l.startswith("k_long_fill")]
+                assert lines in ([], ["k_long_fill<false> 32 16 3"]) and (not lines or k == 2 or [l.split("<")[0] for l in log[-4:]] == ["k_long_fill"] + ["k_fwd_long"] * 3 or
+                                                                          log[-1].startswith("memcpy") or log[-1].startswith("k_copy")), log
+                out.append(len(lines))
+            stub.stub_capture(0)
+            return out
+        a = net()
+        assert [fills(a, B) for B in (65, 64, 1, 256, 256, 8, 64, 65)] == [[0, 0, 1], [0, 0, 0], [0, 0, 0], [1, 0, 1], [0, 0, 1], [0, 0, 0], [0, 0, 0], [1, 0, 1]]
+        b = net()                                      # a captured step of few samples: its replays keep the copies current, a later pass need not
+        assert [fills(b, 64, (0, 1, 2)), fills(b, 256)] == [[0, 0, 1], [0, 0, 1]]
+        c = net()                                      # a graph reads copies that are behind
+        assert [fills(c, 64), fills(c, 65, (0, 1)), fills(c, 64), fills(c, 65), fills(c, 64)] == [[0, 0, 0], [1, 0, 1], [0, 0, 1], [1, 0, 1], [0, 0, 1]]
+        rc, log = a("sdnn_set_weights", 2, X0, XL, None)
+        assert rc == 0 and [l for l in log if l.startswith("k_long_fill")] == ["k_long_fill<false> 32 16 1"]
+        rc, log = a("sdnn_set_weights", 2, None, XL, None)
+        assert rc == 0 and not any(l.startswith("k_long_fill") for l in log)
+    """)
