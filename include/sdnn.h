@@ -22,7 +22,9 @@
  * applied by sdnn_sgd_step.  Delta_0 is not formed.
  *
  * Arithmetic: fp32 storage, every sum accumulated in fp64 and rounded once
- * when stored.  No atomics: results are bit-reproducible from run to run.
+ * when stored.  No sum and no result goes through an atomic operation: results
+ * are bit-reproducible from run to run.  (One kernel hands out its blocks of
+ * rows by a counter in LDS; which wavefront takes a block changes no result.)
  *
  * Layouts
  *   W_l        n_out x n_in, CSR: row_ptr int32[n_out+1], col_idx int32[nnz]
@@ -228,7 +230,8 @@ int sdnn_sgd_step(sdnn_net *net, float lr, void *stream);
 int sdnn_get_activation(sdnn_net *net, int32_t layer /*0..L*/, float *d_dst, void *stream);
 int sdnn_get_delta(sdnn_net *net, int32_t layer /*1..L*/, float *d_dst, void *stream);
 /* Eq. 4 without applying it: d_g [nnz(layer)] in CSR order, d_gb [n_out] (either may be NULL).
- * layer in 1..L; needs a preceding sdnn_backward (does not consume it). */
+ * layer in 1..L; needs a preceding sdnn_backward (does not consume it).  May use the layer's scratch memory in the workspace:
+ * a call is ordered, also across streams, before the next sdnn_backward of the net. */
 int sdnn_weight_grad(sdnn_net *net, int32_t layer, float *d_g, float *d_gb, void *stream);
 int sdnn_get_weights(sdnn_net *net, int32_t layer /*1..L*/, float *d_values, float *d_bias,
                      void *stream);
