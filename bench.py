@@ -183,6 +183,9 @@ def run_config(cfg, args, steps, warmup, headline):
     kernels = {"forward": "k_spmm_panel<8,0>" if panels else "k_fwd_long" if not short_rows and Bt > 64 and N <= 8192 else f"k_spmm<{v},0,{8 if short_rows else 16}>" if not short_rows or (Bt <= 64 and N < 2048) else "k_rows",
                "backward": ("k_bwd_grad<8>" if Bt <= 64 and short_rows and N <= 6144 else "k_bwd_rows" if short_rows or Bt <= 128 else "k_bwd_long") if fused else f"k_spmm<{v},1,{8 if short_rows else 16}>",
                "update": "k_apply + k_spread_vals + k_apply_bias" if fused else "k_update<4>"}
+    single = not fused and short_rows and 1 < Bt <= 256 and L >= 4 and N <= 1400   # all layers of a pass in one launch
+    if single:
+        kernels |= {"forward": "k_train_lds<0>", "backward": "k_train_lds<1>"}
     passes = {"forward": (fwd_ms, fb, L), "backward": (bwd_ms, bb, L if fused else L - 1), "update": (upd_ms, ub, 1)}
     dom = max(passes, key=lambda k: passes[k][0])
     d_ms, d_bytes, d_units = passes[dom]
@@ -200,7 +203,7 @@ def run_config(cfg, args, steps, warmup, headline):
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "units_per_step": d_units, "unit_of_work": "one layer" if dom != "update" else "all layers",
                 "avg_unit_us": round(d_ms * 1e3 / d_units, 3), "bytes_per_unit": int(d_bytes / d_units),
-                "kernel_launches_per_unit": 1,
+                "kernel_launches_per_unit": round(1 / d_units, 4) if single and dom != "update" else 1,
                 "per_pass_frac": {p: round(passes[p][1] / (passes[p][0] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4) for p in passes},
                 "step_frac": round((fb + bb + ub) / (ms_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     net.close()

@@ -27,7 +27,8 @@ struct LayerDev {
     float *X;                 // X_l      [n_out][B]  (training mode)
     float *D;                 // Delta_l  [n_out][B]  (training mode)
     float *G[2];              // [nnz] each: gradient of the stored entries over one half of the batch, in the order of
-                              // the transposed index (fused backward sweep; training mode)
+                              // the transposed index (fused backward sweep; training mode).  Where G[0] holds all of it,
+                              // G[1] is scratch of sdnn_weight_grad
     float *vals_t;            // [nnz]: the values in the order of the transposed index (vals_t[q] == vals[t_perm[q]]),
                               // read by the fused backward sweep; NULL where that sweep is not set up
     // The way back from the transposed order to the CSR order, in two passes that both move whole runs (NULL with
@@ -42,6 +43,7 @@ struct LayerDev {
     // Nets made for one sample per step: lane-major copies of W (0) and W^T (1), the only values such a net steps.  The
     // rows, longest first, in blocks of 64; a block's entries come in chunks of eight per lane (B1_CHUNK_BYTES: the
     // lanes' eight columns, 2 or 4 bytes each, then twice four weights), zero weights past the end of a row.
+    // Nets for k_fwd_long: one of W, of 2-byte columns, beside the values (two chunks more at its end; nothing at (1)).
     int32_t b1_blocks[2];
     const int32_t *b1_cs[2];  // [b1_blocks + 1]: first chunk of a block
     const int2 *b1_row[2];    // [64 b1_blocks]: {row, entries} of a lane, row -1 past the last row
