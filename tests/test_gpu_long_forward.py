@@ -52,6 +52,14 @@ def test_widths(n_out, n_in, lengths):
     assert torch.equal(*outs) and float(outs[0].std()) > 0
 
 
+@pytest.mark.parametrize("b", [1021, 1024, 1601, 2301])
+def test_more_samples_than_a_round_of_workgroups(b):
+    """All groups of four at once on 256 compute units, and in two and three rounds; some places stay empty."""
+    layers, x = [_layer(9615, 1000, 700, (150, 160, 170)), _layer(9616, 961, 1000, (150, 160, 170))], wl.normal_inputs(9617, 700, b)
+    outs = [_net(layers, b, lds).sdnn_forward(P.dev(x), torch.full((961, b), -1.0, device=P.DEV)) for lds in (0, sdnn.SDNN_LDS_OFF)]
+    assert torch.equal(*outs) and float(outs[0].std()) > 0
+
+
 def test_copy_follows_steps_of_other_batches_and_replaced_values():
     layers = [_layer(9620, 1100, 900, (300, 130, 9)), _layer(9621, 1100, 1100, (280, 150))]
     nets = [_net(layers, 200, lds) for lds in (0, sdnn.SDNN_LDS_OFF)]
