@@ -557,7 +557,7 @@ def test_long_forward_by_the_net():
 
 def test_copies_for_the_long_forward_follow_when_they_are_read():
     """After a step whose batch reads them, at once; else before the next pass that does.  In a graph, and once a graph reads
-    them, always.  Replaced values at once, of that layer."""
+    them, always.  Replaced values of a layer likewise, that layer alone."""
     routes.run("""
         def net():
             return Net([layer(2000, 2000, (200,))] * 3, 256, training=True)
@@ -579,8 +579,20 @@ def test_copies_for_the_long_forward_follow_when_they_are_read():
         assert [fills(b, 64, (0, 1, 2)), fills(b, 256)] == [[0, 0, 1], [0, 0, 1]]
         c = net()                                      # a graph reads copies that are behind
         assert [fills(c, 64), fills(c, 65, (0, 1)), fills(c, 64), fills(c, 65), fills(c, 64)] == [[0, 0, 0], [1, 0, 1], [0, 0, 1], [1, 0, 1], [0, 0, 1]]
-        rc, log = a("sdnn_set_weights", 2, X0, XL, None)
-        assert rc == 0 and [l for l in log if l.startswith("k_long_fill")] == ["k_long_fill<false> 32 16 1"]
-        rc, log = a("sdnn_set_weights", 2, None, XL, None)
-        assert rc == 0 and not any(l.startswith("k_long_fill") for l in log)
+        def replaced(net, layers, capture=0):
+            stub.stub_capture(capture)
+            out = []
+            for k, values in layers:
+                rc, log = net("sdnn_set_weights", k, X0 if values else None, XL, None)
+                assert rc == 0
+                out += [l for l in log if l.startswith("k_long_fill")]
+            stub.stub_capture(0)
+            rc, log = net("sdnn_forward", X0, 65, XL, None)
+            assert rc == 0
+            return out, [l for l in log if l.startswith("k_long_fill")]
+        one, two, three = (f"k_long_fill<false> 32 16 {n}" for n in (1, 2, 3))
+        assert replaced(a, [(2, 1)]) == ([], [one]) and replaced(a, [(2, 0)]) == ([], []) and replaced(a, [(3, 1), (2, 1)]) == ([], [two])
+        assert replaced(a, [(1, 1), (3, 1)]) == ([], [one, one]) and replaced(a, [(1, 1), (2, 1), (3, 1)]) == ([], [three]) and replaced(a, []) == ([], [])
+        assert replaced(a, [(2, 1)], 1) == ([one], []) # captured: its replays are not seen
+        assert replaced(c, [(2, 1), (1, 1)]) == ([one, one], []) # a graph reads the copies
     """)
